@@ -21,8 +21,10 @@
 // rather than by issue rate: a binary32-state step takes about as long as a binary64 one.
 #include <cmath>
 
+#include "interface.hpp"
 #include "internal.hpp"
 #include "newton_check.hpp"
+#include "staging.hpp"
 #include "stencil.hpp"
 
 #pragma clang fp contract(off)
@@ -32,31 +34,9 @@ namespace {
 
 constexpr int kWgThreads = 512;   // threads of the whole-system solver
 constexpr int kWgChunk = 16;      // longest chunk a thread of the whole-system solver eliminates
-constexpr int kRedChunk = 16;     // chunk length in the partition levels
 constexpr int kWgRows = kWgThreads * kWgChunk;            // longest system of the exact 512 x 16 kernels
 constexpr int kWholeRows = 2 * kWgRows;                   // longest system solved whole (1024 lanes x 16)
 constexpr int kRedRows = kReduceBlock * kRedChunk;        // rows one partition workgroup stages
-
-// Rows staged in LDS are padded by one element every 32 rows: a thread reads its chunk with a lane
-// stride of q rows, and without the pad q = 16 or 32 would put every lane of a wave on one bank.
-__device__ __forceinline__ int padded(int i) { return i + (i >> 5); }
-constexpr int padded_size(int rows) { return rows + rows / 32 + 1; }
-
-// Reciprocal of a binary64 value to about one ulp: the hardware estimate r (relative error e = 1 - x r
-// below 2^-24 on gfx950, measured) refined to third order, r (1 + e + e^2), whose remaining error e^3
-// is below 2^-72: within one ulp of the correctly rounded reciprocal (99.98% equal to it over 4 M
-// arguments), as two Newton steps are, in four instructions instead of five.  The solve only multiplies
-// by reciprocals of pivots; in binary64 the resulting per-step bias stays near 1e-17 and does not show
-// at the 1e-12 parity bar.
-__device__ __forceinline__ double recip(double x) {
-  const double r = __builtin_amdgcn_rcp(x);
-  const double e = __builtin_fma(-x, r, 1.0);
-  return __builtin_fma(r, __builtin_fma(e, e, e), r);
-}
-
-// Couplings below this fraction of a row's (unit) diagonal are negligible: dropping them changes a
-// solution value by less than half an ulp of the largest value it couples to.
-constexpr double kNegligible = 0x1p-54;
 
 // Row sources of the chunk elimination.  row() returns row k as assembled; boundary() then folds the
 // Dirichlet values into the reduced rows of the chunk that holds the first or last row of the system
@@ -102,26 +82,6 @@ struct RegRows {
   __device__ __forceinline__ void boundary(int, int, int, T&, T&, T&, T&) const {}
 };
 
-// Dirichlet values of a level-0 system: row 0 reads x_{-1} = a, row R-1 reads x_R = b.  In the reduced
-// rows, x_{-1} enters only the chunk's F row (coefficient AF) and x_R only its E row (coefficient CE),
-// so moving the known values to the right-hand side is DF -= AF a, AF = 0 and DE -= CE b, CE = 0.
-struct DirichletEnds {
-  double a, b;
-  bool dirichlet;
-  __device__ __forceinline__ void apply(int s, int m, int R, double& AF, double& DF, double& CE,
-                                        double& DE) const {
-    if (!dirichlet) return;
-    if (s == 0) {
-      DF = __builtin_fma(-AF, a, DF);
-      AF = 0.0;
-    }
-    if (s + m == R) {
-      DE = __builtin_fma(-CE, b, DE);
-      CE = 0.0;
-    }
-  }
-};
-
 // Rows of a level-0 system whose old values sit in LDS (staged coalesced from HBM); row k is held at
 // padded(k - base).
 template <typename S>
@@ -148,16 +108,6 @@ struct LdsDst {
   __device__ __forceinline__ void write(int, int k, double v) const { st[padded(k - base)] = static_cast<S>(v); }
 };
 
-// Old state values of rows s..s+m-1 staged in LDS (row k at padded(k - base)) into de[], the input of
-// the in-place elimination over ValueRows: every LDS read is issued before the pivot chain starts.
-// The rows then round exactly as LdsRows would assemble them.
-template <typename S, typename T, int M>
-__device__ __forceinline__ void load_staged(const S* st, int base, int s, int m, T (&de)[M]) {
-#pragma unroll
-  for (int j = 0; j < M; ++j)
-    if (j < m) de[j] = static_cast<T>(st[padded(s + j - base)]);
-}
-
 // Reduced systems of at least this many rows are read and written by the workgroup solver through LDS
 // (coalesced); smaller ones lane by lane, which saves the transposes' barriers.
 constexpr int kCoalesceRows = 2048;
@@ -180,21 +130,6 @@ __device__ __forceinline__ void stage_transpose(T* st, const T (&v)[MC], int R, 
   }
   __syncthreads();
 }
-
-// Row k of a level-0 system from its old value ui (resident solver, where the values live in registers).
-struct ValueRows {
-  double r, D;
-  DirichletEnds ends;
-  __device__ __forceinline__ void row_value(double ui, int, int, double& al, double& be, double& ga,
-                                            double& de) const {
-    btcs_row(ui, r, D, al, be, ga);
-    de = ui;
-  }
-  __device__ __forceinline__ void boundary(int s, int m, int R, double& AF, double& DF, double& CE,
-                                           double& DE) const {
-    ends.apply(s, m, R, AF, DF, CE, DE);
-  }
-};
 
 // Chunk elimination.  Rows s..s+m-1 (2 <= m <= M) of a system with R rows.  On return, for
 // 1 <= j <= m-2, row j reads  x_j + al[j] F + ga[j] E = de[j]  with F = x_0, E = x_{m-1}, and the two
@@ -293,27 +228,6 @@ struct PtrDst {
   __device__ __forceinline__ void write(int, int k, double v) const { x[k] = static_cast<S>(v); }
 };
 
-// Chunk layout of a system of R rows split into P chunks: sizes q or q+1, the longer ones first.
-__device__ __forceinline__ void chunk_span(int k, int R, int P, int& s, int& m) {
-  const int q = R / P, rho = R - q * P;
-  s = k * q + (k < rho ? k : rho);
-  m = q + (k < rho ? 1 : 0);
-}
-
-// One PCR step on a row normalised to a unit diagonal,  a x_{i-s} + x_i + c x_{i+s} = d,  with its two
-// partners  x_{i-s} + cm x_i + ... = dm  (coefficients am, cm, dm) and  ap x_i + x_{i+s} + ... = dp:
-// subtracting a times the first and c times the second leaves a row coupling x_{i-2s} and x_{i+2s},
-// renormalised.
-template <typename T>
-__device__ __forceinline__ void pcr_combine(T a0, T c0, T d0, T am, T cm, T dm, T ap, T cp, T dp, T& na, T& nc,
-                                            T& nd) {
-  const T inv = recip(__builtin_fma(-c0, ap, __builtin_fma(-a0, cm, T(1))));
-  const T a = a0 * inv, c = c0 * inv;
-  na = -(a * am);
-  nc = -(c * cp);
-  nd = __builtin_fma(-c, dp, __builtin_fma(-a, dm, d0 * inv));
-}
-
 // Workspace of pcr_pairs in LDS: two buffers of three arrays (sub, super, rhs) of 2 NT rows, and one flag
 // per wave for each buffer.
 template <typename T, int NT>
@@ -393,306 +307,34 @@ __device__ __forceinline__ void pcr_pairs(const PcrSpace<T, NT>& w, int P, T fa,
   E = ed;
 }
 
-// ---- Interface partition of a whole system (the resident and the per-step workgroup solvers) ----------
-//
-// Lane t < P owns rows s..s+m-1 (m >= 2) of a system of R rows, and its last row is the chunk's interface
-// unknown y_t = x_{s+m-1}.  The interior rows j = 0..m-2 lie between y_{t-1} (row s-1, the previous
-// chunk's interface; cyclically for a periodic system) and y_t, so eliminating them expresses each as
-//     x_j = de[j] - al[j] y_{t-1} - ga[j] y_t.
-// Substituting into y_t's own row its two neighbours, x_{m-2} of this chunk and the first interior row
-// of the next chunk (received from lane t+1), leaves one row per chunk,
-//     A_t y_{t-1} + y_t + C_t y_{t+1} = D_t,
-// a cyclic system of P rows solved by PCR with one row per lane.  A Dirichlet system moves its two
-// boundary values into the right-hand sides of its first and last rows, which removes the couplings
-// across its ends, so its interface system is not cyclic.  Compared with reducing every chunk to two
-// rows (F, E), this halves the reduced system and replaces its first PCR step by one exchange between
-// neighbouring lanes.
-
-// Eliminates the interior rows and returns the interface row's coefficients (ia on the neighbour
-// x_{m-2}, ib, ic on the row after the chunk, id).  IN_PLACE: de[j] holds row j's old state value on
-// entry (ValueRows); otherwise the source assembles row j itself (LdsRows).
-template <typename T, int M, bool IN_PLACE = true, typename Src>
-__device__ __forceinline__ void interface_eliminate(const Src& src, int s, int m, int R, T (&al)[M], T (&ga)[M],
-                                                    T (&de)[M], T& ia, T& ib, T& ic, T& id) {
-  const DirichletEnds& ends = src.ends;
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    if (j < m) {
-      T aj, bj, cj, dj;
-      if constexpr (IN_PLACE) src.row_value(de[j], s + j, R, aj, bj, cj, dj);
-      else src.row(j, s + j, R, aj, bj, cj, dj);
-      if (j == 0 && ends.dirichlet && s == 0) {   // x_{-1} = a
-        dj = __builtin_fma(-aj, static_cast<T>(ends.a), dj);
-        aj = T(0);
-      }
-      if (j == m - 1) {
-        if (ends.dirichlet && s + m == R) {        // x_R = b
-          dj = __builtin_fma(-cj, static_cast<T>(ends.b), dj);
-          cj = T(0);
-        }
-        ia = aj;
-        ib = bj;
-        ic = cj;
-        id = dj;
-      } else if (j == 0) {
-        const T inv = recip(bj);
-        al[0] = aj * inv;
-        ga[0] = cj * inv;
-        de[0] = dj * inv;
-      } else {
-        const T inv = recip(__builtin_fma(-aj, ga[j - 1], bj));
-        const T ai = aj * inv;
-        al[j] = -(ai * al[j - 1]);
-        ga[j] = cj * inv;
-        de[j] = __builtin_fma(-ai, de[j - 1], dj * inv);
-      }
-    }
-  }
-  // backward: the coupling to x_{j+1} becomes a coupling to y_t (row m-2 already has this form)
-#pragma unroll
-  for (int j = M - 3; j >= 0; --j) {
-    if (j <= m - 3) {
-      const T g = ga[j];
-      de[j] = __builtin_fma(-g, de[j + 1], de[j]);
-      al[j] = __builtin_fma(-g, al[j + 1], al[j]);
-      ga[j] = -(g * ga[j + 1]);
-    }
-  }
-}
-
-// Workgroup barrier.  LdsOnly: for exchanges through LDS alone, it waits for this wave's LDS accesses but
-// not for its vector memory accesses, so that rows streaming into another LDS buffer (global_load_lds,
-// whose LDS writes a full barrier would wait for) stay in flight across it.
-template <bool LdsOnly>
-__device__ __forceinline__ void wg_barrier() {
-  if constexpr (LdsOnly) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else __syncthreads();
-}
-
-// LDS of the interface solve: the first interior rows exchanged between neighbouring lanes, and two
-// buffers of the interface rows for PCR (three arrays of NT each), plus one stop flag per wave and buffer.
-template <typename T, int NT>
-struct InterfaceSpace {
-  static constexpr int kWaves = (NT + 63) / 64;
-  static constexpr int kVoteWords = (kWaves + 7) / 8;   // one byte per wave, read back as 64-bit words
-  static constexpr int kBytes = 3 * 3 * NT * static_cast<int>(sizeof(T));
-  T* xchg;          // 3 x NT
-  T* rows;          // 2 buffers x 3 arrays x NT
-  uint64_t* votes;  // 2 x kVoteWords; zeroed once (clear_votes) before the kernel's first barrier
-  __device__ __forceinline__ void clear_votes() const {
-    if (threadIdx.x < 2 * kVoteWords) votes[threadIdx.x] = 0;
-  }
-};
-
-// Solves the interface system.  Lane t < P passes its chunk's first interior row (al0, ga0, de0), its
-// last interior row (alL, gaL, deL) and its interface row (ia, ib, ic, id); on return y = y_t and
-// yp = y_{t-1}.  Ends with a barrier after its last write to LDS; its last reads (yp) follow that
-// barrier, so a caller that reuses the LDS for anything else must synchronise first.
-template <typename T, int NT, bool LdsOnly = false>
-__device__ __forceinline__ void interface_solve(const InterfaceSpace<T, NT>& w, int P, T al0, T ga0, T de0,
-                                                T alL, T gaL, T deL, T ia, T ib, T ic, T id, T& y, T& yp) {
-  constexpr int kR = NT;
-  const int t = threadIdx.x;
-  const bool own = t < P;
-  const int mask = P - 1;
-  if (own) {
-    w.xchg[t] = al0;
-    w.xchg[NT + t] = ga0;
-    w.xchg[2 * NT + t] = de0;
-  }
-  wg_barrier<LdsOnly>();
-  T a = T(0), c = T(0), d = T(0);
-  if (own) {
-    const int n = (t + 1) & mask;
-    const T nal = w.xchg[n], nga = w.xchg[NT + n], nde = w.xchg[2 * NT + n];
-    const T inv = recip(__builtin_fma(-ic, nal, __builtin_fma(-ia, gaL, ib)));
-    a = -(ia * alL) * inv;
-    c = -(ic * nga) * inv;
-    d = __builtin_fma(-ic, nde, __builtin_fma(-ia, deL, id)) * inv;
-    T* A = w.rows;
-    A[t] = a; A[kR + t] = c; A[2 * kR + t] = d;
-  }
-  wg_barrier<LdsOnly>();
-  int b = 0;
-  bool done = false;
-  for (int s = 1; s < P && !done; s <<= 1) {
-    const T* A = w.rows + b * 3 * kR;
-    const T* C = A + kR;
-    const T* D = C + kR;
-    bool live = false;
-    if (own) {
-      const int mi = (t - s) & mask, pi = (t + s) & mask;
-      pcr_combine(a, c, d, A[mi], C[mi], D[mi], A[pi], C[pi], D[pi], a, c, d);
-      live = (__builtin_fabs(a) + __builtin_fabs(c)) > kNegligible;
-      T* nA = w.rows + (1 - b) * 3 * kR;
-      nA[t] = a; nA[kR + t] = c; nA[2 * kR + t] = d;
-    }
-    const bool wave_live = __ballot(live) != 0;
-    constexpr int kV = InterfaceSpace<T, NT>::kVoteWords;
-    if ((t & 63) == 0) reinterpret_cast<unsigned char*>(w.votes + (1 - b) * kV)[t >> 6] = wave_live ? 1 : 0;
-    wg_barrier<LdsOnly>();
-    b = 1 - b;
-    uint64_t any = 0;
-#pragma unroll
-    for (int k = 0; k < kV; ++k) any |= w.votes[b * kV + k];
-    done = any == 0;
-  }
-  y = T(0);
-  yp = T(0);
-  if (own) {
-    // every row's final coefficients are in buffer b; a row still coupled after all log2(P) steps
-    // couples only to itself
-    const int mi = (t - 1) & mask;
-    const T* A = w.rows + b * 3 * kR;
-    y = d;
-    yp = A[2 * kR + mi];
-    if (!done) {   // (uniform across the workgroup)
-      y = d / ((T(1) + a) + c);
-      yp = yp / ((T(1) + A[mi]) + A[kR + mi]);
-    }
-  }
-}
-
-// One interface-partition solve of a whole system: eliminate (lanes with rows), exchange, PCR.  On
-// return y = y_t and yp = y_{t-1} (see interface_solve for the LDS contract).
-template <typename T, int NT, int M, bool LdsOnly = false>
-__device__ __forceinline__ void interface_step(const InterfaceSpace<T, NT>& w, const ValueRows& src, bool own, int s,
-                                               int m, int R, int P, T (&al)[M], T (&ga)[M], T (&de)[M], T& y,
-                                               T& yp) {
-  T ia = T(0), ib = T(1), ic = T(0), id = T(0);
-  T alL = T(0), gaL = T(0), deL = T(0);
-  if (own) {
-    interface_eliminate<T, M>(src, s, m, R, al, ga, de, ia, ib, ic, id);
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      if (j == m - 2) {
-        alL = al[j];
-        gaL = ga[j];
-        deL = de[j];
-      }
-    }
-  }
-  interface_solve<T, NT, LdsOnly>(w, P, own ? al[0] : T(0), own ? ga[0] : T(0), own ? de[0] : T(0), alL, gaL, deL,
-                                  ia, ib, ic, id, y, yp);
-}
-
-// Interior rows from the interface unknowns (in place, rounded through the state type S as a store to
-// and reload from the state buffer would round them); row m-1 is y_t itself.
-template <typename S, typename T, int M>
-__device__ __forceinline__ void interface_recover_in_place(int m, const T (&al)[M], const T (&ga)[M], T (&de)[M],
-                                                           T yp, T y) {
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    if (j < m - 1) de[j] = static_cast<T>(static_cast<S>(__builtin_fma(-ga[j], y, __builtin_fma(-al[j], yp, de[j]))));
-    if (j == m - 1) de[j] = static_cast<T>(static_cast<S>(y));
-  }
-}
-
-// Coalesced copies of a block's rows between HBM and LDS: all loads are issued before the first LDS
-// store, so a wave has its whole share of the block in flight at once.
-template <typename S, int NT = kReduceBlock, int J = kRedChunk>
-__device__ __forceinline__ void stage_in(S* stage, const S* __restrict__ src, int cnt) {
-  S v[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int i = static_cast<int>(threadIdx.x) + j * NT;
-    v[j] = i < cnt ? src[i] : S(0);
-  }
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int i = static_cast<int>(threadIdx.x) + j * NT;
-    if (i < cnt) stage[padded(i)] = v[j];
-  }
-}
-
-template <typename S, int NT = kReduceBlock, int J = kRedChunk>
-__device__ __forceinline__ void stage_out(const S* stage, S* __restrict__ dst, int cnt) {
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int i = static_cast<int>(threadIdx.x) + j * NT;
-    if (i < cnt) dst[i] = stage[padded(i)];
-  }
-}
-
-// Crank-Nicolson store: the staged rows hold the half-dt BTCS solution y; write 2 y - u, with u re-read
-// (coalesced) from the old state.
-template <typename S, int NT = kReduceBlock, int J = kRedChunk>
-__device__ __forceinline__ void stage_out_cn(const S* stage, const S* __restrict__ old, S* __restrict__ dst,
-                                             int cnt) {
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int i = static_cast<int>(threadIdx.x) + j * NT;
-    if (i < cnt)
-      dst[i] = static_cast<S>(2.0 * static_cast<double>(stage[padded(i)]) - static_cast<double>(old[i]));
-  }
-}
-
-// Whole-system solver: one workgroup per system.  Level-0 systems stage the old state through LDS
-// (coalesced loads), eliminate chunks from LDS, solve the reduced system by PCR in the same LDS, write
-// the new values back into the staging buffer and store them coalesced, with the Dirichlet boundary
-// nodes.  Reduced systems of the partition levels read (A, C, D) and write X in HBM directly.
-// (Reduced systems are few and large, one workgroup each: their rows preloaded in registers matter more
-// than a second workgroup per CU.)
-template <typename S, bool FromState, int NT, int MC, bool EXACT = false>
-__global__ __launch_bounds__(NT, MC == 16 ? (FromState ? 4 : 2) : 1) void btcs_wg_kernel(
-    const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems, const S* __restrict__ u,
-    S* __restrict__ out, const double* __restrict__ LA, const double* __restrict__ LC,
+// Reduced systems of the partition levels (rows (A, 1, C, D) in HBM), one workgroup each: chunk elimination
+// to two rows per lane, PCR in LDS, recovery to X.  (They are few and large: their rows preloaded in
+// registers matter more than a second workgroup per CU.)
+template <int NT, int MC, bool EXACT = false>
+__global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
+    const SysDesc* __restrict__ systems, const double* __restrict__ LA, const double* __restrict__ LC,
     const double* __restrict__ LD, double* __restrict__ LX, const int* __restrict__ only) {
   using T = double;
   using Pcr = PcrSpace<T, NT>;
-  using IS = InterfaceSpace<T, NT>;
-  constexpr int kStageBytes = padded_size(NT * MC) * static_cast<int>(FromState ? sizeof(S) : sizeof(T));
-  constexpr int kSolveBytes = FromState ? IS::kBytes : Pcr::kBytes;
-  constexpr int kBytes = kStageBytes > kSolveBytes ? kStageBytes : kSolveBytes;
+  constexpr int kStageBytes = padded_size(NT * MC) * static_cast<int>(sizeof(T));
+  constexpr int kBytes = kStageBytes > Pcr::kBytes ? kStageBytes : Pcr::kBytes;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
   __shared__ int pcr_flags[2 * Pcr::kWaves];
-  __shared__ uint64_t iface_votes[2 * IS::kVoteWords];
   const Pcr pcr{reinterpret_cast<T*>(smem), pcr_flags};
-  const IS iws{reinterpret_cast<T*>(smem), reinterpret_cast<T*>(smem) + 3 * NT, iface_votes};
-  iws.clear_votes();
-  S* stage = reinterpret_cast<S*>(smem);
-  T* tstage = reinterpret_cast<T*>(smem);   // reduced systems: one coefficient array at a time
+  T* tstage = reinterpret_cast<T*>(smem);   // one coefficient array at a time
 
   if (only && only[-1] == 0) return;         // partition fallback: no window of this step failed
   const SysDesc sys = systems[blockIdx.x];
   if (only && only[sys.inst] == 0) return;   // partition fallback: this instance's windows held
   const int R = sys.rows, P = sys.chunks;
   const int tid = threadIdx.x;
-
-  LdsRows<S> ssrc{};
-  ArrayRows<T> asrc{};
-  LdsDst<S> sdst{};
-  PtrDst<T> adst{};
-  InstDesc d{};
-  if constexpr (FromState) {
-    d = inst[sys.inst];
-    const bool dir = d.bc == kDirichlet;
-    stage_in<S, NT, MC>(stage, u + d.off + (dir ? 1 : 0), R);
-    ssrc = LdsRows<S>{stage, 0, d.r, d.D, DirichletEnds{d.a, d.b, dir}};
-    sdst = LdsDst<S>{stage, 0};
-    if (dir && tid == 0) {
-      out[d.off] = static_cast<S>(d.a);
-      out[d.off + d.n - 1] = static_cast<S>(d.b);
-    }
-    __syncthreads();
-  } else {
-    asrc = ArrayRows<T>{LA + sys.in_off, LC + sys.in_off, LD + sys.in_off};
-    adst.x = LX + sys.in_off;
-  }
-
+  const ArrayRows<T> asrc{LA + sys.in_off, LC + sys.in_off, LD + sys.in_off};
+  const PtrDst<T> adst{LX + sys.in_off};
   if (R == 1) {   // a single Dirichlet unknown
     if (tid == 0) {
       T al, be, ga, de;
-      if constexpr (FromState) {
-        ssrc.row(0, 0, 1, al, be, ga, de);
-        const T y = ((de - al * d.a) - ga * d.b) / be;
-        out[d.off + 1] = sys.cn ? static_cast<S>(2.0 * static_cast<double>(static_cast<S>(y)) -
-                                                 static_cast<double>(u[d.off + 1]))
-                                : static_cast<S>(y);
-      } else {
-        asrc.row(0, 0, 1, al, be, ga, de);
-        adst.write(0, 0, de / be);
-      }
+      asrc.row(0, 0, 1, al, be, ga, de);
+      adst.write(0, 0, de / be);
     }
     return;
   }
@@ -706,64 +348,43 @@ __global__ __launch_bounds__(NT, MC == 16 ? (FromState ? 4 : 2) : 1) void btcs_w
       m = MC;
     }
   }
-  if constexpr (FromState) {
-    // whole systems: the interface partition, as in the resident solver (the two agree bitwise)
-    if (tid < P) load_staged<S>(stage, 0, s, m, de);
-    __syncthreads();                           // every lane's rows read: the interface LDS overlays them
-    T y, yp;
-    interface_step<T, NT, MC>(iws, ValueRows{d.r, d.D, ssrc.ends}, tid < P, s, m, R, P, al, ga, de, y, yp);
-    __syncthreads();                           // the interface unknowns read before the rows are rewritten
-    if (tid < P) {
+  T AF = T(0), CF = T(0), DF = T(0), AE = T(0), CE = T(0), DE = T(0);
+  if (R >= kCoalesceRows) {
+    // One workgroup reads the whole reduced system: coalesced loads of the three arrays (every load in
+    // flight at once), then each array transposed through LDS into the lanes' chunks.
+    T va[MC], vc[MC], vd[MC];
 #pragma unroll
-      for (int j = 0; j < MC; ++j) {
-        if (j < m - 1) sdst.write(j, s + j, __builtin_fma(-ga[j], y, __builtin_fma(-al[j], yp, de[j])));
-        if (j == m - 1) sdst.write(j, s + j, y);
+    for (int j = 0; j < MC; ++j) {
+      const int i = tid + j * NT;
+      if (i < R) {
+        va[j] = asrc.A[i];
+        vc[j] = asrc.C[i];
+        vd[j] = asrc.Dv[i];
       }
     }
+    RegRows<T, MC> rr;
+    stage_transpose<T, NT, MC>(tstage, va, R, P, s, m, rr.a);
+    stage_transpose<T, NT, MC>(tstage, vc, R, P, s, m, rr.c);
+    stage_transpose<T, NT, MC>(tstage, vd, R, P, s, m, rr.d);
+    if (tid < P) chunk_eliminate<T, MC>(rr, s, m, R, al, ga, de, AF, CF, DF, AE, CE, DE);
+  } else if (tid < P) {   // small systems: the lanes' own rows straight from HBM, all loads up front
+    RegRows<T, MC> rr;
+    rr.load(asrc.A, asrc.C, asrc.Dv, s, m);
+    chunk_eliminate<T, MC>(rr, s, m, R, al, ga, de, AF, CF, DF, AE, CE, DE);
+  }
+  T F = T(0), E = T(0);
+  // (PCR's last barrier follows its last read of the rows, so the staging buffer is free on return)
+  pcr_pairs<T, NT>(pcr, P, AF, CF, DF, AE, CE, DE, F, E);
+  if (R >= kCoalesceRows) {   // through LDS again, for a coalesced store
+    if (tid < P) chunk_recover<T, MC>(LdsDst<T>{tstage, 0}, s, m, al, ga, de, F, E);
     __syncthreads();
-    const int64_t o = d.off + (d.bc == kDirichlet ? 1 : 0);
-    if (sys.cn) stage_out_cn<S, NT, MC>(stage, u + o, out + o, R);
-    else stage_out<S, NT, MC>(stage, out + o, R);
-    return;
+#pragma unroll
+    for (int j = 0; j < MC; ++j) {
+      const int i = tid + j * NT;
+      if (i < R) adst.x[i] = tstage[padded(i)];
+    }
   } else {
-    T AF = T(0), CF = T(0), DF = T(0), AE = T(0), CE = T(0), DE = T(0);
-    if (R >= kCoalesceRows) {
-      // One workgroup reads the whole reduced system: coalesced loads of the three arrays (every load in
-      // flight at once), then each array transposed through LDS into the lanes' chunks.
-      T va[MC], vc[MC], vd[MC];
-#pragma unroll
-      for (int j = 0; j < MC; ++j) {
-        const int i = tid + j * NT;
-        if (i < R) {
-          va[j] = asrc.A[i];
-          vc[j] = asrc.C[i];
-          vd[j] = asrc.Dv[i];
-        }
-      }
-      RegRows<T, MC> rr;
-      stage_transpose<T, NT, MC>(tstage, va, R, P, s, m, rr.a);
-      stage_transpose<T, NT, MC>(tstage, vc, R, P, s, m, rr.c);
-      stage_transpose<T, NT, MC>(tstage, vd, R, P, s, m, rr.d);
-      if (tid < P) chunk_eliminate<T, MC>(rr, s, m, R, al, ga, de, AF, CF, DF, AE, CE, DE);
-    } else if (tid < P) {   // small systems: the lanes' own rows straight from HBM, all loads up front
-      RegRows<T, MC> rr;
-      rr.load(asrc.A, asrc.C, asrc.Dv, s, m);
-      chunk_eliminate<T, MC>(rr, s, m, R, al, ga, de, AF, CF, DF, AE, CE, DE);
-    }
-    T F = T(0), E = T(0);
-    // (PCR's last barrier follows its last read of the rows, so the staging buffer is free on return)
-    pcr_pairs<T, NT>(pcr, P, AF, CF, DF, AE, CE, DE, F, E);
-    if (R >= kCoalesceRows) {   // through LDS again, for a coalesced store
-      if (tid < P) chunk_recover<T, MC>(LdsDst<T>{tstage, 0}, s, m, al, ga, de, F, E);
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < MC; ++j) {
-        const int i = tid + j * NT;
-        if (i < R) adst.x[i] = tstage[padded(i)];
-      }
-    } else {
-      if (tid < P) chunk_recover<T, MC>(adst, s, m, al, ga, de, F, E);
-    }
+    if (tid < P) chunk_recover<T, MC>(adst, s, m, al, ga, de, F, E);
   }
 }
 
@@ -884,8 +505,8 @@ __global__ __launch_bounds__(NT, 2) void btcs_stream_kernel(const InstDesc* __re
     }
     const IS iws{reinterpret_cast<T*>(bc), reinterpret_cast<T*>(bc) + 3 * NT, iface_votes};
     T y, yp;
-    interface_step<T, NT, MC, true>(iws, ValueRows{d.r, d.D, DirichletEnds{d.a, d.b, dir}}, true, tid * MC, MC, W,
-                                    NT, al, ga, de, y, yp);
+    slot_step<NT, MC, true, true>(iws, SlotRows{d.r, d.D, d.a, d.b}, slot_lane<MC, true>(tid, W, NT, dir), NT, al, ga,
+                                  de, y, yp);
     wg_barrier<true>();                        // the interface unknowns read before bc takes the results
 #pragma unroll
     for (int h = 0; h < H; ++h) {
@@ -1032,136 +653,6 @@ __global__ __launch_bounds__(NT, MC == 16 ? 4 : 1) void newton_wg_kernel(const I
   else newton_solve<false, S, NT, MC>(pcr, stage, rows, xs, R, P, last != 0);
 }
 
-// An opaque copy of a lane value: address arithmetic built on it cannot be hoisted above this point, so
-// per-lane addresses are formed in the phase that uses them rather than kept live (or spilled) across
-// the kernel.
-__device__ __forceinline__ int opaque_lane(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
-// Stores one step's rows of a system at x (its first unknown; REC of the resident solver): lane t holds
-// rows [s, s + m) in de.  Each wave passes its lanes' rows through a region of LDS of its own, half the
-// wave at a time (32 chunks of MC rows, one slot of padding per chunk), and stores them in row order, 64
-// consecutive slots per instruction.  The region is private to the wave, so no workgroup barrier is
-// needed; a wave's LDS accesses are performed in order, which the wavefront-scope fences keep the
-// compiler from reordering.
-template <typename S, int NT, int MC, bool EXACT>
-__device__ __forceinline__ void record_rows(const double (&de)[MC], double* lds, int R, int P,
-                                            S* __restrict__ x) {
-  constexpr int kHalf = 32, kSlots = kHalf * MC;
-  static_assert(kSlots % 64 == 0, "a half-wave's rows must fill whole store instructions");
-  // (the lane index is formed here, at every step, so that no address of the stores below is kept live
-  // across the solve)
-  const int lt = opaque_lane(static_cast<int>(threadIdx.x));
-  const int lane = lt & 63, wave = lt >> 6;
-  double* region = lds + wave * kHalf * (MC + 1);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if ((lane >> 5) == h) {
-#pragma unroll
-      for (int j = 0; j < MC; ++j) region[(MC + 1) * (lane & 31) + j] = de[j];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 2   // (fully unrolled, the loads held for the stores spill across the solve)
-    for (int i = 0; i < kSlots / 64; ++i) {
-      const int q = lane + 64 * i;
-      const int owner = 64 * wave + kHalf * h + q / MC, j = q % MC;   // the slot's lane and row in its chunk
-      int so = MC * owner, mo = MC;
-      if constexpr (!EXACT) chunk_span(owner, R, P, so, mo);
-      const double v = region[(MC + 1) * (q / MC) + j];
-      if (owner < P && j < mo) x[so + j] = static_cast<S>(v);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// Resident solver: one workgroup keeps one system (<= 8192 rows, or exactly 16384) in registers, MC rows
-// per lane, for all steps of a launch.  Each step is the whole-system solver's step without the trips to
-// HBM; the state is rounded through S once per step as the per-step kernel's store would, so both solvers
-// agree bitwise.  The state buffer is read once and written once per launch (in place).
-// REC: the source u is only read, and the state after each step k (1 <= k <= steps) is stored at
-// rec + (k - 1) rstride (Dirichlet boundary values included) instead of the final one in place; the
-// step's barriers then wait for LDS only, so those stores stay in flight across the next steps.
-template <typename S, int NT, int MC, bool EXACT = false, bool REC = false>
-__global__ __launch_bounds__(NT, MC == 16 ? 4 : 1) void btcs_resident_kernel(
-    const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems, S* __restrict__ u,
-    int steps, S* __restrict__ rec, int64_t rstride) {
-  using T = double;
-  using IS = InterfaceSpace<T, NT>;
-  constexpr int kRecSlots = REC ? (NT / 64) * 32 * (MC + 1) : 1;
-  __shared__ T iface_lds[IS::kBytes / sizeof(T)];
-  __shared__ uint64_t iface_votes[2 * IS::kVoteWords];
-  __shared__ T rec_lds[kRecSlots];
-  const IS ws{iface_lds, iface_lds + 3 * NT, iface_votes};
-  ws.clear_votes();
-  const SysDesc sys = systems[blockIdx.x];
-  if (sys.rows <= 0) return;                   // an empty slot of a resident pool
-  if (sys.limit > 0 && sys.limit < steps) steps = sys.limit;
-  const InstDesc d = inst[sys.inst];
-  const bool dir = d.bc == kDirichlet;
-  const int R = sys.rows, P = sys.chunks;
-  const int tid = threadIdx.x;
-  S* __restrict__ x = u + d.off + (dir ? 1 : 0);
-  S* __restrict__ xr = REC ? rec + d.off + (dir ? 1 : 0) : nullptr;
-  if (dir && tid == 0) {
-    if constexpr (REC) {
-      for (int step = 0; step < steps; ++step) {
-        rec[step * rstride + d.off] = static_cast<S>(d.a);
-        rec[step * rstride + d.off + d.n - 1] = static_cast<S>(d.b);
-      }
-    } else {
-      u[d.off] = static_cast<S>(d.a);
-      u[d.off + d.n - 1] = static_cast<S>(d.b);
-    }
-  }
-  if (R == 1) {   // a single Dirichlet unknown
-    if (tid == 0) {
-      T v = static_cast<T>(x[0]);
-      for (int step = 0; step < steps; ++step) {
-        T al, be, ga;
-        btcs_row(v, d.r, d.D, al, be, ga);
-        const T de = (v - al * d.a) - ga * d.b;
-        v = static_cast<T>(static_cast<S>(de / be));
-        if constexpr (REC) xr[step * rstride] = static_cast<S>(v);
-      }
-      if constexpr (!REC) x[0] = static_cast<S>(v);
-    }
-    return;
-  }
-  int s = 0, m = 0;
-  T al[MC], ga[MC], de[MC];   // de carries the state between steps
-  if (tid < P) {
-    chunk_span(tid, R, P, s, m);
-    if constexpr (EXACT) {
-      s = tid * MC;
-      m = MC;
-    }
-#pragma unroll
-    for (int j = 0; j < MC; ++j)
-      if (j < m) de[j] = static_cast<T>(x[s + j]);
-  }
-  const ValueRows src{d.r, d.D, DirichletEnds{d.a, d.b, dir}};
-  const int mm = EXACT ? MC : m;
-  for (int step = 0; step < steps; ++step) {
-    T y, yp;
-    interface_step<T, NT, MC, REC>(ws, src, tid < P, s, mm, R, P, al, ga, de, y, yp);
-    if (tid < P) interface_recover_in_place<S>(mm, al, ga, de, yp, y);
-    if constexpr (REC) record_rows<S, NT, MC, EXACT>(de, rec_lds, R, P, xr + step * rstride);
-  }
-  if constexpr (!REC) {
-    if (tid < P) {
-#pragma unroll
-      for (int j = 0; j < MC; ++j)
-        if (j < m) x[s + j] = static_cast<S>(de[j]);
-    }
-  }
-}
-
 // ---- Truncated windows of a long system ------------------------------------------------------------
 // A long system's rows are covered by windows of W = 16 x (workgroup lanes) rows (4096 or 8192).  A window keeps the rows at least
 // kWinHalo rows inside its ends and solves them together with the halo as a plain system, in which the
@@ -1291,8 +782,7 @@ __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
   load_staged<S>(stage, 0, s, MC, de);
   __syncthreads();                             // every lane's rows read: the interface LDS overlays them
   T yv, yp;
-  interface_step<T, NT, MC>(iws, ValueRows{d.r, d.D, DirichletEnds{gl, gr, true}}, true, s, MC, W, NT, al, ga, de,
-                            yv, yp);
+  slot_step<NT, MC, true>(iws, SlotRows{d.r, d.D, gl, gr}, slot_lane<MC, true>(tid, W, NT, true), NT, al, ga, de, yv, yp);
   __syncthreads();                             // the interface unknowns read before the rows are rewritten
   const LdsDst<S> sdst{stage, 0};
 #pragma unroll
@@ -1928,21 +1418,19 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
 
 // The reduced systems of a partition level, one workgroup each, in the narrowest width that holds the
 // level's widest system (small reduced systems leave most of a 512-lane workgroup idle).
-template <typename S>
-void reduced_wg_launch(const BtcsPlan::Level& lv, const InstDesc* inst, const S* u, S* out, double* LA,
-                       double* LC, double* LD, double* LX, hipStream_t st, const int* only) {
+void reduced_wg_launch(const BtcsPlan::Level& lv, double* LA, double* LC, double* LD, double* LX, hipStream_t st,
+                       const int* only) {
   const SysDesc* sys = lv.wg->as<SysDesc>();
   const unsigned n = static_cast<unsigned>(lv.n_wg);
   switch (lv.wg_lanes) {
-    case 64: btcs_wg_kernel<S, false, 64, kWgChunk><<<n, 64, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, only); break;
-    case 128: btcs_wg_kernel<S, false, 128, kWgChunk><<<n, 128, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, only); break;
-    case 256: btcs_wg_kernel<S, false, 256, kWgChunk><<<n, 256, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, only); break;
+    case 64: btcs_reduced_kernel<64, kWgChunk><<<n, 64, 0, st>>>(sys, LA, LC, LD, LX, only); break;
+    case 128: btcs_reduced_kernel<128, kWgChunk><<<n, 128, 0, st>>>(sys, LA, LC, LD, LX, only); break;
+    case 256: btcs_reduced_kernel<256, kWgChunk><<<n, 256, 0, st>>>(sys, LA, LC, LD, LX, only); break;
     default:
       if (lv.wg_exact)   // the full layout as a constant: no row is selected at a run-time index
-        btcs_wg_kernel<S, false, kWgThreads, kWgChunk, true><<<n, kWgThreads, 0, st>>>(inst, sys, u, out, LA, LC, LD,
-                                                                                      LX, only);
+        btcs_reduced_kernel<kWgThreads, kWgChunk, true><<<n, kWgThreads, 0, st>>>(sys, LA, LC, LD, LX, only);
       else
-        btcs_wg_kernel<S, false, kWgThreads, kWgChunk><<<n, kWgThreads, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, only);
+        btcs_reduced_kernel<kWgThreads, kWgChunk><<<n, kWgThreads, 0, st>>>(sys, LA, LC, LD, LX, only);
       break;
   }
 }
@@ -2005,43 +1493,28 @@ hipError_t launch_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void*
   // backward: whole-system solves of each level, then back-substitution of the reduced systems
   for (int l = L - 1; l >= 1; --l) {
     const auto& lv = plan.levels[l];
-    if (lv.n_wg) reduced_wg_launch<S>(lv, inst, u, out, LA, LC, LD, LX, st, only);
+    if (lv.n_wg) reduced_wg_launch(lv, LA, LC, LD, LX, st, only);
     if (lv.n_blocks) {
       btcs_array_backsub_kernel<<<lv.n_blocks, kReduceBlock, 0, st>>>(
           lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), LA, LC, LD, LX, only);
     }
   }
-  const int* all = nullptr;
   for (const WgGroup& g : plan.wg_state) {
     if (!g.n) continue;
     const SysDesc* sys = g.sys->as<SysDesc>();
     const unsigned n = static_cast<unsigned>(g.n);
-    if (g.shape.chunk == 16 && g.shape.lanes == 1024) {   // 16384 rows
-      btcs_wg_kernel<S, true, 1024, 16, true><<<n, 1024, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all);
-      continue;
-    }
-    if (g.shape.exact) {
-      // the pipelined kernel moves 16-byte chunks: the state buffers must be 16-byte aligned too
-      const bool stream =
-          g.shape.stream && ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-      if (stream && g.shape.lanes == 1024)
+    // the pipelined kernel moves 16-byte chunks: the state buffers must be 16-byte aligned too
+    if (g.shape.stream && ((reinterpret_cast<uintptr_t>(u) | reinterpret_cast<uintptr_t>(out)) & 15) == 0) {
+      if (g.shape.lanes == 1024)
         btcs_stream_kernel<S, 1024, 8><<<std::min(n, static_cast<unsigned>(stream_grid<S, 1024, 8>(ctx->device))),
                                          1024, 0, st>>>(inst, sys, g.n, u, out);
-      else if (g.shape.lanes == 1024)
-        btcs_wg_kernel<S, true, 1024, 8, true><<<n, 1024, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all);
-      else if (stream)
+      else
         btcs_stream_kernel<S, 512, 16><<<std::min(n, static_cast<unsigned>(stream_grid<S, 512, 16>(ctx->device))),
                                          512, 0, st>>>(inst, sys, g.n, u, out);
-      else
-        btcs_wg_kernel<S, true, 512, 16, true><<<n, 512, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all);
       continue;
     }
-    switch (g.shape.lanes) {
-      case 128: btcs_wg_kernel<S, true, 128, 8><<<n, 128, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all); break;
-      case 256: btcs_wg_kernel<S, true, 256, 8><<<n, 256, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all); break;
-      case 512: btcs_wg_kernel<S, true, 512, 8><<<n, 512, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all); break;
-      default: btcs_wg_kernel<S, true, 1024, 8><<<n, 1024, 0, st>>>(inst, sys, u, out, LA, LC, LD, LX, all); break;
-    }
+    const hipError_t e = launch_btcs_whole(ctx, inst, g, u, out);
+    if (e != hipSuccess) return e;
   }
   if (L > 0 && plan.levels[0].n_blocks) {
     const auto& lv = plan.levels[0];
@@ -2057,73 +1530,6 @@ __global__ void clear_flags_kernel(int* __restrict__ p, int64_t n) {
 }
 
 }  // namespace
-
-template <typename S>
-void resident_launch(const burgers_ctx* ctx, const WgGroup& g, S* u, int steps) {
-  const InstDesc* inst = ctx->inst.as<InstDesc>();
-  const SysDesc* sys = g.sys->as<SysDesc>();
-  const unsigned n = static_cast<unsigned>(g.n);
-  hipStream_t st = ctx->stream;
-  if (g.shape.chunk == 16 && g.shape.lanes == 1024) {   // 16384 rows
-    btcs_resident_kernel<S, 1024, 16, true><<<n, 1024, 0, st>>>(inst, sys, u, steps, nullptr, 0);
-    return;
-  }
-  if (g.shape.exact) {
-    if (g.shape.lanes == 1024)
-      btcs_resident_kernel<S, 1024, 8, true><<<n, 1024, 0, st>>>(inst, sys, u, steps, nullptr, 0);
-    else
-      btcs_resident_kernel<S, 512, 16, true><<<n, 512, 0, st>>>(inst, sys, u, steps, nullptr, 0);
-    return;
-  }
-  switch (g.shape.lanes) {
-    case 128: btcs_resident_kernel<S, 128, 8><<<n, 128, 0, st>>>(inst, sys, u, steps, nullptr, 0); break;
-    case 256: btcs_resident_kernel<S, 256, 8><<<n, 256, 0, st>>>(inst, sys, u, steps, nullptr, 0); break;
-    case 512: btcs_resident_kernel<S, 512, 8><<<n, 512, 0, st>>>(inst, sys, u, steps, nullptr, 0); break;
-    default: btcs_resident_kernel<S, 1024, 8><<<n, 1024, 0, st>>>(inst, sys, u, steps, nullptr, 0); break;
-  }
-}
-
-hipError_t launch_btcs_resident(const burgers_ctx* ctx, const WgGroup& group, void* u, int steps) {
-  if (group.n <= 0 || steps <= 0) return hipSuccess;
-  if (ctx->dtype == BURGERS_F64) resident_launch<double>(ctx, group, static_cast<double*>(u), steps);
-  else resident_launch<float>(ctx, group, static_cast<float*>(u), steps);
-  return hipGetLastError();
-}
-
-// The resident solver recording every step (the adjoint's recompute of a checkpoint segment).
-void record_launch(const burgers_ctx* ctx, const WgGroup& g, const double* src, double* rec, int64_t rstride,
-                   int steps) {
-  const InstDesc* inst = ctx->inst.as<InstDesc>();
-  const SysDesc* sys = g.sys->as<SysDesc>();
-  const unsigned n = static_cast<unsigned>(g.n);
-  hipStream_t st = ctx->stream;
-  double* u = const_cast<double*>(src);   // only read by the recording kernels
-  if (g.shape.chunk == 16 && g.shape.lanes == 1024) {   // 16384 rows
-    btcs_resident_kernel<double, 1024, 16, true, true><<<n, 1024, 0, st>>>(inst, sys, u, steps, rec, rstride);
-    return;
-  }
-  if (g.shape.exact) {
-    if (g.shape.lanes == 1024)
-      btcs_resident_kernel<double, 1024, 8, true, true><<<n, 1024, 0, st>>>(inst, sys, u, steps, rec, rstride);
-    else
-      btcs_resident_kernel<double, 512, 16, true, true><<<n, 512, 0, st>>>(inst, sys, u, steps, rec, rstride);
-    return;
-  }
-  switch (g.shape.lanes) {
-    case 128: btcs_resident_kernel<double, 128, 8, false, true><<<n, 128, 0, st>>>(inst, sys, u, steps, rec, rstride); break;
-    case 256: btcs_resident_kernel<double, 256, 8, false, true><<<n, 256, 0, st>>>(inst, sys, u, steps, rec, rstride); break;
-    case 512: btcs_resident_kernel<double, 512, 8, false, true><<<n, 512, 0, st>>>(inst, sys, u, steps, rec, rstride); break;
-    default: btcs_resident_kernel<double, 1024, 8, false, true><<<n, 1024, 0, st>>>(inst, sys, u, steps, rec, rstride); break;
-  }
-}
-
-hipError_t launch_btcs_record(const burgers_ctx* ctx, const WgGroup& group, const void* src, void* rec,
-                              int64_t rstride, int steps) {
-  if (group.n <= 0 || steps <= 0) return hipSuccess;
-  if (ctx->dtype != BURGERS_F64) return hipErrorInvalidValue;
-  record_launch(ctx, group, static_cast<const double*>(src), static_cast<double*>(rec), rstride, steps);
-  return hipGetLastError();
-}
 
 template <typename S>
 void newton_launch(const burgers_ctx* ctx, const WgGroup& g, const S* u, S* x, int last, int* flags) {
@@ -2149,17 +1555,19 @@ hipError_t launch_newton_whole(const burgers_ctx* ctx, const WgGroup& group, con
   return hipGetLastError();
 }
 
-// Width class of a system solved whole (btcs_solved_whole).  A system of exactly 8192 rows runs the
-// exact kernels (`threads` = 512 lanes of 16 rows, or 1024 of 8), one of exactly 16384 rows 1024 lanes
-// of 16; any other size (up to 8192) takes the narrowest workgroup whose lanes hold at most 8 rows each,
-// so ragged chunks never need more than 8 registers per row array (ragged chunks of up to 16 rows would
-// spill: systems of 8193 to 16383 rows stay on the long-system solvers).
+// Width class of a system solved whole (btcs_solved_whole), by its rows alone, so that every solver of the
+// system (on chip, per step, recording, in a pool) lays it out alike.  Up to 4096 rows a lane takes at most
+// 8: fewer registers, so more workgroups per CU, and a shorter serial chain for a batch too small to fill
+// the chip.  Beyond, 9 to 16 rows a lane: half the lanes, so half the interface solve's share per row, and
+// two workgroups per CU up to 8192 rows (100 steps of the 4097..8191-row systems of a ragged batch of 10^4,
+// as 1024 lanes of at most 8 rows: 2980 us).  `threads` = 1024 asks for 1024 lanes of 8 at 8192 rows.
 WidthClass btcs_width_class(int rows, int threads) {
-  if (rows == kWgRows) return threads == 1024 ? WidthClass{1024, 8, true} : WidthClass{512, 16, true};
-  if (rows == kWholeRows) return WidthClass{1024, 16, true};
-  int lanes = 128;
+  if (rows == kWgRows && threads == 1024) return WidthClass{1024, 8};
+  if (rows > kWgRows) return WidthClass{1024, 16};
+  if (rows > kWgRows / 2) return WidthClass{512, 16};
+  int lanes = 64;
   while (lanes * 8 < rows) lanes *= 2;
-  return WidthClass{lanes, 8, false};
+  return WidthClass{lanes, 8};
 }
 
 // Chunk count of the whole-system and on-chip solvers with `threads` lanes: the largest power of two P <= threads with
@@ -2172,7 +1580,7 @@ int btcs_chunks(int rows, int threads) {
 
 int btcs_wg_capacity() { return kWgRows; }
 int btcs_whole_capacity() { return kWholeRows; }
-bool btcs_solved_whole(int64_t rows) { return rows <= kWgRows || rows == kWholeRows; }
+bool btcs_solved_whole(int64_t rows) { return rows <= kWholeRows; }
 
 int btcs_wg_chunks(int rows) {
   // largest power of two P <= min(threads, rows / 2); rows <= capacity keeps every chunk <= kWgChunk
@@ -2200,10 +1608,7 @@ int btcs_wg_lanes(const std::vector<SysDesc>& systems) {
 // lands in X at each root system's offset.  levels[0] holds the roots that need partitioning.
 hipError_t launch_array_solve(const burgers_ctx* ctx, const BtcsPlan& plan, double* LA, double* LC,
                               double* LD, double* LX, const int* only) {
-  const InstDesc* inst = ctx->inst.as<InstDesc>();
   hipStream_t st = ctx->stream;
-  const double* none = nullptr;
-  double* none_out = nullptr;
   const int L = static_cast<int>(plan.levels.size());
   for (int l = 0; l < L; ++l) {
     const auto& lv = plan.levels[l];
@@ -2213,7 +1618,7 @@ hipError_t launch_array_solve(const burgers_ctx* ctx, const BtcsPlan& plan, doub
   }
   for (int l = L - 1; l >= 0; --l) {
     const auto& lv = plan.levels[l];
-    if (lv.n_wg) reduced_wg_launch<double>(lv, inst, none, none_out, LA, LC, LD, LX, st, only);
+    if (lv.n_wg) reduced_wg_launch(lv, LA, LC, LD, LX, st, only);
     if (lv.n_blocks)
       btcs_array_backsub_kernel<<<lv.n_blocks, kReduceBlock, 0, st>>>(lv.sys->as<SysDesc>(),
                                                                       lv.blocks->as<ChunkBlock>(), LA, LC, LD, LX,

@@ -308,13 +308,13 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   auto add_windows = [&](int32_t i, int32_t R, bool is_cn) {
     burgers::btcs_windows(i, R, ctx->probs[i].bc == BURGERS_BC_PERIODIC, plan->win_rows, is_cn, windows);
   };
-  // whole-system systems grouped by width class (lanes, chunk, exact)
-  std::map<std::tuple<int, int, bool>, std::vector<SysDesc>> wg_state, resident, streamed;
+  // whole-system systems grouped by width class (lanes, chunk)
+  std::map<std::pair<int, int>, std::vector<SysDesc>> wg_state, resident, streamed;
   const int64_t elem = ctx->dtype == BURGERS_F64 ? 8 : 4;
-  auto whole = [&](std::map<std::tuple<int, int, bool>, std::vector<SysDesc>>& groups, int32_t rows, int32_t i,
+  auto whole = [&](std::map<std::pair<int, int>, std::vector<SysDesc>>& groups, int32_t rows, int32_t i,
                    bool is_cn) {
     const burgers::WidthClass w = burgers::btcs_width_class(rows, threads);
-    groups[std::make_tuple(w.lanes, w.chunk, w.exact)].push_back(
+    groups[{w.lanes, w.chunk}].push_back(
         SysDesc{0, -1, rows, burgers::btcs_chunks(rows, w.lanes), i, 0, is_cn ? 1 : 0});
   };
   std::vector<int32_t> stepped, cn, newton;
@@ -329,7 +329,9 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
     const bool is_cn = own_scheme_set(set) && p.scheme == BURGERS_CN;
     if (is_cn) cn.push_back(i);
     const bool is_newton = own_scheme_set(set) && p.scheme == BURGERS_NEWTON;
-    if (want == 2 && (!fits || is_cn || is_newton)) return BURGERS_E_UNSUPPORTED;
+    // (the forced on-chip path takes systems of up to 8192 rows, or of exactly 16384)
+    const bool forced_fits = R0 <= cap || R0 == burgers::btcs_whole_capacity();
+    if (want == 2 && (!forced_fits || is_cn || is_newton)) return BURGERS_E_UNSUPPORTED;
     if (is_newton) {            // Newton iterations of their own, through HBM every step
       stepped.push_back(i);
       newton.push_back(i);
@@ -372,11 +374,11 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   if (rows_used > ctx->level_capacity) return BURGERS_E_NOMEM;   // sized at create for every path
   plan->level_rows = rows_used;
   hipError_t e;
-  auto upload_groups = [&](std::map<std::tuple<int, int, bool>, std::vector<SysDesc>>& groups,
+  auto upload_groups = [&](std::map<std::pair<int, int>, std::vector<SysDesc>>& groups,
                            std::vector<burgers::WgGroup>& out, bool stream) -> hipError_t {
     for (auto& kv : groups) {
       burgers::WgGroup g;
-      g.shape = burgers::WidthClass{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), stream};
+      g.shape = burgers::WidthClass{kv.first.first, kv.first.second, stream};
       g.sys = std::make_unique<DevBuf>();
       g.n = static_cast<int32_t>(kv.second.size());
       hipError_t err = upload_on(ctx->stream, *g.sys, kv.second);
@@ -737,7 +739,7 @@ burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& membe
   const int cap = burgers::btcs_wg_capacity();
   std::vector<burgers::AdjTile> tiles, long_tiles;
   std::vector<std::tuple<int32_t, int64_t, int32_t>> roots;
-  std::map<std::tuple<int, int, bool>, std::vector<SysDesc>> groups;
+  std::map<int, std::vector<SysDesc>> groups;   // by lanes
   int64_t rows = 0;
   for (int32_t i : members) {
     const burgers_problem& p = ctx->probs[i];
@@ -746,10 +748,10 @@ burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& membe
     for (int64_t s0 = 0; s0 < n; s0 += 256)
       tiles.push_back(burgers::AdjTile{ctx->offsets[i], 0, n, p.bc, i, static_cast<int32_t>(s0), 0, 0});
     if (R <= cap) {
-      // 8192-row systems take 1024 lanes of 8 rows (the Newton rows need more registers than BTCS ones)
-      const burgers::WidthClass w = burgers::btcs_width_class(R, 1024);
-      groups[std::make_tuple(w.lanes, w.chunk, w.exact)].push_back(
-          SysDesc{0, -1, R, burgers::btcs_chunks(R, w.lanes), i, 0});
+      // at most 8 rows a lane (the Newton rows need more registers than BTCS ones)
+      int lanes = 128;
+      while (lanes * 8 < R) lanes *= 2;
+      groups[lanes].push_back(SysDesc{0, -1, R, burgers::btcs_chunks(R, lanes), i, 0});
       continue;
     }
     for (int64_t s0 = 0; s0 < n; s0 += 256)
@@ -768,7 +770,7 @@ burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& membe
   np->n_long_tiles = static_cast<int64_t>(long_tiles.size());
   for (auto& kv : groups) {
     burgers::WgGroup g;
-    g.shape = burgers::WidthClass{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first)};
+    g.shape = burgers::WidthClass{kv.first, 8};
     g.sys = std::make_unique<DevBuf>();
     g.n = static_cast<int32_t>(kv.second.size());
     if ((e = upload_on(ctx->stream, *g.sys, kv.second)) != hipSuccess) return from_hip(e);

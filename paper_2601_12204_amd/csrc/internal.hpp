@@ -178,13 +178,12 @@ struct DevBuf {
   template <typename T> T* as() const { return static_cast<T*>(ptr); }
 };
 
-// Shape of the workgroup that solves a system of up to 8192 rows whole: `lanes` threads with chunks of
-// at most `chunk` rows; `exact` when the system has exactly lanes x chunk rows (no ragged chunks).
+// Shape of the workgroup that solves a system of up to 16384 rows whole: `lanes` threads with chunks of
+// at most `chunk` rows.
 struct WidthClass {
   int lanes = 0;
   int chunk = 0;
-  bool exact = false;
-  bool stream = false;   // exact systems with 16-byte aligned rows: the persistent pipelined per-step kernel
+  bool stream = false;   // 8192-row systems with 16-byte aligned rows: the persistent pipelined per-step kernel
 };
 
 // Systems of one width class, one workgroup each.
@@ -394,7 +393,7 @@ hipError_t launch_newton_update(const burgers_ctx* ctx, const AdjTile* tiles, in
 int btcs_wg_capacity();                 // longest system of the exact 512-lane kernels and of the
                                         // partition levels' reduced systems (8192 rows)
 int btcs_whole_capacity();              // longest system one workgroup solves whole (16384 rows)
-bool btcs_solved_whole(int64_t rows);   // up to 8192 rows, or exactly 16384: one workgroup per system
+bool btcs_solved_whole(int64_t rows);   // up to 16384 rows: one workgroup per system
 int btcs_wg_chunks(int rows);
 int btcs_wg_lanes(const std::vector<SysDesc>& systems);
 bool btcs_wg_exact(const std::vector<SysDesc>& systems);   // all of 512 chunks x 16 rows (a constant layout)   // workgroup width that serves all of them           // chunk count the workgroup solver uses for `rows` rows
@@ -410,6 +409,10 @@ hipError_t launch_btcs_resident(const burgers_ctx* ctx, const WgGroup& group, vo
 // (binary64; src is only read).
 hipError_t launch_btcs_record(const burgers_ctx* ctx, const WgGroup& group, const void* src, void* rec,
                               int64_t rstride, int steps);
+// One step of a group's systems, each solved whole, from u to out (inst: the instance table to read, half-dt
+// coefficients for Crank-Nicolson systems).
+hipError_t launch_btcs_whole(const burgers_ctx* ctx, const InstDesc* inst, const WgGroup& group, const void* u,
+                             void* out);
 hipError_t launch_newton_whole(const burgers_ctx* ctx, const WgGroup& group, const void* u, void* x, bool last,
                                int* flags);
 WidthClass btcs_width_class(int rows, int threads);

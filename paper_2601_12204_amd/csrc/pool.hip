@@ -7,7 +7,7 @@
 // That sequence depends only on whether long problems (windows) are in flight, so it is captured into one
 // of two HIP graphs and replayed; the per-slot work lives in device tables refreshed before each tick.  Every slot runs the same
 // kernels, in the same arithmetic, as a context holding its problem alone: the on-chip whole-instance
-// kernels for up to 8192 nodes, and for longer problems the explicit windows (temporal blocking) or the
+// kernels (up to 8192 nodes explicit, 16384 BTCS rows), and for longer problems the explicit windows (temporal blocking) or the
 // truncated BTCS windows.  Pools hold no partition levels, so a BTCS window step whose accuracy bound
 // fails (far beyond the CFL step) is not redone but reported when its slot is retired.
 #include <algorithm>
@@ -28,9 +28,11 @@ using burgers::Tile;
 using burgers::WinDesc;
 
 constexpr int kWholeLanes[4] = {64, 128, 256, 512};
-// BTCS classes of the on-chip solver: (lanes, rows per lane, exact 8192-row layout)
-constexpr int kResLanes[5] = {128, 256, 512, 1024, 512};
-constexpr int kWinGroup = 5;        // launch groups (bits of a mask): whole classes 0-4, windows 5
+// BTCS classes of the on-chip solver: lanes and rows per lane (btcs_width_class)
+constexpr int kResClasses = 6;
+constexpr int kResLanes[kResClasses] = {64, 128, 256, 512, 512, 1024};
+constexpr int kResChunk[kResClasses] = {8, 8, 8, 8, 16, 16};
+constexpr int kWinGroup = kResClasses;   // launch groups (bits of a mask): whole classes, then the windows
 constexpr int kWindowDepth = 128;   // explicit window steps per launch (as a context's default)
 
 size_t align_up(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
@@ -59,7 +61,7 @@ struct burgers_pool {
   // device tables (one buffer) and their host image
   DevBuf tables;
   std::vector<unsigned char> image;
-  size_t off_whole[5] = {}, off_win = 0, off_copy = 0;
+  size_t off_whole[kResClasses] = {}, off_win = 0, off_copy = 0;
   std::vector<burgers::WgGroup> res;                 // BTCS on-chip classes (views into `tables`)
   burgers::BtcsPlan bplan;                           // BTCS windows (views into `tables`), no levels
   DevBuf win_view, copy_view;
@@ -83,7 +85,6 @@ int rows_of(const burgers_problem& p) { return static_cast<int>(p.bc == BURGERS_
 
 // launch group of a problem in the pool
 int group_of(const burgers_pool* pl, const burgers_problem& p) {
-  const int cap_chip = burgers::btcs_wg_capacity();
   if (pl->scheme == BURGERS_EXPLICIT) {
     if (p.n > burgers::explicit_block_capacity()) return kWinGroup;
     const int lanes = burgers::explicit_block_lanes(static_cast<int>(p.n));
@@ -92,12 +93,11 @@ int group_of(const burgers_pool* pl, const burgers_problem& p) {
     return 3;
   }
   const int R = rows_of(p);
-  if (R > cap_chip) return kWinGroup;
+  if (!burgers::btcs_solved_whole(R)) return kWinGroup;
   const burgers::WidthClass w = burgers::btcs_width_class(R, 512);
-  if (w.exact) return 4;
-  for (int c = 0; c < 4; ++c)
-    if (kResLanes[c] == w.lanes) return c;
-  return 3;
+  int c = 0;
+  while (c < kResClasses - 1 && (kResLanes[c] != w.lanes || kResChunk[c] != w.chunk)) ++c;
+  return c;
 }
 
 // Host image of the device tables for the coming tick: every slot's entries, empty (no-op) for free
@@ -175,7 +175,7 @@ hipError_t enqueue_tick(burgers_pool* pl, uint32_t mask) {
     }
     return e;
   }
-  for (int c = 0; c < 5; ++c)
+  for (int c = 0; c < kResClasses; ++c)
     if ((mask & (1u << c)) && (e = burgers::launch_btcs_resident(ctx, pl->res[c], u, K)) != hipSuccess) return e;
   if (mask & (1u << kWinGroup)) {
     if ((e = burgers::launch_btcs_window_reset(ctx, pl->bplan)) != hipSuccess) return e;
@@ -283,13 +283,13 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
     entry = sizeof(BlockTile);
   } else {
     const int64_t kept = 4096 - 2 * burgers::btcs_window_halo();
-    pl->wx = longest - 2 > burgers::btcs_wg_capacity() ? (longest + kept - 1) / kept : 0;
+    pl->wx = !burgers::btcs_solved_whole(longest - 2) ? (longest + kept - 1) / kept : 0;
     entry = sizeof(WinDesc);
   }
   pl->tx = pl->wx ? (pl->cap + tile_nodes - 1) / tile_nodes : 0;
   const size_t whole_entry = scheme == BURGERS_EXPLICIT ? sizeof(BlockTile) : sizeof(SysDesc);
   size_t off = 0;
-  for (int c = 0; c < 5; ++c) {
+  for (int c = 0; c < kResClasses; ++c) {
     pl->off_whole[c] = off;
     off = align_up(off + static_cast<size_t>(slots) * whole_entry);
   }
@@ -316,9 +316,9 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
   view(pl->win_view, pl->tables.ptr, pl->off_win, static_cast<size_t>(slots * pl->wx) * entry, st);
   view(pl->copy_view, pl->tables.ptr, pl->off_copy, static_cast<size_t>(slots * pl->tx) * sizeof(Tile), st);
   if (scheme == BURGERS_BTCS) {
-    for (int c = 0; c < 5; ++c) {
+    for (int c = 0; c < kResClasses; ++c) {
       burgers::WgGroup g;
-      g.shape = c == 4 ? burgers::WidthClass{512, 16, true} : burgers::WidthClass{kResLanes[c], 8, false};
+      g.shape = burgers::WidthClass{kResLanes[c], kResChunk[c]};
       g.sys = std::make_unique<DevBuf>();
       view(*g.sys, pl->tables.ptr, pl->off_whole[c], static_cast<size_t>(slots) * sizeof(SysDesc), st);
       g.n = static_cast<int32_t>(slots);
