@@ -266,13 +266,6 @@ burgers_status ensure_explicit(burgers_ctx* ctx, int set) {
   return BURGERS_OK;
 }
 
-// BTCS launch plan of one instance subset under the context's forced path (0 = automatic).
-//   path 1: every step through HBM; whole-system solves for systems of up to 8192 rows, partition
-//           levels for longer ones.
-//   path 2: systems of up to 8192 rows stay on chip for all steps of a launch (every system must fit).
-//   path 3: partition levels for every system of at least 32 rows (shorter ones solved whole).
-//   automatic: on chip for systems that fit, partition levels for longer ones.
-// Reduced-system rows are carved from the context's level arrays.
 burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& members);
 
 // Rows a partition level leaves for the next one.  Level 0 (from the state) runs the block partition,
@@ -282,6 +275,15 @@ int32_t reduced_rows(int level, int32_t chunks) {
   return 2 * chunks;
 }
 
+// Implicit launch plan of one instance subset under the context's forced path (0 = automatic).
+//   path 1: every step through HBM; whole-system solves for systems of up to 16384 rows, windows or
+//           partition levels for longer ones.
+//   path 2: systems of up to 8192 rows (or exactly 16384) stay on chip for all steps of a launch (every
+//           system must fit).
+//   path 3: partition levels for every system of at least 32 rows (shorter ones solved whole).
+//   automatic: on chip for systems that fit (BTCS up to 16384 rows, Crank-Nicolson and Newton up to 8192),
+//           the others as on path 1.
+// Reduced-system rows are carved from the context's level arrays.
 burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   const int want = set == kSetBtcsHbm ? 1 : ctx->plan.btcs_path;
   const int threads = ctx->plan.btcs_block ? ctx->plan.btcs_block : burgers::kResidentThreadsDefault;
@@ -309,13 +311,18 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
     burgers::btcs_windows(i, R, ctx->probs[i].bc == BURGERS_BC_PERIODIC, plan->win_rows, is_cn, windows);
   };
   // whole-system systems grouped by width class (lanes, chunk)
-  std::map<std::pair<int, int>, std::vector<SysDesc>> wg_state, resident, streamed;
+  std::map<std::pair<int, int>, std::vector<SysDesc>> wg_state, resident, streamed, cn_chip, newton_chip;
   const int64_t elem = ctx->dtype == BURGERS_F64 ? 8 : 4;
   auto whole = [&](std::map<std::pair<int, int>, std::vector<SysDesc>>& groups, int32_t rows, int32_t i,
                    bool is_cn) {
     const burgers::WidthClass w = burgers::btcs_width_class(rows, threads);
     groups[{w.lanes, w.chunk}].push_back(
         SysDesc{0, -1, rows, burgers::btcs_chunks(rows, w.lanes), i, 0, is_cn ? 1 : 0});
+  };
+  // Crank-Nicolson and Newton systems of up to 8192 rows, held on chip on the automatic path
+  auto on_chip = [&](std::map<std::pair<int, int>, std::vector<SysDesc>>& groups, int32_t rows, int32_t i) {
+    const burgers::WidthClass w = burgers::chip_width_class(rows);
+    groups[{w.lanes, w.chunk}].push_back(SysDesc{0, -1, rows, burgers::btcs_chunks(rows, w.lanes), i, 0});
   };
   std::vector<int32_t> stepped, cn, newton;
   std::vector<std::vector<SysDesc>> red_sys, wg_sys;
@@ -324,17 +331,26 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
     const burgers_problem& p = ctx->probs[i];
     const int32_t R0 = static_cast<int32_t>(p.bc == BURGERS_BC_PERIODIC ? p.n : p.n - 2);
     const bool fits = burgers::btcs_solved_whole(R0);
-    // Crank-Nicolson instances (advanced by their own scheme) need the old state after each solve, so
-    // they always step through HBM
+    // (Crank-Nicolson instances are those advanced by their own scheme; burgers_step_btcs takes them as BTCS)
     const bool is_cn = own_scheme_set(set) && p.scheme == BURGERS_CN;
     if (is_cn) cn.push_back(i);
     const bool is_newton = own_scheme_set(set) && p.scheme == BURGERS_NEWTON;
     // (the forced on-chip path takes systems of up to 8192 rows, or of exactly 16384)
     const bool forced_fits = R0 <= cap || R0 == burgers::btcs_whole_capacity();
     if (want == 2 && (!forced_fits || is_cn || is_newton)) return BURGERS_E_UNSUPPORTED;
-    if (is_newton) {            // Newton iterations of their own, through HBM every step
-      stepped.push_back(i);
+    if (is_newton) {            // Newton iterations of their own
       newton.push_back(i);
+      if (want == 0 && R0 <= cap) {
+        on_chip(newton_chip, R0, i);
+        continue;
+      }
+      stepped.push_back(i);
+      plan->newton = true;
+      plan->newton_whole = want != 0;
+      continue;
+    }
+    if (is_cn && want == 0 && R0 <= cap) {
+      on_chip(cn_chip, R0, i);
       continue;
     }
     if ((want == 0 || want == 2) && fits && !is_cn) {
@@ -393,7 +409,6 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   if (!newton.empty()) {
     burgers_status nst = ensure_newton(ctx, newton);
     if (nst != BURGERS_OK) return nst;
-    plan->newton = true;
   }
   plan->inst_half = std::make_unique<DevBuf>();
   if (!cn.empty()) {
@@ -407,6 +422,8 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   if ((e = upload_groups(wg_state, plan->wg_state, false)) != hipSuccess ||
       (e = upload_groups(streamed, plan->wg_state, true)) != hipSuccess ||
       (e = upload_groups(resident, plan->resident, false)) != hipSuccess ||
+      (e = upload_groups(cn_chip, plan->cn_chip, false)) != hipSuccess ||
+      (e = upload_groups(newton_chip, plan->newton_chip, false)) != hipSuccess ||
       (e = upload_on(ctx->stream, *plan->copy, ct)) != hipSuccess)
     return from_hip(e);
   plan->win = std::make_unique<DevBuf>();
@@ -517,6 +534,10 @@ hipError_t enqueue_btcs(burgers_ctx* ctx, int set, void* u, int64_t nsteps, int 
     const int k = static_cast<int>(std::min<int64_t>(nsteps - done, int64_t{1} << 30));
     for (const burgers::WgGroup& g : pl.resident)
       if ((e = burgers::launch_btcs_resident(ctx, g, u, k)) != hipSuccess) return e;
+    for (const burgers::WgGroup& g : pl.cn_chip)
+      if ((e = burgers::launch_cn_resident(ctx, pl.inst_half->as<InstDesc>(), g, u, k)) != hipSuccess) return e;
+    for (const burgers::WgGroup& g : pl.newton_chip)
+      if ((e = burgers::launch_newton_resident(ctx, g, u, k, ctx->newton->flags.as<int>())) != hipSuccess) return e;
     done += k;
   }
   if (pl.n_copy == 0 || part == kPartOnChip) return e;
@@ -527,14 +548,16 @@ hipError_t enqueue_btcs(burgers_ctx* ctx, int set, void* u, int64_t nsteps, int 
     if ((e = burgers::launch_btcs_step(ctx, pl, bufs[cur], bufs[cur ^ 1], s)) != hipSuccess) return e;
     if (pl.newton) {
       burgers::NewtonPlan& np = *ctx->newton;
-      const burgers::AdjTile* nt = np.tiles->as<burgers::AdjTile>();
-      if ((e = burgers::launch_newton_init(ctx, nt, np.n_tiles, bufs[cur], bufs[cur ^ 1])) != hipSuccess) return e;
       const burgers::AdjTile* lt = np.long_tiles->as<burgers::AdjTile>();
+      if ((pl.newton_whole && (e = burgers::launch_newton_init(ctx, np.tiles->as<burgers::AdjTile>(), np.n_tiles,
+                                                               bufs[cur], bufs[cur ^ 1])) != hipSuccess) ||
+          (e = burgers::launch_newton_init(ctx, lt, np.n_long_tiles, bufs[cur], bufs[cur ^ 1])) != hipSuccess)
+        return e;
       int* flags = np.flags.as<int>();
       for (int it = 0; it < burgers::kNewtonIters; ++it) {
         const bool last = it == burgers::kNewtonIters - 1;
         for (const burgers::WgGroup& g : np.whole)
-          if ((e = burgers::launch_newton_whole(ctx, g, bufs[cur], bufs[cur ^ 1], last, flags)) != hipSuccess) return e;
+          if (pl.newton_whole && (e = burgers::launch_newton_whole(ctx, g, bufs[cur], bufs[cur ^ 1], last, flags)) != hipSuccess) return e;
         if (np.n_long_tiles == 0) continue;
         if ((e = burgers::launch_newton_assemble(ctx, lt, np.n_long_tiles, bufs[cur], bufs[cur ^ 1], np.NA.as<double>(),
                                                  np.NC.as<double>(), np.ND.as<double>(), flags)) != hipSuccess ||
@@ -557,7 +580,7 @@ bool explicit_part_busy(const burgers::ExplicitPlan& pl, int part) {
   return part == kPartOnChip ? !pl.whole_classes.empty() : pl.n_win > 0;
 }
 bool btcs_part_busy(const burgers::BtcsPlan& pl, int part) {
-  return part == kPartOnChip ? !pl.resident.empty() : pl.n_copy > 0;
+  return part == kPartOnChip ? !pl.resident.empty() || !pl.cn_chip.empty() || !pl.newton_chip.empty() : pl.n_copy > 0;
 }
 
 // scheme -1: each instance's own scheme, explicit instances nsteps steps and BTCS ones nsteps_btcs.
@@ -731,8 +754,9 @@ hipError_t build_array_solve(burgers_ctx* ctx, const std::vector<std::tuple<int3
   return hipSuccess;
 }
 
-// Newton plan over the given instances (built once per context): systems of up to 8192 rows iterate in
-// one fused kernel per iteration (grouped by width class), longer ones through the array path.
+// Newton plan of the steps through HBM over the given instances (built once per context): systems of up to
+// 8192 rows iterate in one fused kernel per iteration (grouped by width class; the automatic path holds them
+// on chip instead), longer ones through the array path.
 burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& members) {
   if (ctx->newton) return BURGERS_OK;
   auto np = std::make_unique<burgers::NewtonPlan>();
@@ -745,9 +769,9 @@ burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& membe
     const burgers_problem& p = ctx->probs[i];
     const int32_t n = static_cast<int32_t>(p.n);
     const int32_t R = p.bc == BURGERS_BC_PERIODIC ? n : n - 2;
-    for (int64_t s0 = 0; s0 < n; s0 += 256)
-      tiles.push_back(burgers::AdjTile{ctx->offsets[i], 0, n, p.bc, i, static_cast<int32_t>(s0), 0, 0});
     if (R <= cap) {
+      for (int64_t s0 = 0; s0 < n; s0 += 256)
+        tiles.push_back(burgers::AdjTile{ctx->offsets[i], 0, n, p.bc, i, static_cast<int32_t>(s0), 0, 0});
       // at most 8 rows a lane (the Newton rows need more registers than BTCS ones)
       int lanes = 128;
       while (lanes * 8 < R) lanes *= 2;

@@ -271,6 +271,7 @@ __device__ __forceinline__ SlotLane slot_lane(int t, int R, int P, bool dirichle
 // BTCS rows for slot_eliminate: slot j from its old value.
 struct SlotRows {
   double r, D, a, b;   // a, b: Dirichlet values
+  static constexpr bool kInOrder = false;
   __device__ __forceinline__ void row(int, double ui, double& al, double& be, double& ga, double& de) const {
     btcs_row(ui, r, D, al, be, ga);
     de = ui;
@@ -307,6 +308,9 @@ __device__ __forceinline__ void slot_eliminate(const Rows& rows, const SlotLane&
       ga[j] = cj * inv;
       de[j] = __builtin_fma(-ai, de[j - 1], dj * inv);
     }
+    // (rows of many terms: assembled one after another, or the scheduler forms them all up front and holds
+    // them in registers through the pivot chain)
+    if constexpr (Rows::kInOrder) __builtin_amdgcn_sched_barrier(0);
   }
   // backward: the coupling to x_{j+1} becomes a coupling to y_t (slot M-2 already has this form)
 #pragma unroll
@@ -337,6 +341,29 @@ template <int M>
 __device__ __forceinline__ double slot_value(int j, const double (&al)[M], const double (&ga)[M],
                                              const double (&de)[M], double yp, double y) {
   return j < M - 1 ? __builtin_fma(-ga[j], y, __builtin_fma(-al[j], yp, de[j])) : y;
+}
+
+// The slot counts of a class: M = ceil(R / P) is 2 to 8 on 64 lanes (P may be less there), 5 to 8 on wider
+// workgroups, 9 to 16 in the classes of longer chunks (see btcs_width_class).
+template <int NT, int MC, typename F>
+__device__ __forceinline__ void with_slots(int R, int P, F&& f) {
+#define BURGERS_SLOTS(K)                                                             \
+  case K:                                                                            \
+    if constexpr (K <= MC && (MC == 16 ? K > 8 : K > 4 || NT == 64)) f.template run<K, false>(); \
+    break;
+  if constexpr (NT > 64) {
+    if (R == NT * MC) {   // every lane full: no slot is tested
+      f.template run<MC, true>();
+      return;
+    }
+  }
+  switch ((R + P - 1) / P) {
+    BURGERS_SLOTS(2) BURGERS_SLOTS(3) BURGERS_SLOTS(4) BURGERS_SLOTS(5) BURGERS_SLOTS(6) BURGERS_SLOTS(7)
+    BURGERS_SLOTS(8) BURGERS_SLOTS(9) BURGERS_SLOTS(10) BURGERS_SLOTS(11) BURGERS_SLOTS(12) BURGERS_SLOTS(13)
+    BURGERS_SLOTS(14) BURGERS_SLOTS(15) BURGERS_SLOTS(16)
+    default: break;
+  }
+#undef BURGERS_SLOTS
 }
 
 }  // namespace burgers

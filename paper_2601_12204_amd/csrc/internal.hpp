@@ -201,10 +201,13 @@ struct BtcsPlan {
   std::unique_ptr<DevBuf> copy;              // Tile[] of the instances stepped through HBM (copy-back)
   int64_t n_copy = 0;
   std::vector<WgGroup> wg_state;             // solved whole per step, straight from and to the state
-  // Crank-Nicolson instances: solved per step with the coefficients of dt/2 (a copy of the instance
-  // table with r and D halved); their systems carry the `cn` flag and store u' = 2 y - u
+  // Crank-Nicolson instances: solved with the coefficients of dt/2 (a copy of the instance table with r
+  // and D halved); stepped through HBM, their systems carry the `cn` flag and store u' = 2 y - u
   std::unique_ptr<DevBuf> inst_half;         // InstDesc[count], or empty: the context's table
-  bool newton = false;                       // the context's Newton instances step with this plan
+  // Crank-Nicolson and Newton systems of up to 8192 rows kept on chip for all steps of a launch (automatic path)
+  std::vector<WgGroup> cn_chip, newton_chip;
+  bool newton = false;                       // Newton instances step through HBM with this plan: the longer
+  bool newton_whole = false;                 // ones, and (forced paths) those of up to 8192 rows too
   // partition hierarchy for the long systems
   struct Level {
     std::unique_ptr<DevBuf> sys;             // SysDesc[] of the systems reduced at this level
@@ -277,7 +280,7 @@ struct AdjointPlan {
 // binary64 arrays and solved by the partition solver's array path.
 constexpr int kNewtonIters = 4;
 struct NewtonPlan {
-  std::unique_ptr<DevBuf> tiles;                    // AdjTile[] (256 nodes each) of all Newton instances
+  std::unique_ptr<DevBuf> tiles;                    // AdjTile[] (256 nodes each) of the instances below
   int64_t n_tiles = 0;
   std::vector<WgGroup> whole;                       // systems of up to 8192 rows: one fused kernel per iteration
   std::unique_ptr<DevBuf> long_tiles;               // AdjTile[] of the longer ones (array path)
@@ -409,6 +412,11 @@ hipError_t launch_btcs_resident(const burgers_ctx* ctx, const WgGroup& group, vo
 // (binary64; src is only read).
 hipError_t launch_btcs_record(const burgers_ctx* ctx, const WgGroup& group, const void* src, void* rec,
                               int64_t rstride, int steps);
+// Crank-Nicolson (half: the instance table with r and D halved) and Newton systems of up to 8192 rows held on
+// chip for `steps` steps, in place (implicit_chip.hip).
+WidthClass chip_width_class(int rows);
+hipError_t launch_cn_resident(const burgers_ctx* ctx, const InstDesc* half, const WgGroup& group, void* u, int steps);
+hipError_t launch_newton_resident(const burgers_ctx* ctx, const WgGroup& group, void* u, int steps, int* flags);
 // One step of a group's systems, each solved whole, from u to out (inst: the instance table to read, half-dt
 // coefficients for Crank-Nicolson systems).
 hipError_t launch_btcs_whole(const burgers_ctx* ctx, const InstDesc* inst, const WgGroup& group, const void* u,

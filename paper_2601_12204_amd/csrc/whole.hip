@@ -83,29 +83,6 @@ __device__ __forceinline__ void resident_body(const InterfaceSpace<double, NT>& 
   }
 }
 
-// The slot counts of a class: M = ceil(R / P) is 2 to 8 on 64 lanes (P may be less there), 5 to 8 on wider
-// workgroups, 9 to 16 in the classes of longer chunks (see btcs_width_class).
-template <int NT, int MC, typename F>
-__device__ __forceinline__ void with_slots(int R, int P, F&& f) {
-#define BURGERS_SLOTS(K)                                                             \
-  case K:                                                                            \
-    if constexpr (K <= MC && (MC == 16 ? K > 8 : K > 4 || NT == 64)) f.template run<K, false>(); \
-    break;
-  if constexpr (NT > 64) {
-    if (R == NT * MC) {   // every lane full: no slot is tested
-      f.template run<MC, true>();
-      return;
-    }
-  }
-  switch ((R + P - 1) / P) {
-    BURGERS_SLOTS(2) BURGERS_SLOTS(3) BURGERS_SLOTS(4) BURGERS_SLOTS(5) BURGERS_SLOTS(6) BURGERS_SLOTS(7)
-    BURGERS_SLOTS(8) BURGERS_SLOTS(9) BURGERS_SLOTS(10) BURGERS_SLOTS(11) BURGERS_SLOTS(12) BURGERS_SLOTS(13)
-    BURGERS_SLOTS(14) BURGERS_SLOTS(15) BURGERS_SLOTS(16)
-    default: break;
-  }
-#undef BURGERS_SLOTS
-}
-
 template <typename S, int NT, bool REC>
 struct ResidentRun {
   const InterfaceSpace<double, NT>& ws;

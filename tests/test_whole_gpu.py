@@ -38,3 +38,46 @@ def test_btcs_slot_classes(dtype):
     step = device_run(batch, 13, dtype, how="run", plan=dict(btcs_path=1))
     assert np.array_equal(chip, step)
     check_batch(batch, chip, 13, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_cn_slot_classes(dtype):
+    """Crank-Nicolson systems of up to 8192 rows are held on chip, longer ones take the per-step solvers."""
+    batch = edge_batch(3300, ROWS + [8192], W.CN)
+    announce(f"cn slot classes {dtype}, {batch.count} systems, 9 steps")
+    got = device_run(batch, 9, dtype, how="run")
+    check_batch(batch, got, 9, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_newton_slot_classes(dtype):
+    """Newton systems of up to 8192 rows are held on chip (at the CFL step every row stays dominant and the
+    increments converge, so the checks report nothing)."""
+    batch = edge_batch(3500, [r for r in ROWS if 63 <= r <= 8192] + [8192, 9000], W.NEWTON)
+    announce(f"newton slot classes {dtype}, {batch.count} systems, 5 steps")
+    got = device_run(batch, 5, dtype, how="run")
+    check_batch(batch, got, 5, dtype)
+
+
+def test_newton_checks_alike_on_chip_and_per_step():
+    """The dominance and increment checks report the same on chip and through HBM (groups of 64 unknowns),
+    from in range to far beyond it, on row counts whose lanes' chunks straddle the groups."""
+    import paper_2601_12204_amd as B
+    seen = set()
+    for k, (n, factor) in enumerate([(70, 1.0), (70, 12.0), (200, 1.0), (200, 30.0), (777, 1.0), (777, 40.0),
+                                     (1500, 25.0), (5000, 1.0), (5000, 60.0)]):
+        for bc in (W.BC_PERIODIC, W.BC_DIRICHLET):
+            batch = W.random_batch(3700 + 2 * k + bc, 1, n, n, bc=bc, scheme=W.NEWTON, amplitude=3.0, nu_lo=1e-3,
+                                   nu_hi=2e-3)
+            set_cfl_steps(batch, btcs_factor=factor, explicit_factor=factor)
+            reports = []
+            for plan in (None, dict(btcs_path=1)):
+                announce(f"newton checks n={n} bc={bc} x{factor} plan={plan}")
+                try:
+                    device_run(batch, 1, "f64", how="run", plan=plan)
+                    reports.append(0)
+                except B.BurgersError as err:
+                    reports.append(err.status)
+            assert reports[0] == reports[1], (n, bc, factor, reports)
+            seen.add(reports[0])
+    assert seen == {0, -7}
