@@ -85,6 +85,68 @@ InstDesc inst_desc(const burgers_problem& p, int64_t off) {
   return d;
 }
 
+// Runs independent chains of launches: over the context's stream and up to three side streams of the context,
+// forked from it and joined back with events (under graph capture they become parallel branches of the
+// graph).  A process has four hardware queues here, and streams beyond them share one: a stream waiting for an
+// event then holds up the others of its queue, so no more are taken than the chains' estimates need (three
+// contexts in turn on three side streams each, a small ragged batch: 505 us a call, on one each 358).
+// Chains of little work beside the longest stay on one stream: a fork and join cost about as much as they
+// would gain.
+hipError_t run_tasks(burgers_ctx* ctx, std::vector<Task>& tasks, bool serial) {
+  constexpr double kWorthForking = 15.0;   // us
+  std::stable_sort(tasks.begin(), tasks.end(), [](const Task& x, const Task& y) { return x.us > y.us; });
+  double beside = 0;
+  for (size_t k = 1; k < tasks.size(); ++k) beside += tasks[k].us;
+  hipError_t e = hipSuccess;
+  if (serial || beside < kWorthForking) {
+    for (const Task& t : tasks)
+      if ((e = t.run()) != hipSuccess) return e;
+    return e;
+  }
+  // into as few streams as finish with the longest chain (or with an even share of all of it)
+  constexpr int kStreams = 4;
+  const double room = 1.1 * std::max(tasks[0].us, (tasks[0].us + beside) / kStreams);
+  double load[kStreams] = {0, 0, 0, 0};
+  std::vector<int> place(tasks.size());
+  for (size_t k = 0; k < tasks.size(); ++k) {
+    int q = 0;
+    while (q < kStreams && load[q] + tasks[k].us > room) ++q;
+    if (q == kStreams) q = static_cast<int>(std::min_element(load, load + kStreams) - load);
+    place[k] = q;
+    load[q] += tasks[k].us;
+  }
+  for (int q = 1; q < kStreams; ++q) {
+    if (load[q] == 0) continue;
+    if (!ctx->side[q - 1] && (e = hipStreamCreateWithFlags(&ctx->side[q - 1], hipStreamNonBlocking)) != hipSuccess) return e;
+    if (!ctx->joined[q - 1] &&
+        (e = hipEventCreateWithFlags(&ctx->joined[q - 1], hipEventDisableTiming)) != hipSuccess)
+      return e;
+  }
+  if (!ctx->forked && (e = hipEventCreateWithFlags(&ctx->forked, hipEventDisableTiming)) != hipSuccess) return e;
+  hipStream_t main = ctx->stream;
+  if ((e = hipEventRecord(ctx->forked, main)) != hipSuccess) return e;
+  for (int q = 1; q < kStreams && e == hipSuccess; ++q)
+    if (load[q] > 0) e = hipStreamWaitEvent(ctx->side[q - 1], ctx->forked, 0);
+  // chains of few launches first: the host is done with them soon, and a chain of many then delays none
+  std::vector<size_t> order(tasks.size());
+  for (size_t k = 0; k < order.size(); ++k) order[k] = k;
+  std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return tasks[x].launches < tasks[y].launches; });
+  for (size_t k : order) {
+    if (e != hipSuccess) break;
+    if (place[k] > 0) ctx->stream = ctx->side[place[k] - 1];
+    e = tasks[k].run();
+    ctx->stream = main;
+  }
+  // (joined after an error too: nothing enqueued may outlive the context's stream order)
+  for (int q = 1; q < kStreams; ++q) {
+    if (load[q] == 0) continue;
+    hipError_t j = hipEventRecord(ctx->joined[q - 1], ctx->side[q - 1]);
+    if (j == hipSuccess) j = hipStreamWaitEvent(main, ctx->joined[q - 1], 0);
+    if (e == hipSuccess) e = j;
+  }
+  return e;
+}
+
 }  // namespace burgers
 
 namespace {
@@ -217,7 +279,9 @@ burgers_status ensure_explicit(burgers_ctx* ctx, int set) {
     auto lanes_of = [](const BlockTile& x) { return burgers::explicit_block_lanes(x.width); };
     std::stable_sort(whole.begin(), whole.end(), [&](const BlockTile& x, const BlockTile& y) {
       const int lx = lanes_of(x), ly = lanes_of(y);
-      return lx != ly ? lx > ly : x.rk4 < y.rk4;
+      if (lx != ly) return lx > ly;
+      if (x.rk4 != y.rk4) return x.rk4 < y.rk4;
+      return lx == 64 && (x.width + 63) / 64 > (y.width + 63) / 64;   // (one wave each: the longest running first)
     });
     plan->whole_classes.clear();
     for (size_t k = 0; k < whole.size();) {
@@ -228,12 +292,18 @@ burgers_status ensure_explicit(burgers_ctx* ctx, int set) {
       plan->whole_classes.push_back({lanes, static_cast<int64_t>(k), static_cast<int64_t>(e - k) - rk4, rk4});
       k = e;
     }
-    // the narrower classes packed for one launch per scheme, 512 / lanes instances of a class per
+    // the classes below the widest packed for one launch per scheme, 512 / lanes instances of a class per
     // workgroup (widest first); the widest class keeps its own kernel, whose step loop compiles to fewer
-    // registers than the pack kernel's (C2, instances of 8192 nodes: 61.9 against 63.9 ms)
+    // registers than the pack kernel's (4096 instances of 8192 nodes: 61.9 against 63.9 ms).  Instances of one
+    // wave are packed only beside others (one launch instead of two that may have to wait for each other);
+    // alone they take workgroups of four waves, one per SIMD (64 instances of 1000 nodes, binary64: 0.22 us a
+    // step against 0.39 with eight)
+    plan->pack_waves = std::any_of(plan->whole_classes.begin(), plan->whole_classes.end(), [](const auto& c) {
+      return c.lanes > 64 && c.lanes < burgers::explicit_pack_lanes();
+    });
     std::vector<burgers::BlockPack> fe_packs, rk4_packs;
     for (const auto& c : plan->whole_classes) {
-      if (c.lanes >= burgers::explicit_pack_lanes()) continue;
+      if (c.lanes >= burgers::explicit_pack_lanes() || (c.lanes == 64 && !plan->pack_waves)) continue;
       const int per = burgers::explicit_pack_lanes() / c.lanes;
       auto pack = [&](int64_t first, int64_t count, std::vector<burgers::BlockPack>& out) {
         for (int64_t q = 0; q < count; q += per)
@@ -474,73 +544,89 @@ int64_t level_rows_needed(const burgers_ctx* ctx) {
   return rows;
 }
 
-// Independent launch groups of a call (they advance disjoint instances): the whole instances held on chip,
-// and the instances stepped through HBM (windows, per-step solves), of each scheme.
-enum Part { kPartAll = 0, kPartOnChip = 1, kPartThroughHbm = 2 };
-
-// Enqueue nsteps explicit steps of one subset (or of one part of it); the final state lands in u.
-hipError_t enqueue_explicit(burgers_ctx* ctx, int set, void* u, int64_t nsteps, int part = kPartAll) {
-  const burgers::ExplicitPlan& pl = *ctx->explicit_plans[set];
-  void* work = ctx->work.ptr;
-  hipError_t e = hipSuccess;
-  if (pl.path == 1) {
-    if (part == kPartOnChip) return e;
-    void* bufs[2] = {u, work};
-    int cur = 0;
-    for (int64_t s = 0; s < nsteps; ++s) {
-      if ((e = burgers::launch_explicit_stream(ctx, pl.stream->as<Tile>(), pl.n_stream, bufs[cur], bufs[cur ^ 1])) != hipSuccess)
-        return e;
-      cur ^= 1;
-    }
-    if (cur) e = burgers::launch_copy_tiles(ctx, pl.stream->as<Tile>(), pl.n_stream, work, u);
-    return e;
-  }
-  // whole instances, in place: all steps at once, or `depth` per launch on path 3
-  const int64_t whole_chunk = pl.path == 3 ? pl.depth : (int64_t{1} << 30);
-  for (int64_t done = 0; part != kPartThroughHbm && done < nsteps;) {
-    const int k = static_cast<int>(std::min(whole_chunk, nsteps - done));
-    for (const auto& c : pl.whole_classes)
-      if (c.lanes >= burgers::explicit_pack_lanes() &&
-          (e = burgers::launch_explicit_block(ctx, pl.whole->as<BlockTile>() + c.offset, c.n_fe, c.n_rk4, u, u, k,
-                                              c.lanes)) != hipSuccess)
-        return e;
-    if ((e = burgers::launch_explicit_packs(ctx, pl.whole->as<BlockTile>(), pl.packs->as<burgers::BlockPack>(),
-                                            pl.n_packs_fe, pl.n_packs_rk4, u, k)) != hipSuccess)
-      return e;
-    done += k;
-  }
-  // windows of long instances: `depth` steps per launch, ping-pong
-  if (pl.n_win > 0 && part != kPartOnChip) {
-    void* bufs[2] = {u, work};
-    int cur = 0;
-    for (int64_t done = 0; done < nsteps;) {
-      const int k = static_cast<int>(std::min<int64_t>(pl.depth, nsteps - done));
-      if ((e = burgers::launch_explicit_block(ctx, pl.win->as<BlockTile>(), pl.n_win - pl.n_win_rk4, pl.n_win_rk4,
-                                              bufs[cur], bufs[cur ^ 1], k)) != hipSuccess)
-        return e;
-      cur ^= 1;
-      done += k;
-    }
-    if (cur) e = burgers::launch_copy_tiles(ctx, pl.win_copy->as<Tile>(), pl.n_win_copy, work, u);
-  }
-  return e;
+// The independent launch chains of a call (they advance disjoint instances), each with a rough time: the
+// larger of its latency and its throughput on an otherwise idle chip, in us per step, from measurements of
+// the kernels (only their order and rough size matter: run_tasks spreads the chains over streams by it).
+double chain_us(int64_t steps, double latency, double nodes, double nodes_per_us) {
+  return static_cast<double>(steps) * std::max(latency, nodes / nodes_per_us);
 }
 
-// Enqueue nsteps BTCS steps of one subset (or of one part of it); the final state lands in u.
-hipError_t enqueue_btcs(burgers_ctx* ctx, int set, void* u, int64_t nsteps, int part = kPartAll) {
-  const burgers::BtcsPlan& pl = *ctx->btcs[set];
-  hipError_t e = hipSuccess;
-  for (int64_t done = 0; part != kPartThroughHbm && done < nsteps;) {   // on-chip systems, in place
-    const int k = static_cast<int>(std::min<int64_t>(nsteps - done, int64_t{1} << 30));
-    for (const burgers::WgGroup& g : pl.resident)
-      if ((e = burgers::launch_btcs_resident(ctx, g, u, k)) != hipSuccess) return e;
-    for (const burgers::WgGroup& g : pl.cn_chip)
-      if ((e = burgers::launch_cn_resident(ctx, pl.inst_half->as<InstDesc>(), g, u, k)) != hipSuccess) return e;
-    for (const burgers::WgGroup& g : pl.newton_chip)
-      if ((e = burgers::launch_newton_resident(ctx, g, u, k, ctx->newton->flags.as<int>())) != hipSuccess) return e;
-    done += k;
+// nsteps explicit steps of one subset, the final state in u.
+void explicit_tasks(burgers_ctx* ctx, int set, void* u, int64_t nsteps, std::vector<burgers::Task>& tasks) {
+  const burgers::ExplicitPlan* pl = ctx->explicit_plans[set].get();
+  void* work = ctx->work.ptr;
+  const double tile = burgers::explicit_tile_nodes(ctx->dtype);
+  if (pl->path == 1) {
+    if (pl->n_stream == 0) return;
+    tasks.push_back({chain_us(nsteps, 3.0, pl->n_stream * tile, 4e5), nsteps, [=]() -> hipError_t {
+      hipError_t e = hipSuccess;
+      void* bufs[2] = {u, work};
+      int cur = 0;
+      for (int64_t s = 0; s < nsteps; ++s) {
+        if ((e = burgers::launch_explicit_stream(ctx, pl->stream->as<Tile>(), pl->n_stream, bufs[cur], bufs[cur ^ 1])) != hipSuccess)
+          return e;
+        cur ^= 1;
+      }
+      if (cur) e = burgers::launch_copy_tiles(ctx, pl->stream->as<Tile>(), pl->n_stream, work, u);
+      return e;
+    }});
+    return;
   }
-  if (pl.n_copy == 0 || part == kPartOnChip) return e;
+  // whole instances, in place: all steps at once, or `depth` per launch on path 3
+  const int64_t whole_chunk = pl->path == 3 ? pl->depth : (int64_t{1} << 30);
+  auto in_chunks = [=](auto launch) -> hipError_t {
+    for (int64_t done = 0; done < nsteps;) {
+      const int k = static_cast<int>(std::min(whole_chunk, nsteps - done));
+      const hipError_t e = launch(k);
+      if (e != hipSuccess) return e;
+      done += k;
+    }
+    return hipSuccess;
+  };
+  double packed = 0;
+  for (const auto& c : pl->whole_classes) {
+    const double nodes = 12.0 * c.lanes * static_cast<double>(c.n_fe + 4 * c.n_rk4);   // (about 12 of 16 a lane)
+    const bool own = c.lanes >= burgers::explicit_pack_lanes() || (c.lanes == 64 && !pl->pack_waves);
+    if (!own) {
+      packed += nodes;
+      continue;
+    }
+    tasks.push_back({chain_us(nsteps, c.lanes == 64 ? 0.25 : 0.5, nodes, 4e6), 1, [=]() {
+      return in_chunks([&](int k) {
+        return burgers::launch_explicit_block(ctx, pl->whole->as<BlockTile>() + c.offset, c.n_fe, c.n_rk4, u, u, k, c.lanes);
+      });
+    }});
+  }
+  if (pl->n_packs_fe + pl->n_packs_rk4 > 0)
+    tasks.push_back({chain_us(nsteps, 0.5, packed, 4e6), 1, [=]() {
+      return in_chunks([&](int k) {
+        return burgers::launch_explicit_packs(ctx, pl->whole->as<BlockTile>(), pl->packs->as<burgers::BlockPack>(),
+                                              pl->n_packs_fe, pl->n_packs_rk4, u, k);
+      });
+    }});
+  // windows of long instances: `depth` steps per launch, ping-pong
+  if (pl->n_win > 0)
+    tasks.push_back({chain_us(nsteps, 0.6, 8192.0 * static_cast<double>(pl->n_win), 4e6), nsteps / pl->depth + 1,
+                     [=]() -> hipError_t {
+      hipError_t e = hipSuccess;
+      void* bufs[2] = {u, work};
+      int cur = 0;
+      for (int64_t done = 0; done < nsteps;) {
+        const int k = static_cast<int>(std::min<int64_t>(pl->depth, nsteps - done));
+        if ((e = burgers::launch_explicit_block(ctx, pl->win->as<BlockTile>(), pl->n_win - pl->n_win_rk4, pl->n_win_rk4,
+                                                bufs[cur], bufs[cur ^ 1], k)) != hipSuccess)
+          return e;
+        cur ^= 1;
+        done += k;
+      }
+      if (cur) e = burgers::launch_copy_tiles(ctx, pl->win_copy->as<Tile>(), pl->n_win_copy, work, u);
+      return e;
+    }});
+}
+
+// nsteps implicit steps through HBM of a plan's stepped instances, the final state in u.
+hipError_t enqueue_stepped(burgers_ctx* ctx, const burgers::BtcsPlan& pl, void* u, int64_t nsteps) {
+  hipError_t e = hipSuccess;
   void* bufs[2] = {u, ctx->work.ptr};
   int cur = 0;
   if (nsteps > 0 && (e = burgers::launch_btcs_window_reset(ctx, pl)) != hipSuccess) return e;
@@ -574,68 +660,49 @@ hipError_t enqueue_btcs(burgers_ctx* ctx, int set, void* u, int64_t nsteps, int 
   return e;
 }
 
-// Whether a part of a plan launches anything.
-bool explicit_part_busy(const burgers::ExplicitPlan& pl, int part) {
-  if (pl.path == 1) return part != kPartOnChip && pl.n_stream > 0;
-  return part == kPartOnChip ? !pl.whole_classes.empty() : pl.n_win > 0;
-}
-bool btcs_part_busy(const burgers::BtcsPlan& pl, int part) {
-  return part == kPartOnChip ? !pl.resident.empty() || !pl.cn_chip.empty() || !pl.newton_chip.empty() : pl.n_copy > 0;
+// nsteps implicit steps of one subset, the final state in u.
+void btcs_tasks(burgers_ctx* ctx, int set, void* u, int64_t nsteps, std::vector<burgers::Task>& tasks) {
+  const burgers::BtcsPlan* pl = ctx->btcs[set].get();
+  auto on_chip = [&](const burgers::WgGroup& g, double scale, auto launch) {   // on-chip systems, in place
+    const double rows = 0.75 * g.shape.lanes * g.shape.chunk * static_cast<double>(g.n);
+    tasks.push_back({scale * chain_us(nsteps, g.shape.lanes <= 128 ? 1.6 : 2.5, rows, 9e5), 1, [=, &g]() -> hipError_t {
+      for (int64_t done = 0; done < nsteps;) {
+        const int k = static_cast<int>(std::min<int64_t>(nsteps - done, int64_t{1} << 30));
+        const hipError_t e = launch(g, k);
+        if (e != hipSuccess) return e;
+        done += k;
+      }
+      return hipSuccess;
+    }});
+  };
+  for (const burgers::WgGroup& g : pl->resident)
+    on_chip(g, 1.0, [=](const burgers::WgGroup& q, int k) { return burgers::launch_btcs_resident(ctx, q, u, k); });
+  for (const burgers::WgGroup& g : pl->cn_chip)
+    on_chip(g, 1.5, [=](const burgers::WgGroup& q, int k) {
+      return burgers::launch_cn_resident(ctx, pl->inst_half->as<InstDesc>(), q, u, k);
+    });
+  for (const burgers::WgGroup& g : pl->newton_chip)
+    on_chip(g, 6.0, [=](const burgers::WgGroup& q, int k) {
+      return burgers::launch_newton_resident(ctx, q, u, k, ctx->newton->flags.as<int>());
+    });
+  if (pl->n_copy > 0) {
+    const double nodes = static_cast<double>(pl->n_copy) * burgers::explicit_tile_nodes(ctx->dtype);
+    tasks.push_back({chain_us(nsteps, pl->newton ? 100.0 : 11.0, nodes, 3e5), 4 * nsteps,
+                     [=]() { return enqueue_stepped(ctx, *pl, u, nsteps); }});
+  }
 }
 
 // scheme -1: each instance's own scheme, explicit instances nsteps steps and BTCS ones nsteps_btcs.
-// The independent parts (on-chip and through-HBM instances of each scheme) run concurrently: the first on
-// the context's stream, the others on side streams forked from it and joined back with events (under
-// graph capture they become parallel branches of the graph), unless the plan asks for one stream.
 hipError_t enqueue_all(burgers_ctx* ctx, int set, int scheme, void* u, int64_t nsteps, int64_t nsteps_btcs = -1) {
   if (nsteps_btcs < 0) nsteps_btcs = nsteps;
-  struct Group {
-    bool btcs;
-    int set, part;
-    int64_t steps;
-  };
-  std::vector<Group> groups;
   const bool mixed = scheme < 0;
-  const int es = mixed ? kSetExplicit : set, bs = mixed ? kSetBtcs : set;
-  const bool want_exp = scheme == BURGERS_EXPLICIT || (mixed && !ctx->set_explicit.empty() && nsteps > 0);
-  const bool want_btcs = scheme == BURGERS_BTCS || (mixed && !ctx->set_btcs.empty() && nsteps_btcs > 0);
   const int64_t bsteps = mixed ? nsteps_btcs : nsteps;
-  for (int part : {kPartOnChip, kPartThroughHbm}) {
-    if (want_exp && explicit_part_busy(*ctx->explicit_plans[es], part)) groups.push_back({false, es, part, nsteps});
-    if (want_btcs && btcs_part_busy(*ctx->btcs[bs], part)) groups.push_back({true, bs, part, bsteps});
-  }
-  auto run = [&](const Group& g) {
-    return g.btcs ? enqueue_btcs(ctx, g.set, u, g.steps, g.part) : enqueue_explicit(ctx, g.set, u, g.steps, g.part);
-  };
-  if (groups.size() <= 1 || ctx->plan.serial == 1) {
-    for (const Group& g : groups) {
-      hipError_t e = run(g);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  hipError_t e;
-  const size_t nside = groups.size() - 1;
-  for (size_t k = 0; k < nside; ++k) {
-    if (!ctx->side[k] && (e = hipStreamCreateWithFlags(&ctx->side[k], hipStreamNonBlocking)) != hipSuccess) return e;
-    if (!ctx->joined[k] && (e = hipEventCreateWithFlags(&ctx->joined[k], hipEventDisableTiming)) != hipSuccess)
-      return e;
-  }
-  if (!ctx->forked && (e = hipEventCreateWithFlags(&ctx->forked, hipEventDisableTiming)) != hipSuccess) return e;
-  hipStream_t main = ctx->stream;
-  if ((e = hipEventRecord(ctx->forked, main)) != hipSuccess) return e;
-  hipError_t err = hipSuccess;
-  for (size_t k = 0; k < nside && err == hipSuccess; ++k) {
-    if ((err = hipStreamWaitEvent(ctx->side[k], ctx->forked, 0)) != hipSuccess) break;
-    ctx->stream = ctx->side[k];
-    err = run(groups[k + 1]);
-    ctx->stream = main;
-    if (err == hipSuccess) err = hipEventRecord(ctx->joined[k], ctx->side[k]);
-    if (err == hipSuccess) err = hipStreamWaitEvent(main, ctx->joined[k], 0);
-  }
-  ctx->stream = main;
-  if (err != hipSuccess) return err;
-  return run(groups[0]);
+  std::vector<burgers::Task> tasks;
+  if (scheme == BURGERS_EXPLICIT || (mixed && !ctx->set_explicit.empty() && nsteps > 0))
+    explicit_tasks(ctx, mixed ? kSetExplicit : set, u, nsteps, tasks);
+  if (scheme == BURGERS_BTCS || (mixed && !ctx->set_btcs.empty() && bsteps > 0))
+    btcs_tasks(ctx, mixed ? kSetBtcs : set, u, bsteps, tasks);
+  return burgers::run_tasks(ctx, tasks, ctx->plan.serial == 1);
 }
 
 burgers_status prepare(burgers_ctx* ctx, int set, int scheme) {
@@ -1340,8 +1407,10 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
     hipError_t err = hipSuccess;
     for (int64_t k0 = 0; exp_rec && k0 < len && err == hipSuccess; k0 += ep->depth) {
       const int k = static_cast<int>(std::min<int64_t>(ep->depth, len - k0));
-      err = burgers::launch_explicit_record(ctx, ep->whole->as<BlockTile>(), ep->n_whole, at(c, seg, k0),
-                                            at(c, seg, k0 + 1), stride, k);
+      for (const auto& wc : ep->whole_classes)
+        if (err == hipSuccess)
+          err = burgers::launch_explicit_record(ctx, ep->whole->as<BlockTile>() + wc.offset, wc.n_fe, at(c, seg, k0),
+                                                at(c, seg, k0 + 1), stride, k, wc.lanes);
       if (err == hipSuccess)
         err = burgers::launch_explicit_record(ctx, ep->win->as<BlockTile>(), ep->n_win, at(c, seg, k0),
                                               at(c, seg, k0 + 1), stride, k);

@@ -19,7 +19,8 @@
 //    each step (double buffered, one barrier per step) and advances many steps per pass over HBM.  The
 //    window is loaded and stored through LDS so that HBM sees coalesced accesses.  A whole instance
 //    that fits is advanced for all its steps in one launch with exact boundaries, in the narrowest of
-//    64, 128, 256 or 512 lanes that holds it; longer grids are cut into windows with a halo of T nodes
+//    128, 256 or 512 lanes that holds it (explicit_wave_kernel: up to 1024 nodes, one wave each, whose end
+//    values cross lanes without LDS); longer grids are cut into windows with a halo of T nodes
 //    per side that are recomputed redundantly, so that after T steps the window's interior is exact.
 //    Every node goes through the same arithmetic as in the streaming kernel, so both kernels give
 //    bitwise identical results.
@@ -173,28 +174,36 @@ __device__ __forceinline__ void chunk_step(const T (&in)[kBlockChunk], T (&out)[
 }
 
 
+// (acc + K)/6 added to v, as eq. 22's last combination.  Binary64: a product with the rounded 1/6 in one fused
+// operation with the sum.  Binary32 rounds exactly as the division: the binary64 product with 1/6, rounded
+// to binary32, equals s / 6 for every binary32 s (checked over all of them).
+__device__ __forceinline__ double add_sixth(double v, double s) { return __builtin_fma(s, 1.0 / 6.0, v); }
+__device__ __forceinline__ float add_sixth(float v, float s) {
+  return v + static_cast<float>(static_cast<double>(s) * (1.0 / 6.0));
+}
+
 // One RK4 stage of a lane's chunk (Sec. 2.7.1, eq. 22): K = increment of the stage input `in` (with
 // the neighbours' end values `left`, `right`; fixed nodes have K = 0), then by stage
 //   1: acc = K,             out = v + K/2
 //   2: acc = acc + 2K,      out = v + K/2
 //   3: acc = acc + 2K,      out = v + K
 //   4: v = v + (acc + K)/6  (out unused)
+// (2K and K/2 are exact, so the fused sums round as the unfused ones.)
 // `in` and `out` may be the same array: node j reads in[j-1] from a register kept before it is
 // overwritten.
-template <typename T, int STAGE>
-__device__ __forceinline__ void rk4_apply(T (&v)[kBlockChunk], T (&out)[kBlockChunk], T (&acc)[kBlockChunk], int j,
-                                          T K) {
+template <typename T, int STAGE, int M>
+__device__ __forceinline__ void rk4_apply(T (&v)[M], T (&out)[M], T (&acc)[M], int j, T K) {
   if constexpr (STAGE == 1) {
     acc[j] = K;
-    out[j] = v[j] + T(0.5) * K;
+    out[j] = fma_exact(T(0.5), K, v[j]);
   } else if constexpr (STAGE == 2) {
     acc[j] = fma_exact(T(2), K, acc[j]);
-    out[j] = v[j] + T(0.5) * K;
+    out[j] = fma_exact(T(0.5), K, v[j]);
   } else if constexpr (STAGE == 3) {
     acc[j] = fma_exact(T(2), K, acc[j]);
     out[j] = v[j] + K;
   } else {
-    v[j] = v[j] + (acc[j] + K) / T(6);
+    v[j] = add_sixth(v[j], acc[j] + K);
   }
 }
 
@@ -512,16 +521,221 @@ __global__ __launch_bounds__(kBlockThreads) void explicit_record_kernel(
                                   static_cast<int>(threadIdx.x), rec + d.off, rstride);
 }
 
+// ---- Instances of up to 1024 nodes: one wave each ---------------------------------------------------
+// A whole instance is held by one wave, M = ceil(n / 64) consecutive nodes per lane or one fewer (a chunk one
+// short leaves its slot 0 a copy of the left neighbour's last value), in two register arrays that alternate
+// as old and new state.  The chunks' end values cross lanes by whole-wave DPP moves, around the wave for a
+// periodic instance: a step needs no LDS and no barrier, and every lane works whatever n is.
+// What bounds it: the chain of a step (two moves and 6 operations per node, M nodes interleaved) while the
+// chip is not full, binary64 issue when it is.  (The blocks below give a lane 16 nodes and pass end values
+// through LDS with a barrier per step: 101 nodes in 7 of 64 lanes, 274 ns a step for one instance, 1.7 us for
+// 256, which shared workgroups; here 56 and 94 ns.  A wave per instance of up to 1024 nodes, each with 64
+// lanes of M nodes, and several waves with overlapping outer lanes for longer ones were tried too: the
+// latter lost to the blocks, whose barriers the chip's other workgroups cover.)
+// Whole-wave DPP move of a lane value: CTRL 0x138 / 0x130 from lane - 1 / lane + 1 (lane 0 / lane 63 keep
+// their own), 0x13C / 0x134 the same with wrap-around.
+template <int CTRL>
+__device__ __forceinline__ float wave_move(float x) {
+  const int b = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double wave_move(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const int lo = static_cast<int>(b & 0xffffffffu), hi = static_cast<int>(b >> 32);
+  const uint32_t l = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+  const uint32_t h = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false));
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(h) << 32) | l);
+}
+
+// Neighbours' end values of a lane's chunk x: `left` the last of the lane before, `right` the first of the
+// lane after.  ROT: around the wave.  A lane whose slot 0 is no node (`dummy`) offers its slot 1 and takes
+// `left` into slot 0, so that slot 1 reads it there.
+enum class Ends { kShift, kRotate, kFew };
+
+template <typename T, int M, Ends E, bool SLOTS>
+__device__ __forceinline__ void wave_ends(T (&x)[M], bool dummy, int lane_l, int lane_r, T& left, T& right) {
+  const T first = SLOTS && M > 1 ? (dummy ? x[M > 1 ? 1 : 0] : x[0]) : x[0];
+  if constexpr (E == Ends::kFew) {           // fewer than 64 nodes: lane indices of the neighbours
+    left = __shfl(x[M - 1], lane_l, 64);
+    right = __shfl(first, lane_r, 64);
+  } else if constexpr (E == Ends::kRotate) {
+    left = wave_move<0x13C>(x[M - 1]);
+    right = wave_move<0x134>(first);
+  } else {
+    left = wave_move<0x138>(x[M - 1]);
+    right = wave_move<0x130>(first);
+  }
+  if (SLOTS && M > 1) x[0] = dummy ? left : x[0];
+}
+
+// One step of a lane's chunk: out[j] from in[j-1], in[j], in[j+1].  The chunk's two end nodes take their own
+// coefficients, zero at a fixed node (a Dirichlet end), which returns the node's value unchanged.
+template <typename T>
+struct ChunkCoef {
+  T r, D, r0, D0, r1, D1;
+};
+
+template <typename T, int M>
+__device__ __forceinline__ void wave_step(const T (&in)[M], T (&out)[M], T left, T right, const ChunkCoef<T>& c) {
+#pragma unroll
+  for (int j = 1; j < M - 1; ++j) out[j] = upwind_central(in[j], in[j - 1], in[j + 1], c.r, c.D);
+  if constexpr (M == 1) {
+    // (both a first and a last node: r1, D1 are zero where either end is fixed)
+    out[0] = upwind_central(in[0], left, right, c.r1, c.D1);
+  } else {
+    out[0] = upwind_central(in[0], left, in[1], c.r0, c.D0);
+    out[M - 1] = upwind_central(in[M - 1], in[M - 2], right, c.r1, c.D1);
+  }
+}
+
+template <typename T, int STAGE, int M>
+__device__ __forceinline__ void wave_rk4_stage(T (&v)[M], const T (&in)[M], T (&out)[M], T (&acc)[M], T left, T right,
+                                               const ChunkCoef<T>& c) {
+  if constexpr (M == 1) {
+    rk4_apply<T, STAGE>(v, out, acc, 0, rk4_increment(in[0], left, right, c.r1, c.D1));
+  } else {
+    const T i0 = in[0], i1 = in[1], i2 = in[M - 2], i3 = in[M - 1];
+    T prev = i0;
+#pragma unroll
+    for (int j = 1; j < M - 1; ++j) {
+      const T cur = in[j];
+      const T K = rk4_increment(cur, prev, in[j + 1], c.r, c.D);
+      prev = cur;
+      rk4_apply<T, STAGE>(v, out, acc, j, K);
+    }
+    rk4_apply<T, STAGE>(v, out, acc, 0, rk4_increment(i0, left, i1, c.r0, c.D0));
+    rk4_apply<T, STAGE>(v, out, acc, M - 1, rk4_increment(i3, i2, right, c.r1, c.D1));
+  }
+}
+
+// A wave's run: x and to are the instance's first node in the source and result buffers.
+// REC (forward Euler): the state after each step k (1 <= k <= steps) at to + (k - 1) rstride.
+template <typename T, int M, bool RK4, bool REC>
+struct WaveRun {
+  const InstDesc& d;
+  const T* x;       // (the same buffer as `to` where an instance is advanced in place)
+  T* to;
+  int steps;
+  int64_t rstride;
+
+  template <Ends E>
+  __device__ __forceinline__ void advance(T (&v)[M], const ChunkCoef<T>& c, int base, bool held, bool dummy, int lane_l,
+                                          int lane_r) const {
+    constexpr bool SLOTS = E != Ends::kFew;
+    T left, right, w[M];
+    if constexpr (RK4) {
+      T acc[M];
+      for (int step = 0; step < steps; ++step) {
+        wave_ends<T, M, E, SLOTS>(v, dummy, lane_l, lane_r, left, right);
+        wave_rk4_stage<T, 1>(v, v, w, acc, left, right, c);
+        wave_ends<T, M, E, SLOTS>(w, dummy, lane_l, lane_r, left, right);
+        wave_rk4_stage<T, 2>(v, w, w, acc, left, right, c);
+        wave_ends<T, M, E, SLOTS>(w, dummy, lane_l, lane_r, left, right);
+        wave_rk4_stage<T, 3>(v, w, w, acc, left, right, c);
+        wave_ends<T, M, E, SLOTS>(w, dummy, lane_l, lane_r, left, right);
+        wave_rk4_stage<T, 4>(v, w, w, acc, left, right, c);
+      }
+    } else {
+      int step = 0;
+      for (; step + 2 <= steps; step += 2) {
+        wave_ends<T, M, E, SLOTS>(v, dummy, lane_l, lane_r, left, right);
+        wave_step(v, w, left, right, c);
+        if constexpr (REC) store(w, to + step * rstride, base, held, dummy);
+        wave_ends<T, M, E, SLOTS>(w, dummy, lane_l, lane_r, left, right);
+        wave_step(w, v, left, right, c);
+        if constexpr (REC) store(v, to + (step + 1) * rstride, base, held, dummy);
+      }
+      if (step < steps) {
+        wave_ends<T, M, E, SLOTS>(v, dummy, lane_l, lane_r, left, right);
+        wave_step(v, w, left, right, c);
+#pragma unroll
+        for (int j = 0; j < M; ++j) v[j] = w[j];
+        if constexpr (REC) store(v, to + step * rstride, base, held, dummy);
+      }
+    }
+    if constexpr (!REC) store(v, to, base, held, dummy);
+  }
+
+  // (at most 8 KB an instance and once per launch or recorded step: lane by lane)
+  __device__ __forceinline__ void store(const T (&v)[M], T* dst, int base, bool held, bool dummy) const {
+    if (!held) return;
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+      if (j > 0 || !dummy) dst[base + j] = v[j];
+  }
+
+  __device__ __forceinline__ void run() const {
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    const int n = d.n, last = M == 1 ? n - 1 : 63;   // the lane of the instance's last node
+    const bool wraps = d.bc == kPeriodic;
+    const bool held = M > 1 || lane < n;
+    const int rho = n - (M - 1) * 64;                // lanes of M nodes
+    const bool dummy = M > 1 && lane >= rho;
+    const int base = lane * (M - 1) + (dummy ? rho - 1 : lane);
+    T v[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) v[j] = held ? x[base + j] : T(0);
+    const bool edge0 = !wraps && lane == 0, edge1 = !wraps && lane == last;
+    if (edge0) v[0] = static_cast<T>(d.a);
+    if (edge1) v[M - 1] = static_cast<T>(d.b);
+    const T r = static_cast<T>(d.r), D = static_cast<T>(d.D);
+    const bool fix1 = M == 1 ? edge0 || edge1 : edge1;
+    const ChunkCoef<T> c{r, D, edge0 ? T(0) : r, edge0 ? T(0) : D, fix1 ? T(0) : r, fix1 ? T(0) : D};
+    if (M == 1 && n < 64) {
+      const int ll = lane > 0 ? lane - 1 : n - 1, lr = lane < n - 1 ? lane + 1 : 0;
+      advance<Ends::kFew>(v, c, base, held, false, ll, lr);
+    } else if (wraps) {
+      advance<Ends::kRotate>(v, c, base, held, dummy, 0, 0);
+    } else {
+      advance<Ends::kShift>(v, c, base, held, dummy, 0, 0);
+    }
+  }
+};
+
+constexpr int kWaveNodes = 1024;   // longest instance of one wave
+
+// A whole instance on the calling wave; out holds the states, or (REC) the first of the recorded ones.
+template <typename T, bool RK4, bool REC>
+__device__ __forceinline__ void wave_tile(const InstDesc* __restrict__ inst, const BlockTile& bt, const T* u, T* out,
+                                          int steps, int64_t rstride) {
+  if (bt.width <= 0) return;                   // an empty slot of a resident pool
+  if (bt.limit > 0) steps = min(steps, bt.limit);
+  const InstDesc d = inst[bt.inst];
+#define BURGERS_WAVE_CASE(K)                                                            \
+  case K: WaveRun<T, K, RK4, REC>{d, u + d.off, out + d.off, steps, rstride}.run(); break;
+  switch ((d.n + 63) / 64) {
+    BURGERS_WAVE_CASE(1) BURGERS_WAVE_CASE(2) BURGERS_WAVE_CASE(3) BURGERS_WAVE_CASE(4) BURGERS_WAVE_CASE(5)
+    BURGERS_WAVE_CASE(6) BURGERS_WAVE_CASE(7) BURGERS_WAVE_CASE(8) BURGERS_WAVE_CASE(9) BURGERS_WAVE_CASE(10)
+    BURGERS_WAVE_CASE(11) BURGERS_WAVE_CASE(12) BURGERS_WAVE_CASE(13) BURGERS_WAVE_CASE(14)
+    BURGERS_WAVE_CASE(15) BURGERS_WAVE_CASE(16)
+    default: break;
+  }
+#undef BURGERS_WAVE_CASE
+}
+
+// Whole instances of up to kWaveNodes nodes, one wave each (tiles sorted by size, so that the four of a
+// workgroup run about equally long).
+template <typename T, bool RK4, bool REC>
+__global__ __launch_bounds__(256, RK4 ? 3 : 4) void explicit_wave_kernel(const InstDesc* __restrict__ inst,
+                                                                         const BlockTile* __restrict__ tiles,
+                                                                         int n_tiles, const T* u, T* out, int steps,
+                                                                         int64_t rstride) {
+  const int k = 4 * static_cast<int>(blockIdx.x) +
+                __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  if (k >= n_tiles) return;
+  const BlockTile bt = tiles[k];
+  wave_tile<T, RK4, REC>(inst, bt, u, out, steps, rstride);
+}
+
 // LDS of a sub-group of NT lanes in the pack kernel: its exchange buffers and staging area.
 template <int NT>
 constexpr int sub_stage_size() {
   return stage_nodes<NT>() + stage_nodes<NT>() / 16 + 1;
 }
 constexpr int pack_stage_size() {
-  constexpr int a = (kBlockThreads / 64) * sub_stage_size<64>(), b = (kBlockThreads / 128) * sub_stage_size<128>();
-  constexpr int c = (kBlockThreads / 256) * sub_stage_size<256>(), e = sub_stage_size<kBlockThreads>();
-  constexpr int ab = a > b ? a : b, ce = c > e ? c : e;
-  return ab > ce ? ab : ce;
+  constexpr int a = (kBlockThreads / 128) * sub_stage_size<128>(), b = (kBlockThreads / 256) * sub_stage_size<256>();
+  return a > b ? a : b;
 }
 
 template <typename T, bool RK4, int NT>
@@ -539,25 +753,26 @@ __device__ __forceinline__ void pack_member(const InstDesc* __restrict__ inst, c
                           t);
 }
 
-// The whole instances of a call's narrower width classes (64, 128 and 256 lanes) in one launch over a
-// list of packs, widest class first: a workgroup of 512 lanes runs 512 / lanes instances side by side
+// The whole instances of a call's width classes below the widest in one launch over a list of packs, widest class first: a workgroup of 512 lanes runs 512 / lanes instances side by side
 // (instances of 512 lanes would run one per workgroup too, but their own kernel compiles the step loop
 // to fewer registers).  The instances of a pack take the same number of steps, so their barriers
 // coincide.
 template <typename T, bool RK4>
 __global__ __launch_bounds__(kBlockThreads) void explicit_pack_kernel(const InstDesc* __restrict__ inst,
                                                                       const BlockTile* __restrict__ tiles,
-                                                                      const BlockPack* __restrict__ packs,
-                                                                      T* __restrict__ u, int steps) {
+                                                                      const BlockPack* __restrict__ packs, T* u, int steps) {
   __shared__ T s_first[2 * kBlockThreads];
   __shared__ T s_last[2 * kBlockThreads];
   __shared__ T stage[pack_stage_size()];
   const BlockPack pk = packs[blockIdx.x];
   switch (pk.lanes) {
-    case 64: pack_member<T, RK4, 64>(inst, tiles, pk, u, u, steps, s_first, s_last, stage); break;
+    case 64: {                                 // one wave each, without the barriers below
+      const int g = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+      if (g < pk.count) wave_tile<T, RK4, false>(inst, tiles[pk.first + g], u, u, steps, 0);
+      break;
+    }
     case 128: pack_member<T, RK4, 128>(inst, tiles, pk, u, u, steps, s_first, s_last, stage); break;
-    case 256: pack_member<T, RK4, 256>(inst, tiles, pk, u, u, steps, s_first, s_last, stage); break;
-    default: pack_member<T, RK4, kBlockThreads>(inst, tiles, pk, u, u, steps, s_first, s_last, stage); break;
+    default: pack_member<T, RK4, 256>(inst, tiles, pk, u, u, steps, s_first, s_last, stage); break;
   }
 }
 
@@ -638,10 +853,24 @@ void block_launch(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_fe, 
 }
 
 template <typename T>
+void wave_launch(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_fe, int64_t n_rk4, const void* u, void* out,
+                 int steps) {
+  const InstDesc* inst = ctx->inst.as<InstDesc>();
+  const T* src = static_cast<const T*>(u);
+  T* dst = static_cast<T*>(out);
+  if (n_fe > 0)
+    explicit_wave_kernel<T, false, false><<<static_cast<unsigned>((n_fe + 3) / 4), 256, 0, ctx->stream>>>(
+        inst, tiles, static_cast<int>(n_fe), src, dst, steps, 0);
+  if (n_rk4 > 0)
+    explicit_wave_kernel<T, true, false><<<static_cast<unsigned>((n_rk4 + 3) / 4), 256, 0, ctx->stream>>>(
+        inst, tiles + n_fe, static_cast<int>(n_rk4), src, dst, steps, 0);
+}
+
+template <typename T>
 void block_launch_lanes(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_fe, int64_t n_rk4, const void* u,
                         void* out, int steps, int lanes, int first_step) {
   switch (lanes) {
-    case 64: block_launch<T, 64>(ctx, tiles, n_fe, n_rk4, u, out, steps, first_step); break;
+    case 64: wave_launch<T>(ctx, tiles, n_fe, n_rk4, u, out, steps); break;
     case 128: block_launch<T, 128>(ctx, tiles, n_fe, n_rk4, u, out, steps, first_step); break;
     case 256: block_launch<T, 256>(ctx, tiles, n_fe, n_rk4, u, out, steps, first_step); break;
     default: block_launch<T, kBlockThreads>(ctx, tiles, n_fe, n_rk4, u, out, steps, first_step); break;
@@ -679,9 +908,15 @@ hipError_t launch_explicit_packs(const burgers_ctx* ctx, const BlockTile* tiles,
 }
 
 hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_tiles, const void* u,
-                                  void* rec, int64_t rstride, int steps) {
+                                  void* rec, int64_t rstride, int steps, int lanes) {
   if (n_tiles <= 0 || steps <= 0) return hipSuccess;
   if (ctx->dtype != BURGERS_F64) return hipErrorInvalidValue;
+  if (lanes == 64) {
+    explicit_wave_kernel<double, false, true><<<static_cast<unsigned>((n_tiles + 3) / 4), 256, 0, ctx->stream>>>(
+        ctx->inst.as<InstDesc>(), tiles, static_cast<int>(n_tiles), static_cast<const double*>(u),
+        static_cast<double*>(rec), steps, rstride);
+    return hipGetLastError();
+  }
   explicit_record_kernel<double><<<static_cast<unsigned>(n_tiles), kBlockThreads, 0, ctx->stream>>>(
       ctx->inst.as<InstDesc>(), tiles, static_cast<const double*>(u), static_cast<double*>(rec), rstride, steps);
   return hipGetLastError();
@@ -690,7 +925,8 @@ hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles
 int explicit_pack_lanes() { return kBlockThreads; }
 
 int explicit_block_lanes(int n) {
-  int lanes = 64;
+  int lanes = 64;                              // (one wave of its own: up to kWaveNodes nodes)
+  static_assert(kWaveNodes == 64 * kBlockChunk, "the 64-lane class is one wave's");
   while (lanes < kBlockThreads && lanes * kBlockChunk < n) lanes *= 2;
   return lanes;
 }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <functional>
 #include <map>
 #include <memory>
 #include <tuple>
@@ -245,9 +246,11 @@ struct ExplicitPlan {
     int64_t offset, n_fe, n_rk4;
   };
   std::vector<WholeClass> whole_classes;
-  // the narrower classes' instances packed for one launch per scheme (forward Euler packs, then RK4)
+  // the narrower classes' instances packed for one launch per scheme (forward Euler packs, then RK4);
+  // instances of one wave each only when `pack_waves`
   std::unique_ptr<DevBuf> packs;             // BlockPack[]
   int64_t n_packs_fe = 0, n_packs_rk4 = 0;
+  bool pack_waves = false;
   std::unique_ptr<DevBuf> win_copy;          // Tile[] of the windowed instances (copy-back)
   int64_t n_win_copy = 0;
   int path = 1;                              // 1 stream, 2 resident, 3 tiled
@@ -331,7 +334,8 @@ namespace burgers {
 hipError_t launch_explicit_stream(const burgers_ctx* ctx, const Tile* tiles, int64_t n_tiles,
                                   const void* u, void* out);
 // Windows tiles[0, n_fe) advance by forward Euler and tiles[n_fe, n_fe + n_rk4) by RK4.
-// Temporal-blocking launch over `lanes`-wide workgroups (64, 128, 256 or 512; windows always take 512).
+// Temporal-blocking launch over `lanes`-wide workgroups (128, 256 or 512; windows always take 512), or (64)
+// over whole instances of one wave each.
 // `first_step`: the launch's first step counted from the start of the call (tiles with a step limit
 // take only the steps of the call they have left).
 hipError_t launch_explicit_block(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_fe, int64_t n_rk4,
@@ -343,14 +347,23 @@ hipError_t launch_explicit_packs(const burgers_ctx* ctx, const BlockTile* tiles,
                                  int64_t n_fe, int64_t n_rk4, void* u, int steps);
 // Forward-Euler block tiles (whole instances or windows with a halo of at least `steps`) recording the
 // state after each step k (1 <= k <= steps) at rec + (k - 1) rstride (binary64; u is only read).
+// `lanes` 64: whole instances of one wave each.
 hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_tiles, const void* u,
-                                  void* rec, int64_t rstride, int steps);
+                                  void* rec, int64_t rstride, int steps, int lanes = 512);
 // Windows of a long explicit instance `i` of n nodes advanced `depth` steps per launch (halo = depth x
 // stages per side); appends them to `out`.  Returns false when the halo leaves no kept node.
 bool explicit_windows(int32_t i, int32_t n, bool periodic, int depth, bool rk4, std::vector<BlockTile>& out);
 // Truncated BTCS windows of `W` rows over a system of R rows of instance i; appends them to `out`.
 void btcs_windows(int32_t i, int32_t R, bool periodic, int W, bool cn, std::vector<WinDesc>& out);
 hipError_t launch_clear_ints(const burgers_ctx* ctx, int* p, int64_t n);
+// capi.hip: a chain of launches on the context's current stream with a rough time, independent of the others
+// of its list; run_tasks runs a list concurrently (or, `serial`, one after another).
+struct Task {
+  double us;
+  int64_t launches;   // about how many
+  std::function<hipError_t()> run;
+};
+hipError_t run_tasks(burgers_ctx* ctx, std::vector<Task>& tasks, bool serial);
 // capi.hip: argument checks and the kernels' per-instance scalars of a problem at state offset `off`
 bool problem_valid(const burgers_problem& p);
 InstDesc inst_desc(const burgers_problem& p, int64_t off);
