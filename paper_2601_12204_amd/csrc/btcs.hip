@@ -653,166 +653,8 @@ __global__ __launch_bounds__(NT, MC == 16 ? 4 : 1) void newton_wg_kernel(const I
   else newton_solve<false, S, NT, MC>(pcr, stage, rows, xs, R, P, last != 0);
 }
 
-// ---- Truncated windows of a long system ------------------------------------------------------------
-// A long system's rows are covered by windows of W = 16 x (workgroup lanes) rows (4096 or 8192).  A window keeps the rows at least
-// kWinHalo rows inside its ends and solves them together with the halo as a plain system, in which the
-// unknowns just beyond its two ends (its ghosts) take their old values u^n (at a Dirichlet end of the
-// system, the exact boundary value).
-//
-// Error of a kept row.  Let e be the window solution minus the exact one, extended to the ghosts by
-// the ghosts' errors g_L, g_R.  Every window row gives l_i e_{i-1} + d_i e_i + p_i e_{i+1} = 0 with
-// l_i, p_i <= 0 and d_i - |l_i| - |p_i| = 1, so a vector w with that operator >= 0 on the window rows and
-// w >= 0 at the ghosts is >= 0 throughout (at a negative minimum the row would give 1 * w_i < 0).  The
-// barrier v_i = theta^(i+1) (ghost at i = -1) meets -|l_i| + d_i theta - |p_i| theta^2 >= 0 whenever
-// theta is at least the smaller root of that quadratic, which for the BTCS rows (c = r u_i, the
-// couplings D + max(c,0) and D - min(c,0)) is at most
-//     g(C) = 2 (D + C) / (1 + 2D + C + sqrt((1 + C)^2 + 4D)),   C = r max|u_i| over the window
-// (g increases with C, and the mirrored barrier from the right end takes the same bound).  With w =
-// |g_L| v + |g_R| v' -+ e:  |e_i| <= |g_L| theta^(i+1) + |g_R| theta^(W-i).  A ghost's error is its old
-// value minus its new one, at most 2 max|u^n| by the maximum principle of the step, so a kept row (at
-// least kWinHalo + 1 rows from either ghost) is within 4 max|u^n| theta^(kWinHalo+1) of the exact value:
-// at most 2^-54 max|u^n| when theta^(kWinHalo+1) <= 2^-56.  Each window evaluates g(C) from its own
-// rows and flags its instance when the bound fails; the partition levels, which solve the whole system
-// exactly, then redo that instance's step (the old state is still in the step's input buffer).
-//
-// This is the truncation the partition method's PCR already makes when it drops couplings below
-// 2^-54, applied to the spikes between windows (the decay of the inverse of a diagonally dominant
-// tridiagonal matrix behind truncated SPIKE solvers).  One pass over the state per step: the rows are
-// read once (plus 2 kWinHalo rows per window) and the kept rows written once.
+// Halo rows of the adjoint's truncated windows on either side.
 constexpr int kWinHalo = 256;
-
-// A value every lane holds alike, moved to scalar registers.
-__device__ __forceinline__ double uniform(double v) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b & 0xffffffffu)));
-  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)));
-  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// The largest theta the windows accept: theta^(kWinHalo + 1) <= 2^-56, less a relative 1e-12 for the
-// rounding of the device's evaluation of g.
-double window_theta_limit() { return std::exp2(-56.0 / (kWinHalo + 1)) * (1.0 - 1e-12); }
-
-template <typename S, int NT>
-__global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
-    const InstDesc* __restrict__ inst, const WinDesc* __restrict__ wins, const S* __restrict__ u,
-    S* __restrict__ out, int* __restrict__ flag_now, int* __restrict__ flag_next, int* __restrict__ sticky,
-    double theta_lim, int step) {
-  using T = double;
-  constexpr int MC = kWgChunk, W = NT * MC;
-  using IS = InterfaceSpace<T, NT>;
-  constexpr int kStageBytes = padded_size(W) * static_cast<int>(sizeof(S));
-  constexpr int kBytes = kStageBytes > IS::kBytes ? kStageBytes : IS::kBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
-  __shared__ uint64_t iface_votes[2 * IS::kVoteWords];
-  __shared__ T wave_max[NT / 64];
-  const IS iws{reinterpret_cast<T*>(smem), reinterpret_cast<T*>(smem) + 3 * NT, iface_votes};
-  iws.clear_votes();
-  S* stage = reinterpret_cast<S*>(smem);
-  const WinDesc wd = wins[blockIdx.x];
-  if (wd.count <= 0) return;                   // an empty slot of a resident pool
-  const InstDesc d = inst[wd.inst];
-  const bool dir = d.bc == kDirichlet;
-  const int R = dir ? d.n - 2 : d.n;           // > W: only long systems have windows
-  const S* __restrict__ x = u + d.off + (dir ? 1 : 0);
-  S* __restrict__ y = out + d.off + (dir ? 1 : 0);
-  const int tid = threadIdx.x;
-  if (wd.limit > 0 && step >= wd.limit) {      // a slot whose steps are done: carry its kept rows over
-    for (int o = tid; o < wd.count; o += NT) {
-      int k = wd.start + wd.lo + o;
-      if (k >= R) k -= R;
-      y[k] = x[k];
-    }
-    if (dir && tid == 0) {
-      if (wd.start == 0) out[d.off] = static_cast<S>(d.a);
-      if (wd.start + W == R) out[d.off + d.n - 1] = static_cast<S>(d.b);
-    }
-    return;
-  }
-  // the window's rows (periodic windows wrap), every load in flight at once
-  S v[MC];
-  if (wd.start + W <= R) {                     // (uniform) no wrap: one base address
-    const S* __restrict__ xs = x + wd.start + tid;
-#pragma unroll
-    for (int j = 0; j < MC; ++j) v[j] = xs[j * NT];
-  } else {
-#pragma unroll
-    for (int j = 0; j < MC; ++j) {
-      int k = wd.start + tid + j * NT;
-      if (k >= R) k -= R;
-      v[j] = x[k];
-    }
-  }
-  // ghosts: the old values beyond both ends (a Dirichlet end of the system: its boundary value); the
-  // same for every lane, so kept in scalar registers
-  T gl, gr;
-  if (dir && wd.start == 0) gl = d.a;
-  else gl = uniform(static_cast<T>(x[wd.start == 0 ? R - 1 : wd.start - 1]));
-  {
-    const int k = wd.start + W;
-    if (dir && k == R) gr = d.b;
-    else gr = uniform(static_cast<T>(x[k >= R ? k - R : k]));
-  }
-  T big = T(0);
-#pragma unroll
-  for (int j = 0; j < MC; ++j) {
-    big = __builtin_fmax(big, __builtin_fabs(static_cast<T>(v[j])));
-    stage[padded(tid + j * NT)] = v[j];
-  }
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) big = __builtin_fmax(big, __shfl_xor(big, m, 64));
-  if ((tid & 63) == 0) wave_max[tid >> 6] = big;
-  __syncthreads();
-  if (tid == 0) {
-    T M = T(0);
-#pragma unroll
-    for (int k = 0; k < NT / 64; ++k) M = __builtin_fmax(M, wave_max[k]);
-    const T C = d.r * M;
-    const T theta = 2.0 * (d.D + C) / ((1.0 + 2.0 * d.D + C) + __builtin_sqrt((1.0 + C) * (1.0 + C) + 4.0 * d.D));
-    flag_next[wd.inst] = 0;                    // the next step's slot (its last readers have finished)
-    flag_next[-1] = 0;
-    if (!(theta <= theta_lim)) {
-      flag_now[wd.inst] = 1;
-      flag_now[-1] = 1;
-      sticky[wd.inst] = 1;                     // kept until its owner clears it (resident pools report it)
-    }
-  }
-  T al[MC], ga[MC], de[MC];
-  const int s = tid * MC;
-  load_staged<S>(stage, 0, s, MC, de);
-  __syncthreads();                             // every lane's rows read: the interface LDS overlays them
-  T yv, yp;
-  slot_step<NT, MC, true>(iws, SlotRows{d.r, d.D, gl, gr}, slot_lane<MC, true>(tid, W, NT, true), NT, al, ga, de, yv, yp);
-  __syncthreads();                             // the interface unknowns read before the rows are rewritten
-  const LdsDst<S> sdst{stage, 0};
-#pragma unroll
-  for (int j = 0; j < MC; ++j) {
-    if (j < MC - 1) sdst.write(j, s + j, __builtin_fma(-ga[j], yv, __builtin_fma(-al[j], yp, de[j])));
-    else sdst.write(j, s + j, yv);
-  }
-  __syncthreads();
-  // kept rows, counted from the first one (the window's rows [lo, lo + count)).  The lane index is
-  // passed through an empty asm statement so that the compiler recomputes these row indices instead of
-  // keeping the staging loop's ones alive (and spilled) across the solve.
-  const int first = wd.start + wd.lo;         // < 2R
-  int lane = tid;
-  asm volatile("" : "+v"(lane));
-#pragma unroll
-  for (int j = 0; j < (W - 2 * kWinHalo + NT - 1) / NT; ++j) {
-    const int o = lane + j * NT;
-    if (o < wd.count) {
-      int k = first + o;
-      if (k >= R) k -= R;
-      const S val = stage[padded(wd.lo + o)];
-      y[k] = wd.cn ? static_cast<S>(2.0 * static_cast<T>(val) - static_cast<T>(x[k])) : val;
-    }
-  }
-  if (dir && tid == 0) {
-    if (wd.start == 0) out[d.off] = static_cast<S>(d.a);
-    if (wd.start + W == R) out[d.off + d.n - 1] = static_cast<S>(d.b);
-  }
-}
-
 
 // ---- Adjoint BTCS step on truncated windows of the transposed system -----------------------------
 // The discrete adjoint of a BTCS step (y = u^k -> x = u^{k+1}) solves A(y)^T mu = lam' and then sets
@@ -1451,32 +1293,16 @@ int stream_grid(int device) {
   return cached[device];
 }
 
+// The partition levels' launches, forward and back to the level-0 unknowns' interfaces (levels_forward), and
+// the last back-substitution into the new state (levels_finish).  `only` (optional): only the instances whose
+// entry is nonzero; only[-1] is zero when there is none.
 template <typename S>
-hipError_t launch_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void* uv, void* outv, int64_t step) {
-  const S* u = static_cast<const S*>(uv);
-  S* out = static_cast<S*>(outv);
+void levels_forward(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const S* u, const int* only) {
   double* LA = ctx->level_a.as<double>();
   double* LC = ctx->level_c.as<double>();
   double* LD = ctx->level_d.as<double>();
   double* LX = ctx->level_x.as<double>();
-  const InstDesc* inst = plan.inst_half && plan.inst_half->ptr ? plan.inst_half->as<InstDesc>()
-                                                               : ctx->inst.as<InstDesc>();
   hipStream_t st = ctx->stream;
-  // truncated windows of the long systems; the partition levels below then serve only the instances
-  // whose windows flagged a failed bound this step
-  const int* only = nullptr;
-  if (plan.n_win > 0) {
-    int* now = win_flag_slot(plan.win_flags.as<int>(), ctx->count, step);
-    int* next = win_flag_slot(plan.win_flags.as<int>(), ctx->count, step + 1);
-    int* sticky = win_sticky(plan.win_flags.as<int>(), ctx->count);
-    if (plan.win_rows == kWgRows)
-      btcs_window_kernel<S, kWgThreads><<<static_cast<unsigned>(plan.n_win), kWgThreads, 0, st>>>(
-          inst, plan.win->as<WinDesc>(), u, out, now, next, sticky, window_theta_limit(), static_cast<int>(step));
-    else
-      btcs_window_kernel<S, 256><<<static_cast<unsigned>(plan.n_win), 256, 0, st>>>(
-          inst, plan.win->as<WinDesc>(), u, out, now, next, sticky, window_theta_limit(), static_cast<int>(step));
-    only = now;
-  }
   const int L = static_cast<int>(plan.levels.size());
   // forward: reduce level by level
   for (int l = 0; l < L; ++l) {
@@ -1499,6 +1325,36 @@ hipError_t launch_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void*
           lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), LA, LC, LD, LX, only);
     }
   }
+}
+
+template <typename S>
+void levels_finish(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const S* u, S* out,
+                   const int* only) {
+  if (plan.levels.empty() || plan.levels[0].n_blocks == 0) return;
+  const auto& lv = plan.levels[0];
+  btcs_block_backsub_kernel<S><<<lv.n_blocks, kReduceBlock, 0, ctx->stream>>>(
+      inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, out, ctx->level_x.as<double>(), only);
+}
+
+template <typename S>
+hipError_t launch_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void* uv, void* outv, int64_t step) {
+  const S* u = static_cast<const S*>(uv);
+  S* out = static_cast<S*>(outv);
+  const InstDesc* inst = plan.inst_half && plan.inst_half->ptr ? plan.inst_half->as<InstDesc>()
+                                                               : ctx->inst.as<InstDesc>();
+  hipStream_t st = ctx->stream;
+  // truncated windows of the long systems; the partition levels below then serve only the instances
+  // whose windows flagged a failed bound this step
+  const int* only = nullptr;
+  if (plan.n_win > 0) {
+    int* now = win_flag_slot(plan.win_flags.as<int>(), ctx->count, step);
+    const hipError_t e = launch_btcs_windows(ctx, plan, inst, u, out, now,
+                                             win_flag_slot(plan.win_flags.as<int>(), ctx->count, step + 1),
+                                             win_sticky(plan.win_flags.as<int>(), ctx->count));
+    if (e != hipSuccess) return e;
+    only = now;
+  }
+  levels_forward<S>(ctx, plan, inst, u, only);
   for (const WgGroup& g : plan.wg_state) {
     if (!g.n) continue;
     const SysDesc* sys = g.sys->as<SysDesc>();
@@ -1516,11 +1372,7 @@ hipError_t launch_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void*
     const hipError_t e = launch_btcs_whole(ctx, inst, g, u, out);
     if (e != hipSuccess) return e;
   }
-  if (L > 0 && plan.levels[0].n_blocks) {
-    const auto& lv = plan.levels[0];
-    btcs_block_backsub_kernel<S><<<lv.n_blocks, kReduceBlock, 0, st>>>(
-        inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, out, LX, only);
-  }
+  levels_finish<S>(ctx, plan, inst, u, out, only);
   return hipGetLastError();
 }
 
@@ -1630,6 +1482,18 @@ hipError_t launch_array_solve(const burgers_ctx* ctx, const BtcsPlan& plan, doub
 hipError_t launch_btcs_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, int64_t step) {
   if (ctx->dtype == BURGERS_F64) return launch_step<double>(ctx, plan, u, out, step);
   return launch_step<float>(ctx, plan, u, out, step);
+}
+
+hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, const int* only) {
+  const InstDesc* inst = ctx->inst.as<InstDesc>();
+  if (ctx->dtype == BURGERS_F64) {
+    levels_forward<double>(ctx, plan, inst, static_cast<const double*>(u), only);
+    levels_finish<double>(ctx, plan, inst, static_cast<const double*>(u), static_cast<double*>(out), only);
+  } else {
+    levels_forward<float>(ctx, plan, inst, static_cast<const float*>(u), only);
+    levels_finish<float>(ctx, plan, inst, static_cast<const float*>(u), static_cast<float*>(out), only);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_btcs_window_reset(const burgers_ctx* ctx, const BtcsPlan& plan) {

@@ -43,15 +43,14 @@ bool explicit_windows(int32_t i, int32_t n, bool periodic, int depth, bool rk4, 
   return true;
 }
 
-void btcs_windows(int32_t i, int32_t R, bool periodic, int W, bool cn, std::vector<WinDesc>& out) {
+void btcs_windows(int32_t i, int32_t R, bool periodic, int W, std::vector<WinDesc>& out) {
   const int64_t halo = btcs_window_halo(), kept = W - 2 * halo;
   for (int64_t lo = 0; lo < R; lo += kept) {
     const int64_t hi = std::min<int64_t>(R, lo + kept);
     const int64_t start =
         periodic ? ((lo - halo) % R + R) % R : std::min<int64_t>(std::max<int64_t>(lo - halo, 0), R - W);
     const int64_t rel = periodic ? halo : lo - start;
-    out.push_back(WinDesc{i, static_cast<int32_t>(start), static_cast<int32_t>(rel), static_cast<int32_t>(hi - lo),
-                          cn ? 1 : 0, 0});
+    out.push_back(WinDesc{i, static_cast<int32_t>(start), static_cast<int32_t>(rel), static_cast<int32_t>(hi - lo)});
   }
 }
 
@@ -370,15 +369,19 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   plan->stream_exact = pipelined;
   const int cap = burgers::btcs_wg_capacity();
   const int chunk = burgers::btcs_reduce_chunk();
-  // truncated windows of the long systems (automatic and per-step paths): 4096 rows each (8192 when
-  // asked), keeping all but `halo` rows at either end; the partition levels stay as the fallback for
-  // failed bounds.  Narrower windows read 14% more rows than 8192-row ones but take 256-lane workgroups,
-  // four per CU instead of two, whose loads, solves and stores overlap better (C3: 52.6 against 60.8 us
-  // per step).
+  // truncated windows of the long systems (automatic and per-step paths); the partition levels stay as the
+  // fallback for failed bounds.  One step per launch: 4096 rows each (8192 when asked); on the automatic path
+  // also windows of several steps, where they are all that steps through HBM (see enqueue_stepped)
   plan->win_rows = longmode == 2 ? cap : 4096;
-  std::vector<burgers::WinDesc> windows;
+  std::vector<burgers::ChunkWin> windows, deep;
+  std::vector<int32_t> windowed;
+  bool only_windows = want == 0 && !burgers::tl_arena;
   auto add_windows = [&](int32_t i, int32_t R, bool is_cn) {
-    burgers::btcs_windows(i, R, ctx->probs[i].bc == BURGERS_BC_PERIODIC, plan->win_rows, is_cn, windows);
+    const bool periodic = ctx->probs[i].bc == BURGERS_BC_PERIODIC;
+    burgers::btcs_step_windows(i, R, periodic, plan->win_rows, is_cn, windows);
+    if (is_cn) return;
+    burgers::btcs_deep_windows(i, R, periodic, deep);
+    windowed.push_back(i);
   };
   // whole-system systems grouped by width class (lanes, chunk)
   std::map<std::pair<int, int>, std::vector<SysDesc>> wg_state, resident, streamed, cn_chip, newton_chip;
@@ -503,6 +506,18 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
       (e = plan->win_flags.alloc(static_cast<size_t>(burgers::win_flags_words(ctx->count)) * sizeof(int), ctx->stream)) !=
           hipSuccess)
     return from_hip(e);
+  if (only_windows && !windowed.empty() && windowed.size() == stepped.size()) {
+    const int64_t words = burgers::deep_words(ctx->count);
+    plan->deep = std::make_unique<DevBuf>();
+    plan->deep_inst = std::make_unique<DevBuf>();
+    if ((e = upload_on(ctx->stream, *plan->deep, deep)) != hipSuccess ||
+        (e = upload_on(ctx->stream, *plan->deep_inst, windowed)) != hipSuccess ||
+        (e = plan->deep_words.alloc(static_cast<size_t>(words) * sizeof(int), ctx->stream)) != hipSuccess ||
+        (e = burgers::launch_clear_ints(ctx, plan->deep_words.as<int>(), words)) != hipSuccess)
+      return from_hip(e);
+    plan->n_deep = static_cast<int64_t>(deep.size());
+    plan->n_deep_inst = static_cast<int64_t>(windowed.size());
+  }
   plan->levels.resize(red_sys.size());
   for (size_t l = 0; l < red_sys.size(); ++l) {
     auto& lv = plan->levels[l];
@@ -660,6 +675,11 @@ hipError_t enqueue_stepped(burgers_ctx* ctx, const burgers::BtcsPlan& pl, void* 
   return e;
 }
 
+// Windows of several steps serve calls of four steps and more: they begin with a pass over the states for the
+// bound that holds for the whole call, and keep 384 of 512 chunks against 224 of 256.
+constexpr int64_t kDeepLeast = 4, kDeepCall = int64_t{1} << 24;
+bool takes_deep(const burgers::BtcsPlan& pl, int64_t nsteps) { return pl.n_deep > 0 && nsteps >= kDeepLeast; }
+
 // nsteps implicit steps of one subset, the final state in u.
 void btcs_tasks(burgers_ctx* ctx, int set, void* u, int64_t nsteps, std::vector<burgers::Task>& tasks) {
   const burgers::BtcsPlan* pl = ctx->btcs[set].get();
@@ -685,7 +705,25 @@ void btcs_tasks(burgers_ctx* ctx, int set, void* u, int64_t nsteps, std::vector<
     on_chip(g, 6.0, [=](const burgers::WgGroup& q, int k) {
       return burgers::launch_newton_resident(ctx, q, u, k, ctx->newton->flags.as<int>());
     });
-  if (pl->n_copy > 0) {
+  if (takes_deep(*pl, nsteps)) {
+    const double rows = 8192.0 * static_cast<double>(pl->n_deep);
+    tasks.push_back({chain_us(nsteps, 4.0, rows, 8e5), nsteps / 4, [=]() -> hipError_t {
+      hipError_t e = hipSuccess;
+      for (int64_t done = 0; done < nsteps && e == hipSuccess; done += kDeepCall)
+        e = burgers::launch_btcs_deep(ctx, *pl, u, ctx->work.ptr, std::min(nsteps - done, kDeepCall));
+      return e;
+    }});
+    tasks.push_back({chain_us(nsteps, 6.0, 0.0, 1.0), 3 * nsteps, [=]() -> hipError_t {
+      const int* only = burgers::win_flag_slot(pl->win_flags.as<int>(), ctx->count, 0);
+      void* bufs[2] = {u, ctx->work.ptr};
+      hipError_t e = hipSuccess;
+      for (int64_t s = 0; s < nsteps && e == hipSuccess; ++s)
+        e = burgers::launch_btcs_levels(ctx, *pl, bufs[s & 1], bufs[(s & 1) ^ 1], only);
+      if (e == hipSuccess && (nsteps & 1))
+        e = burgers::launch_copy_tiles(ctx, pl->copy->as<Tile>(), pl->n_copy, ctx->work.ptr, u, only);
+      return e;
+    }});
+  } else if (pl->n_copy > 0) {
     const double nodes = static_cast<double>(pl->n_copy) * burgers::explicit_tile_nodes(ctx->dtype);
     tasks.push_back({chain_us(nsteps, pl->newton ? 100.0 : 11.0, nodes, 3e5), 4 * nsteps,
                      [=]() { return enqueue_stepped(ctx, *pl, u, nsteps); }});
@@ -700,8 +738,14 @@ hipError_t enqueue_all(burgers_ctx* ctx, int set, int scheme, void* u, int64_t n
   std::vector<burgers::Task> tasks;
   if (scheme == BURGERS_EXPLICIT || (mixed && !ctx->set_explicit.empty() && nsteps > 0))
     explicit_tasks(ctx, mixed ? kSetExplicit : set, u, nsteps, tasks);
-  if (scheme == BURGERS_BTCS || (mixed && !ctx->set_btcs.empty() && bsteps > 0))
-    btcs_tasks(ctx, mixed ? kSetBtcs : set, u, bsteps, tasks);
+  if (scheme == BURGERS_BTCS || (mixed && !ctx->set_btcs.empty() && bsteps > 0)) {
+    const int bset = mixed ? kSetBtcs : set;
+    const burgers::BtcsPlan& pl = *ctx->btcs[bset];
+    // which instances the windows may step, and which the partition levels must: both of their chains follow
+    if (takes_deep(pl, bsteps))
+      if (const hipError_t e = burgers::launch_btcs_bound(ctx, pl, u, false); e != hipSuccess) return e;
+    btcs_tasks(ctx, bset, u, bsteps, tasks);
+  }
   return burgers::run_tasks(ctx, tasks, ctx->plan.serial == 1);
 }
 
@@ -946,11 +990,11 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
       roots.emplace_back(i, sys_off[i], R);
       if (windows) {
         const size_t w0 = wins.size();
-        burgers::btcs_windows(i, R, p.bc == BURGERS_BC_PERIODIC, 4096, false, wins);
+        burgers::btcs_windows(i, R, p.bc == BURGERS_BC_PERIODIC, 4096, wins);
         for (size_t w = w0; w < wins.size(); ++w) win_slot.push_back(slot++);
       }
       if (whole) {
-        wholes.push_back(burgers::WinDesc{i, 0, 0, R, 0, 0});
+        wholes.push_back(burgers::WinDesc{i, 0, 0, R});
         whole_slot.push_back(slot++);
       }
     }

@@ -780,10 +780,13 @@ __global__ __launch_bounds__(kBlockThreads) void explicit_pack_kernel(const Inst
 template <typename T>
 __global__ __launch_bounds__(kStreamThreads) void copy_tiles_kernel(const Tile* __restrict__ tiles,
                                                                     const T* __restrict__ src,
-                                                                    T* __restrict__ dst) {
+                                                                    T* __restrict__ dst,
+                                                                    const int* __restrict__ only) {
   constexpr int V = Vec<T>::n, K = kStreamVecs<T>;
   using VT = typename Vec<T>::type;
+  if (only && only[-1] == 0) return;
   const Tile t = tiles[blockIdx.x];
+  if (only && only[t.inst] == 0) return;
 #pragma unroll
   for (int q = 0; q < K; ++q) {
     const int i0 = t.start + (q * kStreamThreads + static_cast<int>(threadIdx.x)) * V;
@@ -804,15 +807,15 @@ __global__ __launch_bounds__(kStreamThreads) void copy_tiles_kernel(const Tile* 
 }  // namespace
 
 hipError_t launch_copy_tiles(const burgers_ctx* ctx, const Tile* tiles, int64_t n_tiles, const void* src,
-                             void* dst) {
+                             void* dst, const int* only) {
   if (n_tiles <= 0) return hipSuccess;
   const dim3 grid(static_cast<unsigned>(n_tiles)), block(kStreamThreads);
   if (ctx->dtype == BURGERS_F64) {
     copy_tiles_kernel<double><<<grid, block, 0, ctx->stream>>>(tiles, static_cast<const double*>(src),
-                                                               static_cast<double*>(dst));
+                                                               static_cast<double*>(dst), only);
   } else {
     copy_tiles_kernel<float><<<grid, block, 0, ctx->stream>>>(tiles, static_cast<const float*>(src),
-                                                              static_cast<float*>(dst));
+                                                              static_cast<float*>(dst), only);
   }
   return hipGetLastError();
 }

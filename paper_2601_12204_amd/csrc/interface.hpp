@@ -257,6 +257,7 @@ struct SlotLane {
   bool own;          // lanes P and beyond hold nothing
   bool dummy;        // slot 0 is no row
   bool first, last;  // the Dirichlet system's first row is in slot 0, its last row in slot M - 1
+  double tie = -1.0; // al of a slot 0 that is no row: x_0 = -al y_{t-1}
 };
 
 // FULL: every lane holds M rows (R = P M with P the workgroup's lanes).
@@ -298,7 +299,7 @@ __device__ __forceinline__ void slot_eliminate(const Rows& rows, const SlotLane&
       ib = bj;
     } else if (j == 0) {
       const double inv = recip(bj);
-      al[0] = !FULL && l.dummy ? -1.0 : aj * inv;
+      al[0] = !FULL && l.dummy ? l.tie : aj * inv;
       ga[0] = !FULL && l.dummy ? 0.0 : cj * inv;
       de[0] = !FULL && l.dummy ? 0.0 : dj * inv;
     } else {

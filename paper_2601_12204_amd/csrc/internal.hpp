@@ -102,16 +102,26 @@ struct SysDesc {
   int32_t limit = 0;  // > 0: the on-chip solver advances at most this many of the launch's steps
 };
 
-// A window of a long BTCS system (truncated partition): rows [start, start + 8192) of the system (mod its
-// row count for periodic systems) are solved as a plain system whose neighbours beyond both ends take
-// their old values; rows [start + lo, start + lo + count) of that solve are written to the new state.
+// A window of a long transposed BTCS system (adjoint): rows [start, start + W) of the system (mod its row
+// count for periodic systems) are solved as a plain system; rows [start + lo, start + lo + count) are kept.
 struct WinDesc {
   int32_t inst;
   int32_t start;
   int32_t lo;
   int32_t count;
+};
+
+// A window of a long BTCS or Crank-Nicolson system (window.hip): `chunks` chunks of the system from `first` on
+// (mod its chunk count for periodic systems), of which `count` from the window's `lo` on are written to the
+// new state.
+struct ChunkWin {
+  int32_t inst;
+  int32_t first;
+  uint16_t chunks;
+  uint16_t lo;
+  int32_t count;
   int32_t cn;    // Crank-Nicolson system: the half-dt solve y is stored as 2y - u
-  int32_t limit; // > 0: only the first `limit` steps of a call solve; later ones copy the kept rows
+  int32_t limit; // > 0: only the first `limit` steps of a call
 };
 
 // Flags of truncated windows over `count` instances, one slot per step parity: slot p starts with a word
@@ -121,6 +131,10 @@ struct WinDesc {
 inline int64_t win_flags_words(int64_t count) { return 3 * count + 2; }
 inline int* win_flag_slot(int* base, int64_t count, int64_t step) { return base + (step & 1) * (count + 1) + 1; }
 inline int* win_sticky(int* base, int64_t count) { return base + 2 * (count + 1); }
+// Words of the windows of several steps over `count` instances: per instance the bits of max|u| (64 bits, zero
+// between calls) and, after all of those, its PCR steps per solve for the call under way.
+inline int64_t deep_words(int64_t count) { return 3 * count; }
+inline int* deep_code(int* base, int64_t count) { return base + 2 * count; }
 
 // A block of consecutive chunks of one system (reduce and back-substitution kernels).
 struct ChunkBlock {
@@ -224,9 +238,14 @@ struct BtcsPlan {
   // truncated windows of the long systems (every system of the partition levels at level 0 when
   // present); the partition levels then solve only the systems whose windows flag a failed bound
   int longmode = 0;                          // burgers_plan.btcs_long the plan was built for
-  std::unique_ptr<DevBuf> win;               // WinDesc[]
+  std::unique_ptr<DevBuf> win;               // ChunkWin[]
   int64_t n_win = 0;
   int win_rows = 8192;                       // rows per window: 8192 (512 lanes) or 4096 (256 lanes)
+  // windows of several steps per launch, where every instance stepped through HBM is a long BTCS system;
+  // calls of a few steps take the windows above
+  std::unique_ptr<DevBuf> deep, deep_inst;   // ChunkWin[], int32[] (the windowed instances)
+  int64_t n_deep = 0, n_deep_inst = 0;
+  DevBuf deep_words;                         // see deep_words()
   bool stream_exact = false;                 // per-step exact 8192-row systems: the persistent pipelined kernel
   DevBuf win_flags;                          // win_flags_words(count) int32 (see win_flag_slot)
 };
@@ -353,8 +372,8 @@ hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles
 // Windows of a long explicit instance `i` of n nodes advanced `depth` steps per launch (halo = depth x
 // stages per side); appends them to `out`.  Returns false when the halo leaves no kept node.
 bool explicit_windows(int32_t i, int32_t n, bool periodic, int depth, bool rk4, std::vector<BlockTile>& out);
-// Truncated BTCS windows of `W` rows over a system of R rows of instance i; appends them to `out`.
-void btcs_windows(int32_t i, int32_t R, bool periodic, int W, bool cn, std::vector<WinDesc>& out);
+// Truncated windows of `W` rows over a transposed BTCS system of R rows of instance i; appends them to `out`.
+void btcs_windows(int32_t i, int32_t R, bool periodic, int W, std::vector<WinDesc>& out);
 hipError_t launch_clear_ints(const burgers_ctx* ctx, int* p, int64_t n);
 // capi.hip: a chain of launches on the context's current stream with a rough time, independent of the others
 // of its list; run_tasks runs a list concurrently (or, `serial`, one after another).
@@ -368,8 +387,9 @@ hipError_t run_tasks(burgers_ctx* ctx, std::vector<Task>& tasks, bool serial);
 bool problem_valid(const burgers_problem& p);
 InstDesc inst_desc(const burgers_problem& p, int64_t off);
 int explicit_block_lanes(int n);   // narrowest workgroup that holds a whole instance of n nodes
+// `only` (optional): only the tiles of instances whose entry is nonzero.
 hipError_t launch_copy_tiles(const burgers_ctx* ctx, const Tile* tiles, int64_t n_tiles, const void* src,
-                             void* dst);
+                             void* dst, const int* only = nullptr);
 int explicit_tile_nodes(burgers_dtype dt);
 int explicit_block_capacity();
 
@@ -418,6 +438,22 @@ constexpr int kReduceBlock = 256;       // chunks per workgroup in the partition
 // One BTCS step of the plan from u to out; `step` counts the steps of the current call from 0 (it selects
 // the parity slot of the window flags, which launch_btcs_window_reset clears at the start of a call).
 hipError_t launch_btcs_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, int64_t step);
+// One step of the partition levels alone, for the instances whose entry of `only` is nonzero.
+hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, const int* only);
+// window.hip.  Windows of one step (`rows` of 4096 or 8192) and of several over a system of R > 16384 rows of
+// instance i, appended to `out`; how many of the latter cover any system of up to `rows` rows.
+void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, std::vector<ChunkWin>& out);
+void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out);
+int64_t btcs_deep_windows_max(int64_t rows);
+// One step of plan.win from u to out (inst: half-dt coefficients for Crank-Nicolson systems); the instances with
+// a window beyond the bound are flagged in `now`, and `next` is cleared.
+hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const void* u,
+                               void* out, int* now, int* next, int* sticky);
+// For a call from the states in u: the PCR steps of plan.deep's instances, and the flags (slot 0 of the window
+// flags) of those beyond the bound, which launch_btcs_deep leaves alone; `keep`: it steps them too.
+hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, bool keep);
+// nsteps (below 2^30) steps of plan.deep, the final states in u.
+hipError_t launch_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps);
 hipError_t launch_btcs_window_reset(const burgers_ctx* ctx, const BtcsPlan& plan);
 int btcs_window_halo();                 // halo rows on each side of a window's output rows
 hipError_t launch_btcs_resident(const burgers_ctx* ctx, const WgGroup& group, void* u, int steps);

@@ -25,7 +25,7 @@ using burgers::DevBuf;
 using burgers::InstDesc;
 using burgers::SysDesc;
 using burgers::Tile;
-using burgers::WinDesc;
+using burgers::ChunkWin;
 
 constexpr int kWholeLanes[4] = {64, 128, 256, 512};
 // BTCS classes of the on-chip solver: lanes and rows per lane (btcs_width_class)
@@ -133,11 +133,11 @@ void build_image(burgers_pool* pl) {
       w.resize(std::min<size_t>(w.size(), static_cast<size_t>(pl->wx)));   // (never cut: wx covers cap)
       std::memcpy(pl->image.data() + pl->off_win + s * pl->wx * sizeof(BlockTile), w.data(), w.size() * sizeof(BlockTile));
     } else {
-      std::vector<WinDesc> w;
-      burgers::btcs_windows(i, rows_of(p), periodic, 4096, false, w);
+      std::vector<ChunkWin> w;
+      burgers::btcs_deep_windows(i, rows_of(p), periodic, w);
       for (auto& wd : w) wd.limit = limit;
       w.resize(std::min<size_t>(w.size(), static_cast<size_t>(pl->wx)));
-      std::memcpy(pl->image.data() + pl->off_win + s * pl->wx * sizeof(WinDesc), w.data(), w.size() * sizeof(WinDesc));
+      std::memcpy(pl->image.data() + pl->off_win + s * pl->wx * sizeof(ChunkWin), w.data(), w.size() * sizeof(ChunkWin));
     }
     std::vector<Tile> ct;
     for (int64_t k = 0; k < p.n && static_cast<int64_t>(ct.size()) < pl->tx; k += tile_nodes)
@@ -178,14 +178,8 @@ hipError_t enqueue_tick(burgers_pool* pl, uint32_t mask) {
   for (int c = 0; c < kResClasses; ++c)
     if ((mask & (1u << c)) && (e = burgers::launch_btcs_resident(ctx, pl->res[c], u, K)) != hipSuccess) return e;
   if (mask & (1u << kWinGroup)) {
-    if ((e = burgers::launch_btcs_window_reset(ctx, pl->bplan)) != hipSuccess) return e;
-    void* bufs[2] = {u, work};
-    int cur = 0;
-    for (int s = 0; s < K; ++s) {
-      if ((e = burgers::launch_btcs_step(ctx, pl->bplan, bufs[cur], bufs[cur ^ 1], s)) != hipSuccess) return e;
-      cur ^= 1;
-    }
-    if (cur && (e = burgers::launch_copy_tiles(ctx, copy, n_copy, work, u)) != hipSuccess) return e;
+    if ((e = burgers::launch_btcs_bound(ctx, pl->bplan, u, true)) != hipSuccess) return e;
+    if ((e = burgers::launch_btcs_deep(ctx, pl->bplan, u, work, K)) != hipSuccess) return e;
   }
   return e;
 }
@@ -232,7 +226,7 @@ void pool_free(burgers_pool* pl) {
   if (pl->sticky_host) (void)hipHostFree(pl->sticky_host);
   // views into `tables` must not free anything
   for (auto& g : pl->res) g.sys.reset();
-  pl->bplan.win.reset();
+  pl->bplan.deep.reset();
   delete pl;
 }
 
@@ -282,11 +276,10 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
     pl->wx = longest > burgers::explicit_block_capacity() ? (longest + kept - 1) / kept : 0;
     entry = sizeof(BlockTile);
   } else {
-    const int64_t kept = 4096 - 2 * burgers::btcs_window_halo();
-    pl->wx = !burgers::btcs_solved_whole(longest - 2) ? (longest + kept - 1) / kept : 0;
-    entry = sizeof(WinDesc);
+    pl->wx = !burgers::btcs_solved_whole(longest - 2) ? burgers::btcs_deep_windows_max(longest) : 0;
+    entry = sizeof(ChunkWin);
   }
-  pl->tx = pl->wx ? (pl->cap + tile_nodes - 1) / tile_nodes : 0;
+  pl->tx = pl->wx && scheme == BURGERS_EXPLICIT ? (pl->cap + tile_nodes - 1) / tile_nodes : 0;
   const size_t whole_entry = scheme == BURGERS_EXPLICIT ? sizeof(BlockTile) : sizeof(SysDesc);
   size_t off = 0;
   for (int c = 0; c < kResClasses; ++c) {
@@ -324,12 +317,22 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
       g.n = static_cast<int32_t>(slots);
       pl->res.push_back(std::move(g));
     }
-    pl->bplan.win = std::make_unique<DevBuf>();
-    view(*pl->bplan.win, pl->tables.ptr, pl->off_win, static_cast<size_t>(slots * pl->wx) * entry, st);
-    pl->bplan.n_win = slots * pl->wx;
-    pl->bplan.win_rows = 4096;
-    if (pl->bplan.n_win > 0) {
+    pl->bplan.deep = std::make_unique<DevBuf>();
+    view(*pl->bplan.deep, pl->tables.ptr, pl->off_win, static_cast<size_t>(slots * pl->wx) * entry, st);
+    pl->bplan.n_deep = slots * pl->wx;
+    if (pl->bplan.n_deep > 0) {
+      std::vector<int32_t> members(static_cast<size_t>(slots));
+      for (int64_t s = 0; s < slots; ++s) members[s] = static_cast<int32_t>(s);
+      pl->bplan.deep_inst = std::make_unique<DevBuf>();
+      pl->bplan.n_deep_inst = slots;
       if ((e = pl->bplan.win_flags.alloc(static_cast<size_t>(burgers::win_flags_words(slots)) * sizeof(int), st)) !=
+              hipSuccess ||
+          (e = pl->bplan.deep_inst->alloc(members.size() * sizeof(int32_t), st)) != hipSuccess ||
+          (e = hipMemcpyAsync(pl->bplan.deep_inst->ptr, members.data(), members.size() * sizeof(int32_t),
+                              hipMemcpyHostToDevice, st)) != hipSuccess ||
+          (e = pl->bplan.deep_words.alloc(static_cast<size_t>(burgers::deep_words(slots)) * sizeof(int), st)) !=
+              hipSuccess ||
+          (e = burgers::launch_clear_ints(&pl->ctx, pl->bplan.deep_words.as<int>(), burgers::deep_words(slots))) !=
               hipSuccess ||
           (e = burgers::launch_clear_ints(&pl->ctx, pl->bplan.win_flags.as<int>(), burgers::win_flags_words(slots))) !=
               hipSuccess) {
@@ -368,7 +371,7 @@ burgers_status burgers_pool_admit(burgers_pool* pool, const burgers_problem* p, 
     e = hipMemcpyAsync(pool->ctx.inst.as<InstDesc>() + s, &pool->inst_host[s], sizeof(InstDesc),
                        hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dst, u0, static_cast<size_t>(p->n) * pool->ctx.word, hipMemcpyDefault, st);
-  if (e == hipSuccess && pool->bplan.n_win > 0)
+  if (e == hipSuccess && pool->bplan.n_deep > 0)
     e = burgers::launch_clear_ints(&pool->ctx, burgers::win_sticky(pool->bplan.win_flags.as<int>(), pool->slots) + s, 1);
   if (e != hipSuccess) {
     pool->sticky_err = e;
@@ -404,7 +407,7 @@ burgers_status burgers_pool_tick(burgers_pool* pool) {
                        pool->ctx.stream);
   if (e == hipSuccess) e = tick_graph(pool, mask, &g);
   if (e == hipSuccess) e = hipGraphLaunch(g, pool->ctx.stream);
-  if (e == hipSuccess && pool->bplan.n_win > 0)
+  if (e == hipSuccess && pool->bplan.n_deep > 0)
     e = hipMemcpyAsync(pool->sticky_host, burgers::win_sticky(pool->bplan.win_flags.as<int>(), pool->slots),
                        static_cast<size_t>(pool->slots) * sizeof(int), hipMemcpyDeviceToHost, pool->ctx.stream);
   if (e == hipSuccess) e = hipEventRecord(pool->done, pool->ctx.stream);
@@ -435,14 +438,14 @@ burgers_status burgers_pool_retire(burgers_pool* pool, int64_t slot, void* dst) 
   if (e == hipSuccess)
     e = hipMemcpyAsync(dst, src, static_cast<size_t>(pool->probs[slot].n) * pool->ctx.word, hipMemcpyDefault,
                        pool->ctx.stream);
-  if (e == hipSuccess && pool->bplan.n_win > 0 && hipEventQuery(pool->done) == hipErrorNotReady)
+  if (e == hipSuccess && pool->bplan.n_deep > 0 && hipEventQuery(pool->done) == hipErrorNotReady)
     e = hipEventSynchronize(pool->done);   // the flags of the slot's last tick
   if (e != hipSuccess) {
     pool->sticky_err = e;
     return status_of(e);
   }
   pool->remaining[slot] = -1;
-  return pool->bplan.n_win > 0 && pool->sticky_host[slot] ? BURGERS_E_BOUND : BURGERS_OK;
+  return pool->bplan.n_deep > 0 && pool->sticky_host[slot] ? BURGERS_E_BOUND : BURGERS_OK;
 }
 
 }  // extern "C"

@@ -1,0 +1,525 @@
+// BTCS and Crank-Nicolson systems of more than 16384 rows on truncated windows: several steps per launch
+// (btcs_deep_kernel) or one (btcs_window_kernel), with the same results to the bit.
+//
+// A system is cut into chunks of 16 rows (the last ones of 15 where the rows do not divide), at the same
+// rows for every window, step and launch.  A window is a run of up to 512 (256) chunks, one per lane, solved
+// as a plain system by the interface partition: beyond its two ends the unknowns are taken as zero (at a
+// Dirichlet end of the system: the boundary value).  An interface row whose couplings have fallen below
+// 2^-54 of its diagonal drops them there and then, and the PCR takes at most S steps (strides 1 to
+// 2^(S-1), S <= 4), so a chunk's solution depends on the 2^S chunks on either side and on nothing else: chunks
+// that far inside a window are the same in every window that holds them, whatever steps it has taken before.
+// A window of several steps therefore only loses 2^S chunks at either end with each, and how a call's steps
+// are spread over launches, windows or calls does not show in the results.
+//
+// Error of a kept row.  Let e be the window solution minus the exact one, extended to the ghosts (the unknowns
+// beyond the ends) by the ghosts' errors g_L, g_R.  Every window row gives l_i e_{i-1} + d_i e_i + p_i
+// e_{i+1} = 0 with l_i, p_i <= 0 and d_i - |l_i| - |p_i| = 1, so a vector w with that operator >= 0 on the window
+// rows and w >= 0 at the ghosts is >= 0 throughout (at a negative minimum the row would give 1 * w_i < 0).  The
+// barrier v_i = theta^(i+1) (ghost at i = -1) meets -|l_i| + d_i theta - |p_i| theta^2 >= 0 whenever theta is
+// at least the smaller root of that quadratic, which for the BTCS rows (c = r u_i, the couplings D + max(c,0)
+// and D - min(c,0)) is at most
+//     g(C) = 2 (D + C) / (1 + 2D + C + sqrt((1 + C)^2 + 4D)),   C = r max|u_i| over the window
+// (g increases with C, and the mirrored barrier from the right end takes the same bound).  With w =
+// |g_L| v + |g_R| v' -+ e:  |e_i| <= |g_L| theta^(i+1) + |g_R| theta^(W-i).  By the maximum principle of the
+// step, which the window's system keeps with its zero ghosts, a ghost is off by at most max|u^n|.  The same
+// barrier bounds the couplings that the PCR drops after S steps, between unknowns 2^S chunks (n_S = 15 2^S
+// rows at least, 241 for S = 4) apart, by theta^(n_S) each.  With theta^(n_S) <= 2^-56 a kept row is within
+// 2^-54 max|u^n| of the exact value after every step.  The maximum principle also keeps max|u| from growing,
+// so the bound at the start of a call holds for all of its steps (up to rounding, which the limits' slack
+// covers); the state of a Crank-Nicolson step, 2y - u, has no such bound: those systems are checked, and
+// stepped, once per launch.
+//
+// This is the truncation the partition method's PCR already makes when it drops couplings below 2^-54, applied
+// to the spikes between windows (the decay of the inverse of a diagonally dominant tridiagonal matrix behind
+// truncated SPIKE solvers).  Systems beyond the bound are solved exactly by the partition levels.
+#include <cmath>
+
+#include "interface.hpp"
+#include "internal.hpp"
+#include "staging.hpp"
+#include "stencil.hpp"
+
+#pragma clang fp contract(off)
+
+namespace burgers {
+namespace {
+
+constexpr int kM = 16;             // rows (slots) of a chunk
+constexpr int kMaxS = 4;           // PCR steps of a window's solve at most
+constexpr int kDeepLanes = 512;
+// Chunks lost at either end of a window over a launch of several steps: with S = 3, the usual case at ten
+// times the CFL step, 8 steps a launch.  One grid of 2^24 rows, us per step (384, 416, 448 of 512 chunks kept):
+// see kDeepHalo in the table of launch_btcs_deep.
+constexpr int kDeepHalo = 64;
+constexpr int kStepHalo = 1 << kMaxS;
+
+// The largest theta for S PCR steps, theta^(n_S) <= 2^-56, with slack for rounding (its own evaluation and
+// the growth of max|u| by rounding over a call's steps).
+struct ThetaLimits {
+  double of[kMaxS];   // S = 1 .. kMaxS
+};
+ThetaLimits theta_limits() {
+  ThetaLimits t;
+  for (int s = 1; s <= kMaxS; ++s) t.of[s - 1] = std::exp2(-56.0 / (s < 4 ? 15 << s : 241)) * (1.0 - 1e-9);
+  return t;
+}
+
+__device__ __forceinline__ double theta_bound(const InstDesc& d, double M) {
+  const double C = d.r * M;
+  return 2.0 * (d.D + C) / ((1.0 + 2.0 * d.D + C) + __builtin_sqrt((1.0 + C) * (1.0 + C) + 4.0 * d.D));
+}
+
+// |v| into a running maximum; a NaN counts as infinite, so that its instance fails the bound.
+__device__ __forceinline__ void take_max(double v, double& big) {
+  const double a = __builtin_fabs(v);
+  big = __builtin_fmax(big, a == a ? a : __builtin_inf());
+}
+
+// Chunks of a system of R rows: P of them, the first rho of 16 rows and the others of 15 (R > 16384).
+struct Chunks {
+  int R, P, rho;
+  __device__ __forceinline__ explicit Chunks(int rows) : R(rows), P((rows + kM - 1) / kM), rho(rows - (kM - 1) * P) {}
+  __device__ __forceinline__ int base(int c) const { return (kM - 1) * c + (c < rho ? c : rho); }
+  // rows of the run of n chunks from c on (c < P; the run may pass the end of a periodic system)
+  __device__ __forceinline__ int rows(int c, int n) const {
+    const int e = c + n;
+    return e <= P ? base(e) - base(c) : R - base(c) + base(e - P);
+  }
+};
+
+// Interface solve of a window of L chunks, lane t < L holding chunk t (see interface_solve; the first chunk has
+// no coupling to its left, the last none to its right).  A partner beyond the ends is replaced by the end
+// chunk: its coefficient is zero there.
+template <int NT>
+__device__ __forceinline__ void window_solve(const InterfaceSpace<double, NT>& w, int L, int S, bool own, double al0,
+                                             double ga0, double de0, double alL, double gaL, double deL, double ia,
+                                             double ib, double ic, double id, double& y, double& yp) {
+  const int t = threadIdx.x;
+  constexpr int kV = InterfaceSpace<double, NT>::kVoteWords;
+  if (own) {
+    w.xchg[t] = al0;
+    w.xchg[NT + t] = ga0;
+    w.xchg[2 * NT + t] = de0;
+  }
+  __syncthreads();
+  double a = 0.0, c = 0.0, d = 0.0;
+  bool live = false;
+  if (own) {
+    const int n = t + 1 < L ? t + 1 : t;
+    const double nal = w.xchg[n], nga = w.xchg[NT + n], nde = w.xchg[2 * NT + n];
+    const double inv = recip(__builtin_fma(-ic, nal, __builtin_fma(-ia, gaL, ib)));
+    a = -(ia * alL) * inv;
+    c = -(ic * nga) * inv;
+    d = __builtin_fma(-ic, nde, __builtin_fma(-ia, deL, id)) * inv;
+    live = (__builtin_fabs(a) + __builtin_fabs(c)) > kNegligible;
+    a = live ? a : 0.0;
+    c = live ? c : 0.0;
+    w.rows[t] = a;
+    w.rows[NT + t] = c;
+    w.rows[2 * NT + t] = d;
+  }
+  __syncthreads();
+  int b = 0;
+  bool done = false;
+  for (int i = 0; i < S && !done; ++i) {
+    const double* A = w.rows + b * 3 * NT;
+    const double* C = A + NT;
+    const double* D = C + NT;
+    if (own) {
+      if (live) {
+        const int s = 1 << i;
+        const int mi = t >= s ? t - s : 0, pi = t + s < L ? t + s : L - 1;
+        pcr_combine(a, c, d, A[mi], C[mi], D[mi], A[pi], C[pi], D[pi], a, c, d);
+        live = (__builtin_fabs(a) + __builtin_fabs(c)) > kNegligible;
+        a = live ? a : 0.0;
+        c = live ? c : 0.0;
+      }
+      double* nA = w.rows + (1 - b) * 3 * NT;
+      nA[t] = a;
+      nA[NT + t] = c;
+      nA[2 * NT + t] = d;
+    }
+    const bool wave_live = __ballot(live) != 0;
+    if ((t & 63) == 0) reinterpret_cast<unsigned char*>(w.votes + (1 - b) * kV)[t >> 6] = wave_live ? 1 : 0;
+    __syncthreads();
+    b = 1 - b;
+    uint64_t any = 0;
+#pragma unroll
+    for (int k = 0; k < kV; ++k) any |= w.votes[b * kV + k];
+    done = any == 0;
+  }
+  // (couplings left after S steps are dropped: at most theta^(n_S))
+  y = d;
+  yp = own ? w.rows[b * 3 * NT + 2 * NT + (t > 0 ? t - 1 : 0)] : 0.0;
+}
+
+// LDS of a window: its rows staged between HBM and the lanes, overlaid by the interface solve.
+template <typename S, int NT>
+struct WindowSpace {
+  static constexpr int kStageBytes = padded_size(NT * kM) * static_cast<int>(sizeof(S));
+  static constexpr int kIface = InterfaceSpace<double, NT>::kBytes;
+  static constexpr int kBytes = kStageBytes > kIface ? kStageBytes : kIface;
+};
+
+// A window's place in its system.
+struct Frame {
+  Chunks ch;
+  int r0, total;           // its first row and its rows
+  __device__ __forceinline__ Frame(int R, const ChunkWin& w) : ch(R), r0(ch.base(w.first)), total(ch.rows(w.first, w.chunks)) {}
+};
+
+// The lane's chunk: its slots' first row counted from the window's, and its part in the solve.
+__device__ __forceinline__ int window_lane(const Frame& f, const ChunkWin& w, int t, SlotLane& l) {
+  int c = w.first + t, wrap = 0;
+  if (c >= f.ch.P) {
+    c -= f.ch.P;
+    wrap = f.ch.R;
+  }
+  const bool dummy = c >= f.ch.rho;
+  l.base = 0;
+  l.own = t < w.chunks;
+  l.dummy = dummy;
+  l.first = t == 0;
+  l.last = t == w.chunks - 1;
+  l.tie = t == 0 ? 0.0 : -1.0;
+  return f.ch.base(c) - (dummy ? 1 : 0) - f.r0 + wrap;   // (-1 for a first chunk of 15 rows)
+}
+
+// `steps` steps of a window's rows, from and to the staged rows.
+template <typename S, int NT>
+__device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>& ws, S* stage, const Frame& f,
+                                               const ChunkWin& w, const InstDesc& d, int steps, int pcr) {
+  const int t = threadIdx.x;
+  SlotLane l;
+  const int at = window_lane(f, w, t, l);
+  const bool dir = d.bc == kDirichlet;
+  const SlotRows rows{d.r, d.D, dir && w.first == 0 ? d.a : 0.0,
+                      dir && w.first + w.chunks == f.ch.P ? d.b : 0.0};
+  double al[kM], ga[kM], de[kM];
+#pragma unroll
+  for (int j = 0; j < kM; ++j)
+    de[j] = l.own ? static_cast<double>(stage[padded(j == 0 && at < 0 ? 0 : at + j)]) : 0.0;
+  __syncthreads();                           // every lane's rows read: the interface LDS overlays them
+  for (int step = 0; step < steps; ++step) {
+    double ia = 0.0, ib = 1.0, ic = 0.0, id = 0.0, y, yp;
+    if (l.own) slot_eliminate<kM, false>(rows, l, al, ga, de, ia, ib, ic, id);
+    window_solve<NT>(ws, w.chunks, pcr, l.own, l.dummy ? al[1] : al[0], l.dummy ? ga[1] : ga[0],
+                     l.dummy ? de[1] : de[0], al[kM - 2], ga[kM - 2], de[kM - 2], ia, ib, ic, id, y, yp);
+#pragma unroll
+    for (int j = 0; j < kM; ++j) de[j] = static_cast<double>(static_cast<S>(slot_value<kM>(j, al, ga, de, yp, y)));
+  }
+  __syncthreads();                           // the interface unknowns read before the rows are rewritten
+  SlotLane o;                                // (formed anew: not held across the solve)
+  const int to = window_lane(f, w, opaque_lane(t), o);
+  if (o.own) {
+#pragma unroll
+    for (int j = 0; j < kM; ++j)
+      if (j > 0 || !o.dummy) stage[padded(to + j)] = static_cast<S>(de[j]);
+  }
+  __syncthreads();
+}
+
+// The window's rows into LDS, every load in flight at once; MAX: also their largest magnitude (the lane's).
+template <typename S, int NT, bool MAX>
+__device__ __forceinline__ double window_load(const S* __restrict__ x, S* stage, const Frame& f) {
+  const int t = threadIdx.x;
+  S v[kM];
+#pragma unroll
+  for (int j = 0; j < kM; ++j) {
+    const int i = t + j * NT;
+    int k = f.r0 + (i < f.total ? i : f.total - 1);
+    if (k >= f.ch.R) k -= f.ch.R;
+    v[j] = x[k];
+  }
+  double big = 0.0;
+#pragma unroll
+  for (int j = 0; j < kM; ++j) {
+    if constexpr (MAX) take_max(static_cast<double>(v[j]), big);
+    stage[padded(t + j * NT)] = v[j];
+  }
+  return big;
+}
+
+// The window's kept rows, put(row of the system, row of the window); the lane index is formed anew.
+template <int NT, typename Put>
+__device__ __forceinline__ void window_kept(const Frame& f, const ChunkWin& w, Put&& put) {
+  int c = w.first + w.lo;
+  if (c >= f.ch.P) c -= f.ch.P;
+  const int first = f.ch.base(c), count = f.ch.rows(c, w.count);
+  const int from = first - f.r0 + (first < f.r0 ? f.ch.R : 0);
+  const int t = opaque_lane(static_cast<int>(threadIdx.x));
+#pragma unroll
+  for (int j = 0; j < kM; ++j) {
+    const int o = t + j * NT;
+    if (o < count) {
+      int k = first + o;
+      if (k >= f.ch.R) k -= f.ch.R;
+      put(k, from + o);
+    }
+  }
+}
+
+// The Dirichlet nodes next to the kept rows.
+template <typename S>
+__device__ __forceinline__ void window_ends(const Frame& f, const ChunkWin& w, const InstDesc& d, S* __restrict__ out) {
+  if (d.bc != kDirichlet || threadIdx.x != 0) return;
+  if (w.first + w.lo == 0) out[d.off] = static_cast<S>(d.a);
+  if (w.first + w.lo + w.count == f.ch.P) out[d.off + d.n - 1] = static_cast<S>(d.b);
+}
+
+__device__ __forceinline__ int system_rows(const InstDesc& d) { return d.bc == kDirichlet ? d.n - 2 : d.n; }
+
+template <int NT>
+__device__ __forceinline__ double workgroup_max(double big, double* wave_max) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) big = __builtin_fmax(big, __shfl_xor(big, m, 64));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = big;
+  __syncthreads();
+  double M = 0.0;
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) M = __builtin_fmax(M, wave_max[k]);
+  return M;
+}
+
+// One step per launch.  Every window evaluates the bound from its own rows and flags its instance when it
+// fails; the partition levels then redo that instance's step (the old state is still in u).
+//
+// Bound by HBM and the latency of load, solve and store in turn: 16 x 256 rows per window, so that four
+// workgroups a CU overlap them (52.6 us a step at 2^24 rows, binary64, with 8192-row windows 60.8).
+template <typename S, int NT>
+__global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
+    const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const S* __restrict__ u,
+    S* __restrict__ out, int* __restrict__ flag_now, int* __restrict__ flag_next, int* __restrict__ sticky,
+    double theta_lim) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[WindowSpace<S, NT>::kBytes];
+  __shared__ uint64_t iface_votes[2 * InterfaceSpace<double, NT>::kVoteWords];
+  __shared__ double wave_max[NT / 64];
+  const InterfaceSpace<double, NT> ws{reinterpret_cast<double*>(smem), reinterpret_cast<double*>(smem) + 3 * NT,
+                                      iface_votes};
+  ws.clear_votes();
+  S* stage = reinterpret_cast<S*>(smem);
+  const ChunkWin w = wins[blockIdx.x];
+  const InstDesc d = inst[w.inst];
+  const Frame f(system_rows(d), w);
+  const S* __restrict__ x = u + d.off + (d.bc == kDirichlet ? 1 : 0);
+  S* __restrict__ y = out + d.off + (d.bc == kDirichlet ? 1 : 0);
+  const double M = workgroup_max<NT>(window_load<S, NT, true>(x, stage, f), wave_max);   // (its barrier: the stage is written)
+  if (threadIdx.x == 0) {
+    flag_next[w.inst] = 0;                     // the next step's slot (its last readers have finished)
+    flag_next[-1] = 0;
+    if (!(theta_bound(d, M) <= theta_lim)) {
+      flag_now[w.inst] = 1;
+      flag_now[-1] = 1;
+      sticky[w.inst] = 1;
+    }
+  }
+  window_advance<S, NT>(ws, stage, f, w, d, 1, kMaxS);
+  window_kept<NT>(f, w, [&](int k, int i) {
+    const S val = stage[padded(i)];
+    y[k] = w.cn ? static_cast<S>(2.0 * static_cast<double>(val) - static_cast<double>(x[k])) : val;
+  });
+  window_ends<S>(f, w, d, out);
+}
+
+// Steps of a call that launch `launch` takes on an instance with `pcr` PCR steps per solve, after `done`.
+__device__ __forceinline__ int deep_steps(const ChunkWin& w, int pcr, int launch, int nsteps, int& done) {
+  const int per = kDeepHalo >> pcr, total = w.limit > 0 && w.limit < nsteps ? w.limit : nsteps;
+  done = launch * per;
+  return done >= total ? 0 : (total - done < per ? total - done : per);
+}
+
+// Up to kDeepHalo / 2^S steps of each window with the rows on chip, S of its instance (code; 0: the instance
+// is left to the partition levels).  A launch beyond an instance's last step does nothing for it.
+//
+// Bound by vector issue like the whole systems on chip (whole.hip), with 512 / (512 - 128) of the rows' work, and
+// by the window's load and store once per launch, which the CU's other workgroup covers in part.
+template <typename S>
+__global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
+    const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const int* __restrict__ code,
+    const S* __restrict__ u, S* __restrict__ out, int launch, int nsteps) {
+  constexpr int NT = kDeepLanes;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[WindowSpace<S, NT>::kBytes];
+  __shared__ uint64_t iface_votes[2 * InterfaceSpace<double, NT>::kVoteWords];
+  const InterfaceSpace<double, NT> ws{reinterpret_cast<double*>(smem), reinterpret_cast<double*>(smem) + 3 * NT,
+                                      iface_votes};
+  ws.clear_votes();
+  S* stage = reinterpret_cast<S*>(smem);
+  const ChunkWin w = wins[blockIdx.x];
+  if (w.count <= 0) return;                    // an empty slot of a resident pool
+  const int pcr = code[w.inst];
+  if (pcr <= 0) return;
+  int done;
+  const int steps = deep_steps(w, pcr, launch, nsteps, done);
+  if (steps == 0) return;
+  const InstDesc d = inst[w.inst];
+  const Frame f(system_rows(d), w);
+  const int dir = d.bc == kDirichlet ? 1 : 0;
+  window_load<S, NT, false>(u + d.off + dir, stage, f);
+  __syncthreads();
+  window_advance<S, NT>(ws, stage, f, w, d, steps, pcr);
+  S* __restrict__ y = out + d.off + dir;
+  window_kept<NT>(f, w, [&](int k, int i) { y[k] = stage[padded(i)]; });
+  window_ends<S>(f, w, d, out);
+}
+
+// The kept rows of the instances whose last launch left them in `work`, back to u.
+template <typename S>
+__global__ __launch_bounds__(256) void btcs_settle_kernel(const InstDesc* __restrict__ inst,
+                                                          const ChunkWin* __restrict__ wins,
+                                                          const int* __restrict__ code, const S* __restrict__ work,
+                                                          S* __restrict__ u, int nsteps) {
+  const ChunkWin w = wins[blockIdx.x];
+  if (w.count <= 0) return;
+  const int pcr = code[w.inst];
+  if (pcr <= 0) return;
+  const int per = kDeepHalo >> pcr, total = w.limit > 0 && w.limit < nsteps ? w.limit : nsteps;
+  if (((total + per - 1) / per & 1) == 0) return;
+  const InstDesc d = inst[w.inst];
+  const Frame f(system_rows(d), w);
+  const int64_t o = d.off + (d.bc == kDirichlet ? 1 : 0);
+  int c = w.first + w.lo;
+  if (c >= f.ch.P) c -= f.ch.P;
+  const int first = f.ch.base(c), count = f.ch.rows(c, w.count);   // (kept chunks of a window do not wrap)
+  for (int i = threadIdx.x; i < count; i += 256) u[o + first + i] = work[o + first + i];
+  window_ends<S>(f, w, d, u);
+}
+
+// max|u| of every windowed instance over its windows' kept rows, into top[inst] (the bits of a non-negative
+// binary64 value, which order like integers).
+template <typename S>
+__global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restrict__ inst,
+                                                       const ChunkWin* __restrict__ wins, const S* __restrict__ u,
+                                                       unsigned long long* __restrict__ top) {
+  __shared__ double wave_max[4];
+  const ChunkWin w = wins[blockIdx.x];
+  if (w.count <= 0) return;
+  const InstDesc d = inst[w.inst];
+  const Frame f(system_rows(d), w);
+  const S* __restrict__ x = u + d.off + (d.bc == kDirichlet ? 1 : 0);
+  int c = w.first + w.lo;
+  if (c >= f.ch.P) c -= f.ch.P;
+  const int first = f.ch.base(c), count = f.ch.rows(c, w.count);
+  double big = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < count; i += 256) take_max(static_cast<double>(x[first + i]), big);
+  const double M = workgroup_max<256>(big, wave_max);
+  if (threadIdx.x == 0) atomicMax(top + w.inst, __builtin_bit_cast(unsigned long long, M));
+}
+
+// Every windowed instance's PCR steps for a call from its bound, and the flags of those beyond it (flags[-1]:
+// any), which the partition levels take; `keep`: there are none, so a failed instance steps on and only its
+// sticky word says so.  Leaves `top` cleared for the next call.
+__global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __restrict__ inst,
+                                                          const int32_t* __restrict__ members, int n,
+                                                          unsigned long long* __restrict__ top, int* __restrict__ code,
+                                                          int* __restrict__ flags, int* __restrict__ sticky,
+                                                          ThetaLimits lim, int keep) {
+  bool failed = false;
+  for (int k = threadIdx.x; k < n; k += 256) {
+    const int i = members[k];
+    const InstDesc d = inst[i];
+    double M = __builtin_bit_cast(double, top[i]);
+    top[i] = 0;
+    if (d.bc == kDirichlet) M = __builtin_fmax(M, __builtin_fmax(__builtin_fabs(d.a), __builtin_fabs(d.b)));
+    const double theta = theta_bound(d, M);
+    int s = 0;
+#pragma unroll
+    for (int q = kMaxS; q >= 1; --q) s = theta <= lim.of[q - 1] ? q : s;
+    if (s == 0) sticky[i] = 1;
+    failed = failed || s == 0;
+    flags[i] = s == 0 && !keep ? 1 : 0;
+    code[i] = s == 0 && keep ? kMaxS : s;
+  }
+  const int any = __syncthreads_or(failed && !keep);
+  if (threadIdx.x == 0) flags[-1] = any ? 1 : 0;
+}
+
+template <typename S>
+hipError_t deep_launch(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int64_t nsteps) {
+  const InstDesc* inst = ctx->inst.as<InstDesc>();
+  const ChunkWin* wins = plan.deep->as<ChunkWin>();
+  const int* code = deep_code(plan.deep_words.as<int>(), ctx->count);
+  const unsigned n = static_cast<unsigned>(plan.n_deep);
+  S* bufs[2] = {u, work};
+  // as many launches as instances with the fewest steps per launch need
+  constexpr int kFewest = kDeepHalo >> kMaxS;
+  const int64_t launches = (nsteps + kFewest - 1) / kFewest;
+  for (int64_t j = 0; j < launches; ++j)
+    btcs_deep_kernel<S><<<n, kDeepLanes, 0, ctx->stream>>>(inst, wins, code, bufs[j & 1], bufs[(j & 1) ^ 1],
+                                                           static_cast<int>(j), static_cast<int>(nsteps));
+  btcs_settle_kernel<S><<<n, 256, 0, ctx->stream>>>(inst, wins, code, work, u, static_cast<int>(nsteps));
+  return hipGetLastError();
+}
+
+template <typename S>
+hipError_t step_launch(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const S* u, S* out,
+                       int* now, int* next, int* sticky) {
+  const unsigned n = static_cast<unsigned>(plan.n_win);
+  const double lim = theta_limits().of[kMaxS - 1];
+  const ChunkWin* wins = plan.win->as<ChunkWin>();
+  if (plan.win_rows == kM * 512)
+    btcs_window_kernel<S, 512><<<n, 512, 0, ctx->stream>>>(inst, wins, u, out, now, next, sticky, lim);
+  else
+    btcs_window_kernel<S, 256><<<n, 256, 0, ctx->stream>>>(inst, wins, u, out, now, next, sticky, lim);
+  return hipGetLastError();
+}
+
+// Windows of `lanes` chunks that lose `halo` chunks at either end, over a system of R rows.
+void chunk_windows(int32_t i, int32_t R, bool periodic, int lanes, int halo, bool cn, std::vector<ChunkWin>& out) {
+  const int64_t P = (static_cast<int64_t>(R) + kM - 1) / kM, kept = lanes - 2 * halo;
+  const int64_t n = (P + kept - 1) / kept, per = (P + n - 1) / n;   // evenly: a window's idle waves cost nothing
+  for (int64_t c = 0; c < P; c += per) {
+    const int64_t count = std::min(per, P - c);
+    const int64_t left = periodic ? halo : std::min<int64_t>(halo, c);
+    const int64_t right = periodic ? halo : std::min<int64_t>(halo, P - c - count);
+    out.push_back(ChunkWin{i, static_cast<int32_t>((c - left + P) % P), static_cast<uint16_t>(left + count + right),
+                           static_cast<uint16_t>(left), static_cast<int32_t>(count), cn ? 1 : 0, 0});
+  }
+}
+
+}  // namespace
+
+void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, std::vector<ChunkWin>& out) {
+  chunk_windows(i, R, periodic, rows / kM, kStepHalo, cn, out);
+}
+
+void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out) {
+  chunk_windows(i, R, periodic, kDeepLanes, kDeepHalo, false, out);
+}
+
+int64_t btcs_deep_windows_max(int64_t rows) {
+  const int64_t P = (rows + kM - 1) / kM, kept = kDeepLanes - 2 * kDeepHalo;
+  return (P + kept - 1) / kept;
+}
+
+hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const void* u,
+                               void* out, int* now, int* next, int* sticky) {
+  if (ctx->dtype == BURGERS_F64)
+    return step_launch<double>(ctx, plan, inst, static_cast<const double*>(u), static_cast<double*>(out), now, next, sticky);
+  return step_launch<float>(ctx, plan, inst, static_cast<const float*>(u), static_cast<float*>(out), now, next, sticky);
+}
+
+hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, bool keep) {
+  const InstDesc* inst = ctx->inst.as<InstDesc>();
+  const ChunkWin* wins = plan.deep->as<ChunkWin>();
+  const unsigned n = static_cast<unsigned>(plan.n_deep);
+  unsigned long long* top = plan.deep_words.as<unsigned long long>();
+  if (ctx->dtype == BURGERS_F64)
+    btcs_top_kernel<double><<<n, 256, 0, ctx->stream>>>(inst, wins, static_cast<const double*>(u), top);
+  else
+    btcs_top_kernel<float><<<n, 256, 0, ctx->stream>>>(inst, wins, static_cast<const float*>(u), top);
+  btcs_decide_kernel<<<1, 256, 0, ctx->stream>>>(inst, plan.deep_inst->as<int32_t>(), static_cast<int>(plan.n_deep_inst),
+                                                 top, deep_code(plan.deep_words.as<int>(), ctx->count),
+                                                 win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0),
+                                                 win_sticky(plan.win_flags.as<int>(), ctx->count), theta_limits(),
+                                                 keep ? 1 : 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps) {
+  if (ctx->dtype == BURGERS_F64)
+    return deep_launch<double>(ctx, plan, static_cast<double*>(u), static_cast<double*>(work), nsteps);
+  return deep_launch<float>(ctx, plan, static_cast<float*>(u), static_cast<float*>(work), nsteps);
+}
+
+}  // namespace burgers
