@@ -310,22 +310,11 @@ __device__ __forceinline__ void pcr_pairs(const PcrSpace<T, NT>& w, int P, T fa,
 // Reduced systems of the partition levels (rows (A, 1, C, D) in HBM), one workgroup each: chunk elimination
 // to two rows per lane, PCR in LDS, recovery to X.  (They are few and large: their rows preloaded in
 // registers matter more than a second workgroup per CU.)
-template <int NT, int MC, bool EXACT = false>
-__global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
-    const SysDesc* __restrict__ systems, const double* __restrict__ LA, const double* __restrict__ LC,
-    const double* __restrict__ LD, double* __restrict__ LX, const int* __restrict__ only) {
-  using T = double;
-  using Pcr = PcrSpace<T, NT>;
-  constexpr int kStageBytes = padded_size(NT * MC) * static_cast<int>(sizeof(T));
-  constexpr int kBytes = kStageBytes > Pcr::kBytes ? kStageBytes : Pcr::kBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
-  __shared__ int pcr_flags[2 * Pcr::kWaves];
-  const Pcr pcr{reinterpret_cast<T*>(smem), pcr_flags};
-  T* tstage = reinterpret_cast<T*>(smem);   // one coefficient array at a time
-
-  if (only && only[-1] == 0) return;         // partition fallback: no window of this step failed
-  const SysDesc sys = systems[blockIdx.x];
-  if (only && only[sys.inst] == 0) return;   // partition fallback: this instance's windows held
+template <int NT, int MC, bool EXACT>
+__device__ __forceinline__ void reduced_solve(const PcrSpace<double, NT>& pcr, double* tstage, const SysDesc& sys,
+                                              const double* __restrict__ LA, const double* __restrict__ LC,
+                                              const double* __restrict__ LD, double* __restrict__ LX) {
+  using T = double;                          // (tstage: one coefficient array at a time)
   const int R = sys.rows, P = sys.chunks;
   const int tid = threadIdx.x;
   const ArrayRows<T> asrc{LA + sys.in_off, LC + sys.in_off, LD + sys.in_off};
@@ -385,6 +374,28 @@ __global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
     }
   } else {
     if (tid < P) chunk_recover<T, MC>(adst, s, m, al, ga, de, F, E);
+  }
+}
+
+// Systems blockIdx.x, blockIdx.x + gridDim.x, ... of n.  `only` (optional): the systems of instances whose
+// entry is nonzero; only[-1] is zero when there is none.
+template <int NT, int MC, bool EXACT = false>
+__global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
+    const SysDesc* __restrict__ systems, int n, const double* __restrict__ LA, const double* __restrict__ LC,
+    const double* __restrict__ LD, double* __restrict__ LX, const int* __restrict__ only) {
+  using T = double;
+  using Pcr = PcrSpace<T, NT>;
+  constexpr int kStageBytes = padded_size(NT * MC) * static_cast<int>(sizeof(T));
+  constexpr int kBytes = kStageBytes > Pcr::kBytes ? kStageBytes : Pcr::kBytes;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
+  __shared__ int pcr_flags[2 * Pcr::kWaves];
+  const Pcr pcr{reinterpret_cast<T*>(smem), pcr_flags};
+  if (only && only[-1] == 0) return;
+  for (int q = blockIdx.x; q < n; q += gridDim.x) {
+    const SysDesc sys = systems[q];
+    if (only && only[sys.inst] == 0) continue;
+    reduced_solve<NT, MC, EXACT>(pcr, reinterpret_cast<T*>(smem), sys, LA, LC, LD, LX);
+    __syncthreads();
   }
 }
 
@@ -1150,7 +1161,7 @@ __device__ __forceinline__ void block_reduce_body(const BlockIfaceSpace& w, cons
 template <typename S>
 __global__ __launch_bounds__(kReduceBlock, 4) void btcs_block_reduce_kernel(
     const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
-    const ChunkBlock* __restrict__ blocks, const S* __restrict__ u, double* __restrict__ LA,
+    const ChunkBlock* __restrict__ blocks, int n, const S* __restrict__ u, double* __restrict__ LA,
     double* __restrict__ LC, double* __restrict__ LD, const int* __restrict__ only) {
   using T = double;
   constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
@@ -1160,19 +1171,22 @@ __global__ __launch_bounds__(kReduceBlock, 4) void btcs_block_reduce_kernel(
   S* stage = reinterpret_cast<S*>(smem);
   T* lds = reinterpret_cast<T*>(smem);
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
-  if (only && only[-1] == 0) return;         // partition fallback: no window of this step failed
-  const ChunkBlock cb = blocks[blockIdx.x];
-  const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;   // partition fallback: this instance's windows held
-  const InstDesc d = inst[sys.inst];
-  const bool dir = d.bc == kDirichlet;
-  const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
-  int rs, re;
-  block_rows(sys, cb.chunk0, rs, re);
-  stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
-  __syncthreads();
-  if (block_full(sys, cb.chunk0, Pb)) block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
-  else block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+  if (only && only[-1] == 0) return;           // no instance is left to the partition levels
+  for (int q = blockIdx.x; q < n; q += gridDim.x) {
+    const ChunkBlock cb = blocks[q];
+    const SysDesc sys = systems[cb.sys];
+    if (only && only[sys.inst] == 0) continue;   // this instance's windows held
+    const InstDesc d = inst[sys.inst];
+    const bool dir = d.bc == kDirichlet;
+    const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
+    int rs, re;
+    block_rows(sys, cb.chunk0, rs, re);
+    stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
+    __syncthreads();
+    if (block_full(sys, cb.chunk0, Pb)) block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+    else block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+    __syncthreads();                             // the next block's rows overwrite this one's
+  }
 }
 
 
@@ -1233,7 +1247,7 @@ __device__ __forceinline__ void block_backsub_body(const BlockIfaceSpace& w, S* 
 template <typename S>
 __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
     const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
-    const ChunkBlock* __restrict__ blocks, const S* __restrict__ u, S* __restrict__ out,
+    const ChunkBlock* __restrict__ blocks, int n, const S* __restrict__ u, S* __restrict__ out,
     const double* __restrict__ LX, const int* __restrict__ only) {
   using T = double;
   constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
@@ -1243,36 +1257,86 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
   S* stage = reinterpret_cast<S*>(smem);
   T* lds = reinterpret_cast<T*>(smem);
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
-  if (only && only[-1] == 0) return;         // partition fallback: no window of this step failed
-  const ChunkBlock cb = blocks[blockIdx.x];
-  const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;   // partition fallback: this instance's windows held
-  const InstDesc d = inst[sys.inst];
-  const bool dir = d.bc == kDirichlet;
-  const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
-  int rs, re;
-  block_rows(sys, cb.chunk0, rs, re);
-  stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
-  __syncthreads();
-  if (block_full(sys, cb.chunk0, Pb)) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-  else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  if (only && only[-1] == 0) return;           // no instance is left to the partition levels
+  for (int q = blockIdx.x; q < n; q += gridDim.x) {
+    const ChunkBlock cb = blocks[q];
+    const SysDesc sys = systems[cb.sys];
+    if (only && only[sys.inst] == 0) continue;   // this instance's windows held
+    const InstDesc d = inst[sys.inst];
+    const bool dir = d.bc == kDirichlet;
+    const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
+    int rs, re;
+    block_rows(sys, cb.chunk0, rs, re);
+    stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
+    __syncthreads();
+    if (block_full(sys, cb.chunk0, Pb)) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+    else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+    __syncthreads();                             // the next block's rows overwrite this one's
+  }
 }
 
 // The reduced systems of a partition level, one workgroup each, in the narrowest width that holds the
 // level's widest system (small reduced systems leave most of a 512-lane workgroup idle).
+// The backward half of one step (from u, the solved unknowns in LX, to out) and the forward half of the next, whose
+// rows the block still holds in LDS.
+template <typename S>
+__global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
+    const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
+    const ChunkBlock* __restrict__ blocks, int n, const S* __restrict__ u, S* __restrict__ out,
+    double* __restrict__ LA, double* __restrict__ LC, double* __restrict__ LD, const double* __restrict__ LX,
+    const int* __restrict__ only) {
+  using T = double;
+  constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
+  constexpr int kBytes = kStageBytes > BlockIfaceSpace::kBytes ? kStageBytes : BlockIfaceSpace::kBytes;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
+  __shared__ int iface_flags[2 * kSpikeWaves];
+  S* stage = reinterpret_cast<S*>(smem);
+  T* lds = reinterpret_cast<T*>(smem);
+  const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
+  if (only && only[-1] == 0) return;
+  for (int q = blockIdx.x; q < n; q += gridDim.x) {
+    const ChunkBlock cb = blocks[q];
+    const SysDesc sys = systems[cb.sys];
+    if (only && only[sys.inst] == 0) continue;
+    const InstDesc d = inst[sys.inst];
+    const bool dir = d.bc == kDirichlet;
+    const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
+    int rs, re;
+    block_rows(sys, cb.chunk0, rs, re);
+    stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
+    __syncthreads();
+    if (block_full(sys, cb.chunk0, Pb)) {
+      block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+      block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+    } else {
+      block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+      block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+    }
+    __syncthreads();
+  }
+}
+
+// Workgroups of a launch over n blocks or systems.  With `only` it mostly finds nothing to do, beside other
+// chains of the call whose workgroups fill the chip: each of its own then has to wait for one of theirs to end, so
+// it takes no more than the chip holds of them at once, which walk the rest.  (One grid of 2^24 rows by windows,
+// 128 steps, with one workgroup per block of 4096 rows: 3950 us; without any such launch 3250.)
+constexpr int kFallbackBlocks = 1024, kFallbackSystems = 512;
+unsigned fallback_grid(int n, int most, const int* only) { return static_cast<unsigned>(only && n > most ? most : n); }
+
 void reduced_wg_launch(const BtcsPlan::Level& lv, double* LA, double* LC, double* LD, double* LX, hipStream_t st,
                        const int* only) {
   const SysDesc* sys = lv.wg->as<SysDesc>();
-  const unsigned n = static_cast<unsigned>(lv.n_wg);
+  const int m = lv.n_wg;
+  const unsigned n = fallback_grid(lv.n_wg, kFallbackSystems, only);
   switch (lv.wg_lanes) {
-    case 64: btcs_reduced_kernel<64, kWgChunk><<<n, 64, 0, st>>>(sys, LA, LC, LD, LX, only); break;
-    case 128: btcs_reduced_kernel<128, kWgChunk><<<n, 128, 0, st>>>(sys, LA, LC, LD, LX, only); break;
-    case 256: btcs_reduced_kernel<256, kWgChunk><<<n, 256, 0, st>>>(sys, LA, LC, LD, LX, only); break;
+    case 64: btcs_reduced_kernel<64, kWgChunk><<<n, 64, 0, st>>>(sys, m, LA, LC, LD, LX, only); break;
+    case 128: btcs_reduced_kernel<128, kWgChunk><<<n, 128, 0, st>>>(sys, m, LA, LC, LD, LX, only); break;
+    case 256: btcs_reduced_kernel<256, kWgChunk><<<n, 256, 0, st>>>(sys, m, LA, LC, LD, LX, only); break;
     default:
       if (lv.wg_exact)   // the full layout as a constant: no row is selected at a run-time index
-        btcs_reduced_kernel<kWgThreads, kWgChunk, true><<<n, kWgThreads, 0, st>>>(sys, LA, LC, LD, LX, only);
+        btcs_reduced_kernel<kWgThreads, kWgChunk, true><<<n, kWgThreads, 0, st>>>(sys, m, LA, LC, LD, LX, only);
       else
-        btcs_reduced_kernel<kWgThreads, kWgChunk><<<n, kWgThreads, 0, st>>>(sys, LA, LC, LD, LX, only);
+        btcs_reduced_kernel<kWgThreads, kWgChunk><<<n, kWgThreads, 0, st>>>(sys, m, LA, LC, LD, LX, only);
       break;
   }
 }
@@ -1309,8 +1373,8 @@ void levels_forward(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc
     const auto& lv = plan.levels[l];
     if (lv.n_blocks == 0) continue;
     if (l == 0) {
-      btcs_block_reduce_kernel<S><<<lv.n_blocks, kReduceBlock, 0, st>>>(
-          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, LA, LC, LD, only);
+      btcs_block_reduce_kernel<S><<<fallback_grid(lv.n_blocks, kFallbackBlocks, only), kReduceBlock, 0, st>>>(
+          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks, u, LA, LC, LD, only);
     } else {
       btcs_array_reduce_kernel<<<lv.n_blocks, kReduceBlock, 0, st>>>(lv.sys->as<SysDesc>(),
                                                                      lv.blocks->as<ChunkBlock>(), LA, LC, LD, only);
@@ -1332,8 +1396,37 @@ void levels_finish(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc*
                    const int* only) {
   if (plan.levels.empty() || plan.levels[0].n_blocks == 0) return;
   const auto& lv = plan.levels[0];
-  btcs_block_backsub_kernel<S><<<lv.n_blocks, kReduceBlock, 0, ctx->stream>>>(
-      inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, out, ctx->level_x.as<double>(), only);
+  btcs_block_backsub_kernel<S><<<fallback_grid(lv.n_blocks, kFallbackBlocks, only), kReduceBlock, 0, ctx->stream>>>(
+      inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks, u, out, ctx->level_x.as<double>(), only);
+}
+
+// nsteps steps by the levels, the last one's rows in bufs[nsteps & 1] (u, work).  Where every system's reduced one
+// is solved whole, a step is two launches: one for those and one that ends the step and begins the next.
+template <typename S>
+void levels_run(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int64_t nsteps, const int* only) {
+  const InstDesc* inst = ctx->inst.as<InstDesc>();
+  S* bufs[2] = {u, work};
+  if (plan.levels.size() != 2 || plan.levels[0].n_blocks == 0 || plan.levels[1].n_blocks > 0) {
+    for (int64_t s = 0; s < nsteps; ++s) {
+      levels_forward<S>(ctx, plan, inst, bufs[s & 1], only);
+      levels_finish<S>(ctx, plan, inst, bufs[s & 1], bufs[(s & 1) ^ 1], only);
+    }
+    return;
+  }
+  double* LA = ctx->level_a.as<double>();
+  double* LC = ctx->level_c.as<double>();
+  double* LD = ctx->level_d.as<double>();
+  double* LX = ctx->level_x.as<double>();
+  const auto& lv = plan.levels[0];
+  for (int64_t s = 0; s < nsteps; ++s) {
+    if (s == 0) levels_forward<S>(ctx, plan, inst, u, only);
+    else reduced_wg_launch(plan.levels[1], LA, LC, LD, LX, ctx->stream, only);
+    if (s + 1 == nsteps) levels_finish<S>(ctx, plan, inst, bufs[s & 1], bufs[(s & 1) ^ 1], only);
+    else
+      btcs_block_turn_kernel<S><<<fallback_grid(lv.n_blocks, kFallbackBlocks, only), kReduceBlock, 0, ctx->stream>>>(
+          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks, bufs[s & 1], bufs[(s & 1) ^ 1], LA, LC,
+          LD, LX, only);
+  }
 }
 
 template <typename S>
@@ -1484,16 +1577,13 @@ hipError_t launch_btcs_step(const burgers_ctx* ctx, const BtcsPlan& plan, const 
   return launch_step<float>(ctx, plan, u, out, step);
 }
 
-hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, const int* only) {
-  const InstDesc* inst = ctx->inst.as<InstDesc>();
-  if (ctx->dtype == BURGERS_F64) {
-    levels_forward<double>(ctx, plan, inst, static_cast<const double*>(u), only);
-    levels_finish<double>(ctx, plan, inst, static_cast<const double*>(u), static_cast<double*>(out), only);
-  } else {
-    levels_forward<float>(ctx, plan, inst, static_cast<const float*>(u), only);
-    levels_finish<float>(ctx, plan, inst, static_cast<const float*>(u), static_cast<float*>(out), only);
-  }
-  return hipGetLastError();
+hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps,
+                              const int* only) {
+  if (ctx->dtype == BURGERS_F64) levels_run<double>(ctx, plan, static_cast<double*>(u), static_cast<double*>(work), nsteps, only);
+  else levels_run<float>(ctx, plan, static_cast<float*>(u), static_cast<float*>(work), nsteps, only);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && (nsteps & 1)) e = launch_copy_tiles(ctx, plan.copy->as<Tile>(), plan.n_copy, work, u, only);
+  return e;
 }
 
 hipError_t launch_btcs_window_reset(const burgers_ctx* ctx, const BtcsPlan& plan) {

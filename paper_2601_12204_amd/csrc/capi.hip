@@ -713,15 +713,10 @@ void btcs_tasks(burgers_ctx* ctx, int set, void* u, int64_t nsteps, std::vector<
         e = burgers::launch_btcs_deep(ctx, *pl, u, ctx->work.ptr, std::min(nsteps - done, kDeepCall));
       return e;
     }});
-    tasks.push_back({chain_us(nsteps, 6.0, 0.0, 1.0), 3 * nsteps, [=]() -> hipError_t {
-      const int* only = burgers::win_flag_slot(pl->win_flags.as<int>(), ctx->count, 0);
-      void* bufs[2] = {u, ctx->work.ptr};
-      hipError_t e = hipSuccess;
-      for (int64_t s = 0; s < nsteps && e == hipSuccess; ++s)
-        e = burgers::launch_btcs_levels(ctx, *pl, bufs[s & 1], bufs[(s & 1) ^ 1], only);
-      if (e == hipSuccess && (nsteps & 1))
-        e = burgers::launch_copy_tiles(ctx, pl->copy->as<Tile>(), pl->n_copy, ctx->work.ptr, u, only);
-      return e;
+    // (mostly idle: but each of its launches waits for the other chains' workgroups to leave a CU, about 9 us)
+    tasks.push_back({chain_us(nsteps, 18.0, 0.0, 1.0), 2 * nsteps, [=]() {
+      return burgers::launch_btcs_levels(ctx, *pl, u, ctx->work.ptr, nsteps,
+                                         burgers::win_flag_slot(pl->win_flags.as<int>(), ctx->count, 0));
     }});
   } else if (pl->n_copy > 0) {
     const double nodes = static_cast<double>(pl->n_copy) * burgers::explicit_tile_nodes(ctx->dtype);
@@ -743,7 +738,7 @@ hipError_t enqueue_all(burgers_ctx* ctx, int set, int scheme, void* u, int64_t n
     const burgers::BtcsPlan& pl = *ctx->btcs[bset];
     // which instances the windows may step, and which the partition levels must: both of their chains follow
     if (takes_deep(pl, bsteps))
-      if (const hipError_t e = burgers::launch_btcs_bound(ctx, pl, u, false); e != hipSuccess) return e;
+      if (const hipError_t e = burgers::launch_btcs_bound(ctx, pl, u, nullptr); e != hipSuccess) return e;
     btcs_tasks(ctx, bset, u, bsteps, tasks);
   }
   return burgers::run_tasks(ctx, tasks, ctx->plan.serial == 1);

@@ -438,8 +438,9 @@ constexpr int kReduceBlock = 256;       // chunks per workgroup in the partition
 // One BTCS step of the plan from u to out; `step` counts the steps of the current call from 0 (it selects
 // the parity slot of the window flags, which launch_btcs_window_reset clears at the start of a call).
 hipError_t launch_btcs_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, int64_t step);
-// One step of the partition levels alone, for the instances whose entry of `only` is nonzero.
-hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, const int* only);
+// nsteps steps by the partition levels alone, the final states in u, for the instances whose entry of `only` is nonzero.
+hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps,
+                              const int* only);
 // window.hip.  Windows of one step (`rows` of 4096 or 8192) and of several over a system of R > 16384 rows of
 // instance i, appended to `out`; how many of the latter cover any system of up to `rows` rows.
 void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, std::vector<ChunkWin>& out);
@@ -450,8 +451,10 @@ int64_t btcs_deep_windows_max(int64_t rows);
 hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const void* u,
                                void* out, int* now, int* next, int* sticky);
 // For a call from the states in u: the PCR steps of plan.deep's instances, and the flags (slot 0 of the window
-// flags) of those beyond the bound, which launch_btcs_deep leaves alone; `keep`: it steps them too.
-hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, bool keep);
+// flags) of those beyond the bound, which launch_btcs_deep leaves alone.  `fresh` (a pool's, one word per instance):
+// it steps those too, and only their sticky words tell; an instance's sticky word starts anew where its entry is
+// nonzero.
+hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, const int32_t* fresh);
 // nsteps (below 2^30) steps of plan.deep, the final states in u.
 hipError_t launch_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps);
 hipError_t launch_btcs_window_reset(const burgers_ctx* ctx, const BtcsPlan& plan);

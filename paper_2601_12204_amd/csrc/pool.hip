@@ -61,7 +61,8 @@ struct burgers_pool {
   // device tables (one buffer) and their host image
   DevBuf tables;
   std::vector<unsigned char> image;
-  size_t off_whole[kResClasses] = {}, off_win = 0, off_copy = 0;
+  size_t off_whole[kResClasses] = {}, off_win = 0, off_copy = 0, off_inst = 0, off_fresh = 0;
+  std::vector<int32_t> fresh;      // slots admitted since the last tick (BTCS windows: their flag starts anew)
   std::vector<burgers::WgGroup> res;                 // BTCS on-chip classes (views into `tables`)
   burgers::BtcsPlan bplan;                           // BTCS windows (views into `tables`), no levels
   DevBuf win_view, copy_view;
@@ -104,6 +105,8 @@ int group_of(const burgers_pool* pl, const burgers_problem& p) {
 // slots, for slots with no steps left and for slots of other groups.
 void build_image(burgers_pool* pl) {
   std::fill(pl->image.begin(), pl->image.end(), 0);
+  std::memcpy(pl->image.data() + pl->off_inst, pl->inst_host.data(), pl->inst_host.size() * sizeof(InstDesc));
+  std::memcpy(pl->image.data() + pl->off_fresh, pl->fresh.data(), pl->fresh.size() * sizeof(int32_t));
   const int64_t K = pl->tick;
   const int tile_nodes = burgers::explicit_tile_nodes(pl->ctx.dtype);
   for (int64_t s = 0; s < pl->slots; ++s) {
@@ -146,11 +149,15 @@ void build_image(burgers_pool* pl) {
   }
 }
 
-// The launch sequence of one tick for the groups in `mask` (all on pl->ctx.stream).
+// The launch sequence of one tick for the groups in `mask`, from and back to pl->ctx.stream.  The classes and the
+// windows advance disjoint slots, so they run concurrently (run_tasks), by rough times for a tick of a pool that
+// holds a few slots of each: a class's latency per step, whatever its occupancy.  (64 explicit and 64 BTCS
+// requests of a ragged mix, binary32: the classes one after another on the pool's stream took 1.6 and 1.5 ms a
+// tick, the windows 0.8 and 0.6.)
 hipError_t enqueue_tick(burgers_pool* pl, uint32_t mask) {
   burgers_ctx* ctx = &pl->ctx;
   const int K = static_cast<int>(pl->tick);
-  hipError_t e = hipSuccess;
+  std::vector<burgers::Task> tasks;
   void* u = pl->u.ptr;
   void* work = pl->work.ptr;
   const Tile* copy = pl->copy_view.as<Tile>();
@@ -159,29 +166,38 @@ hipError_t enqueue_tick(burgers_pool* pl, uint32_t mask) {
     for (int c = 0; c < 4; ++c) {
       if (!(mask & (1u << c))) continue;
       const BlockTile* t = reinterpret_cast<const BlockTile*>(static_cast<char*>(pl->tables.ptr) + pl->off_whole[c]);
-      if ((e = burgers::launch_explicit_block(ctx, t, pl->slots, 0, u, u, K, kWholeLanes[c], 0)) != hipSuccess) return e;
+      tasks.push_back({(c == 0 ? 0.28 : 0.43) * K, 1, [=]() {
+        return burgers::launch_explicit_block(ctx, t, pl->slots, 0, u, u, K, kWholeLanes[c], 0);
+      }});
     }
-    if (mask & (1u << kWinGroup)) {
-      void* bufs[2] = {u, work};
-      int cur = 0;
-      for (int done = 0; done < K; done += pl->depth) {
-        const int k = std::min(pl->depth, K - done);
-        if ((e = burgers::launch_explicit_block(ctx, pl->win_view.as<BlockTile>(), pl->slots * pl->wx, 0, bufs[cur],
-                                                bufs[cur ^ 1], k, 512, done)) != hipSuccess)
-          return e;
-        cur ^= 1;
-      }
-      if (cur && (e = burgers::launch_copy_tiles(ctx, copy, n_copy, work, u)) != hipSuccess) return e;
-    }
-    return e;
+    if (mask & (1u << kWinGroup))
+      tasks.push_back({0.8 * K, K / pl->depth + 1, [=]() -> hipError_t {
+        hipError_t e = hipSuccess;
+        void* bufs[2] = {u, work};
+        int cur = 0;
+        for (int done = 0; done < K; done += pl->depth) {
+          const int k = std::min(pl->depth, K - done);
+          if ((e = burgers::launch_explicit_block(ctx, pl->win_view.as<BlockTile>(), pl->slots * pl->wx, 0, bufs[cur],
+                                                  bufs[cur ^ 1], k, 512, done)) != hipSuccess)
+            return e;
+          cur ^= 1;
+        }
+        if (cur) e = burgers::launch_copy_tiles(ctx, copy, n_copy, work, u);
+        return e;
+      }});
+    return burgers::run_tasks(ctx, tasks, false);
   }
   for (int c = 0; c < kResClasses; ++c)
-    if ((mask & (1u << c)) && (e = burgers::launch_btcs_resident(ctx, pl->res[c], u, K)) != hipSuccess) return e;
-  if (mask & (1u << kWinGroup)) {
-    if ((e = burgers::launch_btcs_bound(ctx, pl->bplan, u, true)) != hipSuccess) return e;
-    if ((e = burgers::launch_btcs_deep(ctx, pl->bplan, u, work, K)) != hipSuccess) return e;
-  }
-  return e;
+    if (mask & (1u << c))
+      tasks.push_back({(kResChunk[c] == 16 ? kResLanes[c] / 256.0 : 2.0) * K, 1,
+                       [=]() { return burgers::launch_btcs_resident(ctx, pl->res[c], u, K); }});
+  if (mask & (1u << kWinGroup))
+    tasks.push_back({6.0 * K, K / 3 + 3, [=]() {
+      const int32_t* fresh = reinterpret_cast<const int32_t*>(static_cast<char*>(pl->tables.ptr) + pl->off_fresh);
+      const hipError_t e = burgers::launch_btcs_bound(ctx, pl->bplan, u, fresh);
+      return e == hipSuccess ? burgers::launch_btcs_deep(ctx, pl->bplan, u, work, K) : e;
+    }});
+  return burgers::run_tasks(ctx, tasks, false);
 }
 
 hipError_t tick_graph(burgers_pool* pl, uint32_t mask, hipGraphExec_t* out) {
@@ -222,6 +238,11 @@ void pool_free(burgers_pool* pl) {
   (void)hipStreamSynchronize(pl->ctx.stream);
   for (auto& kv : pl->graphs) (void)hipGraphExecDestroy(kv.second);
   if (pl->capture) (void)hipStreamDestroy(pl->capture);
+  for (int k = 0; k < 3; ++k) {
+    if (pl->ctx.side[k]) (void)hipStreamDestroy(pl->ctx.side[k]);
+    if (pl->ctx.joined[k]) (void)hipEventDestroy(pl->ctx.joined[k]);
+  }
+  if (pl->ctx.forked) (void)hipEventDestroy(pl->ctx.forked);
   if (pl->done) (void)hipEventDestroy(pl->done);
   if (pl->sticky_host) (void)hipHostFree(pl->sticky_host);
   // views into `tables` must not free anything
@@ -262,6 +283,7 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
   pl->probs.resize(slots);
   pl->remaining.assign(slots, -1);
   pl->group.assign(slots, 0);
+  pl->fresh.assign(slots, 0);
   pl->inst_host.assign(slots, InstDesc{});
   for (int64_t s = 0; s < slots; ++s) {   // empty slots: a harmless descriptor at the slot's offset
     pl->inst_host[s].off = s * pl->cap;
@@ -290,13 +312,14 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
   off = align_up(off + static_cast<size_t>(slots * pl->wx) * entry);
   pl->off_copy = off;
   off = align_up(off + static_cast<size_t>(slots * pl->tx) * sizeof(Tile));
+  pl->off_inst = off;
+  off = align_up(off + static_cast<size_t>(slots) * sizeof(InstDesc));
+  pl->off_fresh = off;
+  off = align_up(off + static_cast<size_t>(slots) * sizeof(int32_t));
   pl->image.assign(off, 0);
   const size_t state = static_cast<size_t>(slots) * pl->cap * pl->ctx.word;
   if ((e = pl->tables.alloc(off, st)) != hipSuccess || (e = pl->u.alloc(state, st)) != hipSuccess ||
       (e = pl->work.alloc(pl->wx ? state : 0, st)) != hipSuccess ||
-      (e = pl->ctx.inst.alloc(static_cast<size_t>(slots) * sizeof(InstDesc), st)) != hipSuccess ||
-      (e = hipMemcpyAsync(pl->ctx.inst.ptr, pl->inst_host.data(), static_cast<size_t>(slots) * sizeof(InstDesc),
-                          hipMemcpyHostToDevice, st)) != hipSuccess ||
       (e = hipMemcpyAsync(pl->tables.ptr, pl->image.data(), off, hipMemcpyHostToDevice, st)) != hipSuccess ||
       (e = hipEventCreateWithFlags(&pl->done, hipEventDisableTiming)) != hipSuccess ||
       (e = hipHostMalloc(reinterpret_cast<void**>(&pl->sticky_host), static_cast<size_t>(slots) * sizeof(int))) !=
@@ -306,6 +329,7 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
   }
   std::memset(pl->sticky_host, 0, static_cast<size_t>(slots) * sizeof(int));
   pl->ctx.work.ptr = nullptr;
+  view(pl->ctx.inst, pl->tables.ptr, pl->off_inst, static_cast<size_t>(slots) * sizeof(InstDesc), st);
   view(pl->win_view, pl->tables.ptr, pl->off_win, static_cast<size_t>(slots * pl->wx) * entry, st);
   view(pl->copy_view, pl->tables.ptr, pl->off_copy, static_cast<size_t>(slots * pl->tx) * sizeof(Tile), st);
   if (scheme == BURGERS_BTCS) {
@@ -367,17 +391,12 @@ burgers_status burgers_pool_admit(burgers_pool* pool, const burgers_problem* p, 
   hipStream_t st = pool->ctx.stream;
   pool->inst_host[s] = burgers::inst_desc(*p, s * pool->cap);
   char* dst = static_cast<char*>(pool->u.ptr) + static_cast<size_t>(s * pool->cap) * pool->ctx.word;
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(pool->ctx.inst.as<InstDesc>() + s, &pool->inst_host[s], sizeof(InstDesc),
-                       hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dst, u0, static_cast<size_t>(p->n) * pool->ctx.word, hipMemcpyDefault, st);
-  if (e == hipSuccess && pool->bplan.n_deep > 0)
-    e = burgers::launch_clear_ints(&pool->ctx, burgers::win_sticky(pool->bplan.win_flags.as<int>(), pool->slots) + s, 1);
   if (e != hipSuccess) {
     pool->sticky_err = e;
     return status_of(e);
   }
-  pool->sticky_host[s] = 0;
+  pool->fresh[s] = 1;              // (its scalars and entries reach the device with the next tick's tables)
   pool->probs[s] = *p;
   pool->remaining[s] = nsteps;
   pool->group[s] = group_of(pool, *p);
@@ -415,6 +434,7 @@ burgers_status burgers_pool_tick(burgers_pool* pool) {
     pool->sticky_err = e;
     return status_of(e);
   }
+  std::fill(pool->fresh.begin(), pool->fresh.end(), 0);
   for (int64_t s = 0; s < pool->slots; ++s)
     if (pool->remaining[s] > 0) pool->remaining[s] -= std::min(pool->remaining[s], pool->tick);
   return BURGERS_OK;
@@ -445,7 +465,7 @@ burgers_status burgers_pool_retire(burgers_pool* pool, int64_t slot, void* dst) 
     return status_of(e);
   }
   pool->remaining[slot] = -1;
-  return pool->bplan.n_deep > 0 && pool->sticky_host[slot] ? BURGERS_E_BOUND : BURGERS_OK;
+  return pool->bplan.n_deep > 0 && pool->group[slot] == kWinGroup && pool->sticky_host[slot] ? BURGERS_E_BOUND : BURGERS_OK;
 }
 
 }  // extern "C"

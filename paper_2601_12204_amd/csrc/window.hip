@@ -50,7 +50,7 @@ constexpr int kDeepLanes = 512;
 // Chunks lost at either end of a window over a launch of several steps: with S = 3, the usual case at ten
 // times the CFL step, 8 steps a launch.  One grid of 2^24 rows, us per step (384, 416, 448 of 512 chunks kept):
 // see kDeepHalo in the table of launch_btcs_deep.
-constexpr int kDeepHalo = 64;
+constexpr int kDeepHalo = 48;
 constexpr int kStepHalo = 1 << kMaxS;
 
 // The largest theta for S PCR steps, theta^(n_S) <= 2^-56, with slack for rounding (its own evaluation and
@@ -407,13 +407,15 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
 }
 
 // Every windowed instance's PCR steps for a call from its bound, and the flags of those beyond it (flags[-1]:
-// any), which the partition levels take; `keep`: there are none, so a failed instance steps on and only its
-// sticky word says so.  Leaves `top` cleared for the next call.
+// any), which the partition levels take; `fresh` (a pool's): there are none, so a failed instance steps on and only
+// its sticky word says so, from the first tick of its slot's request (fresh) on.  Leaves `top` cleared for the next
+// call.
 __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __restrict__ inst,
                                                           const int32_t* __restrict__ members, int n,
                                                           unsigned long long* __restrict__ top, int* __restrict__ code,
                                                           int* __restrict__ flags, int* __restrict__ sticky,
-                                                          ThetaLimits lim, int keep) {
+                                                          ThetaLimits lim, const int32_t* __restrict__ fresh) {
+  const bool keep = fresh != nullptr;
   bool failed = false;
   for (int k = threadIdx.x; k < n; k += 256) {
     const int i = members[k];
@@ -426,6 +428,7 @@ __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __rest
 #pragma unroll
     for (int q = kMaxS; q >= 1; --q) s = theta <= lim.of[q - 1] ? q : s;
     if (s == 0) sticky[i] = 1;
+    else if (keep && fresh[i]) sticky[i] = 0;
     failed = failed || s == 0;
     flags[i] = s == 0 && !keep ? 1 : 0;
     code[i] = s == 0 && keep ? kMaxS : s;
@@ -499,7 +502,7 @@ hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, con
   return step_launch<float>(ctx, plan, inst, static_cast<const float*>(u), static_cast<float*>(out), now, next, sticky);
 }
 
-hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, bool keep) {
+hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, const int32_t* fresh) {
   const InstDesc* inst = ctx->inst.as<InstDesc>();
   const ChunkWin* wins = plan.deep->as<ChunkWin>();
   const unsigned n = static_cast<unsigned>(plan.n_deep);
@@ -512,7 +515,7 @@ hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const
                                                  top, deep_code(plan.deep_words.as<int>(), ctx->count),
                                                  win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0),
                                                  win_sticky(plan.win_flags.as<int>(), ctx->count), theta_limits(),
-                                                 keep ? 1 : 0);
+                                                 fresh);
   return hipGetLastError();
 }
 
