@@ -39,34 +39,40 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return tot;
 }
 
-// ---- Explicit reverse steps, blocked ----------------------------------------------------------------
-// lam^k = (dE/du at u^k)^T lam^(k+1) is a 3-point gather stencil whose coefficients come from u^k alone.
-// A workgroup of 256 lanes holds lam over a window of up to 4096 nodes (16 consecutive nodes per lane) in
-// registers for a run of reverse steps: each step reads u^k of the window from HBM (coalesced, passed to
-// the lanes' chunks through a region of LDS private to each wave), exchanges the chunks' end values of u
-// and lam through LDS, and updates lam in place.  lam is read once and written once per launch.  Windows
-// of longer instances keep their middle nodes and carry kAdjHalo nodes on either side, recomputed
-// redundantly: an error at a window edge travels one node per step, so a launch takes at most kAdjHalo
-// steps.
+// ---- Explicit reverse steps ---------------------------------------------------------------------------
+// lam^k = (dE/du at u^k)^T lam^(k+1).  With beta_i = max(r u_i + D, D) and alpha_i = beta_i - r u_i, the weights of the
+// forward update u' = u + alpha (u_p - u) - beta (u - u_m), a node hands q_i = beta_i lam_i to its left neighbour and
+// p_i = alpha_i lam_i to its right one:
+//   lam'_i = lam_i - p_i - q_i - r s_i lam_i + q_{i+1} + p_{i-1},   s_i = u_i >= 0 ? u_i - u_{i-1} : u_{i+1} - u_i.
 //
-// dJ/dD, the sum over nodes and steps of lam^(k+1)_j (u_{j+1} + u_{j-1} - 2 u_j), is accumulated per
-// tile of kAdjSumTile nodes of an instance: per step, each lane sums its kept nodes in node order, the 16
-// lanes of a tile combine by a butterfly, and the tile's first lane adds the result to the tile's running
-// sum (loaded from its slot at launch start, stored at the end).  Tiles are aligned to 16-lane groups in
-// every window, so each (tile, step) partial is formed alike whichever window and launch computes it:
-// the gradient does not depend on how the steps are grouped into launches (the checkpoint interval).
-constexpr int kAdjWinLanes = 256;
-constexpr int kAdjWinChunk = 16;
-constexpr int kAdjWinRegion = 32 * (kAdjWinChunk + 1);   // a half-wave's chunks, padded by one per chunk
-static_assert(kAdjWinLanes * kAdjWinChunk == kAdjWinNodes, "window capacity");
-static_assert(kAdjSumTile == 16 * kAdjWinChunk, "a tile is 16 lanes' chunks");
+// A wave holds lam over a window of up to 1024 nodes (16 consecutive ones per lane) in registers for a run of
+// reverse steps, and passes end values between lanes by whole-wave DPP moves: a step needs no LDS and no barrier.
+// Of the states only every kAdjGroup-th is recorded and read; the ones between are computed again in registers,
+// by the forward kernels' operations (so to the bit), and used in turn.  Windows keep their middle nodes and carry
+// kAdjHalo nodes on either side (a short periodic instance's halo goes around it several times); an error at a
+// window's edge travels one node per reverse step, after kAdjGroup - 1 nodes of the first states' own, so a launch
+// takes at most kAdjRun = kAdjHalo - (kAdjGroup - 1) steps, rounded down to whole groups.
+//
+// dJ/dD, the sum over nodes and steps of lam^(k+1)_j (u_{j+1} + u_{j-1} - 2 u_j), is accumulated per lane over its 16
+// nodes and all steps, in a slot per 16 nodes of the instance that carries the sum from launch to launch.  Lanes hold
+// the same 16 nodes in every window that keeps them, so the gradient does not depend on how the steps are grouped into
+// launches (the checkpoint interval).
+//
+// Bound by vector issue: 23 to 24 instructions per node and step, 4.5 of them the states' second computation, with 12%
+// of the nodes halo.  (256 x 16384 nodes, us per reverse step, the recording of the states on another stream included: 7 here;
+// 18 with every state recorded and read, 8 + 8 bytes per node and step, by workgroups of 256 lanes with
+// an exchange and a barrier a step.)
+constexpr int kAdjChunk = 16;
+constexpr int kAdjRegion = 32 * (kAdjChunk + 1);   // a half-wave's chunks, padded by one per chunk
+static_assert(64 * kAdjChunk == kAdjWinNodes && kAdjChunk == kAdjSumNodes, "window layout");
+static_assert(kAdjRun % kAdjGroup == 0 && kAdjRun + kAdjGroup - 1 <= kAdjHalo, "run of a launch");
 
 __device__ __forceinline__ int apad(int i) { return i + (i >> 4); }
 
 // A lane index that the compiler cannot treat as known, so that the addresses built on it are formed
 // where they are used rather than kept live across the step loop.
 __device__ __forceinline__ int fresh_lane() {
-  int v = static_cast<int>(threadIdx.x);
+  int v = static_cast<int>(threadIdx.x) & 63;
   asm volatile("" : "+v"(v));
   return v;
 }
@@ -79,31 +85,47 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Window nodes of src (the instance's first node) for the lane's chunk [16 t, 16 t + 16), in two steps so
-// that the loads can be issued long before their values are needed: window_fetch loads, for each of the
-// two halves of the wave, the 512 consecutive window nodes of that half's chunks (64 per instruction,
-// coalesced) into v; window_spread passes them to the lanes' chunks through the wave's region of LDS.
-__device__ __forceinline__ void window_fetch(const double* __restrict__ src, const AdjWindow& w, int n,
-                                             double (&v)[2 * 8]) {
-  const int lt = fresh_lane();
-  const int lane = lt & 63, wave = lt >> 6;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int w0 = kAdjWinChunk * (64 * wave + 32 * h);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int k = w0 + lane + 64 * i;
-      int g = w.first + k;
-      if (g >= n) g -= n;
-      v[8 * h + i] = k < w.width ? src[g] : 0.0;
-    }
+// Whole-wave DPP moves: the value of the lane before (after), around the wave.
+template <int CTRL>
+__device__ __forceinline__ double wave_rotate(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const int lo = static_cast<int>(b & 0xffffffffu), hi = static_cast<int>(b >> 32);
+  const uint32_t l = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+  const uint32_t h = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false));
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(h) << 32) | l);
+}
+__device__ __forceinline__ double from_left(double x) { return wave_rotate<0x13C>(x); }
+__device__ __forceinline__ double from_right(double x) { return wave_rotate<0x134>(x); }
+
+// Instance nodes of the window nodes lane, lane + 64, lane + 128, ...: an instance shorter than the window is gone
+// around as often as it takes (beyond a Dirichlet window's end the nodes are any).
+struct NodeWalk {
+  int g, step, n;
+  __device__ __forceinline__ NodeWalk(const AdjWindow& w, int nodes, int lane) : g(w.first + lane), n(nodes) {
+    step = n >= 64 ? 64 : 64 % n;
+    if (g >= n) g = n >= 64 ? g - n : g % n;
   }
+  __device__ __forceinline__ int next() {
+    const int now = g;
+    g += step;
+    g = g >= n ? g - n : g;
+    return now;
+  }
+};
+
+// Window nodes of src (the instance's first node) for the lane's chunk [16 t, 16 t + 16), in two steps so
+// that the loads can be issued long before their values are needed: window_fetch loads 64 consecutive window
+// nodes per instruction into v; window_spread passes them to the lanes' chunks, half the wave at a time, through the
+// wave's region of LDS.
+__device__ __forceinline__ void window_fetch(const double* __restrict__ src, const AdjWindow& w, int n,
+                                             double (&v)[kAdjChunk]) {
+  NodeWalk at(w, n, fresh_lane());
+#pragma unroll
+  for (int i = 0; i < kAdjChunk; ++i) v[i] = src[at.next()];
 }
 
-__device__ __forceinline__ void window_spread(const double (&v)[2 * 8], double* lds, double (&out)[kAdjWinChunk]) {
-  const int lt = fresh_lane();
-  const int lane = lt & 63, wave = lt >> 6;
-  double* region = lds + wave * kAdjWinRegion;
+__device__ __forceinline__ void window_spread(const double (&v)[kAdjChunk], double* region, double (&out)[kAdjChunk]) {
+  const int lane = fresh_lane();
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
 #pragma unroll
@@ -111,140 +133,161 @@ __device__ __forceinline__ void window_spread(const double (&v)[2 * 8], double* 
     wave_sync();
     if ((lane >> 5) == h) {
 #pragma unroll
-      for (int j = 0; j < kAdjWinChunk; ++j) out[j] = region[apad(kAdjWinChunk * (lane & 31) + j)];
+      for (int j = 0; j < kAdjChunk; ++j) out[j] = region[apad(kAdjChunk * (lane & 31) + j)];
     }
     wave_sync();
   }
 }
 
 // The lane's chunk to the window's kept nodes of dst (the instance's first node), the way back.
-__device__ __forceinline__ void window_store(const double (&x)[kAdjWinChunk], const AdjWindow& w, int n,
-                                             double* lds, double* __restrict__ dst) {
-  const int lt = fresh_lane();
-  const int lane = lt & 63, wave = lt >> 6;
-  double* region = lds + wave * kAdjWinRegion;
+__device__ __forceinline__ void window_store(const double (&x)[kAdjChunk], const AdjWindow& w, int n, double* region,
+                                             double* __restrict__ dst) {
+  const int lane = fresh_lane();
+  NodeWalk at(w, n, lane);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     if ((lane >> 5) == h) {
 #pragma unroll
-      for (int j = 0; j < kAdjWinChunk; ++j) region[apad(kAdjWinChunk * (lane & 31) + j)] = x[j];
+      for (int j = 0; j < kAdjChunk; ++j) region[apad(kAdjChunk * (lane & 31) + j)] = x[j];
     }
     wave_sync();
-    const int w0 = kAdjWinChunk * (64 * wave + 32 * h);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int q = lane + 64 * i, k = w0 + q;
-      const double v = region[apad(q)];
-      if (k >= w.lo && k < w.lo + w.count) {
-        int g = w.first + k;
-        if (g >= n) g -= n;
-        dst[g] = v;
-      }
+      const int k = 512 * h + lane + 64 * i, node = at.next();
+      const double v = region[apad(lane + 64 * i)];
+      if (k >= w.lo && k < w.lo + w.count) dst[node] = v;
     }
     wave_sync();
   }
 }
 
-// (Four workgroups of 256 lanes per CU, 128 registers, the next step's loads in flight: C5, 256 x 16384,
-// 36.6 ms per gradient, against 41.5 ms with windows of 8192 nodes on 512 lanes, two per CU, whose halos
-// are a smaller share; 54.4 ms with 131 registers and one 512-lane workgroup per CU.)
-// Reverse steps k = k_hi - 1 down to k_lo of a segment: u^k at u0 for k = 0, else at useg + (k - 1) ustride
-// (binary64 states); lam^(k_hi) from lamp, lam^(k_lo) to lam (the window's kept nodes).
-// PERIODIC: every window of the launch belongs to a periodic instance (no boundary cases are compiled);
-// otherwise every window belongs to a Dirichlet one.
-template <bool PERIODIC>
-__global__ __launch_bounds__(kAdjWinLanes, 4) void adj_explicit_block_kernel(
-    const InstDesc* __restrict__ inst, const AdjWindow* __restrict__ wins, const double* __restrict__ u0,
+// What a lane knows of its chunk.  EDGE: the window holds a Dirichlet node or keeps part of a chunk.
+struct AdjLane {
+  double r, D;
+  bool first;   // node 0 of a Dirichlet instance is the chunk's first
+  int last;     // place of its node n - 1 in the chunk, or none (negative or beyond)
+  int kept;     // kept nodes: a prefix of the chunk
+  template <bool EDGE>
+  __device__ __forceinline__ bool fixed(int j) const {
+    return EDGE && ((j == 0 && first) || j == last);
+  }
+};
+
+// The state after u.
+template <bool EDGE>
+__device__ __forceinline__ void adj_forward(const double (&u)[kAdjChunk], double (&x)[kAdjChunk], const AdjLane& l) {
+  const double left = from_left(u[kAdjChunk - 1]), right = from_right(u[0]);
+#pragma unroll
+  for (int j = 0; j < kAdjChunk; ++j) {
+    const double um = j > 0 ? u[j > 0 ? j - 1 : 0] : left;
+    const double up = j < kAdjChunk - 1 ? u[j < kAdjChunk - 1 ? j + 1 : j] : right;
+    const double v = upwind_central(u[j], um, up, l.r, l.D);
+    x[j] = l.fixed<EDGE>(j) ? u[j] : v;
+    if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// lam at the step from u, in place, and its terms of dJ/dD.
+template <bool EDGE>
+__device__ __forceinline__ void adj_back(double (&u)[kAdjChunk], double (&lam)[kAdjChunk], double& g, const AdjLane& l) {
+  constexpr int M = kAdjChunk;
+  // (opaque, or the compiler keeps adj_forward's differences and weights of u for this and spills)
+#pragma unroll
+  for (int j = 0; j < M; ++j) asm volatile("" : "+v"(u[j]));
+  const double left = from_left(u[M - 1]), right = from_right(u[0]);
+  auto weights = [&](int j, double& p, double& q) {
+    const double be = __builtin_fmax(__builtin_fma(l.r, u[j], l.D), l.D);
+    p = __builtin_fma(-l.r, u[j], be) * lam[j];
+    q = be * lam[j];
+    if (l.fixed<EDGE>(j)) p = q = 0.0;
+  };
+  double p, q, pl, ql;
+  weights(M - 1, pl, ql);
+  weights(0, p, q);
+  double pm = from_left(pl);                 // p of the node before
+  const double q_right = from_right(q);
+  double dm = u[0] - left;                   // u_j - u_{j-1}
+#pragma unroll
+  for (int j = 0; j < M; ++j) {
+    const double um = j > 0 ? u[j > 0 ? j - 1 : 0] : left, up = j < M - 1 ? u[j < M - 1 ? j + 1 : j] : right;
+    const double dp = up - u[j];
+    double pn = 0.0, qn = q_right;
+    if (j + 2 < M) weights(j + 1, pn, qn);
+    else if (j + 2 == M) {
+      pn = pl;
+      qn = ql;
+    }
+    const double own = u[j] >= 0.0 ? dm : dp, lj = lam[j];
+    double t = (lj - p) - q;
+    t = __builtin_fma(-own, l.r * lj, t);
+    t = (t + qn) + pm;
+    const double lap = fma_exact(-2.0, u[j], up + um);   // (rounded as eq. 4 reads, like the oracle's)
+    if constexpr (EDGE) g = j < l.kept ? __builtin_fma(lj, lap, g) : g;
+    else g = __builtin_fma(lj, lap, g);
+    lam[j] = l.fixed<EDGE>(j) ? 0.0 : t;
+    pm = p;
+    p = pn;
+    q = qn;
+    dm = dp;
+    // (a few nodes at a time, or the scheduler forms every node's terms up front and spills)
+    if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Reverse steps k = k_hi - 1 down to k_lo (a multiple of kAdjGroup) of a segment: the states u^k with k a multiple of
+// kAdjGroup at u0 for k = 0, else at useg + (k - 1) ustride; lam^(k_hi) from lamp, lam^(k_lo) to lam (the kept
+// nodes).  One window per wave.
+template <bool EDGE>
+__global__ __launch_bounds__(256, 2) void adj_explicit_kernel(
+    const InstDesc* __restrict__ inst, const AdjWindow* __restrict__ wins, int n_wins, const double* __restrict__ u0,
     const double* __restrict__ useg, int64_t ustride, int k_lo, int k_hi, const double* __restrict__ lamp,
     double* __restrict__ lam, double* __restrict__ gslot) {
-  constexpr int M = kAdjWinChunk, NT = kAdjWinLanes;
-  __shared__ double ends[2][4][NT];            // per step parity: u first, u last, lam first, lam last
-  __shared__ double region[(NT / 64) * kAdjWinRegion];
-  const AdjWindow w = wins[blockIdx.x];
+  constexpr int M = kAdjChunk;
+  __shared__ double lds[4 * kAdjRegion];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int index = 4 * static_cast<int>(blockIdx.x) + wave;
+  if (index >= n_wins) return;
+  double* region = lds + wave * kAdjRegion;
+  const AdjWindow w = wins[index];
   const InstDesc d = inst[w.inst];
-  const int n = d.n;
-  constexpr bool periodic = PERIODIC;
-  const double r = d.r, D = d.D;
-  const int t = threadIdx.x;
-  const int P = (w.width + M - 1) / M;         // lanes holding nodes; the last holds mlast
-  const int mlast = w.width - M * (P - 1);
-  const int m = t < P ? (t == P - 1 ? mlast : M) : 0;
-  // the lane's kept nodes are a prefix of its chunk (w.lo is a multiple of M): the first kc
-  const int kc = M * t >= w.lo ? min(M, max(0, w.lo + w.count - M * t)) : 0;
-  // the lane's tile (16-lane groups start on tile boundaries) and its running dJ/dD sum
-  const bool tile_lane = (t & 15) == 0 && M * t >= w.lo && M * t < w.lo + w.count;
-  const int slot = w.slot0 + (M * t - w.lo) / kAdjSumTile;
-  double tile_sum = tile_lane ? gslot[slot] : 0.0;
+  const int n = d.n, at = M * (static_cast<int>(threadIdx.x) & 63);
+  const bool dir = EDGE && d.bc == kDirichlet;
+  const AdjLane l{d.r, d.D, dir && w.first + at == 0, dir ? n - 1 - w.first - at : -1,
+                  at >= w.lo ? w.lo + w.count - at : 0};
+  const int slot = w.slot0 + (at - w.lo) / M;
+  double g = l.kept > 0 ? gslot[slot] : 0.0;
   auto state = [&](int k) { return (k == 0 ? u0 : useg + static_cast<int64_t>(k - 1) * ustride) + d.off; };
-  double L[M], U[M], V[2 * 8];
-  window_fetch(lamp + d.off, w, n, V);
-  window_spread(V, region, L);
-  window_fetch(state(k_hi - 1), w, n, V);
-  for (int k = k_hi - 1; k >= k_lo; --k) {
-    window_spread(V, region, U);
-    const int b = k & 1;
-    if (t < P) {
-      double ul = U[M - 1], ll = L[M - 1];
-#pragma unroll
-      for (int j = 0; j < M; ++j)
-        if (j == m - 1) {
-          ul = U[j];
-          ll = L[j];
-        }
-      ends[b][0][t] = U[0];
-      ends[b][1][t] = ul;
-      ends[b][2][t] = L[0];
-      ends[b][3][t] = ll;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    double g = 0.0;
-    // neighbours beyond the window's ends wrap around it: exact for a whole periodic instance, and only
-    // the halo is affected otherwise (the indices are formed here, not kept live across the step)
-    const int tf = fresh_lane();
-    const int tl = tf > 0 ? tf - 1 : P - 1, tr = tf < P - 1 ? tf + 1 : 0;
-    const double uL = ends[b][1][tl], uR = ends[b][0][tr];
-    const double lL = ends[b][3][tl], lR = ends[b][2][tr];
-    // the next step's state is in flight during this step's update: issued after every read that the
-    // update waits for, since a wait on the in-order memory counter would also wait for these loads
-    if (k > k_lo) window_fetch(state(k - 1), w, n, V);
-    if (t < P) {
-      double lprev = lL;                        // lam^(k+1) of the node before, kept before it is overwritten
+  auto ends = [&](double (&x)[M], double a, double b) {   // the fixed nodes' values
+    if constexpr (EDGE) {
 #pragma unroll
       for (int j = 0; j < M; ++j) {
-        if (j < m) {
-          int jn = w.first + M * t + j;         // instance node (only a Dirichlet window needs it)
-          if (jn >= n) jn -= n;
-          const double uj = U[j];
-          const double uprev = j == 0 ? uL : U[j > 0 ? j - 1 : 0];
-          const double unext = j + 1 < m ? U[j + 1 < M ? j + 1 : j] : uR;
-          const double lj = L[j];
-          const double lnext = j + 1 < m ? L[j + 1 < M ? j + 1 : j] : lR;
-          double acc = 0.0;
-          if (periodic || (jn > 0 && jn < n - 1)) {
-            const double um = (!periodic && jn == 1) ? d.a : uprev;
-            const double up = (!periodic && jn == n - 2) ? d.b : unext;
-            // own update
-            const double self = uj >= 0.0 ? ((1.0 - r * (uj - um)) - r * uj) - 2.0 * D
-                                          : ((1.0 - r * (up - uj)) + r * uj) - 2.0 * D;
-            acc = self * lj;
-            if (j < kc) g = g + lj * ((up + um) - 2.0 * uj);
-            // node j+1 reads u_j as its left neighbour
-            if (periodic || jn + 1 <= n - 2) acc = acc + (unext >= 0.0 ? r * unext + D : D) * lnext;
-            // node j-1 reads u_j as its right neighbour
-            if (periodic || jn - 1 >= 1) acc = acc + (uprev >= 0.0 ? D : D - r * uprev) * lprev;
-          }
-          lprev = lj;
-          L[j] = acc;
-        }
+        if (j == 0 && l.first) x[j] = a;
+        if (j == l.last) x[j] = b;
       }
     }
-    // the tile's partial for this step: a butterfly over its 16 lanes, taken from its first lane
-#pragma unroll
-    for (int s = 8; s >= 1; s >>= 1) g = g + __shfl_xor(g, s, 64);
-    if (tile_lane) tile_sum = tile_sum + g;
+  };
+  double L[M], U0[M], U1[M], U2[M], U3[M], V[M];
+  window_fetch(lamp + d.off, w, n, V);
+  window_spread(V, region, L);
+  ends(L, 0.0, 0.0);
+  static_assert(kAdjGroup == 4, "a group's states");
+  int k = (k_hi - 1) / kAdjGroup * kAdjGroup;
+  window_fetch(state(k), w, n, V);
+  for (int top = k_hi - k; k >= k_lo; k -= kAdjGroup, top = kAdjGroup) {   // steps k + top - 1 .. k
+    window_spread(V, region, U0);
+    ends(U0, d.a, d.b);
+    if (top > 1) adj_forward<EDGE>(U0, U1, l);
+    if (top > 2) adj_forward<EDGE>(U1, U2, l);
+    if (top > 3) adj_forward<EDGE>(U2, U3, l);
+    // the next group's state is in flight during this one's reverse steps
+    if (k > k_lo) window_fetch(state(k - kAdjGroup), w, n, V);
+    if (top > 3) adj_back<EDGE>(U3, L, g, l);
+    if (top > 2) adj_back<EDGE>(U2, L, g, l);
+    if (top > 1) adj_back<EDGE>(U1, L, g, l);
+    adj_back<EDGE>(U0, L, g, l);
   }
   window_store(L, w, n, region, lam + d.off);
-  if (tile_lane) gslot[slot] = tile_sum;
+  if (l.kept > 0) gslot[slot] = g;
 }
 
 // Row k of A(y)^T, normalised by its diagonal, and the right-hand side lamp / d, for every unknown of
@@ -326,14 +369,18 @@ __global__ __launch_bounds__(kAdjThreads) void adj_btcs_finish_kernel(
   if (threadIdx.x == 0) gslot[t.slot] = gslot[t.slot] + tot;
 }
 
-// grad_nu[i] = (sum of instance i's tile partials, in tile order) * dt/dx^2.
-__global__ void adj_nu_kernel(const InstDesc* __restrict__ inst, const int32_t* __restrict__ slot_begin,
-                              const double* __restrict__ gslot, double* __restrict__ grad_nu, int count) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
+// grad_nu[i] = (sum of instance i's slots) * dt/dx^2, a workgroup per instance: each lane's every 256th slot in
+// order, then the lanes in a fixed order.
+__global__ __launch_bounds__(kAdjThreads) void adj_nu_kernel(const InstDesc* __restrict__ inst,
+                                                             const int32_t* __restrict__ slot_begin,
+                                                             const double* __restrict__ gslot,
+                                                             double* __restrict__ grad_nu) {
+  __shared__ double red[kAdjThreads / 64];
+  const int i = blockIdx.x;
   double s = 0.0;
-  for (int k = slot_begin[i]; k < slot_begin[i + 1]; ++k) s = s + gslot[k];
-  grad_nu[i] = s * inst[i].dtdx2;
+  for (int k = slot_begin[i] + static_cast<int>(threadIdx.x); k < slot_begin[i + 1]; k += kAdjThreads) s = s + gslot[k];
+  s = block_sum(s, red);
+  if (threadIdx.x == 0) grad_nu[i] = s * inst[i].dtdx2;
 }
 
 // Dirichlet boundary nodes carry no gradient.
@@ -356,16 +403,17 @@ __global__ void fill_kernel(double* __restrict__ p, int64_t n, double v) {
 
 int adjoint_tile_nodes() { return kAdjTile; }
 
-hipError_t launch_adj_explicit_block(const burgers_ctx* ctx, const AdjWindow* wins, int64_t n_wins, int64_t n_periodic,
-                                     const double* u0, const double* useg, int64_t ustride, int k_lo, int k_hi,
-                                     const double* lamp, double* lam, double* gslot) {
+hipError_t launch_adj_explicit(const burgers_ctx* ctx, const AdjWindow* wins, int64_t n_wins, int64_t n_inner,
+                               const double* u0, const double* useg, int64_t ustride, int k_lo, int k_hi,
+                               const double* lamp, double* lam, double* gslot) {
   if (n_wins <= 0 || k_hi <= k_lo) return hipSuccess;
-  if (n_periodic > 0)
-    adj_explicit_block_kernel<true><<<static_cast<unsigned>(n_periodic), kAdjWinLanes, 0, ctx->stream>>>(
-        ctx->inst.as<InstDesc>(), wins, u0, useg, ustride, k_lo, k_hi, lamp, lam, gslot);
-  if (n_wins > n_periodic)
-    adj_explicit_block_kernel<false><<<static_cast<unsigned>(n_wins - n_periodic), kAdjWinLanes, 0, ctx->stream>>>(
-        ctx->inst.as<InstDesc>(), wins + n_periodic, u0, useg, ustride, k_lo, k_hi, lamp, lam, gslot);
+  const int inner = static_cast<int>(n_inner), edge = static_cast<int>(n_wins - n_inner);
+  if (inner > 0)
+    adj_explicit_kernel<false><<<static_cast<unsigned>((inner + 3) / 4), 256, 0, ctx->stream>>>(
+        ctx->inst.as<InstDesc>(), wins, inner, u0, useg, ustride, k_lo, k_hi, lamp, lam, gslot);
+  if (edge > 0)
+    adj_explicit_kernel<true><<<static_cast<unsigned>((edge + 3) / 4), 256, 0, ctx->stream>>>(
+        ctx->inst.as<InstDesc>(), wins + n_inner, edge, u0, useg, ustride, k_lo, k_hi, lamp, lam, gslot);
   return hipGetLastError();
 }
 
@@ -391,9 +439,8 @@ hipError_t launch_adj_btcs_finish(const burgers_ctx* ctx, const AdjTile* tiles, 
 
 hipError_t launch_adj_nu(const burgers_ctx* ctx, const int32_t* slot_begin, const double* gslot,
                          double* grad_nu) {
-  const int count = static_cast<int>(ctx->count);
-  adj_nu_kernel<<<(count + 255) / 256, 256, 0, ctx->stream>>>(ctx->inst.as<InstDesc>(), slot_begin, gslot,
-                                                              grad_nu, count);
+  adj_nu_kernel<<<static_cast<unsigned>(ctx->count), kAdjThreads, 0, ctx->stream>>>(ctx->inst.as<InstDesc>(), slot_begin,
+                                                                                    gslot, grad_nu);
   return hipGetLastError();
 }
 

@@ -957,26 +957,20 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
     const int32_t R = static_cast<int32_t>(p.bc == BURGERS_BC_PERIODIC ? p.n : p.n - 2);
     slot_begin[i] = slot;
     if (p.scheme != BURGERS_BTCS) {
-      // explicit: one slot per tile of kAdjSumTile nodes; the whole instance in one window, or windows
-      // keeping kAdjWinNodes - 2 kAdjHalo nodes (whole tiles) with kAdjHalo more on either side
-      constexpr int32_t H = burgers::kAdjHalo, kept = burgers::kAdjWinNodes - 2 * burgers::kAdjHalo;
-      static_assert(kept % burgers::kAdjSumTile == 0, "windows keep whole tiles");
-      if (n <= burgers::kAdjWinNodes) {
-        ew.push_back(burgers::AdjWindow{i, 0, n, 0, n, slot});
-      } else {
-        for (int32_t lo = 0; lo < n; lo += kept) {
-          const int32_t hi = std::min(n, lo + kept);
-          if (p.bc == BURGERS_BC_PERIODIC) {
-            ew.push_back(burgers::AdjWindow{i, ((lo - H) % n + n) % n, (hi - lo) + 2 * H, H, hi - lo,
-                                            slot + lo / burgers::kAdjSumTile});
-          } else {
-            const int32_t first = std::max(0, lo - H), end = std::min(n, hi + H);
-            ew.push_back(burgers::AdjWindow{i, first, end - first, lo - first, hi - lo,
-                                            slot + lo / burgers::kAdjSumTile});
-          }
+      // explicit: one slot per kAdjSumNodes nodes, and windows of equal shares of whole slots
+      constexpr int32_t H = burgers::kAdjHalo, G = burgers::kAdjSumNodes, most = burgers::kAdjWinNodes - 2 * H;
+      static_assert(most % G == 0 && H % G == 0, "windows keep whole slots");
+      const int32_t shares = (n + most - 1) / most, kept = ((n + shares - 1) / shares + G - 1) / G * G;
+      for (int32_t lo = 0; lo < n; lo += kept) {
+        const int32_t hi = std::min(n, lo + kept);
+        if (p.bc == BURGERS_BC_PERIODIC) {
+          ew.push_back(burgers::AdjWindow{i, ((lo - H) % n + n) % n, (hi - lo) + 2 * H, H, hi - lo, slot + lo / G});
+        } else {
+          const int32_t first = std::max(0, lo - H), end = std::min(n, hi + H);
+          ew.push_back(burgers::AdjWindow{i, first, end - first, lo - first, hi - lo, slot + lo / G});
         }
       }
-      slot += (n + burgers::kAdjSumTile - 1) / burgers::kAdjSumTile;
+      slot += (n + G - 1) / G;
       continue;
     }
     for (int64_t s = 0; s < n; s += btcs_tile)
@@ -996,13 +990,13 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
   }
   slot_begin[ctx->count] = slot;
   hipError_t e;
-  // windows of periodic instances first (their launch compiles no boundary cases)
-  std::stable_partition(ew.begin(), ew.end(), [&](const burgers::AdjWindow& w) {
-    return ctx->probs[w.inst].bc == BURGERS_BC_PERIODIC;
-  });
-  ap->n_exp_wins_periodic = std::count_if(ew.begin(), ew.end(), [&](const burgers::AdjWindow& w) {
-    return ctx->probs[w.inst].bc == BURGERS_BC_PERIODIC;
-  });
+  // windows without a Dirichlet node or part of a slot first (their launch compiles neither case)
+  auto inner = [&](const burgers::AdjWindow& w) {
+    const burgers_problem& p = ctx->probs[w.inst];
+    return w.count % burgers::kAdjSumNodes == 0 &&
+           (p.bc == BURGERS_BC_PERIODIC || (w.first > 0 && w.first + w.width < p.n));
+  };
+  ap->n_exp_inner = std::stable_partition(ew.begin(), ew.end(), inner) - ew.begin();
   ap->exp_wins = std::make_unique<DevBuf>();
   ap->btcs_tiles = std::make_unique<DevBuf>();
   ap->slot_begin = std::make_unique<DevBuf>();
@@ -1431,9 +1425,9 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
   // State k of segment c: the checkpoint for k = 0, else slot k - 1 of the segment's buffer.
   auto at = [&](int64_t c, DevBuf& seg, int64_t k) { return k == 0 ? state(ap.ckpt, c) : state(seg, k - 1); };
   // A segment's states are recomputed out of place.  Instances that the forward sweep keeps on chip are
-  // kept on chip here too, by kernels that store the state after every step (one launch per segment, or
-  // per `depth` steps for the explicit windows, whose halos cover that many steps): each state is written
-  // once and nothing is read back.  The others step one launch at a time from state k - 1 straight into
+  // kept on chip here too, by kernels that store the state after every step, or for the explicit ones every
+  // kAdjGroup-th (one launch per segment, or per `depth` steps for the explicit windows, whose halos cover that
+  // many steps): each is written once and nothing is read back.  The others step one launch at a time from state k - 1 straight into
   // state k: the streaming kernel for explicit instances, the per-step solves for BTCS ones.
   const burgers::ExplicitPlan* ep = ctx->set_explicit.empty() ? nullptr : ctx->explicit_plans[kSetExplicit].get();
   const bool exp_rec = ep && ep->path != 1;
@@ -1449,10 +1443,10 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
       for (const auto& wc : ep->whole_classes)
         if (err == hipSuccess)
           err = burgers::launch_explicit_record(ctx, ep->whole->as<BlockTile>() + wc.offset, wc.n_fe, at(c, seg, k0),
-                                                at(c, seg, k0 + 1), stride, k, wc.lanes);
+                                                at(c, seg, k0 + 1), stride, k, static_cast<int>(k0), wc.lanes);
       if (err == hipSuccess)
         err = burgers::launch_explicit_record(ctx, ep->win->as<BlockTile>(), ep->n_win, at(c, seg, k0),
-                                              at(c, seg, k0 + 1), stride, k);
+                                              at(c, seg, k0 + 1), stride, k, static_cast<int>(k0));
     }
     if (btcs_rec)
       for (const burgers::WgGroup& g : bres->resident)
@@ -1498,16 +1492,19 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
       if (e == hipSuccess) e = hipEventRecord(ctx->joined[0], ctx->side[0]);
       if (e != hipSuccess) return note(ctx, e);
     }
-    // explicit instances: runs of up to kAdjHalo reverse steps per launch, lam on chip (out of place)
-    for (int64_t hi = len; ap.n_exp_wins > 0 && hi > 0; hi -= burgers::kAdjHalo) {
-      const int64_t lo = std::max<int64_t>(0, hi - burgers::kAdjHalo);
-      if ((e = burgers::launch_adj_explicit_block(ctx, ap.exp_wins->as<burgers::AdjWindow>(), ap.n_exp_wins,
-                                                  ap.n_exp_wins_periodic, reinterpret_cast<const double*>(at(c, cur, 0)),
-                                                  reinterpret_cast<const double*>(at(c, cur, 1)), ctx->total,
-                                                  static_cast<int>(lo), static_cast<int>(hi), lam_e, lam_e_next,
-                                                  ap.gslot.as<double>())) != hipSuccess)
+    // explicit instances: equal runs of up to kAdjRun reverse steps per launch, lam on chip (out of place)
+    const int64_t runs = (len + burgers::kAdjRun - 1) / burgers::kAdjRun;
+    const int64_t run = ((len + runs - 1) / runs + burgers::kAdjGroup - 1) / burgers::kAdjGroup * burgers::kAdjGroup;
+    for (int64_t hi = len; ap.n_exp_wins > 0 && hi > 0;) {
+      const int64_t lo = (hi - 1) / run * run;
+      if ((e = burgers::launch_adj_explicit(ctx, ap.exp_wins->as<burgers::AdjWindow>(), ap.n_exp_wins, ap.n_exp_inner,
+                                            reinterpret_cast<const double*>(at(c, cur, 0)),
+                                            reinterpret_cast<const double*>(at(c, cur, 1)), ctx->total,
+                                            static_cast<int>(lo), static_cast<int>(hi), lam_e, lam_e_next,
+                                            ap.gslot.as<double>())) != hipSuccess)
         return note(ctx, e);
       std::swap(lam_e, lam_e_next);
+      hi = lo;
     }
     // BTCS instances: the segment's reverse steps in one launch when every system is solved whole (lam
     // on chip between them), else one reverse step per launch

@@ -324,19 +324,25 @@ __device__ __forceinline__ void record_window(const T (&x)[kBlockChunk], T* stag
   }
 }
 
+// Whether the state after step k of a recording launch of `steps` steps is stored: every kAdjGroup-th of the call's,
+// which begins `first_step` steps before the launch, and the last (the next launch begins there).
+__device__ __forceinline__ bool recorded(int first_step, int k, int steps) {
+  return (first_step + k) % kAdjGroup == 0 || k == steps;
+}
+
 // Temporal-blocking body over NT lanes.  EXACT: the window has exactly NT * kBlockChunk nodes, so every lane
 // holds a full chunk and the guards below fold away.
 // t: the lane's index among the NT lanes that take the window (the workgroup's lane, or its lane within
 // its sub-group when several windows share a workgroup).  Every call executes the same sequence of
 // workgroup barriers for a given `steps`, whatever the window (an empty one included).
-// REC (forward Euler, t the workgroup's lane): instead of the final state, the state after each step k
-// (1 <= k <= steps) is stored at rec + (k - 1) rstride (the instance's first node), so that a segment of
+// REC (forward Euler, t the workgroup's lane): instead of the final state, recorded states (recorded()) after
+// steps k (1 <= k <= steps) are stored at rec + (k - 1) rstride (the instance's first node), so that a segment of
 // states is computed in one pass over HBM that writes each of them once.
 template <typename T, bool EXACT, bool RK4, int NT, int ML = 0, bool REC = false>
 __device__ __forceinline__ void block_body(const BlockTile& bt, const InstDesc& d, const T* __restrict__ src,
                                            T* __restrict__ dst, int steps, T* stage,
                                            T (*s_first)[NT], T (*s_last)[NT], int t, T* __restrict__ rec = nullptr,
-                                           int64_t rstride = 0) {
+                                           int64_t rstride = 0, int first_step = 0) {
   static_assert(!(REC && RK4), "recording is for forward Euler");
   constexpr int M = kBlockChunk;
   const T r = static_cast<T>(d.r), D = static_cast<T>(d.D);
@@ -413,12 +419,14 @@ __device__ __forceinline__ void block_body(const BlockTile& bt, const InstDesc& 
     if (active) {
       chunk_step<T, EXACT, ML>(v, w, left, right, r, D, r0, D0, r1, D1, is_last, rE, DE);
     }
-    if constexpr (REC) record_window<T, NT>(w, stage, bt, n, rec + step * rstride);
+    if constexpr (REC)
+      if (recorded(first_step, step + 1, steps)) record_window<T, NT>(w, stage, bt, n, rec + step * rstride);
     exchange_ends<T, EXACT, NT, ML, REC>(w, 1, t, P, mlast, active, s_first, s_last, left, right);
     if (active) {
       chunk_step<T, EXACT, ML>(w, v, left, right, r, D, r0, D0, r1, D1, is_last, rE, DE);
     }
-    if constexpr (REC) record_window<T, NT>(v, stage, bt, n, rec + (step + 1) * rstride);
+    if constexpr (REC)
+      if (recorded(first_step, step + 2, steps)) record_window<T, NT>(v, stage, bt, n, rec + (step + 1) * rstride);
   }
   if (step < steps) {
     exchange_ends<T, EXACT, NT, ML, REC>(v, 0, t, P, mlast, active, s_first, s_last, left, right);
@@ -459,10 +467,10 @@ template <typename T, bool RK4, int NT, bool REC = false>
 __device__ __forceinline__ void window_body(const BlockTile& bt, const InstDesc& d, const T* __restrict__ src,
                                             T* __restrict__ dst, int steps, T* stage, T (*s_first)[NT],
                                             T (*s_last)[NT], int t, T* __restrict__ rec = nullptr,
-                                            int64_t rstride = 0) {
+                                            int64_t rstride = 0, int first_step = 0) {
   if constexpr (NT == kBlockThreads) {
     if (bt.width == NT * kBlockChunk) {
-      block_body<T, true, RK4, NT, 0, REC>(bt, d, src, dst, steps, stage, s_first, s_last, t, rec, rstride);
+      block_body<T, true, RK4, NT, 0, REC>(bt, d, src, dst, steps, stage, s_first, s_last, t, rec, rstride, first_step);
       return;
     }
   }
@@ -470,7 +478,7 @@ __device__ __forceinline__ void window_body(const BlockTile& bt, const InstDesc&
   const int mlast = bt.width - kBlockChunk * ((bt.width + kBlockChunk - 1) / kBlockChunk - 1);
   switch (mlast) {
 #define BURGERS_RAGGED_CASE(K) \
-  case K: block_body<T, false, RK4, NT, K, REC>(bt, d, src, dst, steps, stage, s_first, s_last, t, rec, rstride); break;
+  case K: block_body<T, false, RK4, NT, K, REC>(bt, d, src, dst, steps, stage, s_first, s_last, t, rec, rstride, first_step); break;
     BURGERS_RAGGED_CASE(1) BURGERS_RAGGED_CASE(2) BURGERS_RAGGED_CASE(3) BURGERS_RAGGED_CASE(4)
     BURGERS_RAGGED_CASE(5) BURGERS_RAGGED_CASE(6) BURGERS_RAGGED_CASE(7) BURGERS_RAGGED_CASE(8)
     BURGERS_RAGGED_CASE(9) BURGERS_RAGGED_CASE(10) BURGERS_RAGGED_CASE(11) BURGERS_RAGGED_CASE(12)
@@ -503,12 +511,12 @@ __global__ __launch_bounds__(NT) void explicit_block_kernel(
   window_body<T, RK4, NT>(bt, d, src, dst, steps, stage, s_first, s_last, static_cast<int>(threadIdx.x));
 }
 
-// Forward-Euler windows and whole instances that record every step's state (the adjoint's recompute of
-// a checkpoint segment): states 1..steps of the launch at rec + (k - 1) rstride; the source is only read.
+// Forward-Euler windows and whole instances that record states (the adjoint's recompute of a checkpoint segment):
+// state k of the launch's 1..steps at rec + (k - 1) rstride where recorded(); the source is only read.
 template <typename T>
 __global__ __launch_bounds__(kBlockThreads) void explicit_record_kernel(
     const InstDesc* __restrict__ inst, const BlockTile* __restrict__ tiles, const T* __restrict__ u,
-    T* __restrict__ rec, int64_t rstride, int steps) {
+    T* __restrict__ rec, int64_t rstride, int steps, int first_step) {
   constexpr int NT = kBlockThreads;
   constexpr int kStage = stage_nodes<NT>();
   __shared__ T s_first[2][NT];
@@ -518,7 +526,7 @@ __global__ __launch_bounds__(kBlockThreads) void explicit_record_kernel(
   if (bt.width <= 0) return;
   const InstDesc d = inst[bt.inst];
   window_body<T, false, NT, true>(bt, d, u + d.off, nullptr, steps, stage, s_first, s_last,
-                                  static_cast<int>(threadIdx.x), rec + d.off, rstride);
+                                  static_cast<int>(threadIdx.x), rec + d.off, rstride, first_step);
 }
 
 // ---- Instances of up to 1024 nodes: one wave each ---------------------------------------------------
@@ -610,7 +618,7 @@ __device__ __forceinline__ void wave_rk4_stage(T (&v)[M], const T (&in)[M], T (&
 }
 
 // A wave's run: x and to are the instance's first node in the source and result buffers.
-// REC (forward Euler): the state after each step k (1 <= k <= steps) at to + (k - 1) rstride.
+// REC (forward Euler): recorded states after steps k (1 <= k <= steps) at to + (k - 1) rstride.
 template <typename T, int M, bool RK4, bool REC>
 struct WaveRun {
   const InstDesc& d;
@@ -618,6 +626,7 @@ struct WaveRun {
   T* to;
   int steps;
   int64_t rstride;
+  int first_step;
 
   template <Ends E>
   __device__ __forceinline__ void advance(T (&v)[M], const ChunkCoef<T>& c, int base, bool held, bool dummy, int lane_l,
@@ -641,10 +650,12 @@ struct WaveRun {
       for (; step + 2 <= steps; step += 2) {
         wave_ends<T, M, E, SLOTS>(v, dummy, lane_l, lane_r, left, right);
         wave_step(v, w, left, right, c);
-        if constexpr (REC) store(w, to + step * rstride, base, held, dummy);
+        if constexpr (REC)
+          if (recorded(first_step, step + 1, steps)) store(w, to + step * rstride, base, held, dummy);
         wave_ends<T, M, E, SLOTS>(w, dummy, lane_l, lane_r, left, right);
         wave_step(w, v, left, right, c);
-        if constexpr (REC) store(v, to + (step + 1) * rstride, base, held, dummy);
+        if constexpr (REC)
+          if (recorded(first_step, step + 2, steps)) store(v, to + (step + 1) * rstride, base, held, dummy);
       }
       if (step < steps) {
         wave_ends<T, M, E, SLOTS>(v, dummy, lane_l, lane_r, left, right);
@@ -698,12 +709,12 @@ constexpr int kWaveNodes = 1024;   // longest instance of one wave
 // A whole instance on the calling wave; out holds the states, or (REC) the first of the recorded ones.
 template <typename T, bool RK4, bool REC>
 __device__ __forceinline__ void wave_tile(const InstDesc* __restrict__ inst, const BlockTile& bt, const T* u, T* out,
-                                          int steps, int64_t rstride) {
+                                          int steps, int64_t rstride, int first_step = 0) {
   if (bt.width <= 0) return;                   // an empty slot of a resident pool
   if (bt.limit > 0) steps = min(steps, bt.limit);
   const InstDesc d = inst[bt.inst];
 #define BURGERS_WAVE_CASE(K)                                                            \
-  case K: WaveRun<T, K, RK4, REC>{d, u + d.off, out + d.off, steps, rstride}.run(); break;
+  case K: WaveRun<T, K, RK4, REC>{d, u + d.off, out + d.off, steps, rstride, first_step}.run(); break;
   switch ((d.n + 63) / 64) {
     BURGERS_WAVE_CASE(1) BURGERS_WAVE_CASE(2) BURGERS_WAVE_CASE(3) BURGERS_WAVE_CASE(4) BURGERS_WAVE_CASE(5)
     BURGERS_WAVE_CASE(6) BURGERS_WAVE_CASE(7) BURGERS_WAVE_CASE(8) BURGERS_WAVE_CASE(9) BURGERS_WAVE_CASE(10)
@@ -720,12 +731,12 @@ template <typename T, bool RK4, bool REC>
 __global__ __launch_bounds__(256, RK4 ? 3 : 4) void explicit_wave_kernel(const InstDesc* __restrict__ inst,
                                                                          const BlockTile* __restrict__ tiles,
                                                                          int n_tiles, const T* u, T* out, int steps,
-                                                                         int64_t rstride) {
+                                                                         int64_t rstride, int first_step) {
   const int k = 4 * static_cast<int>(blockIdx.x) +
                 __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   if (k >= n_tiles) return;
   const BlockTile bt = tiles[k];
-  wave_tile<T, RK4, REC>(inst, bt, u, out, steps, rstride);
+  wave_tile<T, RK4, REC>(inst, bt, u, out, steps, rstride, first_step);
 }
 
 // LDS of a sub-group of NT lanes in the pack kernel: its exchange buffers and staging area.
@@ -863,10 +874,10 @@ void wave_launch(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_fe, i
   T* dst = static_cast<T*>(out);
   if (n_fe > 0)
     explicit_wave_kernel<T, false, false><<<static_cast<unsigned>((n_fe + 3) / 4), 256, 0, ctx->stream>>>(
-        inst, tiles, static_cast<int>(n_fe), src, dst, steps, 0);
+        inst, tiles, static_cast<int>(n_fe), src, dst, steps, 0, 0);
   if (n_rk4 > 0)
     explicit_wave_kernel<T, true, false><<<static_cast<unsigned>((n_rk4 + 3) / 4), 256, 0, ctx->stream>>>(
-        inst, tiles + n_fe, static_cast<int>(n_rk4), src, dst, steps, 0);
+        inst, tiles + n_fe, static_cast<int>(n_rk4), src, dst, steps, 0, 0);
 }
 
 template <typename T>
@@ -911,17 +922,17 @@ hipError_t launch_explicit_packs(const burgers_ctx* ctx, const BlockTile* tiles,
 }
 
 hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_tiles, const void* u,
-                                  void* rec, int64_t rstride, int steps, int lanes) {
+                                  void* rec, int64_t rstride, int steps, int first_step, int lanes) {
   if (n_tiles <= 0 || steps <= 0) return hipSuccess;
   if (ctx->dtype != BURGERS_F64) return hipErrorInvalidValue;
   if (lanes == 64) {
     explicit_wave_kernel<double, false, true><<<static_cast<unsigned>((n_tiles + 3) / 4), 256, 0, ctx->stream>>>(
         ctx->inst.as<InstDesc>(), tiles, static_cast<int>(n_tiles), static_cast<const double*>(u),
-        static_cast<double*>(rec), steps, rstride);
+        static_cast<double*>(rec), steps, rstride, first_step);
     return hipGetLastError();
   }
   explicit_record_kernel<double><<<static_cast<unsigned>(n_tiles), kBlockThreads, 0, ctx->stream>>>(
-      ctx->inst.as<InstDesc>(), tiles, static_cast<const double*>(u), static_cast<double*>(rec), rstride, steps);
+      ctx->inst.as<InstDesc>(), tiles, static_cast<const double*>(u), static_cast<double*>(rec), rstride, steps, first_step);
   return hipGetLastError();
 }
 

@@ -76,16 +76,17 @@ struct AdjTile {
   int32_t pad;
 };
 
-// A window of the explicit adjoint's blocked reverse steps: window node w (0 <= w < width) is instance
-// node (first + w) mod n; nodes [lo, lo + count) are kept, and their tiles of kAdjSumTile nodes take the
-// dJ/dD slots slot0, slot0 + 1, ...  (lo and the instance node of window node lo are multiples of
-// kAdjSumTile.)
+// A window of the explicit adjoint's reverse steps: window node w (0 <= w < width) is instance node (first + w)
+// mod n; nodes [lo, lo + count) are kept, and their runs of kAdjSumNodes nodes take the dJ/dD slots slot0, slot0 + 1,
+// ...  (lo and the instance node of window node lo are multiples of kAdjSumNodes.)
 struct AdjWindow {
   int32_t inst, first, width, lo, count, slot0;
 };
-constexpr int kAdjWinNodes = 4096;   // window capacity (256 lanes x 16 nodes)
-constexpr int kAdjHalo = 256;        // halo nodes per side of a window of a longer instance; steps per launch
-constexpr int kAdjSumTile = 256;     // nodes per dJ/dD slot of an explicit instance
+constexpr int kAdjWinNodes = 1024;   // window capacity (one wave, 16 nodes a lane)
+constexpr int kAdjHalo = 64;         // halo nodes per side
+constexpr int kAdjGroup = 4;         // one state in so many is recorded and read
+constexpr int kAdjRun = 60;          // steps per launch at most
+constexpr int kAdjSumNodes = 16;     // nodes per dJ/dD slot of an explicit instance
 
 // One tridiagonal system of the BTCS solve at some level of the partition hierarchy.
 //   level 0: rows assembled from the state of instance `inst`; level > 0: rows (A, 1, C, D) stored in
@@ -280,7 +281,7 @@ struct ExplicitPlan {
 struct AdjointPlan {
   std::unique_ptr<DevBuf> exp_wins, btcs_tiles;     // AdjWindow[] of the explicit instances, AdjTile[]
   int64_t n_exp_wins = 0, n_btcs_tiles = 0;
-  int64_t n_exp_wins_periodic = 0;                 // the first windows of exp_wins, of periodic instances
+  int64_t n_exp_inner = 0;                          // the first windows of exp_wins (see launch_adj_explicit)
   std::unique_ptr<DevBuf> slot_begin;               // int32[count + 1]
   int64_t n_slots = 0;
   BtcsPlan solve;                                   // partition hierarchy over the transposed systems
@@ -364,11 +365,11 @@ hipError_t launch_explicit_block(const burgers_ctx* ctx, const BlockTile* tiles,
 int explicit_pack_lanes();                  // lanes of a pack kernel workgroup
 hipError_t launch_explicit_packs(const burgers_ctx* ctx, const BlockTile* tiles, const BlockPack* packs,
                                  int64_t n_fe, int64_t n_rk4, void* u, int steps);
-// Forward-Euler block tiles (whole instances or windows with a halo of at least `steps`) recording the
-// state after each step k (1 <= k <= steps) at rec + (k - 1) rstride (binary64; u is only read).
-// `lanes` 64: whole instances of one wave each.
+// Forward-Euler block tiles (whole instances or windows with a halo of at least `steps`) recording states after
+// their steps k (1 <= k <= steps) at rec + (k - 1) rstride (binary64; u is only read): those with first_step + k a
+// multiple of kAdjGroup, and the last.  `lanes` 64: whole instances of one wave each.
 hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles, int64_t n_tiles, const void* u,
-                                  void* rec, int64_t rstride, int steps, int lanes = 512);
+                                  void* rec, int64_t rstride, int steps, int first_step, int lanes = 512);
 // Windows of a long explicit instance `i` of n nodes advanced `depth` steps per launch (halo = depth x
 // stages per side); appends them to `out`.  Returns false when the halo leaves no kept node.
 bool explicit_windows(int32_t i, int32_t n, bool periodic, int depth, bool rk4, std::vector<BlockTile>& out);
@@ -395,13 +396,13 @@ int explicit_block_capacity();
 
 // adjoint.hip
 int adjoint_tile_nodes();   // nodes per dJ/dD slot of a BTCS instance
-// Explicit reverse steps k = k_hi - 1 .. k_lo over the windows (those of periodic instances first, n_periodic
-// of them): u^k at u0 (k = 0) or useg + (k - 1) ustride, lam^(k_hi) in lamp, lam^(k_lo) to lam (out of
-// place), dJ/dD added to the windows' tile slots of gslot.  Windows of longer instances take at most
-// kAdjHalo steps per launch.
-hipError_t launch_adj_explicit_block(const burgers_ctx* ctx, const AdjWindow* wins, int64_t n_wins, int64_t n_periodic,
-                                     const double* u0, const double* useg, int64_t ustride, int k_lo, int k_hi,
-                                     const double* lamp, double* lam, double* gslot);
+// Explicit reverse steps k = k_hi - 1 .. k_lo (a multiple of kAdjGroup; at most kAdjRun steps) over the windows (the
+// first n_inner hold no Dirichlet node and keep whole runs of kAdjSumNodes nodes): u^k at u0 (k = 0) or useg +
+// (k - 1) ustride, k a multiple of kAdjGroup; lam^(k_hi) in lamp, lam^(k_lo) to lam (out of place), dJ/dD added to
+// the windows' slots of gslot.
+hipError_t launch_adj_explicit(const burgers_ctx* ctx, const AdjWindow* wins, int64_t n_wins, int64_t n_inner,
+                               const double* u0, const double* useg, int64_t ustride, int k_lo, int k_hi,
+                               const double* lamp, double* lam, double* gslot);
 // `only` (optional): only the instances whose entry is nonzero (those whose windows flagged a failed
 // bound); the finish launch also adds the windows' partials (wins/win_slot/wpart, n_win may be 0).
 hipError_t launch_adj_btcs_assemble(const burgers_ctx* ctx, const AdjTile* tiles, int64_t n_tiles,
