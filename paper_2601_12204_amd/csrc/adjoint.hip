@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kAdjThreads) void adj_btcs_assemble_kernel(
     const InstDesc* __restrict__ inst, const AdjTile* __restrict__ tiles, const double* __restrict__ u,
     const double* __restrict__ lamp, double* __restrict__ LA, double* __restrict__ LC,
     double* __restrict__ LD, const int* __restrict__ only) {
-  if (only && only[-1] == 0) return;          // no window of this step failed
+  if (only && only[-1] == 0) return;          // every instance is within its windows' bound
   const AdjTile t = tiles[blockIdx.x];
   if (only && only[t.inst] == 0) return;      // this instance's windows held
   const InstDesc d = inst[t.inst];
@@ -327,20 +327,13 @@ __global__ __launch_bounds__(kAdjThreads) void adj_btcs_assemble_kernel(
   }
 }
 
-// lam = (1 - G) mu and the tile's partial -mu . (L x); boundary nodes get zero.  With windows (n_win > 0),
-// workgroup b first adds window b's partial (wpart) to the window's slot unless its instance was flagged,
-// and only the flagged instances' tiles are finished here.
+// lam = (1 - G) mu and the tile's partial -mu . (L x); boundary nodes get zero.
 __global__ __launch_bounds__(kAdjThreads) void adj_btcs_finish_kernel(
     const InstDesc* __restrict__ inst, const AdjTile* __restrict__ tiles, const double* __restrict__ u,
     const double* __restrict__ x, const double* __restrict__ X, double* __restrict__ lam,
-    double* __restrict__ gslot, const int* __restrict__ only, const WinDesc* __restrict__ wins, int64_t n_win,
-    const int32_t* __restrict__ win_slot, const double* __restrict__ wpart) {
+    double* __restrict__ gslot, const int* __restrict__ only) {
   __shared__ double red[kAdjThreads / 64];
-  if (static_cast<int64_t>(blockIdx.x) < n_win && threadIdx.x == 0) {
-    const int wi = wins[blockIdx.x].inst;
-    if (only[wi] == 0) gslot[win_slot[blockIdx.x]] = gslot[win_slot[blockIdx.x]] + wpart[blockIdx.x];
-  }
-  if (only && only[-1] == 0) return;          // no window of this step failed
+  if (only && only[-1] == 0) return;          // every instance is within its windows' bound
   const AdjTile t = tiles[blockIdx.x];
   if (only && only[t.inst] == 0) return;
   const InstDesc d = inst[t.inst];
@@ -428,12 +421,10 @@ hipError_t launch_adj_btcs_assemble(const burgers_ctx* ctx, const AdjTile* tiles
 
 hipError_t launch_adj_btcs_finish(const burgers_ctx* ctx, const AdjTile* tiles, int64_t n_tiles,
                                   const double* u, const double* x, const double* X, double* lam,
-                                  double* gslot, const int* only, const WinDesc* wins, int64_t n_win,
-                                  const int32_t* win_slot, const double* wpart) {
+                                  double* gslot, const int* only) {
   if (n_tiles <= 0) return hipSuccess;
-  if (n_win > n_tiles) return hipErrorInvalidValue;   // every window's partial needs a workgroup
   adj_btcs_finish_kernel<<<static_cast<unsigned>(n_tiles), kAdjThreads, 0, ctx->stream>>>(
-      ctx->inst.as<InstDesc>(), tiles, u, x, X, lam, gslot, only, wins, n_win, win_slot, wpart);
+      ctx->inst.as<InstDesc>(), tiles, u, x, X, lam, gslot, only);
   return hipGetLastError();
 }
 

@@ -664,230 +664,6 @@ __global__ __launch_bounds__(NT, MC == 16 ? 4 : 1) void newton_wg_kernel(const I
   else newton_solve<false, S, NT, MC>(pcr, stage, rows, xs, R, P, last != 0);
 }
 
-// Halo rows of the adjoint's truncated windows on either side.
-constexpr int kWinHalo = 256;
-
-// ---- Adjoint BTCS step on truncated windows of the transposed system -----------------------------
-// The discrete adjoint of a BTCS step (y = u^k -> x = u^{k+1}) solves A(y)^T mu = lam' and then sets
-// lam = (1 - G) mu with G_i = r (x_i - x_{i-1}) for y_i >= 0, r (x_{i+1} - x_i) otherwise, and adds
-// -mu . (2 x_i - x_{i-1} - x_{i+1}) to dJ/dD.  Row i of A^T couples mu_{i-1} with p_{i-1} (the
-// super-diagonal entry of row i-1 of A), mu_i with d_i and mu_{i+1} with l_{i+1}.
-//
-// A window of W rows solves those rows of A^T with the unknowns beyond its ends taken as zero, keeps the
-// rows at least kWinHalo inside, and finishes them in the same kernel.  The error of a kept row: the window
-// solution differs from the exact one by A_w^{-T} applied to the two dropped couplings times the exact
-// mu at the ghosts, i.e. |e_i| <= (A_w^{-1})_{f,i} |p_{s-1}| |mu| + (A_w^{-1})_{l,i} |l_{s+W}| |mu| for the
-// window's first and last rows f, l.  A_w is a strictly row-diagonally dominant M-matrix with row sums
-// >= 1, so A_w^{-1} >= 0 with row sums <= 1, and a column of A_w^{-1} decays from its diagonal like the
-// barrier of the forward windows: (A_w^{-1})_{f,i} <= theta^(i-f).  The couplings are at most D + C.  A
-// kept row is therefore within 2 (D + C) theta^(kWinHalo+1) max|mu| of the exact solution, and each
-// window checks (kWinHalo + 1) log2 theta + log2(D + C) <= -55 (error <= 2^-54 max|mu|).  A window that
-// fails flags its instance; the array path (assembled rows, partition levels, finish) then redoes that
-// instance's step.  The window writes its partial sum of dJ/dD (kept rows, fixed order) to wpart; the
-// finish launch adds it to the window's slot unless the instance was redone.
-struct AdjRows {
-  const double* ys;   // y of window row k at ys[padded(k + 1)], k = -1..W
-  double r, D;
-  DirichletEnds ends; // zero ghosts: the dropped couplings just vanish
-  __device__ __forceinline__ void row_value(double lamp, int k, int, double& al, double& be, double& ga,
-                                            double& de) const {
-    double t0, t1, t2, t3;
-    btcs_row(ys[padded(k)], r, D, t0, t1, al);       // p_{k-1}
-    btcs_row(ys[padded(k + 1)], r, D, t2, be, t3);   // d_k
-    btcs_row(ys[padded(k + 2)], r, D, ga, t0, t1);   // l_{k+1}
-    de = lamp;
-  }
-};
-
-// WHOLE: the window is a whole system of exactly W rows (start 0, every row kept), solved exactly: cyclic
-// for a periodic instance, no bound to check, and the system's partial of dJ/dD is added straight to its
-// slot (gslot[slots[b]]: one workgroup per slot, so the sums stay deterministic).  A whole system takes
-// the reverse steps k = k_hi - 1 down to k_lo in one launch (y = u^k and x = u^(k+1) at state(k), state(k
-// + 1)), keeping lam on chip between them: each step reads only the two states.  Its partial is added to
-// the slot after every step, in step order, as one launch per step would.  Windows take one step.
-template <int NT, bool WHOLE = false>
-__global__ __launch_bounds__(NT, 4) void adj_btcs_window_kernel(
-    const InstDesc* __restrict__ inst, const WinDesc* __restrict__ wins, const double* __restrict__ u0,
-    const double* __restrict__ useg, int64_t ustride, int k_lo, int k_hi, const double* __restrict__ lamp,
-    double* __restrict__ lam, double* __restrict__ wpart, int* __restrict__ flag_now, int* __restrict__ flag_next,
-    double* __restrict__ gslot = nullptr, const int32_t* __restrict__ slots = nullptr) {
-  using T = double;
-  constexpr int MC = kWgChunk, W = NT * MC;
-  using IS = InterfaceSpace<T, NT>;
-  constexpr int kStageBytes = padded_size(W + 2) * 8;
-  constexpr int kBytes = kStageBytes > IS::kBytes ? kStageBytes : IS::kBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
-  __shared__ uint64_t iface_votes[2 * IS::kVoteWords];
-  __shared__ T wave_val[NT / 64];
-  const IS iws{reinterpret_cast<T*>(smem), reinterpret_cast<T*>(smem) + 3 * NT, iface_votes};
-  iws.clear_votes();
-  T* stage = reinterpret_cast<T*>(smem);
-  const WinDesc wd = wins[blockIdx.x];
-  const InstDesc d = inst[wd.inst];
-  const bool dir = d.bc == kDirichlet;
-  const int first = dir ? 1 : 0;
-  const int R = dir ? d.n - 2 : d.n;           // > W
-  const int n = d.n;
-  const int tid = threadIdx.x;
-  // state k of the launch: u0 for k = 0, else useg + (k - 1) ustride (by node)
-  auto state = [&](int k) { return (k == 0 ? u0 : useg + static_cast<int64_t>(k - 1) * ustride) + d.off; };
-  // node of window row k (k = -1..W): periodic rows wrap; Dirichlet rows -1 and R are the end nodes
-  auto node_of = [&](int k) {
-    int row = wd.start + k;
-    if (!dir) {
-      if (row < 0) row += R;
-      if (row >= R) row -= R;
-    }
-    return row + first;
-  };
-  // lam' of the window's rows, row tid + q NT in de[q] (coalesced); between steps de carries lam in that
-  // layout
-  T de[MC];
-#pragma unroll
-  for (int j = 0; j < MC; ++j) de[j] = lamp[d.off + node_of(tid + j * NT)];
-  __shared__ T gacc;                           // the system's running slot value (WHOLE, thread 0)
-  if (WHOLE && tid == 0) gacc = gslot[slots[blockIdx.x]];
-  const int s = tid * MC;
-  // (a window takes the single step 0: constant bounds, so its body is not a loop)
-  const int step_hi = WHOLE ? k_hi - 1 : 0, step_lo = WHOLE ? k_lo : 0;
-  for (int step = step_hi; step >= step_lo; --step) {
-  const double* __restrict__ yn = state(step);
-  // lam' into the lanes' chunks (through LDS; the addresses are formed here at every step, not kept live)
-  {
-    const int lw = opaque_lane(tid);
-#pragma unroll
-    for (int j = 0; j < MC; ++j) stage[padded(lw + j * NT)] = de[j];
-    __syncthreads();
-    const int lr = opaque_lane(tid) * MC;
-#pragma unroll
-    for (int j = 0; j < MC; ++j) de[j] = stage[padded(lr + j)];
-    __syncthreads();
-  }
-  // y of rows -1..W (every load in flight at once), and max |y| over them; bit q of ypos: the upwind
-  // side of row tid + q NT (y >= 0), for the finish
-  T big = T(0);
-  unsigned ypos = 0;
-  {
-    const int lt = opaque_lane(tid);
-    T ge = T(0);
-    if (tid < 2) ge = yn[node_of(lt == 0 ? -1 : W)];
-#pragma unroll
-    for (int h = 0; h < MC; h += MC / 2) {     // (in two halves, so that lam' and the loads fit registers)
-      T v[MC / 2];
-#pragma unroll
-      for (int j = 0; j < MC / 2; ++j) v[j] = yn[node_of(lt + (h + j) * NT)];
-#pragma unroll
-      for (int j = 0; j < MC / 2; ++j) {
-        stage[padded(lt + (h + j) * NT + 1)] = v[j];
-        big = __builtin_fmax(big, __builtin_fabs(v[j]));
-        ypos |= (v[j] >= 0.0 ? 1u : 0u) << (h + j);
-      }
-    }
-    if (tid < 2) {
-      stage[padded(tid == 0 ? 0 : W + 1)] = ge;
-      big = __builtin_fmax(big, __builtin_fabs(ge));
-    }
-  }
-  ypos = static_cast<unsigned>(opaque_lane(static_cast<int>(ypos)));   // (formed here, not from y kept live)
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) big = __builtin_fmax(big, __shfl_xor(big, m, 64));
-  if ((tid & 63) == 0) wave_val[tid >> 6] = big;
-  __syncthreads();
-  if (!WHOLE && tid == 0) {
-    T M = T(0);
-#pragma unroll
-    for (int k = 0; k < NT / 64; ++k) M = __builtin_fmax(M, wave_val[k]);
-    const T C = d.r * M;
-    const T theta = 2.0 * (d.D + C) / ((1.0 + 2.0 * d.D + C) + __builtin_sqrt((1.0 + C) * (1.0 + C) + 4.0 * d.D));
-    const T coup = d.D + C;
-    flag_next[wd.inst] = 0;
-    flag_next[-1] = 0;
-    const bool ok = coup == 0.0 || theta == 0.0 ||
-                    (kWinHalo + 1) * log2(theta) + log2(coup) <= -55.0;
-    if (!ok) {
-      flag_now[wd.inst] = 1;
-      flag_now[-1] = 1;
-    }
-  }
-  T al[MC], ga[MC];
-  T ia = T(0), ib = T(1), ic = T(0), id = T(0);
-  // zero ghosts: a window is a plain system; a whole periodic system keeps its cyclic couplings
-  const AdjRows rows{stage, d.r, d.D, DirichletEnds{0.0, 0.0, WHOLE ? dir : true}};
-  interface_eliminate<T, MC, true>(rows, s, MC, W, al, ga, de, ia, ib, ic, id);
-  __syncthreads();                             // every row read: the interface LDS overlays the stage
-  T yv, yp;
-  interface_solve<T, NT>(iws, NT, al[0], ga[0], de[0], al[MC - 2], ga[MC - 2], de[MC - 2], ia, ib, ic, id, yv, yp);
-  __syncthreads();                             // the interface unknowns read before mu is written
-  // mu through the stage from the lanes' chunks to rows tid + q NT
-#pragma unroll
-  for (int j = 0; j < MC; ++j)
-    stage[padded(s + j)] = j < MC - 1 ? __builtin_fma(-ga[j], yv, __builtin_fma(-al[j], yp, de[j])) : yv;
-  __syncthreads();
-  const int lm = opaque_lane(tid);
-#pragma unroll
-  for (int q = 0; q < MC; ++q) de[q] = stage[padded(lm + q * NT)];
-  __syncthreads();                             // mu read: the stage takes x
-  // x = u^(k+1) of rows -1..W through the stage (every load in flight)
-  const double* __restrict__ xn = state(step + 1);
-  {
-    const int lt = opaque_lane(tid);
-    T ge = T(0);
-    if (tid < 2) ge = xn[node_of(lt == 0 ? -1 : W)];
-#pragma unroll
-    for (int h = 0; h < MC; h += MC / 2) {
-      T v[MC / 2];
-#pragma unroll
-      for (int j = 0; j < MC / 2; ++j) v[j] = xn[node_of(lt + (h + j) * NT)];
-#pragma unroll
-      for (int j = 0; j < MC / 2; ++j) stage[padded(lt + (h + j) * NT + 1)] = v[j];
-    }
-    if (tid < 2) stage[padded(tid == 0 ? 0 : W + 1)] = ge;
-  }
-  __syncthreads();
-  // finish the kept rows tid + q NT: lam = (1 - G) mu (into de[q]), and the lane's partial sum of
-  // -mu (2 x_j - x_{j-1} - x_{j+1}) in row order
-  T g = T(0);
-  const int lf = opaque_lane(tid);
-#pragma unroll
-  for (int q = 0; q < MC; ++q) {
-    const int k = lf + q * NT;
-    if (k < wd.lo || k >= wd.lo + wd.count) continue;
-    const int j = node_of(k);
-    const T mu = de[q];
-    const T xm = dir && j == 1 ? d.a : stage[padded(k)];
-    const T xp = dir && j == n - 2 ? d.b : stage[padded(k + 2)];
-    const T xj = stage[padded(k + 1)];
-    const T G = (ypos >> q) & 1u ? d.r * (xj - xm) : d.r * (xp - xj);
-    de[q] = (1.0 - G) * mu;
-    g = g - mu * ((2.0 * xj - xm) - xp);
-  }
-  // the window's partial, summed in a fixed order (the barrier also ends this step's reads of the stage)
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) g = g + __shfl_xor(g, m, 64);
-  if ((tid & 63) == 0) wave_val[tid >> 6] = g;
-  __syncthreads();
-  if (tid == 0) {
-    T tot = wave_val[0];
-#pragma unroll
-    for (int k = 1; k < NT / 64; ++k) tot = tot + wave_val[k];
-    if constexpr (WHOLE) gacc = gacc + tot;
-    else wpart[blockIdx.x] = tot;
-  }
-  }
-  // lam of the kept rows (coalesced stores); Dirichlet end nodes carry none
-  const int ls = opaque_lane(tid);
-#pragma unroll
-  for (int q = 0; q < MC; ++q) {
-    const int k = ls + q * NT;
-    if (k >= wd.lo && k < wd.lo + wd.count) lam[d.off + node_of(k)] = de[q];
-  }
-  if (dir && tid == 0) {
-    if (wd.start == 0) lam[d.off] = 0.0;
-    if (wd.start + W == R) lam[d.off + n - 1] = 0.0;
-  }
-  if (WHOLE && tid == 0) gslot[slots[blockIdx.x]] = gacc;
-}
-
 constexpr int kSpikeWaves = kReduceBlock / 64;
 
 // One row of a block's interface system in spike form: unit diagonal, couplings a (row i - s) and c
@@ -1590,28 +1366,6 @@ hipError_t launch_btcs_window_reset(const burgers_ctx* ctx, const BtcsPlan& plan
   if (plan.n_win == 0) return hipSuccess;
   const int64_t n = 2 * (ctx->count + 1);     // both parity slots, not the sticky words
   clear_flags_kernel<<<static_cast<unsigned>((n + 255) / 256), 256, 0, ctx->stream>>>(plan.win_flags.as<int>(), n);
-  return hipGetLastError();
-}
-
-int btcs_window_halo() { return kWinHalo; }
-
-hipError_t launch_adj_btcs_whole(const burgers_ctx* ctx, const WinDesc* wins, int64_t n, const double* u0,
-                                 const double* useg, int64_t ustride, int k_lo, int k_hi, const double* lamp,
-                                 double* lam, double* gslot, const int32_t* slots) {
-  if (n <= 0 || k_hi <= k_lo) return hipSuccess;
-  adj_btcs_window_kernel<kWholeRows / kWgChunk, true><<<static_cast<unsigned>(n), kWholeRows / kWgChunk, 0,
-                                                         ctx->stream>>>(ctx->inst.as<InstDesc>(), wins, u0, useg,
-                                                                        ustride, k_lo, k_hi, lamp, lam, nullptr,
-                                                                        nullptr, nullptr, gslot, slots);
-  return hipGetLastError();
-}
-
-hipError_t launch_adj_btcs_windows(const burgers_ctx* ctx, const WinDesc* wins, int64_t n_win, const double* u,
-                                   const double* x, const double* lamp, double* lam, double* wpart, int* flag_now,
-                                   int* flag_next) {
-  if (n_win <= 0) return hipSuccess;
-  adj_btcs_window_kernel<256><<<static_cast<unsigned>(n_win), 256, 0, ctx->stream>>>(
-      ctx->inst.as<InstDesc>(), wins, u, x, 0, 0, 1, lamp, lam, wpart, flag_now, flag_next);
   return hipGetLastError();
 }
 

@@ -43,17 +43,6 @@ bool explicit_windows(int32_t i, int32_t n, bool periodic, int depth, bool rk4, 
   return true;
 }
 
-void btcs_windows(int32_t i, int32_t R, bool periodic, int W, std::vector<WinDesc>& out) {
-  const int64_t halo = btcs_window_halo(), kept = W - 2 * halo;
-  for (int64_t lo = 0; lo < R; lo += kept) {
-    const int64_t hi = std::min<int64_t>(R, lo + kept);
-    const int64_t start =
-        periodic ? ((lo - halo) % R + R) % R : std::min<int64_t>(std::max<int64_t>(lo - halo, 0), R - W);
-    const int64_t rel = periodic ? halo : lo - start;
-    out.push_back(WinDesc{i, static_cast<int32_t>(start), static_cast<int32_t>(rel), static_cast<int32_t>(hi - lo)});
-  }
-}
-
 }  // namespace burgers
 
 namespace {
@@ -929,28 +918,17 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
   std::vector<int64_t> sys_off(ctx->count, -1);
   for (int32_t i = 0; i < ctx->count; ++i) {
     const burgers_problem& p = ctx->probs[i];
-    if (p.scheme == BURGERS_BTCS) {
+    const int64_t R = p.bc == BURGERS_BC_PERIODIC ? p.n : p.n - 2;
+    if (p.scheme == BURGERS_BTCS && !burgers::btcs_solved_whole(R)) {
       sys_off[i] = sys_rows;
-      sys_rows += p.bc == BURGERS_BC_PERIODIC ? p.n : p.n - 2;
+      sys_rows += R;
     }
   }
   std::vector<std::tuple<int32_t, int64_t, int32_t>> roots;
   int64_t rows_used = sys_rows;
-  // every BTCS instance of exactly 16384 rows: each transposed system solved whole; otherwise windows of
-  // the transposed systems when every BTCS instance is longer than 8192 rows
-  bool whole = !ctx->set_btcs.empty();
-  for (int32_t i : ctx->set_btcs) {
-    const burgers_problem& p = ctx->probs[i];
-    whole = whole && (p.bc == BURGERS_BC_PERIODIC ? p.n : p.n - 2) == burgers::btcs_whole_capacity();
-  }
-  bool windows = false;
-  for (int32_t i : ctx->set_btcs) {
-    const burgers_problem& p = ctx->probs[i];
-    windows = !whole && (p.bc == BURGERS_BC_PERIODIC ? p.n : p.n - 2) > burgers::btcs_wg_capacity();
-    if (!windows) break;
-  }
-  std::vector<burgers::WinDesc> wins, wholes;
-  std::vector<int32_t> win_slot, whole_slot;
+  std::vector<burgers::ChunkWin> deep;
+  std::vector<int32_t> windowed, longs;
+  std::map<std::pair<int, int>, std::vector<SysDesc>> wholes, beyond;
   for (int32_t i = 0; i < ctx->count; ++i) {
     const burgers_problem& p = ctx->probs[i];
     const int32_t n = static_cast<int32_t>(p.n);
@@ -973,20 +951,24 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
       slot += (n + G - 1) / G;
       continue;
     }
+    const bool windows = R > burgers::btcs_wg_capacity();
+    if (windows) {                             // one slot per chunk of 16 rows
+      burgers::btcs_deep_windows(i, R, p.bc == BURGERS_BC_PERIODIC, deep);
+      windowed.push_back(i);
+    }
+    if (burgers::btcs_solved_whole(R)) {       // one slot per lane
+      const burgers::WidthClass w = burgers::btcs_width_class(R, burgers::kResidentThreadsDefault);
+      const int32_t P = burgers::btcs_chunks(R, w.lanes);
+      (windows ? beyond : wholes)[{w.lanes, w.chunk}].push_back(SysDesc{0, -1, R, P, i, 0});
+      slot += P;                               // (1024 lanes: as many as a window's chunks or more)
+      continue;
+    }
+    const int32_t tile_slot = slot + (R + 15) / 16;
+    slot = tile_slot;
+    longs.push_back(i);
     for (int64_t s = 0; s < n; s += btcs_tile)
       bt.push_back(burgers::AdjTile{ctx->offsets[i], sys_off[i], n, p.bc, i, static_cast<int32_t>(s), slot++, 0});
-    {
-      roots.emplace_back(i, sys_off[i], R);
-      if (windows) {
-        const size_t w0 = wins.size();
-        burgers::btcs_windows(i, R, p.bc == BURGERS_BC_PERIODIC, 4096, wins);
-        for (size_t w = w0; w < wins.size(); ++w) win_slot.push_back(slot++);
-      }
-      if (whole) {
-        wholes.push_back(burgers::WinDesc{i, 0, 0, R});
-        whole_slot.push_back(slot++);
-      }
-    }
+    roots.emplace_back(i, sys_off[i], R);
   }
   slot_begin[ctx->count] = slot;
   hipError_t e;
@@ -1006,23 +988,41 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
   ap->n_exp_wins = static_cast<int64_t>(ew.size());
   ap->n_btcs_tiles = static_cast<int64_t>(bt.size());
   ap->n_slots = slot;
-  ap->whole = std::make_unique<DevBuf>();
-  ap->whole_slot = std::make_unique<DevBuf>();
-  if ((e = upload_on(ctx->stream, *ap->whole, wholes)) != hipSuccess ||
-      (e = upload_on(ctx->stream, *ap->whole_slot, whole_slot)) != hipSuccess)
+  auto upload_whole = [&](std::map<std::pair<int, int>, std::vector<SysDesc>>& groups,
+                          std::vector<burgers::WgGroup>& out) -> hipError_t {
+    for (auto& kv : groups) {
+      burgers::WgGroup g;
+      g.shape = burgers::WidthClass{kv.first.first, kv.first.second};
+      g.sys = std::make_unique<DevBuf>();
+      g.n = static_cast<int32_t>(kv.second.size());
+      const hipError_t err = upload_on(ctx->stream, *g.sys, kv.second);
+      if (err != hipSuccess) return err;
+      out.push_back(std::move(g));
+    }
+    return hipSuccess;
+  };
+  if ((e = upload_whole(wholes, ap->whole)) != hipSuccess || (e = upload_whole(beyond, ap->whole_beyond)) != hipSuccess)
     return from_hip(e);
-  ap->n_whole = static_cast<int64_t>(wholes.size());
-  ap->win = std::make_unique<DevBuf>();
-  ap->win_slot = std::make_unique<DevBuf>();
-  if ((e = upload_on(ctx->stream, *ap->win, wins)) != hipSuccess ||
-      (e = upload_on(ctx->stream, *ap->win_slot, win_slot)) != hipSuccess)
-    return from_hip(e);
-  ap->n_win = static_cast<int64_t>(wins.size());
-  if (ap->n_win > ap->n_btcs_tiles) return BURGERS_E_UNSUPPORTED;   // (tiles of 1024 nodes outnumber windows)
-  if (ap->n_win > 0 && ((e = ap->wpart.alloc(static_cast<size_t>(ap->n_win) * sizeof(double), ctx->stream)) != hipSuccess ||
-                        (e = ap->flags.alloc(static_cast<size_t>(burgers::win_flags_words(ctx->count)) * sizeof(int),
-                                                          ctx->stream)) != hipSuccess))
-    return from_hip(e);
+  ap->long_copy = std::make_unique<DevBuf>();
+  const auto lc = stream_tiles(ctx, longs);
+  if ((e = upload_on(ctx->stream, *ap->long_copy, lc)) != hipSuccess) return from_hip(e);
+  ap->n_long_copy = static_cast<int64_t>(lc.size());
+  if (!deep.empty()) {
+    burgers::BtcsPlan& w = ap->windows;
+    const int64_t words = burgers::deep_words(ctx->count);
+    w.transposed = true;
+    w.deep = std::make_unique<DevBuf>();
+    w.deep_inst = std::make_unique<DevBuf>();
+    if ((e = upload_on(ctx->stream, *w.deep, deep)) != hipSuccess ||
+        (e = upload_on(ctx->stream, *w.deep_inst, windowed)) != hipSuccess ||
+        (e = w.deep_words.alloc(static_cast<size_t>(words) * sizeof(int), ctx->stream)) != hipSuccess ||
+        (e = w.win_flags.alloc(static_cast<size_t>(burgers::win_flags_words(ctx->count)) * sizeof(int), ctx->stream)) !=
+            hipSuccess ||
+        (e = burgers::launch_clear_ints(ctx, w.deep_words.as<int>(), words)) != hipSuccess)
+      return from_hip(e);
+    w.n_deep = static_cast<int64_t>(deep.size());
+    w.n_deep_inst = static_cast<int64_t>(windowed.size());
+  }
   if ((e = build_array_solve(ctx, roots, ap->solve, rows_used)) != hipSuccess) return from_hip(e);
   const size_t lb = static_cast<size_t>(rows_used) * sizeof(double);
   if ((e = ap->LA.alloc(lb, ctx->stream)) != hipSuccess || (e = ap->LC.alloc(lb, ctx->stream)) != hipSuccess ||
@@ -1038,27 +1038,12 @@ hipError_t grow(DevBuf& b, size_t bytes, hipStream_t stream) {
   return b.alloc(bytes, stream);
 }
 
-// One adjoint step of the BTCS instances: lam_out from lam_in at the forward pair (y = u^k, x = u^{k+1});
-// `step` counts the BTCS steps of the reverse sweep (it selects the parity slot of the window flags).
+// One adjoint step of the BTCS instances of more than 16384 rows that are beyond their windows' bound: lam_out from
+// lam_in at the forward pair (y = u^k, x = u^{k+1}).
 hipError_t enqueue_adjoint_step(burgers_ctx* ctx, const double* y, const double* x, const double* lam_in,
-                                double* lam_out, int64_t step) {
+                                double* lam_out, const int* only) {
   burgers::AdjointPlan& ap = *ctx->adjoint;
-  double* g = ap.gslot.as<double>();
-  hipError_t e = hipSuccess;
-  if (ap.n_btcs_tiles == 0) return e;
-  if (ap.n_whole > 0)   // every BTCS system solved whole and exactly: nothing is left for the array path
-    return burgers::launch_adj_btcs_whole(ctx, ap.whole->as<burgers::WinDesc>(), ap.n_whole, y, x, 0, 0, 1, lam_in,
-                                          lam_out,
-                                          g, ap.whole_slot->as<int32_t>());
-  const int* only = nullptr;
-  if (ap.n_win > 0) {
-    int* now = burgers::win_flag_slot(ap.flags.as<int>(), ctx->count, step);
-    int* next = burgers::win_flag_slot(ap.flags.as<int>(), ctx->count, step + 1);
-    if ((e = burgers::launch_adj_btcs_windows(ctx, ap.win->as<burgers::WinDesc>(), ap.n_win, y, x, lam_in, lam_out,
-                                              ap.wpart.as<double>(), now, next)) != hipSuccess)
-      return e;
-    only = now;
-  }
+  hipError_t e;
   if ((e = burgers::launch_adj_btcs_assemble(ctx, ap.btcs_tiles->as<burgers::AdjTile>(), ap.n_btcs_tiles, y,
                                              lam_in, ap.LA.as<double>(), ap.LC.as<double>(),
                                              ap.LD.as<double>(), only)) != hipSuccess)
@@ -1067,8 +1052,7 @@ hipError_t enqueue_adjoint_step(burgers_ctx* ctx, const double* y, const double*
                                        ap.LX.as<double>(), only)) != hipSuccess)
     return e;
   return burgers::launch_adj_btcs_finish(ctx, ap.btcs_tiles->as<burgers::AdjTile>(), ap.n_btcs_tiles, y, x,
-                                         ap.LX.as<double>(), lam_out, g, only, ap.win->as<burgers::WinDesc>(),
-                                         ap.n_win, ap.win_slot->as<int32_t>(), ap.wpart.as<double>());
+                                         ap.LX.as<double>(), lam_out, ap.gslot.as<double>(), only);
 }
 
 // A context for `count` problems on the current device: validated, laid out, its workspace allocated
@@ -1419,9 +1403,10 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
   double* lam_e_next = lam_next;
   if ((e = hipMemcpyAsync(lam, lambda_T, state_bytes, d2d, ctx->stream)) != hipSuccess ||
       (e = burgers::launch_fill(ctx, ap.gslot.as<double>(), ap.n_slots, 0.0)) != hipSuccess ||
-      (ap.n_win > 0 && (e = burgers::launch_clear_ints(ctx, ap.flags.as<int>(), 2 * (ctx->count + 1))) != hipSuccess))
+      (ap.windows.n_deep > 0 && (e = burgers::launch_btcs_bound(ctx, ap.windows, u0, nullptr)) != hipSuccess))
     return note(ctx, e);
-  int64_t rstep = 0;
+  const int* code = ap.windows.n_deep > 0 ? burgers::deep_code(ap.windows.deep_words.as<int>(), ctx->count) : nullptr;
+  const int* beyond = ap.windows.n_deep > 0 ? burgers::win_flag_slot(ap.windows.win_flags.as<int>(), ctx->count, 0) : nullptr;
   // State k of segment c: the checkpoint for k = 0, else slot k - 1 of the segment's buffer.
   auto at = [&](int64_t c, DevBuf& seg, int64_t k) { return k == 0 ? state(ap.ckpt, c) : state(seg, k - 1); };
   // A segment's states are recomputed out of place.  Instances that the forward sweep keeps on chip are
@@ -1462,69 +1447,70 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
     }
     return err;
   };
-  // Segment c's reverse steps run on the context's stream while segment c - 1 is recomputed into the
-  // other segment buffer on a side stream (the recompute uses none of the reverse steps' buffers): both
-  // are HBM-bound chains of short launches, which fill each other's gaps.  The side stream starts after
-  // the previous segment's reverse steps (which read the buffer it overwrites) and the context's stream
-  // waits for it before the next segment's reverse steps.
-  if (ncp > 1) {
-    if (!ctx->side[0] && (e = hipStreamCreateWithFlags(&ctx->side[0], hipStreamNonBlocking)) != hipSuccess)
-      return note(ctx, e);
-    if (!ctx->joined[0] && (e = hipEventCreateWithFlags(&ctx->joined[0], hipEventDisableTiming)) != hipSuccess)
-      return note(ctx, e);
-    if (!ctx->forked && (e = hipEventCreateWithFlags(&ctx->forked, hipEventDisableTiming)) != hipSuccess)
-      return note(ctx, e);
-  }
+  // Segment c's reverse steps run beside the recompute of segment c - 1 into the other segment buffer (which uses
+  // none of the reverse steps' buffers), and beside each other by class, as chains of one set of tasks: the
+  // recompute begins after the previous segment's reverse steps (which read the buffer it overwrites), and the next
+  // segment's reverse steps after both.
   DevBuf* segs[2] = {&ap.seg, &ap.seg2};
   if (ncp > 0 && (e = recompute(ncp - 1, ap.seg)) != hipSuccess) return note(ctx, e);
   for (int64_t c = ncp - 1; c >= 0; --c) {
     const int64_t len = std::min(K, nsteps - c * K);
     DevBuf& cur = *segs[(ncp - 1 - c) & 1];
-    if (c > 0) {   // fork: recompute the next segment beside this one's reverse steps
-      hipStream_t main = ctx->stream;
-      e = hipEventRecord(ctx->forked, main);
-      if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side[0], ctx->forked, 0);
-      if (e == hipSuccess) {
-        ctx->stream = ctx->side[0];
-        e = recompute(c - 1, *segs[(ncp - c) & 1]);
-        ctx->stream = main;
-      }
-      if (e == hipSuccess) e = hipEventRecord(ctx->joined[0], ctx->side[0]);
-      if (e != hipSuccess) return note(ctx, e);
-    }
+    const double* y0 = reinterpret_cast<const double*>(at(c, cur, 0));
+    const double* y1 = reinterpret_cast<const double*>(at(c, cur, 1));
+    double* gslot = ap.gslot.as<double>();
+    std::vector<burgers::Task> tasks;
+    // (a state's share of the time: the recompute and the reverse steps are of one order, and both long)
+    const double us = static_cast<double>(len) * (2.0 + static_cast<double>(ctx->total) / 1e6);
+    if (c > 0) tasks.push_back({us, 2, [&, c]() { return recompute(c - 1, *segs[(ncp - c) & 1]); }});
     // explicit instances: equal runs of up to kAdjRun reverse steps per launch, lam on chip (out of place)
     const int64_t runs = (len + burgers::kAdjRun - 1) / burgers::kAdjRun;
     const int64_t run = ((len + runs - 1) / runs + burgers::kAdjGroup - 1) / burgers::kAdjGroup * burgers::kAdjGroup;
-    for (int64_t hi = len; ap.n_exp_wins > 0 && hi > 0;) {
-      const int64_t lo = (hi - 1) / run * run;
-      if ((e = burgers::launch_adj_explicit(ctx, ap.exp_wins->as<burgers::AdjWindow>(), ap.n_exp_wins, ap.n_exp_inner,
-                                            reinterpret_cast<const double*>(at(c, cur, 0)),
-                                            reinterpret_cast<const double*>(at(c, cur, 1)), ctx->total,
-                                            static_cast<int>(lo), static_cast<int>(hi), lam_e, lam_e_next,
-                                            ap.gslot.as<double>())) != hipSuccess)
-        return note(ctx, e);
-      std::swap(lam_e, lam_e_next);
-      hi = lo;
-    }
-    // BTCS instances: the segment's reverse steps in one launch when every system is solved whole (lam
-    // on chip between them), else one reverse step per launch
-    if (ap.n_whole > 0) {
-      if ((e = burgers::launch_adj_btcs_whole(ctx, ap.whole->as<burgers::WinDesc>(), ap.n_whole,
-                                              reinterpret_cast<const double*>(at(c, cur, 0)),
-                                              reinterpret_cast<const double*>(at(c, cur, 1)), ctx->total, 0,
-                                              static_cast<int>(len), lam, lam_next, ap.gslot.as<double>(),
-                                              ap.whole_slot->as<int32_t>())) != hipSuccess)
-        return note(ctx, e);
-      std::swap(lam, lam_next);
-    }
-    for (int64_t k = len - 1; ap.n_btcs_tiles > 0 && ap.n_whole == 0 && k >= 0; --k) {
-      if ((e = enqueue_adjoint_step(ctx, reinterpret_cast<const double*>(at(c, cur, k)),
-                                    reinterpret_cast<const double*>(at(c, cur, k + 1)), lam, lam_next,
-                                    rstep++)) != hipSuccess)
-        return note(ctx, e);
-      std::swap(lam, lam_next);
-    }
-    if (c > 0 && (e = hipStreamWaitEvent(ctx->stream, ctx->joined[0], 0)) != hipSuccess) return note(ctx, e);   // join
+    if (ap.n_exp_wins > 0)
+      tasks.push_back({us, runs, [&]() -> hipError_t {
+        for (int64_t hi = len; hi > 0;) {
+          const int64_t lo = (hi - 1) / run * run;
+          const hipError_t err = burgers::launch_adj_explicit(
+              ctx, ap.exp_wins->as<burgers::AdjWindow>(), ap.n_exp_wins, ap.n_exp_inner, y0, y1, ctx->total,
+              static_cast<int>(lo), static_cast<int>(hi), lam_e, lam_e_next, gslot);
+          if (err != hipSuccess) return err;
+          std::swap(lam_e, lam_e_next);
+          hi = lo;
+        }
+        return hipSuccess;
+      }});
+    // BTCS instances, from lam to lam_next: the segment's steps in one launch where the system is solved whole, in
+    // launches of several steps on windows, and one step at a time on the array path
+    for (const burgers::WgGroup& g : ap.whole)
+      tasks.push_back({us, 1, [&]() {
+        return burgers::launch_adj_btcs_whole(ctx, g, ap.slot_begin->as<int32_t>(), y0, y1, ctx->total, 0,
+                                              static_cast<int>(len), lam, lam_next, gslot);
+      }});
+    if (ap.windows.n_deep > 0)
+      tasks.push_back({us, len / 3 + 1, [&]() {
+        return burgers::launch_adj_btcs_deep(ctx, ap.windows, ap.slot_begin->as<int32_t>(), y0, y1, ctx->total,
+                                             static_cast<int>(len), lam, lam_next, gslot);
+      }});
+    for (const burgers::WgGroup& g : ap.whole_beyond)   // (mostly idle)
+      tasks.push_back({5.0, 1, [&]() {
+        return burgers::launch_adj_btcs_whole(ctx, g, ap.slot_begin->as<int32_t>(), y0, y1, ctx->total, 0,
+                                              static_cast<int>(len), lam, lam_next, gslot, code);
+      }});
+    if (ap.n_btcs_tiles > 0)
+      tasks.push_back({us + 20.0 * static_cast<double>(len), 6 * len, [&]() -> hipError_t {
+        double* in = lam;
+        double* out = lam_next;
+        for (int64_t k = len - 1; k >= 0; --k) {
+          const hipError_t err = enqueue_adjoint_step(ctx, reinterpret_cast<const double*>(at(c, cur, k)),
+                                                      reinterpret_cast<const double*>(at(c, cur, k + 1)), in, out, beyond);
+          if (err != hipSuccess) return err;
+          std::swap(in, out);
+        }
+        if (in == lam_next) return hipSuccess;
+        return burgers::launch_copy_tiles(ctx, ap.long_copy->as<Tile>(), ap.n_long_copy, in, lam_next, beyond);
+      }});
+    if ((e = burgers::run_tasks(ctx, tasks, false)) != hipSuccess) return note(ctx, e);
+    if (!ctx->set_btcs.empty()) std::swap(lam, lam_next);
   }
   const bool split = lam_e != lam && !ctx->set_explicit.empty() && !ctx->set_btcs.empty();
   if ((e = ensure_copy(ctx, split ? kSetExplicit : kSetAll)) != hipSuccess ||

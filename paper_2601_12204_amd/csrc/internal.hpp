@@ -103,15 +103,6 @@ struct SysDesc {
   int32_t limit = 0;  // > 0: the on-chip solver advances at most this many of the launch's steps
 };
 
-// A window of a long transposed BTCS system (adjoint): rows [start, start + W) of the system (mod its row
-// count for periodic systems) are solved as a plain system; rows [start + lo, start + lo + count) are kept.
-struct WinDesc {
-  int32_t inst;
-  int32_t start;
-  int32_t lo;
-  int32_t count;
-};
-
 // A window of a long BTCS or Crank-Nicolson system (window.hip): `chunks` chunks of the system from `first` on
 // (mod its chunk count for periodic systems), of which `count` from the window's `lo` on are written to the
 // new state.
@@ -247,6 +238,7 @@ struct BtcsPlan {
   std::unique_ptr<DevBuf> deep, deep_inst;   // ChunkWin[], int32[] (the windowed instances)
   int64_t n_deep = 0, n_deep_inst = 0;
   DevBuf deep_words;                         // see deep_words()
+  bool transposed = false;                   // the windows solve the transposed systems (adjoint)
   bool stream_exact = false;                 // per-step exact 8192-row systems: the persistent pipelined kernel
   DevBuf win_flags;                          // win_flags_words(count) int32 (see win_flag_slot)
 };
@@ -287,15 +279,13 @@ struct AdjointPlan {
   BtcsPlan solve;                                   // partition hierarchy over the transposed systems
   DevBuf LA, LC, LD, LX, gslot;
   DevBuf ckpt, seg, seg2, lam0, lam1;               // grown on demand (seg2: the segment recomputed alongside)
-  // truncated windows of the transposed systems (when every BTCS instance has more than 8192 rows); the
-  // array path above is then the fallback of the instances whose windows flag a failed bound
-  std::unique_ptr<DevBuf> win, win_slot;           // WinDesc[], int32[] (dJ/dD slot of each window)
-  int64_t n_win = 0;
-  DevBuf wpart, flags;                              // double[n_win]; win_flags_words(count) int32
-  // every BTCS instance of exactly 16384 rows: each transposed system solved whole, exactly, by one
-  // workgroup per step (WinDesc covering it, and its dJ/dD slot); the array path is then not used
-  std::unique_ptr<DevBuf> whole, whole_slot;
-  int64_t n_whole = 0;
+  // systems of more than 8192 rows: windows of several steps of the transposed systems (`deep` alone).  Those beyond
+  // the windows' bound are solved whole (up to 16384 rows) or by the array path above
+  BtcsPlan windows;
+  // systems of up to 16384 rows: each transposed system solved whole, lam on chip for a segment's steps
+  std::vector<WgGroup> whole, whole_beyond;         // (the latter: those that have windows)
+  std::unique_ptr<DevBuf> long_copy;                // Tile[] of the longer ones
+  int64_t n_long_copy = 0;
 };
 
 // Fully implicit central-convection instances (Newton-Raphson, a fixed number of iterations per step):
@@ -373,8 +363,6 @@ hipError_t launch_explicit_record(const burgers_ctx* ctx, const BlockTile* tiles
 // Windows of a long explicit instance `i` of n nodes advanced `depth` steps per launch (halo = depth x
 // stages per side); appends them to `out`.  Returns false when the halo leaves no kept node.
 bool explicit_windows(int32_t i, int32_t n, bool periodic, int depth, bool rk4, std::vector<BlockTile>& out);
-// Truncated windows of `W` rows over a transposed BTCS system of R rows of instance i; appends them to `out`.
-void btcs_windows(int32_t i, int32_t R, bool periodic, int W, std::vector<WinDesc>& out);
 hipError_t launch_clear_ints(const burgers_ctx* ctx, int* p, int64_t n);
 // capi.hip: a chain of launches on the context's current stream with a rough time, independent of the others
 // of its list; run_tasks runs a list concurrently (or, `serial`, one after another).
@@ -403,15 +391,13 @@ int adjoint_tile_nodes();   // nodes per dJ/dD slot of a BTCS instance
 hipError_t launch_adj_explicit(const burgers_ctx* ctx, const AdjWindow* wins, int64_t n_wins, int64_t n_inner,
                                const double* u0, const double* useg, int64_t ustride, int k_lo, int k_hi,
                                const double* lamp, double* lam, double* gslot);
-// `only` (optional): only the instances whose entry is nonzero (those whose windows flagged a failed
-// bound); the finish launch also adds the windows' partials (wins/win_slot/wpart, n_win may be 0).
+// `only` (optional): only the instances whose entry is nonzero (those beyond their windows' bound).
 hipError_t launch_adj_btcs_assemble(const burgers_ctx* ctx, const AdjTile* tiles, int64_t n_tiles,
                                     const double* u, const double* lamp, double* LA, double* LC, double* LD,
                                     const int* only);
 hipError_t launch_adj_btcs_finish(const burgers_ctx* ctx, const AdjTile* tiles, int64_t n_tiles,
                                   const double* u, const double* x, const double* X, double* lam,
-                                  double* gslot, const int* only, const WinDesc* wins, int64_t n_win,
-                                  const int32_t* win_slot, const double* wpart);
+                                  double* gslot, const int* only);
 hipError_t launch_adj_nu(const burgers_ctx* ctx, const int32_t* slot_begin, const double* gslot,
                          double* grad_nu);
 hipError_t launch_fill(const burgers_ctx* ctx, double* p, int64_t n, double v);
@@ -459,7 +445,6 @@ hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const
 // nsteps (below 2^30) steps of plan.deep, the final states in u.
 hipError_t launch_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps);
 hipError_t launch_btcs_window_reset(const burgers_ctx* ctx, const BtcsPlan& plan);
-int btcs_window_halo();                 // halo rows on each side of a window's output rows
 hipError_t launch_btcs_resident(const burgers_ctx* ctx, const WgGroup& group, void* u, int steps);
 // The resident solver recording the state after each step k (1 <= k <= steps) at rec + (k - 1) rstride
 // (binary64; src is only read).
@@ -481,17 +466,18 @@ int btcs_chunks(int rows, int threads);
 // `only` (optional): solve only the systems of instances whose entry is nonzero.
 hipError_t launch_array_solve(const burgers_ctx* ctx, const BtcsPlan& plan, double* LA, double* LC,
                               double* LD, double* LX, const int* only = nullptr);
-// Adjoint BTCS steps k = k_hi - 1 .. k_lo of systems of exactly 16384 rows, each transposed system solved
-// whole (u^k at u0 for k = 0, else useg + (k - 1) ustride; lam^(k_hi) in lamp, lam^(k_lo) to lam, out of
-// place); each system's dJ/dD partial added to gslot[slots[b]] after every step.
-hipError_t launch_adj_btcs_whole(const burgers_ctx* ctx, const WinDesc* wins, int64_t n, const double* u0,
-                                 const double* useg, int64_t ustride, int k_lo, int k_hi, const double* lamp,
-                                 double* lam, double* gslot, const int32_t* slots);
-// Adjoint BTCS step of the long instances on truncated windows of the transposed system (lam from lamp
-// at the forward pair u -> x); per-window partials of dJ/dD into wpart; failed bounds flag instances.
-hipError_t launch_adj_btcs_windows(const burgers_ctx* ctx, const WinDesc* wins, int64_t n_win, const double* u,
-                                   const double* x, const double* lamp, double* lam, double* wpart, int* flag_now,
-                                   int* flag_next);
+// adjoint_btcs.hip.  Adjoint BTCS steps k = k_hi - 1 .. k_lo of a group's systems, each transposed system solved whole
+// (u^k at u0 for k = 0, else useg + (k - 1) ustride; lam^(k_hi) in lamp, lam^(k_lo) to lam, out of place); dJ/dD
+// added to the slots of the systems' chunks from slot_begin[instance] on.  `code` (optional): only the instances whose
+// entry is zero (those beyond their windows' bound).
+hipError_t launch_adj_btcs_whole(const burgers_ctx* ctx, const WgGroup& group, const int32_t* slot_begin,
+                                 const double* u0, const double* useg, int64_t ustride, int k_lo, int k_hi,
+                                 const double* lamp, double* lam, double* gslot, const int* code = nullptr);
+// A segment's `len` reverse steps on plan.deep's windows, from lam to lam_next (both overwritten), the instances' PCR
+// steps as launch_btcs_bound left them.
+hipError_t launch_adj_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, const int32_t* slot_begin,
+                                const double* u0, const double* useg, int64_t ustride, int len, double* lam,
+                                double* lam_next, double* gslot);
 constexpr int kResidentThreadsDefault = 512;
 
 }  // namespace burgers

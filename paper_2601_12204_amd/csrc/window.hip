@@ -38,29 +38,29 @@
 #include "internal.hpp"
 #include "staging.hpp"
 #include "stencil.hpp"
+#include "windows.hpp"
 
 #pragma clang fp contract(off)
 
 namespace burgers {
 namespace {
 
-constexpr int kM = 16;             // rows (slots) of a chunk
-constexpr int kMaxS = 4;           // PCR steps of a window's solve at most
-constexpr int kDeepLanes = 512;
-// Chunks lost at either end of a window over a launch of several steps: with S = 3, the usual case at ten
-// times the CFL step, 8 steps a launch.  One grid of 2^24 rows, us per step (384, 416, 448 of 512 chunks kept):
-// see kDeepHalo in the table of launch_btcs_deep.
-constexpr int kDeepHalo = 48;
+constexpr int kM = kChunkRows;
+constexpr int kMaxS = kMaxPcr;
 constexpr int kStepHalo = 1 << kMaxS;
 
 // The largest theta for S PCR steps, theta^(n_S) <= 2^-56, with slack for rounding (its own evaluation and
 // the growth of max|u| by rounding over a call's steps).
 struct ThetaLimits {
-  double of[kMaxS];   // S = 1 .. kMaxS
+  double of[kMaxS];     // S = 1 .. kMaxS
+  double rows[kMaxS];   // n_S
 };
 ThetaLimits theta_limits() {
   ThetaLimits t;
-  for (int s = 1; s <= kMaxS; ++s) t.of[s - 1] = std::exp2(-56.0 / (s < 4 ? 15 << s : 241)) * (1.0 - 1e-9);
+  for (int s = 1; s <= kMaxS; ++s) {
+    t.rows[s - 1] = s < 4 ? 15 << s : 241;
+    t.of[s - 1] = std::exp2(-56.0 / t.rows[s - 1]) * (1.0 - 1e-9);
+  }
   return t;
 }
 
@@ -73,84 +73,6 @@ __device__ __forceinline__ double theta_bound(const InstDesc& d, double M) {
 __device__ __forceinline__ void take_max(double v, double& big) {
   const double a = __builtin_fabs(v);
   big = __builtin_fmax(big, a == a ? a : __builtin_inf());
-}
-
-// Chunks of a system of R rows: P of them, the first rho of 16 rows and the others of 15 (R > 16384).
-struct Chunks {
-  int R, P, rho;
-  __device__ __forceinline__ explicit Chunks(int rows) : R(rows), P((rows + kM - 1) / kM), rho(rows - (kM - 1) * P) {}
-  __device__ __forceinline__ int base(int c) const { return (kM - 1) * c + (c < rho ? c : rho); }
-  // rows of the run of n chunks from c on (c < P; the run may pass the end of a periodic system)
-  __device__ __forceinline__ int rows(int c, int n) const {
-    const int e = c + n;
-    return e <= P ? base(e) - base(c) : R - base(c) + base(e - P);
-  }
-};
-
-// Interface solve of a window of L chunks, lane t < L holding chunk t (see interface_solve; the first chunk has
-// no coupling to its left, the last none to its right).  A partner beyond the ends is replaced by the end
-// chunk: its coefficient is zero there.
-template <int NT>
-__device__ __forceinline__ void window_solve(const InterfaceSpace<double, NT>& w, int L, int S, bool own, double al0,
-                                             double ga0, double de0, double alL, double gaL, double deL, double ia,
-                                             double ib, double ic, double id, double& y, double& yp) {
-  const int t = threadIdx.x;
-  constexpr int kV = InterfaceSpace<double, NT>::kVoteWords;
-  if (own) {
-    w.xchg[t] = al0;
-    w.xchg[NT + t] = ga0;
-    w.xchg[2 * NT + t] = de0;
-  }
-  __syncthreads();
-  double a = 0.0, c = 0.0, d = 0.0;
-  bool live = false;
-  if (own) {
-    const int n = t + 1 < L ? t + 1 : t;
-    const double nal = w.xchg[n], nga = w.xchg[NT + n], nde = w.xchg[2 * NT + n];
-    const double inv = recip(__builtin_fma(-ic, nal, __builtin_fma(-ia, gaL, ib)));
-    a = -(ia * alL) * inv;
-    c = -(ic * nga) * inv;
-    d = __builtin_fma(-ic, nde, __builtin_fma(-ia, deL, id)) * inv;
-    live = (__builtin_fabs(a) + __builtin_fabs(c)) > kNegligible;
-    a = live ? a : 0.0;
-    c = live ? c : 0.0;
-    w.rows[t] = a;
-    w.rows[NT + t] = c;
-    w.rows[2 * NT + t] = d;
-  }
-  __syncthreads();
-  int b = 0;
-  bool done = false;
-  for (int i = 0; i < S && !done; ++i) {
-    const double* A = w.rows + b * 3 * NT;
-    const double* C = A + NT;
-    const double* D = C + NT;
-    if (own) {
-      if (live) {
-        const int s = 1 << i;
-        const int mi = t >= s ? t - s : 0, pi = t + s < L ? t + s : L - 1;
-        pcr_combine(a, c, d, A[mi], C[mi], D[mi], A[pi], C[pi], D[pi], a, c, d);
-        live = (__builtin_fabs(a) + __builtin_fabs(c)) > kNegligible;
-        a = live ? a : 0.0;
-        c = live ? c : 0.0;
-      }
-      double* nA = w.rows + (1 - b) * 3 * NT;
-      nA[t] = a;
-      nA[NT + t] = c;
-      nA[2 * NT + t] = d;
-    }
-    const bool wave_live = __ballot(live) != 0;
-    if ((t & 63) == 0) reinterpret_cast<unsigned char*>(w.votes + (1 - b) * kV)[t >> 6] = wave_live ? 1 : 0;
-    __syncthreads();
-    b = 1 - b;
-    uint64_t any = 0;
-#pragma unroll
-    for (int k = 0; k < kV; ++k) any |= w.votes[b * kV + k];
-    done = any == 0;
-  }
-  // (couplings left after S steps are dropped: at most theta^(n_S))
-  y = d;
-  yp = own ? w.rows[b * 3 * NT + 2 * NT + (t > 0 ? t - 1 : 0)] : 0.0;
 }
 
 // LDS of a window: its rows staged between HBM and the lanes, overlaid by the interface solve.
@@ -321,17 +243,10 @@ __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
   window_ends<S>(f, w, d, out);
 }
 
-// Steps of a call that launch `launch` takes on an instance with `pcr` PCR steps per solve, after `done`.
-__device__ __forceinline__ int deep_steps(const ChunkWin& w, int pcr, int launch, int nsteps, int& done) {
-  const int per = kDeepHalo >> pcr, total = w.limit > 0 && w.limit < nsteps ? w.limit : nsteps;
-  done = launch * per;
-  return done >= total ? 0 : (total - done < per ? total - done : per);
-}
-
 // Up to kDeepHalo / 2^S steps of each window with the rows on chip, S of its instance (code; 0: the instance
 // is left to the partition levels).  A launch beyond an instance's last step does nothing for it.
 //
-// Bound by vector issue like the whole systems on chip (whole.hip), with 512 / (512 - 128) of the rows' work, and
+// Bound by vector issue like the whole systems on chip (whole.hip), with 512 / (512 - 2 kDeepHalo) of the rows' work, and
 // by the window's load and store once per launch, which the CU's other workgroup covers in part.
 template <typename S>
 __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
@@ -408,13 +323,14 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
 
 // Every windowed instance's PCR steps for a call from its bound, and the flags of those beyond it (flags[-1]:
 // any), which the partition levels take; `fresh` (a pool's): there are none, so a failed instance steps on and only
-// its sticky word says so, from the first tick of its slot's request (fresh) on.  Leaves `top` cleared for the next
+// its sticky word says so, from the first tick of its slot's request (fresh) on; `transposed`: the adjoint's bound.  Leaves `top` cleared for the next
 // call.
 __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __restrict__ inst,
                                                           const int32_t* __restrict__ members, int n,
                                                           unsigned long long* __restrict__ top, int* __restrict__ code,
                                                           int* __restrict__ flags, int* __restrict__ sticky,
-                                                          ThetaLimits lim, const int32_t* __restrict__ fresh) {
+                                                          ThetaLimits lim, const int32_t* __restrict__ fresh,
+                                                          int transposed) {
   const bool keep = fresh != nullptr;
   bool failed = false;
   for (int k = threadIdx.x; k < n; k += 256) {
@@ -423,10 +339,14 @@ __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __rest
     double M = __builtin_bit_cast(double, top[i]);
     top[i] = 0;
     if (d.bc == kDirichlet) M = __builtin_fmax(M, __builtin_fmax(__builtin_fabs(d.a), __builtin_fabs(d.b)));
-    const double theta = theta_bound(d, M);
+    const double theta = theta_bound(d, M), coupling = __builtin_fmax(d.D + d.r * M, 1.0);
     int s = 0;
 #pragma unroll
-    for (int q = kMaxS; q >= 1; --q) s = theta <= lim.of[q - 1] ? q : s;
+    for (int q = kMaxS; q >= 1; --q) {
+      bool holds = theta <= lim.of[q - 1];
+      if (transposed) holds = holds && (theta == 0.0 || lim.rows[q - 1] * log2(theta) + log2(coupling) <= -56.0);
+      s = holds ? q : s;
+    }
     if (s == 0) sticky[i] = 1;
     else if (keep && fresh[i]) sticky[i] = 0;
     failed = failed || s == 0;
@@ -515,7 +435,7 @@ hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const
                                                  top, deep_code(plan.deep_words.as<int>(), ctx->count),
                                                  win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0),
                                                  win_sticky(plan.win_flags.as<int>(), ctx->count), theta_limits(),
-                                                 fresh);
+                                                 fresh, plan.transposed ? 1 : 0);
   return hipGetLastError();
 }
 
