@@ -119,7 +119,14 @@ struct NodeWalk {
 // wave's region of LDS.
 __device__ __forceinline__ void window_fetch(const double* __restrict__ src, const AdjWindow& w, int n,
                                              double (&v)[kAdjChunk]) {
-  NodeWalk at(w, n, fresh_lane());
+  const int lane = fresh_lane();
+  if (w.first + kAdjWinNodes <= n) {           // (uniform) one address
+    const double* __restrict__ p = src + w.first;
+#pragma unroll
+    for (int i = 0; i < kAdjChunk; ++i) v[i] = p[lane + 64 * i];
+    return;
+  }
+  NodeWalk at(w, n, lane);
 #pragma unroll
   for (int i = 0; i < kAdjChunk; ++i) v[i] = src[at.next()];
 }
@@ -129,11 +136,11 @@ __device__ __forceinline__ void window_spread(const double (&v)[kAdjChunk], doub
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) region[apad(lane + 64 * i)] = v[8 * h + i];
+    for (int i = 0; i < 8; ++i) region[apad(lane) + 68 * i] = v[8 * h + i];   // (apad(lane + 64 i))
     wave_sync();
     if ((lane >> 5) == h) {
 #pragma unroll
-      for (int j = 0; j < kAdjChunk; ++j) out[j] = region[apad(kAdjChunk * (lane & 31) + j)];
+      for (int j = 0; j < kAdjChunk; ++j) out[j] = region[17 * (lane & 31) + j];   // (apad)
     }
     wave_sync();
   }
@@ -148,13 +155,13 @@ __device__ __forceinline__ void window_store(const double (&x)[kAdjChunk], const
   for (int h = 0; h < 2; ++h) {
     if ((lane >> 5) == h) {
 #pragma unroll
-      for (int j = 0; j < kAdjChunk; ++j) region[apad(kAdjChunk * (lane & 31) + j)] = x[j];
+      for (int j = 0; j < kAdjChunk; ++j) region[17 * (lane & 31) + j] = x[j];   // (apad)
     }
     wave_sync();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int k = 512 * h + lane + 64 * i, node = at.next();
-      const double v = region[apad(lane + 64 * i)];
+      const double v = region[apad(lane) + 68 * i];
       if (k >= w.lo && k < w.lo + w.count) dst[node] = v;
     }
     wave_sync();

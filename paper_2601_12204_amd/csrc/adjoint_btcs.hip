@@ -50,9 +50,9 @@ struct WholeLayout {
 };
 struct WindowLayout {
   Chunks ch;
-  int c0, L, first;
+  int R, c0, L, first;
   __device__ __forceinline__ WindowLayout(const InstDesc& d, const ChunkWin& w)
-      : ch(d.bc == kDirichlet ? d.n - 2 : d.n), c0(w.first), L(w.chunks), first(d.bc == kDirichlet ? 1 : 0) {}
+      : ch(d.bc == kDirichlet ? d.n - 2 : d.n), R(ch.R), c0(w.first), L(w.chunks), first(d.bc == kDirichlet ? 1 : 0) {}
   __device__ __forceinline__ int row(int t) const {
     const int c = c0 + t;
     return c >= ch.P ? ch.base(c - ch.P) + ch.R : ch.base(c);
@@ -75,7 +75,14 @@ __device__ __forceinline__ void fetch(const double* __restrict__ src, const Lay&
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int ta = t0 + 32 * h < lay.L ? t0 + 32 * h : lay.L, tb = ta + 32 < lay.L ? ta + 32 : lay.L;
-    const int ra = lay.row(ta), last = lay.row(tb) - 1;
+    const int ra = lay.row(ta), at = ra >= lay.R ? ra - lay.R : ra;
+    if (at + 64 * H <= lay.R) {                // (uniform) the rows from here on are there, whosever: one address
+      const double* __restrict__ p = src + lay.first + at;
+#pragma unroll
+      for (int i = 0; i < H; ++i) v[H * h + i] = p[lane + 64 * i];
+      continue;
+    }
+    const int last = lay.row(tb) - 1;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
       const int k = ra + lane + 64 * i;
@@ -93,12 +100,14 @@ __device__ __forceinline__ void spread(const double (&v)[2 * ((M + 1) / 2)], dou
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int i = 0; i < H; ++i) region[apad(lane + 64 * i)] = v[H * h + i];
+    for (int i = 0; i < H; ++i) region[apad(lane) + 68 * i] = v[H * h + i];   // (apad(lane + 64 i))
     wave_sync();
     if ((lane >> 5) == h && lt < lay.L) {
-      const int at = lay.row(lt) - lay.row(t0 + 32 * h), shift = lay.dummy(lt) ? 1 : 0;
+      const int at = lay.row(lt) - lay.row(t0 + 32 * h) - (lay.dummy(lt) ? 1 : 0);
+      const int low = at & 15, from = apad(at);
 #pragma unroll
-      for (int j = 0; j < M; ++j) out[j] = region[apad(j > 0 ? at - shift + j : at)];
+      for (int j = 0; j < M; ++j)              // (apad(at + j); slot 0's place may be the one before the region)
+        out[j] = region[j > 0 ? from + j + (low + j > 15 ? 1 : 0) : (at < 0 ? 0 : from)];
     }
     wave_sync();
   }
@@ -125,7 +134,7 @@ __device__ __forceinline__ void put_rows(const double (&x)[M], double* region, c
 #pragma unroll
     for (int i = 0; i < H; ++i) {
       const int k = ra + lane + 64 * i;
-      const double v = region[apad(lane + 64 * i)];
+      const double v = region[apad(lane) + 68 * i];   // (apad(lane + 64 i))
       if (k < rb && k >= lo && k < hi) dst[lay.node(k)] = v;
     }
     wave_sync();
@@ -188,11 +197,14 @@ __device__ __forceinline__ void reverse_steps(const AdjSpace<NT, MC>& ws, const 
   double xl, xr, yl, yr;
 #pragma unroll
   for (int j = 0; j < M; ++j) de[j] = X[j] = Y[j] = 0.0;
-  fetch<M>(lam_in, lay, V);
-  spread<M>(V, ws.region, lay, de);
-  fetch<M>(state(k_hi), lay, V);
-  spread<M>(V, ws.region, lay, X);
-  fetch<M>(state(k_hi - 1), lay, V);
+  {
+    double V0[2 * ((M + 1) / 2)], V1[2 * ((M + 1) / 2)];   // (all in flight at once)
+    fetch<M>(lam_in, lay, V0);
+    fetch<M>(state(k_hi), lay, V1);
+    fetch<M>(state(k_hi - 1), lay, V);
+    spread<M>(V0, ws.region, lay, de);
+    spread<M>(V1, ws.region, lay, X);
+  }
   neighbours<NT>(X, ws.ends, lay.L, l.own, l.dummy, xl, xr);
   wg_barrier<true>();                          // ends read before they are written again
   double g = slot ? *slot : 0.0;
@@ -298,7 +310,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void adj_btcs_whole_kernel(
                      AdjWholeRun<NT, MC>{ws, d, sys.rows, sys.chunks, u0, useg, lamp, ustride, k_lo, k_hi, lam, slot});
 }
 
-// Launch `launch` of a segment of `len` reverse steps on windows: kDeepHalo / 2^S steps with S of the window's instance
+// Launch `launch` of a segment of `len` reverse steps on windows: kAdjDeepHalo / 2^S steps with S of the window's instance
 // (0: left to other kernels), from lam[launch & 1] to the other.
 __global__ __launch_bounds__(kDeepLanes, 2) void adj_btcs_deep_kernel(
     const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const int* __restrict__ code,
@@ -319,7 +331,7 @@ __global__ __launch_bounds__(kDeepLanes, 2) void adj_btcs_deep_kernel(
   const int pcr = code[w.inst];
   if (pcr <= 0) return;
   int done;
-  const int steps = deep_steps(w, pcr, launch, len, done);
+  const int steps = deep_steps<kAdjDeepHalo>(w, pcr, launch, len, done);
   if (steps == 0) return;
   const InstDesc d = inst[w.inst];
   const bool dir = d.bc == kDirichlet;
@@ -347,7 +359,7 @@ __global__ __launch_bounds__(256) void adj_btcs_settle_kernel(const InstDesc* __
   const ChunkWin w = wins[blockIdx.x];
   const int pcr = code[w.inst];
   if (pcr <= 0) return;
-  const int per = kDeepHalo >> pcr;
+  const int per = kAdjDeepHalo >> pcr;
   if ((len + per - 1) / per & 1) return;
   const InstDesc d = inst[w.inst];
   const WindowLayout lay(d, w);
@@ -369,7 +381,7 @@ hipError_t launch_adj_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, co
   const ChunkWin* wins = plan.deep->as<ChunkWin>();
   const int* code = deep_code(plan.deep_words.as<int>(), ctx->count);
   const unsigned n = static_cast<unsigned>(plan.n_deep);
-  constexpr int kFewest = kDeepHalo >> kMaxPcr;
+  constexpr int kFewest = kAdjDeepHalo >> kMaxPcr;
   double* bufs[2] = {lam, lam_next};
   for (int j = 0; j < (len + kFewest - 1) / kFewest; ++j)
     adj_btcs_deep_kernel<<<n, kDeepLanes, 0, ctx->stream>>>(inst, wins, code, slot_begin, u0, useg, ustride, len, j,

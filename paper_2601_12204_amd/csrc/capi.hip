@@ -953,7 +953,7 @@ burgers_status ensure_adjoint(burgers_ctx* ctx) {
     }
     const bool windows = R > burgers::btcs_wg_capacity();
     if (windows) {                             // one slot per chunk of 16 rows
-      burgers::btcs_deep_windows(i, R, p.bc == BURGERS_BC_PERIODIC, deep);
+      burgers::btcs_deep_windows(i, R, p.bc == BURGERS_BC_PERIODIC, deep, true);
       windowed.push_back(i);
     }
     if (burgers::btcs_solved_whole(R)) {       // one slot per lane

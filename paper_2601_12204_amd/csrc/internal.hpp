@@ -431,7 +431,7 @@ hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, void
 // window.hip.  Windows of one step (`rows` of 4096 or 8192) and of several over a system of R > 16384 rows of
 // instance i, appended to `out`; how many of the latter cover any system of up to `rows` rows.
 void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, std::vector<ChunkWin>& out);
-void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out);
+void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out, bool adjoint = false);
 int64_t btcs_deep_windows_max(int64_t rows);
 // One step of plan.win from u to out (inst: half-dt coefficients for Crank-Nicolson systems); the instances with
 // a window beyond the bound are flagged in `now`, and `next` is cleared.

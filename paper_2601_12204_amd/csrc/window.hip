@@ -406,8 +406,8 @@ void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, s
   chunk_windows(i, R, periodic, rows / kM, kStepHalo, cn, out);
 }
 
-void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out) {
-  chunk_windows(i, R, periodic, kDeepLanes, kDeepHalo, false, out);
+void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out, bool adjoint) {
+  chunk_windows(i, R, periodic, kDeepLanes, adjoint ? kAdjDeepHalo : kDeepHalo, false, out);
 }
 
 int64_t btcs_deep_windows_max(int64_t rows) {

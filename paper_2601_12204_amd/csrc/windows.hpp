@@ -30,9 +30,14 @@ struct Chunks {
   }
 };
 
+// ... and over a launch of reverse steps (10 of them with S = 3), whose windows take longer to load: three states a
+// window of one workgroup per CU.  (256 x 16384 rows, us per reverse step: 48 chunks 21, 80: 18.)
+constexpr int kAdjDeepHalo = 80;
+
 // Steps of a call that launch `launch` takes on an instance with `pcr` PCR steps per solve, after `done`.
+template <int HALO = kDeepHalo>
 __device__ __forceinline__ int deep_steps(const ChunkWin& w, int pcr, int launch, int nsteps, int& done) {
-  const int per = kDeepHalo >> pcr, total = w.limit > 0 && w.limit < nsteps ? w.limit : nsteps;
+  const int per = HALO >> pcr, total = w.limit > 0 && w.limit < nsteps ? w.limit : nsteps;
   done = launch * per;
   return done >= total ? 0 : (total - done < per ? total - done : per);
 }
