@@ -166,6 +166,78 @@ struct NextChunk {
   T y;            // y_{t+1}
 };
 
+// A binary64 value of the lane at byte address `at` (4 x lane); of the lane before / after by a whole-wave DPP move
+// around the wave (CTRL 0x13C / 0x134).
+__device__ __forceinline__ double lane_value(double v, int at) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(at, static_cast<int>(b & 0xffffffffu)));
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(at, static_cast<int>(b >> 32)));
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double rotated(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const int l = static_cast<int>(b & 0xffffffffu), h = static_cast<int>(b >> 32);
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(l, l, CTRL, 0xf, 0xf, false));
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(h, h, CTRL, 0xf, 0xf, false));
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// interface_solve on one wave: the rows cross lanes by permutes (between neighbours of a full wave by DPP moves)
+// instead of LDS, and the stop vote is a ballot.  full: P = 64.  (us a step of one / 4096 systems, with the rows written
+// to LDS, waited for and read back and with the votes there: 101 rows 1.56 / 3.19, 200 rows 1.50 / 3.52, 500 rows
+// 1.44 / 3.77; this way 1.18 / 3.33, 0.95 / 3.08, 0.93 / 3.19.  As one body that tests `full` at each exchange: 1.37,
+// 1.32 and 1.22 for one system.)
+template <bool full>
+__device__ __forceinline__ void wave_interface_solve(int P, double al0, double ga0, double de0, double alL, double gaL,
+                                                     double deL, double ia, double ib, double ic, double id, double& y,
+                                                     double& yp, NextChunk<double>* next) {
+  const int t = static_cast<int>(threadIdx.x) & 63;
+  const bool own = full || t < P;
+  const int mask = 4 * (P - 1);
+  const int before = (4 * t - 4) & mask, after = (4 * t + 4) & mask;
+  double a = 0.0, c = 0.0, d = 0.0, nal, nga, nde;
+  if (full) {
+    nal = rotated<0x134>(al0);
+    nga = rotated<0x134>(ga0);
+    nde = rotated<0x134>(de0);
+  } else {
+    nal = lane_value(al0, after);
+    nga = lane_value(ga0, after);
+    nde = lane_value(de0, after);
+  }
+  if (next) {
+    next->al = nal;
+    next->ga = nga;
+    next->de = nde;
+  }
+  if (own) {
+    const double inv = recip(__builtin_fma(-ic, nal, __builtin_fma(-ia, gaL, ib)));
+    a = -(ia * alL) * inv;
+    c = -(ic * nga) * inv;
+    d = __builtin_fma(-ic, nde, __builtin_fma(-ia, deL, id)) * inv;
+  }
+  bool done = false;
+  auto combine = [&](double am, double cm, double dm, double ap, double cp, double dp) {
+    bool live = false;
+    if (own) {
+      pcr_combine(a, c, d, am, cm, dm, ap, cp, dp, a, c, d);
+      live = (__builtin_fabs(a) + __builtin_fabs(c)) > kNegligible;
+    }
+    done = __ballot(live) == 0;
+  };
+  if constexpr (full)
+    combine(rotated<0x13C>(a), rotated<0x13C>(c), rotated<0x13C>(d), rotated<0x134>(a), rotated<0x134>(c), rotated<0x134>(d));
+  for (int s = full ? 2 : 1; s < P && !done; s <<= 1) {
+    const int mi = (4 * (t - s)) & mask, pi = (4 * (t + s)) & mask;
+    combine(lane_value(a, mi), lane_value(c, mi), lane_value(d, mi), lane_value(a, pi), lane_value(c, pi), lane_value(d, pi));
+  }
+  y = d;
+  if (!done) y = d / ((1.0 + a) + c);   // (uniform) every row still coupled couples only to itself
+  yp = full ? rotated<0x13C>(y) : lane_value(y, before);
+  if (next) next->y = full ? rotated<0x134>(y) : lane_value(y, after);
+}
+
 // Solves the interface system.  Lane t < P passes its chunk's first interior row (al0, ga0, de0), its
 // last interior row (alL, gaL, deL) and its interface row (ia, ib, ic, id); on return y = y_t and
 // yp = y_{t-1}, and `next` (optional) holds the next chunk's first row and unknown.  Ends with a barrier after its last write to LDS; its last reads (yp) follow that
@@ -174,6 +246,11 @@ template <typename T, int NT, bool LdsOnly = false>
 __device__ __forceinline__ void interface_solve(const InterfaceSpace<T, NT>& w, int P, T al0, T ga0, T de0,
                                                 T alL, T gaL, T deL, T ia, T ib, T ic, T id, T& y, T& yp,
                                                 NextChunk<T>* next = nullptr) {
+  if constexpr (NT == 64) {
+    if (P == 64) wave_interface_solve<true>(P, al0, ga0, de0, alL, gaL, deL, ia, ib, ic, id, y, yp, next);
+    else wave_interface_solve<false>(P, al0, ga0, de0, alL, gaL, deL, ia, ib, ic, id, y, yp, next);
+    return;
+  }
   constexpr int kR = NT;
   const int t = threadIdx.x;
   const bool own = t < P;
