@@ -117,17 +117,20 @@ typedef struct burgers_ctx burgers_ctx; /* opaque */
  *                  1024 of 8; 0 automatic = 512).  Other whole systems of up to 4096 rows take the
  *                  narrowest of 64, 128, 256 or 512 lanes that holds them at <= 8 rows per lane, up to 8192
  *                  rows 512 lanes of 9 to 16 and up to 16384 rows 1024 lanes of 9 to 16.
- *   btcs_long      solver of the systems longer than 16384 rows (every BTCS and Crank-Nicolson step of
- *                  them goes through HBM):
- *                  0 truncated windows (default): each window of 4096 rows (2: of 8192 rows, in
- *                    wider workgroups) is solved as a plain system
- *                    whose neighbours beyond its ends take their old values, and only its rows at least
- *                    256 rows inside are kept.  By the discrete maximum principle of the M-matrix
- *                    (strictly diagonally dominant rows, non-positive couplings) a kept row then differs
- *                    from the exact solution by at most 2^-54 max|u| whenever theta^257 <= 2^-56, with
- *                    theta = 2(D + C)/(1 + 2D + C + sqrt((1 + C)^2 + 4D)), C = r max|u| over the
- *                    window; every window checks this on the device each step, and an instance with a
- *                    window that fails it is solved again that step by the partition levels;
+ *   btcs_long      solver of the systems longer than 16384 rows:
+ *                  0 truncated windows (default): a window of rows is solved as a plain system whose
+ *                    neighbours beyond its ends are taken as zero, and only its rows far enough inside are
+ *                    kept.  By the discrete maximum principle of the M-matrix (strictly diagonally
+ *                    dominant rows, non-positive couplings) a kept row then differs from the exact
+ *                    solution by at most 2^-54 max|u| per step whenever theta^241 <= 2^-56, with
+ *                    theta = 2(D + C)/(1 + 2D + C + sqrt((1 + C)^2 + 4D)), C = r max|u|.  On the automatic
+ *                    path BTCS calls of three steps and more keep windows of 8192 rows on chip for several
+ *                    steps, with the bound taken once, from the instance's state at the start of the call;
+ *                    instances beyond it step by the partition levels.  Otherwise windows of 4096 rows
+ *                    (2: of 8192 rows, in wider workgroups) take one step per launch and check the bound
+ *                    themselves, and an instance with a window that fails it is solved again that step by
+ *                    the partition levels.  Results do not depend, bit for bit, on how steps are spread over
+ *                    windows, launches and calls;
  *                  1 partition levels: the exact partition method across workgroups (three passes over
  *                    the state per step).
  *   serial         a call advances disjoint groups of instances: those held on chip (whole instances
@@ -204,9 +207,9 @@ burgers_status burgers_step_btcs(burgers_ctx* ctx, void* u, int64_t nsteps);
  * Advance every instance nsteps >= 0 steps of its own `scheme` (forward-Euler, RK4 and BTCS instances
  * may be mixed in one context).  u as for burgers_step_explicit.  Errors as for burgers_step_explicit;
  * BURGERS_E_UNSUPPORTED also when RK4 instances meet a plan forcing explicit_path 1 (the one-step
- * streaming kernel is forward Euler only) or Crank-Nicolson or Newton instances meet btcs_path 2 (they
- * are solved per step through HBM: a Crank-Nicolson step is a BTCS solve with dt/2, y, followed by
- * u' = 2y - u; a Newton step is four assemble-solve-update iterations).
+ * streaming kernel is forward Euler only) or Crank-Nicolson or Newton instances meet btcs_path 2 (a
+ * Crank-Nicolson step is a BTCS solve with dt/2, y, followed by u' = 2y - u; a Newton step is four
+ * assemble-solve-update iterations; the automatic path holds those of up to 8192 rows on chip).
  */
 burgers_status burgers_run(burgers_ctx* ctx, void* u, int64_t nsteps);
 

@@ -377,11 +377,11 @@ __device__ __forceinline__ void reduced_solve(const PcrSpace<double, NT>& pcr, d
   }
 }
 
-// Systems blockIdx.x, blockIdx.x + gridDim.x, ... of n.  `only` (optional): the systems of instances whose
-// entry is nonzero; only[-1] is zero when there is none.
+// One system per workgroup.  `only` (optional): the systems of instances whose entry is nonzero; only[-1] is zero when
+// there is none.
 template <int NT, int MC, bool EXACT = false>
 __global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
-    const SysDesc* __restrict__ systems, int n, const double* __restrict__ LA, const double* __restrict__ LC,
+    const SysDesc* __restrict__ systems, const double* __restrict__ LA, const double* __restrict__ LC,
     const double* __restrict__ LD, double* __restrict__ LX, const int* __restrict__ only) {
   using T = double;
   using Pcr = PcrSpace<T, NT>;
@@ -391,12 +391,9 @@ __global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
   __shared__ int pcr_flags[2 * Pcr::kWaves];
   const Pcr pcr{reinterpret_cast<T*>(smem), pcr_flags};
   if (only && only[-1] == 0) return;
-  for (int q = blockIdx.x; q < n; q += gridDim.x) {
-    const SysDesc sys = systems[q];
-    if (only && only[sys.inst] == 0) continue;
-    reduced_solve<NT, MC, EXACT>(pcr, reinterpret_cast<T*>(smem), sys, LA, LC, LD, LX);
-    __syncthreads();
-  }
+  const SysDesc sys = systems[blockIdx.x];
+  if (only && only[sys.inst] == 0) return;
+  reduced_solve<NT, MC, EXACT>(pcr, reinterpret_cast<T*>(smem), sys, LA, LC, LD, LX);
 }
 
 // Per-step whole-system solver for systems of exactly NT x MC rows whose first row is 16-byte aligned,
@@ -937,7 +934,7 @@ __device__ __forceinline__ void block_reduce_body(const BlockIfaceSpace& w, cons
 template <typename S>
 __global__ __launch_bounds__(kReduceBlock, 4) void btcs_block_reduce_kernel(
     const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
-    const ChunkBlock* __restrict__ blocks, int n, const S* __restrict__ u, double* __restrict__ LA,
+    const ChunkBlock* __restrict__ blocks, const S* __restrict__ u, double* __restrict__ LA,
     double* __restrict__ LC, double* __restrict__ LD, const int* __restrict__ only) {
   using T = double;
   constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
@@ -947,22 +944,19 @@ __global__ __launch_bounds__(kReduceBlock, 4) void btcs_block_reduce_kernel(
   S* stage = reinterpret_cast<S*>(smem);
   T* lds = reinterpret_cast<T*>(smem);
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
-  if (only && only[-1] == 0) return;           // no instance is left to the partition levels
-  for (int q = blockIdx.x; q < n; q += gridDim.x) {
-    const ChunkBlock cb = blocks[q];
-    const SysDesc sys = systems[cb.sys];
-    if (only && only[sys.inst] == 0) continue;   // this instance's windows held
-    const InstDesc d = inst[sys.inst];
-    const bool dir = d.bc == kDirichlet;
-    const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
-    int rs, re;
-    block_rows(sys, cb.chunk0, rs, re);
-    stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
-    __syncthreads();
-    if (block_full(sys, cb.chunk0, Pb)) block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
-    else block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
-    __syncthreads();                             // the next block's rows overwrite this one's
-  }
+  if (only && only[-1] == 0) return;         // no instance is left to the partition levels
+  const ChunkBlock cb = blocks[blockIdx.x];
+  const SysDesc sys = systems[cb.sys];
+  if (only && only[sys.inst] == 0) return;   // this instance's windows held
+  const InstDesc d = inst[sys.inst];
+  const bool dir = d.bc == kDirichlet;
+  const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
+  int rs, re;
+  block_rows(sys, cb.chunk0, rs, re);
+  stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
+  __syncthreads();
+  if (block_full(sys, cb.chunk0, Pb)) block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+  else block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
 }
 
 
@@ -1023,7 +1017,7 @@ __device__ __forceinline__ void block_backsub_body(const BlockIfaceSpace& w, S* 
 template <typename S>
 __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
     const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
-    const ChunkBlock* __restrict__ blocks, int n, const S* __restrict__ u, S* __restrict__ out,
+    const ChunkBlock* __restrict__ blocks, const S* __restrict__ u, S* __restrict__ out,
     const double* __restrict__ LX, const int* __restrict__ only) {
   using T = double;
   constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
@@ -1033,22 +1027,19 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
   S* stage = reinterpret_cast<S*>(smem);
   T* lds = reinterpret_cast<T*>(smem);
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
-  if (only && only[-1] == 0) return;           // no instance is left to the partition levels
-  for (int q = blockIdx.x; q < n; q += gridDim.x) {
-    const ChunkBlock cb = blocks[q];
-    const SysDesc sys = systems[cb.sys];
-    if (only && only[sys.inst] == 0) continue;   // this instance's windows held
-    const InstDesc d = inst[sys.inst];
-    const bool dir = d.bc == kDirichlet;
-    const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
-    int rs, re;
-    block_rows(sys, cb.chunk0, rs, re);
-    stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
-    __syncthreads();
-    if (block_full(sys, cb.chunk0, Pb)) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-    else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-    __syncthreads();                             // the next block's rows overwrite this one's
-  }
+  if (only && only[-1] == 0) return;         // no instance is left to the partition levels
+  const ChunkBlock cb = blocks[blockIdx.x];
+  const SysDesc sys = systems[cb.sys];
+  if (only && only[sys.inst] == 0) return;   // this instance's windows held
+  const InstDesc d = inst[sys.inst];
+  const bool dir = d.bc == kDirichlet;
+  const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
+  int rs, re;
+  block_rows(sys, cb.chunk0, rs, re);
+  stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
+  __syncthreads();
+  if (block_full(sys, cb.chunk0, Pb)) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
 }
 
 // The reduced systems of a partition level, one workgroup each, in the narrowest width that holds the
@@ -1058,7 +1049,7 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
 template <typename S>
 __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
     const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
-    const ChunkBlock* __restrict__ blocks, int n, const S* __restrict__ u, S* __restrict__ out,
+    const ChunkBlock* __restrict__ blocks, const S* __restrict__ u, S* __restrict__ out,
     double* __restrict__ LA, double* __restrict__ LC, double* __restrict__ LD, const double* __restrict__ LX,
     const int* __restrict__ only) {
   using T = double;
@@ -1070,49 +1061,38 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
   T* lds = reinterpret_cast<T*>(smem);
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
   if (only && only[-1] == 0) return;
-  for (int q = blockIdx.x; q < n; q += gridDim.x) {
-    const ChunkBlock cb = blocks[q];
-    const SysDesc sys = systems[cb.sys];
-    if (only && only[sys.inst] == 0) continue;
-    const InstDesc d = inst[sys.inst];
-    const bool dir = d.bc == kDirichlet;
-    const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
-    int rs, re;
-    block_rows(sys, cb.chunk0, rs, re);
-    stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
-    __syncthreads();
-    if (block_full(sys, cb.chunk0, Pb)) {
-      block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-      block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
-    } else {
-      block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-      block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
-    }
-    __syncthreads();
+  const ChunkBlock cb = blocks[blockIdx.x];
+  const SysDesc sys = systems[cb.sys];
+  if (only && only[sys.inst] == 0) return;
+  const InstDesc d = inst[sys.inst];
+  const bool dir = d.bc == kDirichlet;
+  const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
+  int rs, re;
+  block_rows(sys, cb.chunk0, rs, re);
+  stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
+  __syncthreads();
+  if (block_full(sys, cb.chunk0, Pb)) {
+    block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+    block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+  } else {
+    block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+    block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
   }
 }
-
-// Workgroups of a launch over n blocks or systems.  With `only` it mostly finds nothing to do, beside other
-// chains of the call whose workgroups fill the chip: each of its own then has to wait for one of theirs to end, so
-// it takes no more than the chip holds of them at once, which walk the rest.  (One grid of 2^24 rows by windows,
-// 128 steps, with one workgroup per block of 4096 rows: 3950 us; without any such launch 3250.)
-constexpr int kFallbackBlocks = 1024, kFallbackSystems = 512;
-unsigned fallback_grid(int n, int most, const int* only) { return static_cast<unsigned>(only && n > most ? most : n); }
 
 void reduced_wg_launch(const BtcsPlan::Level& lv, double* LA, double* LC, double* LD, double* LX, hipStream_t st,
                        const int* only) {
   const SysDesc* sys = lv.wg->as<SysDesc>();
-  const int m = lv.n_wg;
-  const unsigned n = fallback_grid(lv.n_wg, kFallbackSystems, only);
+  const unsigned n = static_cast<unsigned>(lv.n_wg);
   switch (lv.wg_lanes) {
-    case 64: btcs_reduced_kernel<64, kWgChunk><<<n, 64, 0, st>>>(sys, m, LA, LC, LD, LX, only); break;
-    case 128: btcs_reduced_kernel<128, kWgChunk><<<n, 128, 0, st>>>(sys, m, LA, LC, LD, LX, only); break;
-    case 256: btcs_reduced_kernel<256, kWgChunk><<<n, 256, 0, st>>>(sys, m, LA, LC, LD, LX, only); break;
+    case 64: btcs_reduced_kernel<64, kWgChunk><<<n, 64, 0, st>>>(sys, LA, LC, LD, LX, only); break;
+    case 128: btcs_reduced_kernel<128, kWgChunk><<<n, 128, 0, st>>>(sys, LA, LC, LD, LX, only); break;
+    case 256: btcs_reduced_kernel<256, kWgChunk><<<n, 256, 0, st>>>(sys, LA, LC, LD, LX, only); break;
     default:
       if (lv.wg_exact)   // the full layout as a constant: no row is selected at a run-time index
-        btcs_reduced_kernel<kWgThreads, kWgChunk, true><<<n, kWgThreads, 0, st>>>(sys, m, LA, LC, LD, LX, only);
+        btcs_reduced_kernel<kWgThreads, kWgChunk, true><<<n, kWgThreads, 0, st>>>(sys, LA, LC, LD, LX, only);
       else
-        btcs_reduced_kernel<kWgThreads, kWgChunk><<<n, kWgThreads, 0, st>>>(sys, m, LA, LC, LD, LX, only);
+        btcs_reduced_kernel<kWgThreads, kWgChunk><<<n, kWgThreads, 0, st>>>(sys, LA, LC, LD, LX, only);
       break;
   }
 }
@@ -1149,8 +1129,8 @@ void levels_forward(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc
     const auto& lv = plan.levels[l];
     if (lv.n_blocks == 0) continue;
     if (l == 0) {
-      btcs_block_reduce_kernel<S><<<fallback_grid(lv.n_blocks, kFallbackBlocks, only), kReduceBlock, 0, st>>>(
-          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks, u, LA, LC, LD, only);
+      btcs_block_reduce_kernel<S><<<lv.n_blocks, kReduceBlock, 0, st>>>(
+          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, LA, LC, LD, only);
     } else {
       btcs_array_reduce_kernel<<<lv.n_blocks, kReduceBlock, 0, st>>>(lv.sys->as<SysDesc>(),
                                                                      lv.blocks->as<ChunkBlock>(), LA, LC, LD, only);
@@ -1172,8 +1152,8 @@ void levels_finish(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc*
                    const int* only) {
   if (plan.levels.empty() || plan.levels[0].n_blocks == 0) return;
   const auto& lv = plan.levels[0];
-  btcs_block_backsub_kernel<S><<<fallback_grid(lv.n_blocks, kFallbackBlocks, only), kReduceBlock, 0, ctx->stream>>>(
-      inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks, u, out, ctx->level_x.as<double>(), only);
+  btcs_block_backsub_kernel<S><<<lv.n_blocks, kReduceBlock, 0, ctx->stream>>>(
+      inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, out, ctx->level_x.as<double>(), only);
 }
 
 // nsteps steps by the levels, the last one's rows in bufs[nsteps & 1] (u, work).  Where every system's reduced one
@@ -1199,8 +1179,8 @@ void levels_run(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int
     else reduced_wg_launch(plan.levels[1], LA, LC, LD, LX, ctx->stream, only);
     if (s + 1 == nsteps) levels_finish<S>(ctx, plan, inst, bufs[s & 1], bufs[(s & 1) ^ 1], only);
     else
-      btcs_block_turn_kernel<S><<<fallback_grid(lv.n_blocks, kFallbackBlocks, only), kReduceBlock, 0, ctx->stream>>>(
-          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks, bufs[s & 1], bufs[(s & 1) ^ 1], LA, LC,
+      btcs_block_turn_kernel<S><<<lv.n_blocks, kReduceBlock, 0, ctx->stream>>>(
+          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), bufs[s & 1], bufs[(s & 1) ^ 1], LA, LC,
           LD, LX, only);
   }
 }

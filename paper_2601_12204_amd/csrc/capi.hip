@@ -664,9 +664,10 @@ hipError_t enqueue_stepped(burgers_ctx* ctx, const burgers::BtcsPlan& pl, void* 
   return e;
 }
 
-// Windows of several steps serve calls of four steps and more: they begin with a pass over the states for the
-// bound that holds for the whole call, and keep 384 of 512 chunks against 224 of 256.
-constexpr int64_t kDeepLeast = 4, kDeepCall = int64_t{1} << 24;
+// Windows of several steps serve calls of three steps and more: they begin with a pass over the states for the
+// bound that holds for the whole call, and keep 416 of 512 chunks against 224 of 256.  (2^24 rows, us per step with the
+// copy of the state, by windows of one step / of several: 2 steps 83 / 110, 3 steps 87 / 82, 4 steps 85 / 66.)
+constexpr int64_t kDeepLeast = 3, kDeepCall = int64_t{1} << 24;
 bool takes_deep(const burgers::BtcsPlan& pl, int64_t nsteps) { return pl.n_deep > 0 && nsteps >= kDeepLeast; }
 
 // nsteps implicit steps of one subset, the final state in u.

@@ -69,11 +69,16 @@ __device__ __forceinline__ double theta_bound(const InstDesc& d, double M) {
   return 2.0 * (d.D + C) / ((1.0 + 2.0 * d.D + C) + __builtin_sqrt((1.0 + C) * (1.0 + C) + 4.0 * d.D));
 }
 
-// |v| into a running maximum; a NaN counts as infinite, so that its instance fails the bound.
-__device__ __forceinline__ void take_max(double v, double& big) {
-  const double a = __builtin_fabs(v);
-  big = __builtin_fmax(big, a == a ? a : __builtin_inf());
-}
+// A running maximum of |v|, infinite once a value is not finite, so that its instance fails the bound (`zero` turns into
+// a NaN then, which the maximum itself would pass over).
+struct Magnitude {
+  double big = 0.0, zero = 0.0;
+  __device__ __forceinline__ void take(double v) {
+    big = __builtin_fmax(big, __builtin_fabs(v));
+    zero = __builtin_fma(v, 0.0, zero);
+  }
+  __device__ __forceinline__ double value() const { return zero == 0.0 ? big : __builtin_inf(); }
+};
 
 // LDS of a window: its rows staged between HBM and the lanes, overlaid by the interface solve.
 template <typename S, int NT>
@@ -146,20 +151,26 @@ template <typename S, int NT, bool MAX>
 __device__ __forceinline__ double window_load(const S* __restrict__ x, S* stage, const Frame& f) {
   const int t = threadIdx.x;
   S v[kM];
+  if (f.r0 + NT * kM <= f.ch.R) {              // (uniform) the rows from r0 on are there: one address
+    const S* __restrict__ p = x + f.r0;
 #pragma unroll
-  for (int j = 0; j < kM; ++j) {
-    const int i = t + j * NT;
-    int k = f.r0 + (i < f.total ? i : f.total - 1);
-    if (k >= f.ch.R) k -= f.ch.R;
-    v[j] = x[k];
+    for (int j = 0; j < kM; ++j) v[j] = p[t + j * NT];
+  } else {
+#pragma unroll
+    for (int j = 0; j < kM; ++j) {
+      const int i = t + j * NT;
+      int k = f.r0 + (i < f.total ? i : f.total - 1);
+      if (k >= f.ch.R) k -= f.ch.R;
+      v[j] = x[k];
+    }
   }
-  double big = 0.0;
+  Magnitude m;                                 // (rows beyond the window's at most raise it)
 #pragma unroll
   for (int j = 0; j < kM; ++j) {
-    if constexpr (MAX) take_max(static_cast<double>(v[j]), big);
+    if constexpr (MAX) m.take(static_cast<double>(v[j]));
     stage[padded(t + j * NT)] = v[j];
   }
-  return big;
+  return m.value();
 }
 
 // The window's kept rows, put(row of the system, row of the window); the lane index is formed anew.
@@ -173,11 +184,7 @@ __device__ __forceinline__ void window_kept(const Frame& f, const ChunkWin& w, P
 #pragma unroll
   for (int j = 0; j < kM; ++j) {
     const int o = t + j * NT;
-    if (o < count) {
-      int k = first + o;
-      if (k >= f.ch.R) k -= f.ch.R;
-      put(k, from + o);
-    }
+    if (o < count) put(first + o, from + o);   // (kept chunks of a window do not wrap)
   }
 }
 
@@ -314,10 +321,10 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
   int c = w.first + w.lo;
   if (c >= f.ch.P) c -= f.ch.P;
   const int first = f.ch.base(c), count = f.ch.rows(c, w.count);
-  double big = 0.0;
+  Magnitude m;
 #pragma unroll 8
-  for (int i = threadIdx.x; i < count; i += 256) take_max(static_cast<double>(x[first + i]), big);
-  const double M = workgroup_max<256>(big, wave_max);
+  for (int i = threadIdx.x; i < count; i += 256) m.take(static_cast<double>(x[first + i]));
+  const double M = workgroup_max<256>(m.value(), wave_max);
   if (threadIdx.x == 0) atomicMax(top + w.inst, __builtin_bit_cast(unsigned long long, M));
 }
 
