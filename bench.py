@@ -345,7 +345,7 @@ def dominant_roofline(c2):
     bytes_ = 2 * word * nodes
     achieved = bytes_ / (per_launch * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "btcs_wg_kernel<double, true>",
+            "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "btcs_whole_kernel<double, 512, 16>",
             "launches": c2["btcs_launches"], "algorithmic_bytes_per_launch": bytes_}
 
 

@@ -406,7 +406,7 @@ __global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
 // H = MC * sizeof(S) / 16) sits at H t + (h ^ f(t)), f(t) = (t / (16 / H)) mod H, so that 16 lanes
 // reading either their own chunks (one h each) or 16 consecutive chunks touch 16 different 16-byte bank
 // groups.  The interface solve's LDS overlays the buffer of the system being solved (its rows are in
-// registers by then).  Same operations in the same order as btcs_wg_kernel<S, true, NT, MC, true>:
+// registers by then).  Same operations in the same order as btcs_whole_kernel<S, NT, MC>:
 // bitwise the same results.
 template <typename S>
 struct Chunk16;

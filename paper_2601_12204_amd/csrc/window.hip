@@ -214,7 +214,7 @@ __device__ __forceinline__ double workgroup_max(double big, double* wave_max) {
 // fails; the partition levels then redo that instance's step (the old state is still in u).
 //
 // Bound by HBM and the latency of load, solve and store in turn: 16 x 256 rows per window, so that four
-// workgroups a CU overlap them (52.6 us a step at 2^24 rows, binary64, with 8192-row windows 60.8).
+// workgroups a CU overlap them (58.6 us a step at 2^24 rows, binary64, the idle launches of the levels included).
 template <typename S, int NT>
 __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
     const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const S* __restrict__ u,
