@@ -252,7 +252,8 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
  * device array of BURGERS_STATIC_SCRATCH_BYTES, one per GPU the library runs on, held until the process
  * ends.  Every call on a GPU reuses that GPU's array: calls on one stream are ordered, but calls that
  * overlap on one GPU (other streams, other threads) race and corrupt each other's results.  Nothing in
- * the array needs to start at zero.  Launches are eager (no graph).
+ * the array needs to start at zero.  Launches are eager (no graph); the side streams of the concurrent
+ * groups (up to three per GPU) are made by the first call that forks and held with the array.
  * Errors: BURGERS_E_INVALID (as burgers_create and burgers_run), BURGERS_E_BUDGET when the workspace
  * would exceed BURGERS_STATIC_SCRATCH_BYTES (nothing is run), BURGERS_E_UNSUPPORTED for Newton instances
  * (their checks report through burgers_sync of a context), BURGERS_E_DEVICE.

@@ -103,33 +103,34 @@ hipError_t run_tasks(burgers_ctx* ctx, std::vector<Task>& tasks, bool serial) {
     place[k] = q;
     load[q] += tasks[k].us;
   }
+  SideStreams& sides = ctx->sides;
   for (int q = 1; q < kStreams; ++q) {
     if (load[q] == 0) continue;
-    if (!ctx->side[q - 1] && (e = hipStreamCreateWithFlags(&ctx->side[q - 1], hipStreamNonBlocking)) != hipSuccess) return e;
-    if (!ctx->joined[q - 1] &&
-        (e = hipEventCreateWithFlags(&ctx->joined[q - 1], hipEventDisableTiming)) != hipSuccess)
+    if (!sides.stream[q - 1] && (e = hipStreamCreateWithFlags(&sides.stream[q - 1], hipStreamNonBlocking)) != hipSuccess) return e;
+    if (!sides.joined[q - 1] &&
+        (e = hipEventCreateWithFlags(&sides.joined[q - 1], hipEventDisableTiming)) != hipSuccess)
       return e;
   }
-  if (!ctx->forked && (e = hipEventCreateWithFlags(&ctx->forked, hipEventDisableTiming)) != hipSuccess) return e;
+  if (!sides.forked && (e = hipEventCreateWithFlags(&sides.forked, hipEventDisableTiming)) != hipSuccess) return e;
   hipStream_t main = ctx->stream;
-  if ((e = hipEventRecord(ctx->forked, main)) != hipSuccess) return e;
+  if ((e = hipEventRecord(sides.forked, main)) != hipSuccess) return e;
   for (int q = 1; q < kStreams && e == hipSuccess; ++q)
-    if (load[q] > 0) e = hipStreamWaitEvent(ctx->side[q - 1], ctx->forked, 0);
+    if (load[q] > 0) e = hipStreamWaitEvent(sides.stream[q - 1], sides.forked, 0);
   // chains of few launches first: the host is done with them soon, and a chain of many then delays none
   std::vector<size_t> order(tasks.size());
   for (size_t k = 0; k < order.size(); ++k) order[k] = k;
   std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return tasks[x].launches < tasks[y].launches; });
   for (size_t k : order) {
     if (e != hipSuccess) break;
-    if (place[k] > 0) ctx->stream = ctx->side[place[k] - 1];
+    if (place[k] > 0) ctx->stream = sides.stream[place[k] - 1];
     e = tasks[k].run();
     ctx->stream = main;
   }
   // (joined after an error too: nothing enqueued may outlive the context's stream order)
   for (int q = 1; q < kStreams; ++q) {
     if (load[q] == 0) continue;
-    hipError_t j = hipEventRecord(ctx->joined[q - 1], ctx->side[q - 1]);
-    if (j == hipSuccess) j = hipStreamWaitEvent(main, ctx->joined[q - 1], 0);
+    hipError_t j = hipEventRecord(sides.joined[q - 1], sides.stream[q - 1]);
+    if (j == hipSuccess) j = hipStreamWaitEvent(main, sides.joined[q - 1], 0);
     if (e == hipSuccess) e = j;
   }
   return e;
@@ -1119,6 +1120,11 @@ constexpr int kMaxDevices = 64;
 std::mutex scratch_mutex;
 void* scratch_ptr[kMaxDevices] = {};
 
+// Beside each device's scratch, one set of side streams for the calls on it, lent to one call at a time while it
+// enqueues.
+std::mutex static_sides_mutex[kMaxDevices];
+burgers::SideStreams static_sides[kMaxDevices];
+
 // Device address of the current device's scratch array.
 hipError_t scratch_address(int device, void** out) {
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
@@ -1196,11 +1202,7 @@ void burgers_destroy(burgers_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   for (auto& kv : ctx->graph_cache) (void)hipGraphExecDestroy(kv.second);
   if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
-  for (int k = 0; k < 3; ++k) {
-    if (ctx->side[k]) (void)hipStreamDestroy(ctx->side[k]);
-    if (ctx->joined[k]) (void)hipEventDestroy(ctx->joined[k]);
-  }
-  if (ctx->forked) (void)hipEventDestroy(ctx->forked);
+  ctx->sides.release();
   delete ctx;
 }
 
@@ -1250,8 +1252,12 @@ burgers_status burgers_run_static(const burgers_problem* problems, int64_t count
     burgers_ctx* ctx = nullptr;
     st = new_context(problems, count, dtype, hip_stream, &ctx);
     if (st == BURGERS_OK) {
+      std::unique_lock<std::mutex> lent(static_sides_mutex[device], std::try_to_lock);
+      if (lent) std::swap(ctx->sides, static_sides[device]);
+      else ctx->plan.serial = 1;                   // (another thread's call has them)
       st = advance(ctx, u, nsteps, kSetAll, -1);   // plan tables carved too; eager launches
       if (st == BURGERS_OK && ctx->sticky != hipSuccess) st = from_hip(ctx->sticky);
+      if (lent) std::swap(ctx->sides, static_sides[device]);
       delete ctx;                                  // host side only: carved buffers free nothing
     }
   }

@@ -303,6 +303,21 @@ struct NewtonPlan {
   DevBuf flags;                                     // int32[2]: dominance lost, not converged (read by burgers_sync)
 };
 
+// Side streams (default priority) and events of the concurrent launch chains of a call, made as run_tasks needs them.
+struct SideStreams {
+  hipStream_t stream[3] = {nullptr, nullptr, nullptr};
+  hipEvent_t joined[3] = {nullptr, nullptr, nullptr};
+  hipEvent_t forked = nullptr;
+  void release() {
+    for (int k = 0; k < 3; ++k) {
+      if (stream[k]) (void)hipStreamDestroy(stream[k]);
+      if (joined[k]) (void)hipEventDestroy(joined[k]);
+    }
+    if (forked) (void)hipEventDestroy(forked);
+    *this = SideStreams{};
+  }
+};
+
 }  // namespace burgers
 
 struct burgers_ctx {
@@ -329,10 +344,7 @@ struct burgers_ctx {
   // launch sequences captured as graphs, keyed by (subset, scheme, steps, BTCS steps, state buffer)
   std::map<std::tuple<int, int, int64_t, int64_t, void*>, hipGraphExec_t> graph_cache;
   hipStream_t capture_stream = nullptr;      // private non-blocking stream used only for capture
-  // side streams (default priority) and events of the concurrent launch groups of a call
-  hipStream_t side[3] = {nullptr, nullptr, nullptr};
-  hipEvent_t joined[3] = {nullptr, nullptr, nullptr};
-  hipEvent_t forked = nullptr;
+  burgers::SideStreams sides;
   std::unique_ptr<burgers::AdjointPlan> adjoint;
   std::unique_ptr<burgers::NewtonPlan> newton;
   hipError_t sticky = hipSuccess;

@@ -241,11 +241,7 @@ void pool_free(burgers_pool* pl) {
   (void)hipStreamSynchronize(pl->ctx.stream);
   for (auto& kv : pl->graphs) (void)hipGraphExecDestroy(kv.second);
   if (pl->capture) (void)hipStreamDestroy(pl->capture);
-  for (int k = 0; k < 3; ++k) {
-    if (pl->ctx.side[k]) (void)hipStreamDestroy(pl->ctx.side[k]);
-    if (pl->ctx.joined[k]) (void)hipEventDestroy(pl->ctx.joined[k]);
-  }
-  if (pl->ctx.forked) (void)hipEventDestroy(pl->ctx.forked);
+  pl->ctx.sides.release();
   if (pl->done) (void)hipEventDestroy(pl->done);
   if (pl->sticky_host) (void)hipHostFree(pl->sticky_host);
   // views into `tables` must not free anything
