@@ -122,7 +122,7 @@ typedef struct burgers_ctx burgers_ctx; /* opaque */
  *                    neighbours beyond its ends are taken as zero, and only its rows far enough inside are
  *                    kept.  By the discrete maximum principle of the M-matrix (strictly diagonally
  *                    dominant rows, non-positive couplings) a kept row then differs from the exact
- *                    solution by at most 2^-54 max|u| per step whenever theta^241 <= 2^-56, with
+ *                    solution by at most about 2^-53 max|u| per step whenever theta^257 <= 2^-56, with
  *                    theta = 2(D + C)/(1 + 2D + C + sqrt((1 + C)^2 + 4D)), C = r max|u|.  On the automatic
  *                    path BTCS calls of three steps and more keep windows of 8192 rows on chip for several
  *                    steps, with the bound taken once, from the instance's state at the start of the call;

@@ -11,13 +11,14 @@
 // each step, and how the steps are spread over launches does not show.  dJ/dD is carried per lane over its rows and all steps, in a slot per
 // chunk of the system, so the sums do not depend on how the steps are grouped into launches.
 //
-// Error of a window's kept row, per step: the window solution differs from the exact one by A_w^{-T} applied to the two
-// couplings beyond its ends (at most D + C, C = r max|u|) times the exact mu there.  A_w is a strictly row-diagonally
-// dominant M-matrix with row sums >= 1, so A_w^{-1} >= 0 with row sums <= 1, and its columns decay from the diagonal
-// like the barrier of the forward windows: a kept row is within 2 (D + C) theta^(n_S + 1) max|mu|, and the couplings
-// dropped after S PCR steps are as small.  With (D + C) theta^(n_S) <= 2^-56, from the largest |u| at the start of the
-// call (the states' maximum principle), that is at most 2^-54 max|mu|.  Systems beyond the bound are solved whole by
-// one workgroup of 1024 lanes (up to 16384 rows, with registers spilled) or by the partition levels' array path.
+// Error of a window's kept row, per step: as of the forward windows, that of the couplings dropped.  A row that couples
+// mu_f outside a run of rows to mu_i inside it through A_w^{-T} does so with at most D + C (C = r max|u|) times
+// (A_w^{-1})_{f',i}, f' the run's row beside f.  A_w is a strictly row-diagonally dominant M-matrix with row sums >= 1, so
+// A_w^{-1} >= 0 with row sums <= 1, and its columns decay from the diagonal like theta of the forward windows: after S
+// PCR steps the couplings are within (D + C) theta^(n_S - 1).  With (D + C) theta^257 <= 2^-55 (S = 4) or (D + C)
+// theta^(n_S) <= 2^-56 (S < 4), theta from the largest |u| at the start of the call (the states' maximum principle), what
+// is dropped costs about 2^-53 max|mu| at most.  Systems beyond the bound are solved whole by one workgroup of 1024
+// lanes (up to 16384 rows, with registers spilled) or by the partition levels' array path.
 #include "interface.hpp"
 #include "internal.hpp"
 #include "staging.hpp"
@@ -60,7 +61,7 @@ struct WindowLayout {
   __device__ __forceinline__ int node(int k) const { return (k >= ch.R ? k - ch.R : k) + first; }
   __device__ __forceinline__ bool dummy(int t) const {
     const int c = c0 + t;
-    return (c >= ch.P ? c - ch.P : c) >= ch.rho;
+    return ch.lacks(c >= ch.P ? c - ch.P : c);
   }
 };
 

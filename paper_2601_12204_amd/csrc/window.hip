@@ -1,8 +1,8 @@
 // BTCS and Crank-Nicolson systems of more than 16384 rows on truncated windows: several steps per launch
 // (btcs_deep_kernel) or one (btcs_window_kernel), with the same results to the bit.
 //
-// A system is cut into chunks of 16 rows (the last ones of 15 where the rows do not divide), at the same
-// rows for every window, step and launch.  A window is a run of up to 512 (256) chunks, one per lane, solved
+// A system is cut into chunks of 16 rows (some of 15 where the rows do not divide), at the same rows for every
+// window, step and launch.  A window is a run of up to 512 (256) chunks, one per lane, solved
 // as a plain system by the interface partition: beyond its two ends the unknowns are taken as zero (at a
 // Dirichlet end of the system: the boundary value).  An interface row whose couplings have fallen below
 // 2^-54 of its diagonal drops them there and then, and the PCR takes at most S steps (strides 1 to
@@ -11,27 +11,24 @@
 // A window of several steps therefore only loses 2^S chunks at either end with each, and how a call's steps
 // are spread over launches, windows or calls does not show in the results.
 //
-// Error of a kept row.  Let e be the window solution minus the exact one, extended to the ghosts (the unknowns
-// beyond the ends) by the ghosts' errors g_L, g_R.  Every window row gives l_i e_{i-1} + d_i e_i + p_i
-// e_{i+1} = 0 with l_i, p_i <= 0 and d_i - |l_i| - |p_i| = 1, so a vector w with that operator >= 0 on the window
-// rows and w >= 0 at the ghosts is >= 0 throughout (at a negative minimum the row would give 1 * w_i < 0).  The
-// barrier v_i = theta^(i+1) (ghost at i = -1) meets -|l_i| + d_i theta - |p_i| theta^2 >= 0 whenever theta is
-// at least the smaller root of that quadratic, which for the BTCS rows (c = r u_i, the couplings D + max(c,0)
-// and D - min(c,0)) is at most
-//     g(C) = 2 (D + C) / (1 + 2D + C + sqrt((1 + C)^2 + 4D)),   C = r max|u_i| over the window
-// (g increases with C, and the mirrored barrier from the right end takes the same bound).  With w =
-// |g_L| v + |g_R| v' -+ e:  |e_i| <= |g_L| theta^(i+1) + |g_R| theta^(W-i).  By the maximum principle of the
-// step, which the window's system keeps with its zero ghosts, a ghost is off by at most max|u^n|.  The same
-// barrier bounds the couplings that the PCR drops after S steps, between unknowns 2^S chunks (n_S = 15 2^S
-// rows at least, 241 for S = 4) apart, by theta^(n_S) each.  With theta^(n_S) <= 2^-56 a kept row is within
-// 2^-54 max|u^n| of the exact value after every step.  The maximum principle also keeps max|u| from growing,
-// so the bound at the start of a call holds for all of its steps (up to rounding, which the limits' slack
-// covers); the state of a Crank-Nicolson step, 2y - u, has no such bound: those systems are checked, and
-// stepped, once per launch.
+// Error of a kept row.  Dropping couplings a and c of a row changes its right-hand side by at most (|a| + |c|)
+// max|x|.  After s PCR steps they join interface unknowns 2^s chunks, n_s >= 16 2^s - 1 rows, apart, and the influence
+// of one of those unknowns on the other is a solution of the rows between that is 1 at one end and 0 at the other:
+// with a lower coupling -l_i, an upper one -p_i and d_i - l_i - p_i = 1 in every row, v = theta^k over the distance k
+// is above it whenever -l_i + d_i theta - p_i theta^2 >= 0, that is for any theta from the smaller root of that
+// quadratic on, which for the BTCS rows (c = r u_i, the couplings D + max(c,0) and D - min(c,0)) is at most
+//     g(C) = 2 (D + C) / (1 + 2D + C + sqrt((1 + C)^2 + 4D)),   C = r max|u_i|
+// (g increases with C).  So |a| + |c| <= 2 theta^(n_s).  With theta^257 <= 2^-56 that is below 2^-54 after four steps:
+// the S-th step cuts nothing that is not negligible by then, and the kept rows are within about 2^-53 max|u^n| of the
+// exact ones after every step: a row's couplings are dropped once, for 2^-54 max|u^n|, and reach other rows through
+// couplings that add up to 0.3 over the PCR steps.  A smaller S serves a theta with theta^(n_S) <= 2^-56, for the same
+// results to the bit.  By the maximum principle max|u| does not grow, so the bound at the start of a call holds for
+// all of its steps (up to rounding, which the slack of the limits covers); the state of a Crank-Nicolson step, 2y - u,
+// has no such bound: those systems are checked, and stepped, once per launch.
 //
-// This is the truncation the partition method's PCR already makes when it drops couplings below 2^-54, applied
-// to the spikes between windows (the decay of the inverse of a diagonally dominant tridiagonal matrix behind
-// truncated SPIKE solvers).  Systems beyond the bound are solved exactly by the partition levels.
+// This is the truncation that the whole systems' PCR makes too when it drops couplings below 2^-54 (the decay of
+// the inverse of a diagonally dominant tridiagonal matrix, behind truncated SPIKE solvers).  Systems beyond the bound
+// are solved exactly by the partition levels.
 #include <cmath>
 
 #include "interface.hpp"
@@ -49,17 +46,17 @@ constexpr int kM = kChunkRows;
 constexpr int kMaxS = kMaxPcr;
 constexpr int kStepHalo = 1 << kMaxS;
 
-// The largest theta for S PCR steps, theta^(n_S) <= 2^-56, with slack for rounding (its own evaluation and
-// the growth of max|u| by rounding over a call's steps).
+// The largest theta for S PCR steps, with slack for rounding (of its own evaluation, and for S < 4 of the growth of
+// max|u| by rounding over a call's steps: S = 4 has it in hand).
 struct ThetaLimits {
-  double of[kMaxS];     // S = 1 .. kMaxS
-  double rows[kMaxS];   // n_S
+  double of[kMaxS];     // S = 1 .. kMaxS: theta^rows <= 2^-56
+  double rows[kMaxS];   // n_S; S = 4: 257
 };
 ThetaLimits theta_limits() {
   ThetaLimits t;
   for (int s = 1; s <= kMaxS; ++s) {
-    t.rows[s - 1] = s < 4 ? 15 << s : 241;
-    t.of[s - 1] = std::exp2(-56.0 / t.rows[s - 1]) * (1.0 - 1e-9);
+    t.rows[s - 1] = s < kMaxS ? (kM << s) - 1 : 257;
+    t.of[s - 1] = std::exp2(-56.0 / t.rows[s - 1]) * (1.0 - (s < kMaxS ? 1e-9 : 1e-12));
   }
   return t;
 }
@@ -102,7 +99,7 @@ __device__ __forceinline__ int window_lane(const Frame& f, const ChunkWin& w, in
     c -= f.ch.P;
     wrap = f.ch.R;
   }
-  const bool dummy = c >= f.ch.rho;
+  const bool dummy = f.ch.lacks(c);
   l.base = 0;
   l.own = t < w.chunks;
   l.dummy = dummy;
@@ -351,7 +348,8 @@ __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __rest
 #pragma unroll
     for (int q = kMaxS; q >= 1; --q) {
       bool holds = theta <= lim.of[q - 1];
-      if (transposed) holds = holds && (theta == 0.0 || lim.rows[q - 1] * log2(theta) + log2(coupling) <= -56.0);
+      if (transposed)
+        holds = holds && (theta == 0.0 || lim.rows[q - 1] * log2(theta) + log2(coupling) <= (q < kMaxS ? -56.0 : -55.0));
       s = holds ? q : s;
     }
     if (s == 0) sticky[i] = 1;

@@ -17,12 +17,15 @@ constexpr int kDeepLanes = 512;
 // the CFL step, 6 steps a launch (one grid of 2^24 rows, 128 steps: 32 chunks 3.48 ms, 48: 3.16, 64: 3.21).
 constexpr int kDeepHalo = 48;
 
-// Chunks of a system of R rows: P of them, the first rho of 16 rows and the others of 15 (R > 8192).
+// Chunks of a system of R > 8192 rows: P = ceil(R / 16) of them, all of 16 rows but `lack` < 16 of 15 rows, the chunks
+// 31, 63, 95, ... (P > 32 lack): no two of those are within 32 chunks of each other, around a periodic system too, so
+// 2^S <= 16 consecutive chunks hold at least 16 2^S - 1 rows.
 struct Chunks {
-  int R, P, rho;
+  int R, P, lack;
   __device__ __forceinline__ explicit Chunks(int rows)
-      : R(rows), P((rows + kChunkRows - 1) / kChunkRows), rho(rows - (kChunkRows - 1) * P) {}
-  __device__ __forceinline__ int base(int c) const { return (kChunkRows - 1) * c + (c < rho ? c : rho); }
+      : R(rows), P((rows + kChunkRows - 1) / kChunkRows), lack(kChunkRows * P - rows) {}
+  __device__ __forceinline__ bool lacks(int c) const { return (c & 31) == 31 && (c >> 5) < lack; }
+  __device__ __forceinline__ int base(int c) const { return kChunkRows * c - (c >> 5 < lack ? c >> 5 : lack); }
   // rows of the run of n chunks from c on (c < P; the run may pass the end of a periodic system)
   __device__ __forceinline__ int rows(int c, int n) const {
     const int e = c + n;
