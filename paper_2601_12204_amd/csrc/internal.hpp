@@ -239,6 +239,7 @@ struct BtcsPlan {
   int64_t n_deep = 0, n_deep_inst = 0;
   DevBuf deep_words;                         // see deep_words()
   bool transposed = false;                   // the windows solve the transposed systems (adjoint)
+  bool pool = false;                         // a pool's windows: no levels, failed steps are reported
   bool stream_exact = false;                 // per-step exact 8192-row systems: the persistent pipelined kernel
   DevBuf win_flags;                          // win_flags_words(count) int32 (see win_flag_slot)
 };
@@ -451,8 +452,8 @@ hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, con
                                void* out, int* now, int* next, int* sticky);
 // For a call from the states in u: the PCR steps of plan.deep's instances, and the flags (slot 0 of the window
 // flags) of those beyond the bound, which launch_btcs_deep leaves alone.  `fresh` (a pool's, one word per instance):
-// it steps those too, and only their sticky words tell; an instance's sticky word starts anew where its entry is
-// nonzero.
+// it steps those too, and their sticky words tell of steps that fail the bound; an instance's sticky word starts anew
+// where its entry is nonzero.
 hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, const int32_t* fresh);
 // nsteps (below 2^30) steps of plan.deep, the final states in u.
 hipError_t launch_btcs_deep(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps);

@@ -340,6 +340,7 @@ burgers_status burgers_pool_create(burgers_dtype dtype, int32_t scheme, int64_t 
       g.n = static_cast<int32_t>(slots);
       pl->res.push_back(std::move(g));
     }
+    pl->bplan.pool = true;
     pl->bplan.deep = std::make_unique<DevBuf>();
     view(*pl->bplan.deep, pl->tables.ptr, pl->off_win, static_cast<size_t>(slots * pl->wx) * entry, st);
     pl->bplan.n_deep = slots * pl->wx;

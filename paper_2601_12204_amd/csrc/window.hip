@@ -45,6 +45,7 @@ namespace {
 constexpr int kM = kChunkRows;
 constexpr int kMaxS = kMaxPcr;
 constexpr int kStepHalo = 1 << kMaxS;
+constexpr int kWatched = 8;   // beside the PCR steps of an instance's code: a pool's, beyond the bound at the tick's start
 
 // The largest theta for S PCR steps, with slack for rounding (of its own evaluation, and for S < 4 of the growth of
 // max|u| by rounding over a call's steps: S = 4 has it in hand).
@@ -109,10 +110,10 @@ __device__ __forceinline__ int window_lane(const Frame& f, const ChunkWin& w, in
   return f.ch.base(c) - (dummy ? 1 : 0) - f.r0 + wrap;   // (-1 for a first chunk of 15 rows)
 }
 
-// `steps` steps of a window's rows, from and to the staged rows.
-template <typename S, int NT>
+// `steps` steps of a window's rows, from and to the staged rows; watch(de) sees the lane's rows before each of them.
+template <typename S, int NT, typename Watch>
 __device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>& ws, S* stage, const Frame& f,
-                                               const ChunkWin& w, const InstDesc& d, int steps, int pcr) {
+                                               const ChunkWin& w, const InstDesc& d, int steps, int pcr, Watch&& watch) {
   const int t = threadIdx.x;
   SlotLane l;
   const int at = window_lane(f, w, t, l);
@@ -125,6 +126,7 @@ __device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>&
     de[j] = l.own ? static_cast<double>(stage[padded(j == 0 && at < 0 ? 0 : at + j)]) : 0.0;
   __syncthreads();                           // every lane's rows read: the interface LDS overlays them
   for (int step = 0; step < steps; ++step) {
+    watch(de);
     double ia = 0.0, ib = 1.0, ic = 0.0, id = 0.0, y, yp;
     if (l.own) slot_eliminate<kM, false>(rows, l, al, ga, de, ia, ib, ic, id);
     window_solve<NT>(ws, w.chunks, pcr, l.own, l.dummy ? al[1] : al[0], l.dummy ? ga[1] : ga[0],
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
       sticky[w.inst] = 1;
     }
   }
-  window_advance<S, NT>(ws, stage, f, w, d, 1, kMaxS);
+  window_advance<S, NT>(ws, stage, f, w, d, 1, kMaxS, [](const auto&) {});
   window_kept<NT>(f, w, [&](int k, int i) {
     const S val = stage[padded(i)];
     y[k] = w.cn ? static_cast<S>(2.0 * static_cast<double>(val) - static_cast<double>(x[k])) : val;
@@ -249,13 +251,15 @@ __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
 
 // Up to kDeepHalo / 2^S steps of each window with the rows on chip, S of its instance (code; 0: the instance
 // is left to the partition levels).  A launch beyond an instance's last step does nothing for it.
+// WATCH (pools): an instance whose code says so (kWatched) is stepped with the bound checked at every step, from the
+// rows it keeps; the steps that fail it are told by its sticky word.
 //
 // Bound by vector issue like the whole systems on chip (whole.hip), with 512 / (512 - 2 kDeepHalo) of the rows' work, and
 // by the window's load and store once per launch, which the CU's other workgroup covers in part.
-template <typename S>
+template <typename S, bool WATCH>
 __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
     const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const int* __restrict__ code,
-    const S* __restrict__ u, S* __restrict__ out, int launch, int nsteps) {
+    const S* __restrict__ u, S* __restrict__ out, int launch, int nsteps, int* __restrict__ sticky, double theta_lim) {
   constexpr int NT = kDeepLanes;
   __shared__ __attribute__((aligned(16))) unsigned char smem[WindowSpace<S, NT>::kBytes];
   __shared__ uint64_t iface_votes[2 * InterfaceSpace<double, NT>::kVoteWords];
@@ -265,7 +269,7 @@ __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
   S* stage = reinterpret_cast<S*>(smem);
   const ChunkWin w = wins[blockIdx.x];
   if (w.count <= 0) return;                    // an empty slot of a resident pool
-  const int pcr = code[w.inst];
+  const int word = code[w.inst], pcr = WATCH ? word & ~kWatched : word;
   if (pcr <= 0) return;
   int done;
   const int steps = deep_steps(w, pcr, launch, nsteps, done);
@@ -275,7 +279,17 @@ __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
   const int dir = d.bc == kDirichlet ? 1 : 0;
   window_load<S, NT, false>(u + d.off + dir, stage, f);
   __syncthreads();
-  window_advance<S, NT>(ws, stage, f, w, d, steps, pcr);
+  window_advance<S, NT>(ws, stage, f, w, d, steps, pcr, [&](const double (&rows)[kM]) {
+    if constexpr (WATCH) {
+      const int t = opaque_lane(static_cast<int>(threadIdx.x));
+      if ((word & kWatched) && t >= w.lo && t < w.lo + w.count) {
+        Magnitude m;
+#pragma unroll
+        for (int j = 0; j < kM; ++j) m.take(rows[j]);
+        if (!(theta_bound(d, m.value()) <= theta_lim)) sticky[w.inst] = 1;
+      }
+    }
+  });
   S* __restrict__ y = out + d.off + dir;
   window_kept<NT>(f, w, [&](int k, int i) { y[k] = stage[padded(i)]; });
   window_ends<S>(f, w, d, out);
@@ -289,7 +303,7 @@ __global__ __launch_bounds__(256) void btcs_settle_kernel(const InstDesc* __rest
                                                           S* __restrict__ u, int nsteps) {
   const ChunkWin w = wins[blockIdx.x];
   if (w.count <= 0) return;
-  const int pcr = code[w.inst];
+  const int pcr = code[w.inst] & ~kWatched;
   if (pcr <= 0) return;
   const int per = kDeepHalo >> pcr, total = w.limit > 0 && w.limit < nsteps ? w.limit : nsteps;
   if (((total + per - 1) / per & 1) == 0) return;
@@ -326,16 +340,16 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
 }
 
 // Every windowed instance's PCR steps for a call from its bound, and the flags of those beyond it (flags[-1]:
-// any), which the partition levels take; `fresh` (a pool's): there are none, so a failed instance steps on and only
-// its sticky word says so, from the first tick of its slot's request (fresh) on; `transposed`: the adjoint's bound.  Leaves `top` cleared for the next
-// call.
+// any), which the partition levels take.  `fresh` (a pool's): there are none, so such an instance steps on, watched, and
+// its sticky word (zero from the first tick of its slot's request, fresh, on) tells if a step fails the bound.
+// `transposed`: the adjoint's bound.  Leaves `top` cleared for the next call.
 __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __restrict__ inst,
                                                           const int32_t* __restrict__ members, int n,
                                                           unsigned long long* __restrict__ top, int* __restrict__ code,
                                                           int* __restrict__ flags, int* __restrict__ sticky,
                                                           ThetaLimits lim, const int32_t* __restrict__ fresh,
                                                           int transposed) {
-  const bool keep = fresh != nullptr;
+  const bool pool = fresh != nullptr;
   bool failed = false;
   for (int k = threadIdx.x; k < n; k += 256) {
     const int i = members[k];
@@ -352,13 +366,17 @@ __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __rest
         holds = holds && (theta == 0.0 || lim.rows[q - 1] * log2(theta) + log2(coupling) <= (q < kMaxS ? -56.0 : -55.0));
       s = holds ? q : s;
     }
-    if (s == 0) sticky[i] = 1;
-    else if (keep && fresh[i]) sticky[i] = 0;
-    failed = failed || s == 0;
-    flags[i] = s == 0 && !keep ? 1 : 0;
-    code[i] = s == 0 && keep ? kMaxS : s;
+    if (pool) {
+      if (fresh[i]) sticky[i] = 0;
+      code[i] = s == 0 ? kMaxS | kWatched : s;
+      flags[i] = 0;
+    } else {
+      code[i] = s;
+      flags[i] = s == 0 ? 1 : 0;
+      failed = failed || s == 0;
+    }
   }
-  const int any = __syncthreads_or(failed && !keep);
+  const int any = __syncthreads_or(failed);
   if (threadIdx.x == 0) flags[-1] = any ? 1 : 0;
 }
 
@@ -372,9 +390,12 @@ hipError_t deep_launch(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* wo
   // as many launches as instances with the fewest steps per launch need
   constexpr int kFewest = kDeepHalo >> kMaxS;
   const int64_t launches = (nsteps + kFewest - 1) / kFewest;
+  auto kernel = plan.pool ? btcs_deep_kernel<S, true> : btcs_deep_kernel<S, false>;
+  int* sticky = win_sticky(plan.win_flags.as<int>(), ctx->count);
+  const double lim = theta_limits().of[kMaxS - 1];
   for (int64_t j = 0; j < launches; ++j)
-    btcs_deep_kernel<S><<<n, kDeepLanes, 0, ctx->stream>>>(inst, wins, code, bufs[j & 1], bufs[(j & 1) ^ 1],
-                                                           static_cast<int>(j), static_cast<int>(nsteps));
+    kernel<<<n, kDeepLanes, 0, ctx->stream>>>(inst, wins, code, bufs[j & 1], bufs[(j & 1) ^ 1], static_cast<int>(j),
+                                              static_cast<int>(nsteps), sticky, lim);
   btcs_settle_kernel<S><<<n, 256, 0, ctx->stream>>>(inst, wins, code, work, u, static_cast<int>(nsteps));
   return hipGetLastError();
 }
