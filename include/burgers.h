@@ -126,7 +126,9 @@ typedef struct burgers_ctx burgers_ctx; /* opaque */
  *                    theta = 2(D + C)/(1 + 2D + C + sqrt((1 + C)^2 + 4D)), C = r max|u|.  On the automatic
  *                    path BTCS calls of three steps and more keep windows of 8192 rows on chip for several
  *                    steps, with the bound taken once, from the instance's state at the start of the call;
- *                    instances beyond it step by the partition levels.  Otherwise windows of 4096 rows
+ *                    instances beyond it step by the partition levels until a state is within it, by windows
+ *                    of one step from there on.  Otherwise (other calls, and contexts with a Dirichlet value
+ *                    beyond the bound or with long Crank-Nicolson or Newton systems) windows of 4096 rows
  *                    (2: of 8192 rows, in wider workgroups) take one step per launch and check the bound
  *                    themselves, and an instance with a window that fails it is solved again that step by
  *                    the partition levels.  Results do not depend, bit for bit, on how steps are spread over

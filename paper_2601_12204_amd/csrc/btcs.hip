@@ -19,6 +19,7 @@
 // path within its one rounding per step of the exact discrete solution.  Binary64 instructions issue at
 // half the binary32 rate on gfx950, but the solve is bound by its pivot chain's latency and its barriers
 // rather than by issue rate: a binary32-state step takes about as long as a binary64 one.
+#include <algorithm>
 #include <cmath>
 
 #include "interface.hpp"
@@ -26,6 +27,7 @@
 #include "newton_check.hpp"
 #include "staging.hpp"
 #include "stencil.hpp"
+#include "windows.hpp"
 
 #pragma clang fp contract(off)
 
@@ -377,8 +379,8 @@ __device__ __forceinline__ void reduced_solve(const PcrSpace<double, NT>& pcr, d
   }
 }
 
-// One system per workgroup.  `only` (optional): the systems of instances whose entry is nonzero; only[-1] is zero when
-// there is none.
+// One system per workgroup.  `only` (optional): the systems of instances whose entry is 1; only[-1] is zero when there
+// is none.
 template <int NT, int MC, bool EXACT = false>
 __global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
     const SysDesc* __restrict__ systems, const double* __restrict__ LA, const double* __restrict__ LC,
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(NT, MC == 16 ? 2 : 1) void btcs_reduced_kernel(
   const Pcr pcr{reinterpret_cast<T*>(smem), pcr_flags};
   if (only && only[-1] == 0) return;
   const SysDesc sys = systems[blockIdx.x];
-  if (only && only[sys.inst] == 0) return;
+  if (only && only[sys.inst] != 1) return;
   reduced_solve<NT, MC, EXACT>(pcr, reinterpret_cast<T*>(smem), sys, LA, LC, LD, LX);
 }
 
@@ -882,7 +884,7 @@ __global__ __launch_bounds__(kReduceBlock, 2) void btcs_array_reduce_kernel(
   if (only && only[-1] == 0) return;
   const ChunkBlock cb = blocks[blockIdx.x];
   const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;
+  if (only && only[sys.inst] != 1) return;
   const int k = cb.chunk0 + static_cast<int>(threadIdx.x);
   if (k >= sys.chunks) return;
   if (block_full(sys, cb.chunk0, min(kReduceBlock, sys.chunks - cb.chunk0))) array_reduce_chunk<true>(sys, k, LA, LC, LD);
@@ -897,7 +899,7 @@ __global__ __launch_bounds__(kReduceBlock, 2) void btcs_array_backsub_kernel(
   if (only && only[-1] == 0) return;
   const ChunkBlock cb = blocks[blockIdx.x];
   const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;
+  if (only && only[sys.inst] != 1) return;
   const int k = cb.chunk0 + static_cast<int>(threadIdx.x);
   if (k >= sys.chunks) return;
   if (block_full(sys, cb.chunk0, min(kReduceBlock, sys.chunks - cb.chunk0))) array_backsub_chunk<true>(sys, k, LA, LC, LD, LX);
@@ -947,7 +949,7 @@ __global__ __launch_bounds__(kReduceBlock, 4) void btcs_block_reduce_kernel(
   if (only && only[-1] == 0) return;         // no instance is left to the partition levels
   const ChunkBlock cb = blocks[blockIdx.x];
   const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;   // this instance's windows held
+  if (only && only[sys.inst] != 1) return;   // this instance's windows held
   const InstDesc d = inst[sys.inst];
   const bool dir = d.bc == kDirichlet;
   const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
@@ -1030,7 +1032,7 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
   if (only && only[-1] == 0) return;         // no instance is left to the partition levels
   const ChunkBlock cb = blocks[blockIdx.x];
   const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;   // this instance's windows held
+  if (only && only[sys.inst] != 1) return;   // this instance's windows held
   const InstDesc d = inst[sys.inst];
   const bool dir = d.bc == kDirichlet;
   const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
@@ -1042,44 +1044,86 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
   else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
 }
 
-// The reduced systems of a partition level, one workgroup each, in the narrowest width that holds the
-// level's widest system (small reduced systems leave most of a 512-lane workgroup idle).
-// The backward half of one step (from u, the solved unknowns in LX, to out) and the forward half of the next, whose
-// rows the block still holds in LDS.
-template <typename S>
+// Step `step` of a call, from u to out, of the instances beyond the windows' bound (state 1), whose solved unknowns
+// are in LX: the backward half of it and (NEXT) the forward half of the next step, whose rows the block still holds in
+// LDS.  The windows of one step take the step, and all later ones, of an instance whose state has come within the
+// bound (a workgroup takes one of either: the launch mostly finds nothing to do): top holds max|u| of step s's states at s mod 3, gathered as they are formed.  By the
+// maximum principle such an instance stays within it (its boundary values are, or the plan has no such calls), so steps
+// are solved alike however a call is split.
+template <typename S, bool NEXT>
 __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
-    const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems,
-    const ChunkBlock* __restrict__ blocks, const S* __restrict__ u, S* __restrict__ out,
-    double* __restrict__ LA, double* __restrict__ LC, double* __restrict__ LD, const double* __restrict__ LX,
-    const int* __restrict__ only) {
+    const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems, const ChunkBlock* __restrict__ blocks,
+    int n_blocks, const ChunkWin* __restrict__ wins, int n_wins, const S* __restrict__ u, S* __restrict__ out,
+    double* __restrict__ LA, double* __restrict__ LC, double* __restrict__ LD, const double* __restrict__ LX, int* state,
+    unsigned long long* top, int64_t count, int64_t step, double theta_lim) {
   using T = double;
+  constexpr int NT = kReduceBlock;
   constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
-  constexpr int kBytes = kStageBytes > BlockIfaceSpace::kBytes ? kStageBytes : BlockIfaceSpace::kBytes;
+  constexpr int kBlockBytes = kStageBytes > BlockIfaceSpace::kBytes ? kStageBytes : BlockIfaceSpace::kBytes;
+  constexpr int kBytes = kBlockBytes > WindowSpace<S, NT>::kBytes ? kBlockBytes : WindowSpace<S, NT>::kBytes;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kBytes];
   __shared__ int iface_flags[2 * kSpikeWaves];
+  __shared__ uint64_t iface_votes[2 * InterfaceSpace<T, NT>::kVoteWords];
+  __shared__ double wave_max[NT / 64];
+  if (state[-1] == 0) return;
   S* stage = reinterpret_cast<S*>(smem);
   T* lds = reinterpret_cast<T*>(smem);
+  auto within = [&](const InstDesc& d, int i) {
+    return step > 0 && theta_bound(d, __builtin_bit_cast(double, top[step % 3 * count + i])) <= theta_lim;
+  };
+  // a window, ...
+  const int turn = static_cast<int>(blockIdx.x);
+  const ChunkWin cw = turn < n_wins ? wins[turn] : ChunkWin{};
+  const int was = turn < n_wins ? state[cw.inst] : 0;
+  if (was != 0) {
+    const InstDesc d = inst[cw.inst];
+    if (was == 2 || within(d, cw.inst)) {
+      if (threadIdx.x == 0) state[cw.inst] = 2;   // (other workgroups of the launch find 1 or 2, and decide alike)
+      const InterfaceSpace<T, NT> ws{lds, lds + 3 * NT, iface_votes};
+      ws.clear_votes();
+      const Frame f(system_rows(d), cw);
+      const int dir = d.bc == kDirichlet ? 1 : 0;
+      window_load<S, NT, false>(u + d.off + dir, stage, f);
+      __syncthreads();
+      window_advance<S, NT>(ws, stage, f, cw, d, 1, kMaxPcr, [](const auto&) {});
+      S* __restrict__ y = out + d.off + dir;
+      window_kept<NT>(f, cw, [&](int k, int i) { y[k] = stage[padded(i)]; });
+      window_ends<S>(f, cw, d, out);
+      __syncthreads();                           // (the rows below take their place)
+    }
+  }
+  // ... then a block
+  if (turn >= n_blocks) return;
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
-  if (only && only[-1] == 0) return;
   const ChunkBlock cb = blocks[blockIdx.x];
   const SysDesc sys = systems[cb.sys];
-  if (only && only[sys.inst] == 0) return;
+  if (state[sys.inst] != 1) return;
   const InstDesc d = inst[sys.inst];
+  if (within(d, sys.inst)) return;
   const bool dir = d.bc == kDirichlet;
   const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
   int rs, re;
   block_rows(sys, cb.chunk0, rs, re);
   stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
   __syncthreads();
-  if (block_full(sys, cb.chunk0, Pb)) {
-    block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-    block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
-  } else {
-    block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-    block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+  const bool full = block_full(sys, cb.chunk0, Pb);
+  if (full) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  Magnitude m;
+  for (int i = threadIdx.x; i < re - rs; i += NT) m.take(static_cast<double>(stage[padded(i)]));
+  const double M = workgroup_max<NT>(m.value(), wave_max);
+  if (threadIdx.x == 0) {
+    atomicMax(top + (step + 1) % 3 * count + sys.inst, __builtin_bit_cast(unsigned long long, M));
+    if (cb.chunk0 == 0) top[(step + 2) % 3 * count + sys.inst] = 0;   // (the last step's, read by the launch before)
+  }
+  if constexpr (NEXT) {
+    if (full) block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
+    else block_reduce_body<false>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
   }
 }
 
+// The reduced systems of a partition level, one workgroup each, in the narrowest width that holds the
+// level's widest system (small reduced systems leave most of a 512-lane workgroup idle).
 void reduced_wg_launch(const BtcsPlan::Level& lv, double* LA, double* LC, double* LD, double* LX, hipStream_t st,
                        const int* only) {
   const SysDesc* sys = lv.wg->as<SysDesc>();
@@ -1115,7 +1159,7 @@ int stream_grid(int device) {
 
 // The partition levels' launches, forward and back to the level-0 unknowns' interfaces (levels_forward), and
 // the last back-substitution into the new state (levels_finish).  `only` (optional): only the instances whose
-// entry is nonzero; only[-1] is zero when there is none.
+// entry is 1; only[-1] is zero when there is none.
 template <typename S>
 void levels_forward(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const S* u, const int* only) {
   double* LA = ctx->level_a.as<double>();
@@ -1156,32 +1200,32 @@ void levels_finish(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc*
       inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), u, out, ctx->level_x.as<double>(), only);
 }
 
-// nsteps steps by the levels, the last one's rows in bufs[nsteps & 1] (u, work).  Where every system's reduced one
-// is solved whole, a step is two launches: one for those and one that ends the step and begins the next.
+// nsteps steps of the instances beyond the windows' bound, the last one's rows in bufs[nsteps & 1] (u, work).  Where
+// every system's reduced one is solved whole, a step is two launches: one for those and one that ends the step and
+// begins the next.
 template <typename S>
-void levels_run(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int64_t nsteps, const int* only) {
+void beyond_run(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int64_t nsteps) {
   const InstDesc* inst = ctx->inst.as<InstDesc>();
-  S* bufs[2] = {u, work};
-  if (plan.levels.size() != 2 || plan.levels[0].n_blocks == 0 || plan.levels[1].n_blocks > 0) {
-    for (int64_t s = 0; s < nsteps; ++s) {
-      levels_forward<S>(ctx, plan, inst, bufs[s & 1], only);
-      levels_finish<S>(ctx, plan, inst, bufs[s & 1], bufs[(s & 1) ^ 1], only);
-    }
-    return;
-  }
+  int* state = win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0);
+  unsigned long long* top = beyond_top(plan.deep_words.as<int>(), ctx->count);
   double* LA = ctx->level_a.as<double>();
   double* LC = ctx->level_c.as<double>();
   double* LD = ctx->level_d.as<double>();
   double* LX = ctx->level_x.as<double>();
   const auto& lv = plan.levels[0];
+  const double lim = btcs_window_limit();
+  const unsigned n = static_cast<unsigned>(std::max<int64_t>(lv.n_blocks, plan.n_turn));
+  const bool two = plan.levels.size() == 2 && plan.levels[1].n_blocks == 0;
+  S* bufs[2] = {u, work};
   for (int64_t s = 0; s < nsteps; ++s) {
-    if (s == 0) levels_forward<S>(ctx, plan, inst, u, only);
-    else reduced_wg_launch(plan.levels[1], LA, LC, LD, LX, ctx->stream, only);
-    if (s + 1 == nsteps) levels_finish<S>(ctx, plan, inst, bufs[s & 1], bufs[(s & 1) ^ 1], only);
-    else
-      btcs_block_turn_kernel<S><<<lv.n_blocks, kReduceBlock, 0, ctx->stream>>>(
-          inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), bufs[s & 1], bufs[(s & 1) ^ 1], LA, LC,
-          LD, LX, only);
+    const S* from = bufs[s & 1];
+    S* to = bufs[(s & 1) ^ 1];
+    if (s == 0 || !two) levels_forward<S>(ctx, plan, inst, from, state);
+    else reduced_wg_launch(plan.levels[1], LA, LC, LD, LX, ctx->stream, state);
+    auto kernel = two && s + 1 < nsteps ? btcs_block_turn_kernel<S, true> : btcs_block_turn_kernel<S, false>;
+    kernel<<<n, kReduceBlock, 0, ctx->stream>>>(inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks,
+                                                plan.turn->as<ChunkWin>(), static_cast<int>(plan.n_turn), from, to, LA, LC, LD, LX, state, top,
+                                                ctx->count, s, lim);
   }
 }
 
@@ -1333,12 +1377,13 @@ hipError_t launch_btcs_step(const burgers_ctx* ctx, const BtcsPlan& plan, const 
   return launch_step<float>(ctx, plan, u, out, step);
 }
 
-hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps,
-                              const int* only) {
-  if (ctx->dtype == BURGERS_F64) levels_run<double>(ctx, plan, static_cast<double*>(u), static_cast<double*>(work), nsteps, only);
-  else levels_run<float>(ctx, plan, static_cast<float*>(u), static_cast<float*>(work), nsteps, only);
+hipError_t launch_btcs_beyond(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps) {
+  if (ctx->dtype == BURGERS_F64) beyond_run<double>(ctx, plan, static_cast<double*>(u), static_cast<double*>(work), nsteps);
+  else beyond_run<float>(ctx, plan, static_cast<float*>(u), static_cast<float*>(work), nsteps);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && (nsteps & 1)) e = launch_copy_tiles(ctx, plan.copy->as<Tile>(), plan.n_copy, work, u, only);
+  if (e == hipSuccess && (nsteps & 1))
+    e = launch_copy_tiles(ctx, plan.copy->as<Tile>(), plan.n_copy, work, u,
+                          win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0));
   return e;
 }
 

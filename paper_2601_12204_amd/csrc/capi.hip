@@ -363,7 +363,7 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
   // fallback for failed bounds.  One step per launch: 4096 rows each (8192 when asked); on the automatic path
   // also windows of several steps, where they are all that steps through HBM (see enqueue_stepped)
   plan->win_rows = longmode == 2 ? cap : 4096;
-  std::vector<burgers::ChunkWin> windows, deep;
+  std::vector<burgers::ChunkWin> windows, deep, turn;
   std::vector<int32_t> windowed;
   bool only_windows = want == 0 && !burgers::tl_arena;
   auto add_windows = [&](int32_t i, int32_t R, bool is_cn) {
@@ -371,7 +371,13 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
     burgers::btcs_step_windows(i, R, periodic, plan->win_rows, is_cn, windows);
     if (is_cn) return;
     burgers::btcs_deep_windows(i, R, periodic, deep);
+    burgers::btcs_step_windows(i, R, periodic, 4096, false, turn);
     windowed.push_back(i);
+    // (boundary values beyond the bound may bring an instance within it beyond it again: every step is then judged
+    // by itself)
+    const burgers::InstDesc& d = ctx->inst_host[i];
+    const double edge = std::max(std::abs(d.a), std::abs(d.b));
+    only_windows = only_windows && burgers::btcs_window_theta(d, edge) <= burgers::btcs_window_limit() * (1.0 - 1e-9);
   };
   // whole-system systems grouped by width class (lanes, chunk)
   std::map<std::pair<int, int>, std::vector<SysDesc>> wg_state, resident, streamed, cn_chip, newton_chip;
@@ -500,13 +506,16 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
     const int64_t words = burgers::deep_words(ctx->count);
     plan->deep = std::make_unique<DevBuf>();
     plan->deep_inst = std::make_unique<DevBuf>();
+    plan->turn = std::make_unique<DevBuf>();
     if ((e = upload_on(ctx->stream, *plan->deep, deep)) != hipSuccess ||
         (e = upload_on(ctx->stream, *plan->deep_inst, windowed)) != hipSuccess ||
+        (e = upload_on(ctx->stream, *plan->turn, turn)) != hipSuccess ||
         (e = plan->deep_words.alloc(static_cast<size_t>(words) * sizeof(int), ctx->stream)) != hipSuccess ||
         (e = burgers::launch_clear_ints(ctx, plan->deep_words.as<int>(), words)) != hipSuccess)
       return from_hip(e);
     plan->n_deep = static_cast<int64_t>(deep.size());
     plan->n_deep_inst = static_cast<int64_t>(windowed.size());
+    plan->n_turn = static_cast<int64_t>(turn.size());
   }
   plan->levels.resize(red_sys.size());
   for (size_t l = 0; l < red_sys.size(); ++l) {
@@ -706,8 +715,7 @@ void btcs_tasks(burgers_ctx* ctx, int set, void* u, int64_t nsteps, std::vector<
     }});
     // (mostly idle: but each of its launches waits for the other chains' workgroups to leave a CU, about 9 us)
     tasks.push_back({chain_us(nsteps, 18.0, 0.0, 1.0), 2 * nsteps, [=]() {
-      return burgers::launch_btcs_levels(ctx, *pl, u, ctx->work.ptr, nsteps,
-                                         burgers::win_flag_slot(pl->win_flags.as<int>(), ctx->count, 0));
+      return burgers::launch_btcs_beyond(ctx, *pl, u, ctx->work.ptr, nsteps);
     }});
   } else if (pl->n_copy > 0) {
     const double nodes = static_cast<double>(pl->n_copy) * burgers::explicit_tile_nodes(ctx->dtype);

@@ -117,16 +117,22 @@ struct ChunkWin {
 };
 
 // Flags of truncated windows over `count` instances, one slot per step parity: slot p starts with a word
-// that is nonzero when any window of that step failed its bound, followed by one word per instance (the
-// instance must be redone); after both slots, a sticky word per instance (resident pools report it).
-// Fallback kernels read the slot's first word before anything else and exit when it is zero.
+// that is nonzero when any window of that step failed its bound, followed by one word per instance (1: the
+// partition levels take the instance); after both slots, a sticky word per instance (resident pools report it).
+// Fallback kernels read the slot's first word before anything else and exit when it is zero.  In a call by windows of
+// several steps slot 0 holds for all of them; an instance that comes within the bound turns from 1 to 2, and is stepped
+// by windows of one step from there on.
 inline int64_t win_flags_words(int64_t count) { return 3 * count + 2; }
 inline int* win_flag_slot(int* base, int64_t count, int64_t step) { return base + (step & 1) * (count + 1) + 1; }
 inline int* win_sticky(int* base, int64_t count) { return base + 2 * (count + 1); }
 // Words of the windows of several steps over `count` instances: per instance the bits of max|u| (64 bits, zero
-// between calls) and, after all of those, its PCR steps per solve for the call under way.
-inline int64_t deep_words(int64_t count) { return 3 * count; }
-inline int* deep_code(int* base, int64_t count) { return base + 2 * count; }
+// between calls), then those of the states of three consecutive steps of the instances beyond the bound (3 x 64 bits,
+// zero at the start of a call) and, after all of those, its PCR steps per solve for the call under way.
+inline int64_t deep_words(int64_t count) { return 9 * count; }
+inline unsigned long long* beyond_top(int* base, int64_t count) {
+  return reinterpret_cast<unsigned long long*>(base) + count;
+}
+inline int* deep_code(int* base, int64_t count) { return base + 8 * count; }
 
 // A block of consecutive chunks of one system (reduce and back-substitution kernels).
 struct ChunkBlock {
@@ -237,6 +243,8 @@ struct BtcsPlan {
   // calls of a few steps take the windows above
   std::unique_ptr<DevBuf> deep, deep_inst;   // ChunkWin[], int32[] (the windowed instances)
   int64_t n_deep = 0, n_deep_inst = 0;
+  std::unique_ptr<DevBuf> turn;              // ChunkWin[]: one-step windows of 4096 rows for those that come
+  int64_t n_turn = 0;                        // within the bound
   DevBuf deep_words;                         // see deep_words()
   bool transposed = false;                   // the windows solve the transposed systems (adjoint)
   bool pool = false;                         // a pool's windows: no levels, failed steps are reported
@@ -438,14 +446,16 @@ constexpr int kReduceBlock = 256;       // chunks per workgroup in the partition
 // One BTCS step of the plan from u to out; `step` counts the steps of the current call from 0 (it selects
 // the parity slot of the window flags, which launch_btcs_window_reset clears at the start of a call).
 hipError_t launch_btcs_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, void* out, int64_t step);
-// nsteps steps by the partition levels alone, the final states in u, for the instances whose entry of `only` is nonzero.
-hipError_t launch_btcs_levels(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps,
-                              const int* only);
+// nsteps steps of the instances that launch_btcs_bound flagged, the final states in u: by the partition levels, and by
+// one-step windows from the step on whose state is within the bound.
+hipError_t launch_btcs_beyond(const burgers_ctx* ctx, const BtcsPlan& plan, void* u, void* work, int64_t nsteps);
 // window.hip.  Windows of one step (`rows` of 4096 or 8192) and of several over a system of R > 16384 rows of
 // instance i, appended to `out`; how many of the latter cover any system of up to `rows` rows.
 void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, std::vector<ChunkWin>& out);
 void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out, bool adjoint = false);
 int64_t btcs_deep_windows_max(int64_t rows);
+double btcs_window_limit();   // the largest theta of the windows' bound, ...
+double btcs_window_theta(const InstDesc& d, double M);   // ... and that of an instance whose largest magnitude is M
 // One step of plan.win from u to out (inst: half-dt coefficients for Crank-Nicolson systems); the instances with
 // a window beyond the bound are flagged in `now`, and `next` is cleared.
 hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const void* u,

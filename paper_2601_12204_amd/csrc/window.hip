@@ -33,8 +33,6 @@
 
 #include "interface.hpp"
 #include "internal.hpp"
-#include "staging.hpp"
-#include "stencil.hpp"
 #include "windows.hpp"
 
 #pragma clang fp contract(off)
@@ -42,7 +40,6 @@
 namespace burgers {
 namespace {
 
-constexpr int kM = kChunkRows;
 constexpr int kMaxS = kMaxPcr;
 constexpr int kStepHalo = 1 << kMaxS;
 constexpr int kWatched = 8;   // beside the PCR steps of an instance's code: a pool's, beyond the bound at the tick's start
@@ -56,157 +53,10 @@ struct ThetaLimits {
 ThetaLimits theta_limits() {
   ThetaLimits t;
   for (int s = 1; s <= kMaxS; ++s) {
-    t.rows[s - 1] = s < kMaxS ? (kM << s) - 1 : 257;
+    t.rows[s - 1] = s < kMaxS ? (kChunkRows << s) - 1 : 257;
     t.of[s - 1] = std::exp2(-56.0 / t.rows[s - 1]) * (1.0 - (s < kMaxS ? 1e-9 : 1e-12));
   }
   return t;
-}
-
-__device__ __forceinline__ double theta_bound(const InstDesc& d, double M) {
-  const double C = d.r * M;
-  return 2.0 * (d.D + C) / ((1.0 + 2.0 * d.D + C) + __builtin_sqrt((1.0 + C) * (1.0 + C) + 4.0 * d.D));
-}
-
-// A running maximum of |v|, infinite once a value is not finite, so that its instance fails the bound (`zero` turns into
-// a NaN then, which the maximum itself would pass over).
-struct Magnitude {
-  double big = 0.0, zero = 0.0;
-  __device__ __forceinline__ void take(double v) {
-    big = __builtin_fmax(big, __builtin_fabs(v));
-    zero = __builtin_fma(v, 0.0, zero);
-  }
-  __device__ __forceinline__ double value() const { return zero == 0.0 ? big : __builtin_inf(); }
-};
-
-// LDS of a window: its rows staged between HBM and the lanes, overlaid by the interface solve.
-template <typename S, int NT>
-struct WindowSpace {
-  static constexpr int kStageBytes = padded_size(NT * kM) * static_cast<int>(sizeof(S));
-  static constexpr int kIface = InterfaceSpace<double, NT>::kBytes;
-  static constexpr int kBytes = kStageBytes > kIface ? kStageBytes : kIface;
-};
-
-// A window's place in its system.
-struct Frame {
-  Chunks ch;
-  int r0, total;           // its first row and its rows
-  __device__ __forceinline__ Frame(int R, const ChunkWin& w) : ch(R), r0(ch.base(w.first)), total(ch.rows(w.first, w.chunks)) {}
-};
-
-// The lane's chunk: its slots' first row counted from the window's, and its part in the solve.
-__device__ __forceinline__ int window_lane(const Frame& f, const ChunkWin& w, int t, SlotLane& l) {
-  int c = w.first + t, wrap = 0;
-  if (c >= f.ch.P) {
-    c -= f.ch.P;
-    wrap = f.ch.R;
-  }
-  const bool dummy = f.ch.lacks(c);
-  l.base = 0;
-  l.own = t < w.chunks;
-  l.dummy = dummy;
-  l.first = t == 0;
-  l.last = t == w.chunks - 1;
-  l.tie = t == 0 ? 0.0 : -1.0;
-  return f.ch.base(c) - (dummy ? 1 : 0) - f.r0 + wrap;   // (-1 for a first chunk of 15 rows)
-}
-
-// `steps` steps of a window's rows, from and to the staged rows; watch(de) sees the lane's rows before each of them.
-template <typename S, int NT, typename Watch>
-__device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>& ws, S* stage, const Frame& f,
-                                               const ChunkWin& w, const InstDesc& d, int steps, int pcr, Watch&& watch) {
-  const int t = threadIdx.x;
-  SlotLane l;
-  const int at = window_lane(f, w, t, l);
-  const bool dir = d.bc == kDirichlet;
-  const SlotRows rows{d.r, d.D, dir && w.first == 0 ? d.a : 0.0,
-                      dir && w.first + w.chunks == f.ch.P ? d.b : 0.0};
-  double al[kM], ga[kM], de[kM];
-#pragma unroll
-  for (int j = 0; j < kM; ++j)
-    de[j] = l.own ? static_cast<double>(stage[padded(j == 0 && at < 0 ? 0 : at + j)]) : 0.0;
-  __syncthreads();                           // every lane's rows read: the interface LDS overlays them
-  for (int step = 0; step < steps; ++step) {
-    watch(de);
-    double ia = 0.0, ib = 1.0, ic = 0.0, id = 0.0, y, yp;
-    if (l.own) slot_eliminate<kM, false>(rows, l, al, ga, de, ia, ib, ic, id);
-    window_solve<NT>(ws, w.chunks, pcr, l.own, l.dummy ? al[1] : al[0], l.dummy ? ga[1] : ga[0],
-                     l.dummy ? de[1] : de[0], al[kM - 2], ga[kM - 2], de[kM - 2], ia, ib, ic, id, y, yp);
-#pragma unroll
-    for (int j = 0; j < kM; ++j) de[j] = static_cast<double>(static_cast<S>(slot_value<kM>(j, al, ga, de, yp, y)));
-  }
-  __syncthreads();                           // the interface unknowns read before the rows are rewritten
-  SlotLane o;                                // (formed anew: not held across the solve)
-  const int to = window_lane(f, w, opaque_lane(t), o);
-  if (o.own) {
-#pragma unroll
-    for (int j = 0; j < kM; ++j)
-      if (j > 0 || !o.dummy) stage[padded(to + j)] = static_cast<S>(de[j]);
-  }
-  __syncthreads();
-}
-
-// The window's rows into LDS, every load in flight at once; MAX: also their largest magnitude (the lane's).
-template <typename S, int NT, bool MAX>
-__device__ __forceinline__ double window_load(const S* __restrict__ x, S* stage, const Frame& f) {
-  const int t = threadIdx.x;
-  S v[kM];
-  if (f.r0 + NT * kM <= f.ch.R) {              // (uniform) the rows from r0 on are there: one address
-    const S* __restrict__ p = x + f.r0;
-#pragma unroll
-    for (int j = 0; j < kM; ++j) v[j] = p[t + j * NT];
-  } else {
-#pragma unroll
-    for (int j = 0; j < kM; ++j) {
-      const int i = t + j * NT;
-      int k = f.r0 + (i < f.total ? i : f.total - 1);
-      if (k >= f.ch.R) k -= f.ch.R;
-      v[j] = x[k];
-    }
-  }
-  Magnitude m;                                 // (rows beyond the window's at most raise it)
-#pragma unroll
-  for (int j = 0; j < kM; ++j) {
-    if constexpr (MAX) m.take(static_cast<double>(v[j]));
-    stage[padded(t + j * NT)] = v[j];
-  }
-  return m.value();
-}
-
-// The window's kept rows, put(row of the system, row of the window); the lane index is formed anew.
-template <int NT, typename Put>
-__device__ __forceinline__ void window_kept(const Frame& f, const ChunkWin& w, Put&& put) {
-  int c = w.first + w.lo;
-  if (c >= f.ch.P) c -= f.ch.P;
-  const int first = f.ch.base(c), count = f.ch.rows(c, w.count);
-  const int from = first - f.r0 + (first < f.r0 ? f.ch.R : 0);
-  const int t = opaque_lane(static_cast<int>(threadIdx.x));
-#pragma unroll
-  for (int j = 0; j < kM; ++j) {
-    const int o = t + j * NT;
-    if (o < count) put(first + o, from + o);   // (kept chunks of a window do not wrap)
-  }
-}
-
-// The Dirichlet nodes next to the kept rows.
-template <typename S>
-__device__ __forceinline__ void window_ends(const Frame& f, const ChunkWin& w, const InstDesc& d, S* __restrict__ out) {
-  if (d.bc != kDirichlet || threadIdx.x != 0) return;
-  if (w.first + w.lo == 0) out[d.off] = static_cast<S>(d.a);
-  if (w.first + w.lo + w.count == f.ch.P) out[d.off + d.n - 1] = static_cast<S>(d.b);
-}
-
-__device__ __forceinline__ int system_rows(const InstDesc& d) { return d.bc == kDirichlet ? d.n - 2 : d.n; }
-
-template <int NT>
-__device__ __forceinline__ double workgroup_max(double big, double* wave_max) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) big = __builtin_fmax(big, __shfl_xor(big, m, 64));
-  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = big;
-  __syncthreads();
-  double M = 0.0;
-#pragma unroll
-  for (int k = 0; k < NT / 64; ++k) M = __builtin_fmax(M, wave_max[k]);
-  return M;
 }
 
 // One step per launch.  Every window evaluates the bound from its own rows and flags its instance when it
@@ -279,13 +129,13 @@ __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
   const int dir = d.bc == kDirichlet ? 1 : 0;
   window_load<S, NT, false>(u + d.off + dir, stage, f);
   __syncthreads();
-  window_advance<S, NT>(ws, stage, f, w, d, steps, pcr, [&](const double (&rows)[kM]) {
+  window_advance<S, NT>(ws, stage, f, w, d, steps, pcr, [&](const double (&rows)[kChunkRows]) {
     if constexpr (WATCH) {
       const int t = opaque_lane(static_cast<int>(threadIdx.x));
       if ((word & kWatched) && t >= w.lo && t < w.lo + w.count) {
         Magnitude m;
 #pragma unroll
-        for (int j = 0; j < kM; ++j) m.take(rows[j]);
+        for (int j = 0; j < kChunkRows; ++j) m.take(rows[j]);
         if (!(theta_bound(d, m.value()) <= theta_lim)) sticky[w.inst] = 1;
       }
     }
@@ -345,8 +195,9 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
 // `transposed`: the adjoint's bound.  Leaves `top` cleared for the next call.
 __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __restrict__ inst,
                                                           const int32_t* __restrict__ members, int n,
-                                                          unsigned long long* __restrict__ top, int* __restrict__ code,
-                                                          int* __restrict__ flags, int* __restrict__ sticky,
+                                                          unsigned long long* __restrict__ top,
+                                                          unsigned long long* __restrict__ beyond, int64_t count,
+                                                          int* __restrict__ code, int* __restrict__ flags, int* __restrict__ sticky,
                                                           ThetaLimits lim, const int32_t* __restrict__ fresh,
                                                           int transposed) {
   const bool pool = fresh != nullptr;
@@ -357,6 +208,7 @@ __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __rest
     double M = __builtin_bit_cast(double, top[i]);
     top[i] = 0;
     if (d.bc == kDirichlet) M = __builtin_fmax(M, __builtin_fmax(__builtin_fabs(d.a), __builtin_fabs(d.b)));
+    for (int q = 0; q < 3; ++q) beyond[static_cast<int64_t>(q) * count + i] = 0;
     const double theta = theta_bound(d, M), coupling = __builtin_fmax(d.D + d.r * M, 1.0);
     int s = 0;
 #pragma unroll
@@ -392,7 +244,7 @@ hipError_t deep_launch(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* wo
   const int64_t launches = (nsteps + kFewest - 1) / kFewest;
   auto kernel = plan.pool ? btcs_deep_kernel<S, true> : btcs_deep_kernel<S, false>;
   int* sticky = win_sticky(plan.win_flags.as<int>(), ctx->count);
-  const double lim = theta_limits().of[kMaxS - 1];
+  const double lim = btcs_window_limit();
   for (int64_t j = 0; j < launches; ++j)
     kernel<<<n, kDeepLanes, 0, ctx->stream>>>(inst, wins, code, bufs[j & 1], bufs[(j & 1) ^ 1], static_cast<int>(j),
                                               static_cast<int>(nsteps), sticky, lim);
@@ -404,9 +256,9 @@ template <typename S>
 hipError_t step_launch(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const S* u, S* out,
                        int* now, int* next, int* sticky) {
   const unsigned n = static_cast<unsigned>(plan.n_win);
-  const double lim = theta_limits().of[kMaxS - 1];
+  const double lim = btcs_window_limit();
   const ChunkWin* wins = plan.win->as<ChunkWin>();
-  if (plan.win_rows == kM * 512)
+  if (plan.win_rows == kChunkRows * 512)
     btcs_window_kernel<S, 512><<<n, 512, 0, ctx->stream>>>(inst, wins, u, out, now, next, sticky, lim);
   else
     btcs_window_kernel<S, 256><<<n, 256, 0, ctx->stream>>>(inst, wins, u, out, now, next, sticky, lim);
@@ -415,7 +267,7 @@ hipError_t step_launch(const burgers_ctx* ctx, const BtcsPlan& plan, const InstD
 
 // Windows of `lanes` chunks that lose `halo` chunks at either end, over a system of R rows.
 void chunk_windows(int32_t i, int32_t R, bool periodic, int lanes, int halo, bool cn, std::vector<ChunkWin>& out) {
-  const int64_t P = (static_cast<int64_t>(R) + kM - 1) / kM, kept = lanes - 2 * halo;
+  const int64_t P = (static_cast<int64_t>(R) + kChunkRows - 1) / kChunkRows, kept = lanes - 2 * halo;
   const int64_t n = (P + kept - 1) / kept, per = (P + n - 1) / n;   // evenly: a window's idle waves cost nothing
   for (int64_t c = 0; c < P; c += per) {
     const int64_t count = std::min(per, P - c);
@@ -429,15 +281,18 @@ void chunk_windows(int32_t i, int32_t R, bool periodic, int lanes, int halo, boo
 }  // namespace
 
 void btcs_step_windows(int32_t i, int32_t R, bool periodic, int rows, bool cn, std::vector<ChunkWin>& out) {
-  chunk_windows(i, R, periodic, rows / kM, kStepHalo, cn, out);
+  chunk_windows(i, R, periodic, rows / kChunkRows, kStepHalo, cn, out);
 }
 
 void btcs_deep_windows(int32_t i, int32_t R, bool periodic, std::vector<ChunkWin>& out, bool adjoint) {
   chunk_windows(i, R, periodic, kDeepLanes, adjoint ? kAdjDeepHalo : kDeepHalo, false, out);
 }
 
+double btcs_window_limit() { return theta_limits().of[kMaxS - 1]; }
+double btcs_window_theta(const InstDesc& d, double M) { return theta_bound(d, M); }
+
 int64_t btcs_deep_windows_max(int64_t rows) {
-  const int64_t P = (rows + kM - 1) / kM, kept = kDeepLanes - 2 * kDeepHalo;
+  const int64_t P = (rows + kChunkRows - 1) / kChunkRows, kept = kDeepLanes - 2 * kDeepHalo;
   return (P + kept - 1) / kept;
 }
 
@@ -458,7 +313,8 @@ hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const
   else
     btcs_top_kernel<float><<<n, 256, 0, ctx->stream>>>(inst, wins, static_cast<const float*>(u), top);
   btcs_decide_kernel<<<1, 256, 0, ctx->stream>>>(inst, plan.deep_inst->as<int32_t>(), static_cast<int>(plan.n_deep_inst),
-                                                 top, deep_code(plan.deep_words.as<int>(), ctx->count),
+                                                 top, beyond_top(plan.deep_words.as<int>(), ctx->count), ctx->count,
+                                                 deep_code(plan.deep_words.as<int>(), ctx->count),
                                                  win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0),
                                                  win_sticky(plan.win_flags.as<int>(), ctx->count), theta_limits(),
                                                  fresh, plan.transposed ? 1 : 0);

@@ -1,10 +1,13 @@
-// Windows of chunks of a long system: device code shared by the forward solver (window.hip) and the adjoint.
+// Windows of chunks of a long system: device code shared by the forward solvers (window.hip, and btcs.hip where a
+// system beyond the windows' bound comes within it) and the adjoint.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include "interface.hpp"
 #include "internal.hpp"
+#include "staging.hpp"
+#include "stencil.hpp"
 
 #pragma clang fp contract(off)
 
@@ -109,6 +112,157 @@ __device__ __forceinline__ void window_solve(const InterfaceSpace<double, NT>& w
   // (couplings left after S steps are dropped: at most theta^(n_S))
   y = d;
   yp = own ? w.rows[b * 3 * NT + 2 * NT + (t > 0 ? t - 1 : 0)] : 0.0;
+}
+
+// ---- Steps on windows (forward) ------------------------------------------------------------------------
+
+__host__ __device__ __forceinline__ double theta_bound(const InstDesc& d, double M) {
+  const double C = d.r * M;
+  return 2.0 * (d.D + C) / ((1.0 + 2.0 * d.D + C) + __builtin_sqrt((1.0 + C) * (1.0 + C) + 4.0 * d.D));
+}
+
+// A running maximum of |v|, infinite once a value is not finite, so that its instance fails the bound (`zero` turns into
+// a NaN then, which the maximum itself would pass over).
+struct Magnitude {
+  double big = 0.0, zero = 0.0;
+  __device__ __forceinline__ void take(double v) {
+    big = __builtin_fmax(big, __builtin_fabs(v));
+    zero = __builtin_fma(v, 0.0, zero);
+  }
+  __device__ __forceinline__ double value() const { return zero == 0.0 ? big : __builtin_inf(); }
+};
+
+// LDS of a window: its rows staged between HBM and the lanes, overlaid by the interface solve.
+template <typename S, int NT>
+struct WindowSpace {
+  static constexpr int kStageBytes = padded_size(NT * kChunkRows) * static_cast<int>(sizeof(S));
+  static constexpr int kIface = InterfaceSpace<double, NT>::kBytes;
+  static constexpr int kBytes = kStageBytes > kIface ? kStageBytes : kIface;
+};
+
+// A window's place in its system.
+struct Frame {
+  Chunks ch;
+  int r0, total;           // its first row and its rows
+  __device__ __forceinline__ Frame(int R, const ChunkWin& w) : ch(R), r0(ch.base(w.first)), total(ch.rows(w.first, w.chunks)) {}
+};
+
+// The lane's chunk: its slots' first row counted from the window's, and its part in the solve.
+__device__ __forceinline__ int window_lane(const Frame& f, const ChunkWin& w, int t, SlotLane& l) {
+  int c = w.first + t, wrap = 0;
+  if (c >= f.ch.P) {
+    c -= f.ch.P;
+    wrap = f.ch.R;
+  }
+  const bool dummy = f.ch.lacks(c);
+  l.base = 0;
+  l.own = t < w.chunks;
+  l.dummy = dummy;
+  l.first = t == 0;
+  l.last = t == w.chunks - 1;
+  l.tie = t == 0 ? 0.0 : -1.0;
+  return f.ch.base(c) - (dummy ? 1 : 0) - f.r0 + wrap;   // (-1 for a first chunk of 15 rows)
+}
+
+// `steps` steps of a window's rows, from and to the staged rows; watch(de) sees the lane's rows before each of them.
+template <typename S, int NT, typename Watch>
+__device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>& ws, S* stage, const Frame& f,
+                                               const ChunkWin& w, const InstDesc& d, int steps, int pcr, Watch&& watch) {
+  const int t = threadIdx.x;
+  SlotLane l;
+  const int at = window_lane(f, w, t, l);
+  const bool dir = d.bc == kDirichlet;
+  const SlotRows rows{d.r, d.D, dir && w.first == 0 ? d.a : 0.0,
+                      dir && w.first + w.chunks == f.ch.P ? d.b : 0.0};
+  double al[kChunkRows], ga[kChunkRows], de[kChunkRows];
+#pragma unroll
+  for (int j = 0; j < kChunkRows; ++j)
+    de[j] = l.own ? static_cast<double>(stage[padded(j == 0 && at < 0 ? 0 : at + j)]) : 0.0;
+  __syncthreads();                           // every lane's rows read: the interface LDS overlays them
+  for (int step = 0; step < steps; ++step) {
+    watch(de);
+    double ia = 0.0, ib = 1.0, ic = 0.0, id = 0.0, y, yp;
+    if (l.own) slot_eliminate<kChunkRows, false>(rows, l, al, ga, de, ia, ib, ic, id);
+    constexpr int k = kChunkRows - 2;
+    window_solve<NT>(ws, w.chunks, pcr, l.own, l.dummy ? al[1] : al[0], l.dummy ? ga[1] : ga[0],
+                     l.dummy ? de[1] : de[0], al[k], ga[k], de[k], ia, ib, ic, id, y, yp);
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j)
+      de[j] = static_cast<double>(static_cast<S>(slot_value<kChunkRows>(j, al, ga, de, yp, y)));
+  }
+  __syncthreads();                           // the interface unknowns read before the rows are rewritten
+  SlotLane o;                                // (formed anew: not held across the solve)
+  const int to = window_lane(f, w, opaque_lane(t), o);
+  if (o.own) {
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j)
+      if (j > 0 || !o.dummy) stage[padded(to + j)] = static_cast<S>(de[j]);
+  }
+  __syncthreads();
+}
+
+// The window's rows into LDS, every load in flight at once; MAX: also their largest magnitude (the lane's).
+template <typename S, int NT, bool MAX>
+__device__ __forceinline__ double window_load(const S* __restrict__ x, S* stage, const Frame& f) {
+  const int t = threadIdx.x;
+  S v[kChunkRows];
+  if (f.r0 + NT * kChunkRows <= f.ch.R) {      // (uniform) the rows from r0 on are there: one address
+    const S* __restrict__ p = x + f.r0;
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j) v[j] = p[t + j * NT];
+  } else {
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j) {
+      const int i = t + j * NT;
+      int k = f.r0 + (i < f.total ? i : f.total - 1);
+      if (k >= f.ch.R) k -= f.ch.R;
+      v[j] = x[k];
+    }
+  }
+  Magnitude m;                                 // (rows beyond the window's at most raise it)
+#pragma unroll
+  for (int j = 0; j < kChunkRows; ++j) {
+    if constexpr (MAX) m.take(static_cast<double>(v[j]));
+    stage[padded(t + j * NT)] = v[j];
+  }
+  return m.value();
+}
+
+// The window's kept rows, put(row of the system, row of the window); the lane index is formed anew.
+template <int NT, typename Put>
+__device__ __forceinline__ void window_kept(const Frame& f, const ChunkWin& w, Put&& put) {
+  int c = w.first + w.lo;
+  if (c >= f.ch.P) c -= f.ch.P;
+  const int first = f.ch.base(c), count = f.ch.rows(c, w.count);
+  const int from = first - f.r0 + (first < f.r0 ? f.ch.R : 0);
+  const int t = opaque_lane(static_cast<int>(threadIdx.x));
+#pragma unroll
+  for (int j = 0; j < kChunkRows; ++j) {
+    const int o = t + j * NT;
+    if (o < count) put(first + o, from + o);   // (kept chunks of a window do not wrap)
+  }
+}
+
+// The Dirichlet nodes next to the kept rows.
+template <typename S>
+__device__ __forceinline__ void window_ends(const Frame& f, const ChunkWin& w, const InstDesc& d, S* __restrict__ out) {
+  if (d.bc != kDirichlet || threadIdx.x != 0) return;
+  if (w.first + w.lo == 0) out[d.off] = static_cast<S>(d.a);
+  if (w.first + w.lo + w.count == f.ch.P) out[d.off + d.n - 1] = static_cast<S>(d.b);
+}
+
+__device__ __forceinline__ int system_rows(const InstDesc& d) { return d.bc == kDirichlet ? d.n - 2 : d.n; }
+
+template <int NT>
+__device__ __forceinline__ double workgroup_max(double big, double* wave_max) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) big = __builtin_fmax(big, __shfl_xor(big, m, 64));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = big;
+  __syncthreads();
+  double M = 0.0;
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) M = __builtin_fmax(M, wave_max[k]);
+  return M;
 }
 
 }  // namespace burgers
