@@ -962,9 +962,10 @@ __global__ __launch_bounds__(kReduceBlock, 4) void btcs_block_reduce_kernel(
 }
 
 
-// Backward half of a block-partition step after the block is staged (FULL: every chunk has kRedChunk rows).
-template <bool FULL, typename S>
-__device__ __forceinline__ void block_backsub_body(const BlockIfaceSpace& w, S* stage, const InstDesc& d,
+// Backward half of a block-partition step after the block is staged (FULL: every chunk has kRedChunk rows; TOP: returns
+// the lane's share of the new rows' largest magnitude).
+template <bool FULL, bool TOP, typename S>
+__device__ __forceinline__ double block_backsub_body(const BlockIfaceSpace& w, S* stage, const InstDesc& d,
                                                    const SysDesc& sys, const ChunkBlock& cb, int rs, int re,
                                                    int Pb, const S* __restrict__ u, S* __restrict__ out,
                                                    const double* __restrict__ LX) {
@@ -993,12 +994,16 @@ __device__ __forceinline__ void block_backsub_body(const BlockIfaceSpace& w, S* 
     }
   }
   __syncthreads();                             // the interface rows read before the stage is rewritten
+  Magnitude top;
   if (tid < Pb) {
     const LdsDst<S> dst{stage, rs};
 #pragma unroll
     for (int j = 0; j < kRedChunk; ++j) {
-      if (j < m - 1) dst.write(j, s + j, __builtin_fma(-ga[j], y, __builtin_fma(-al[j], yp, de[j])));
-      if (j == m - 1) dst.write(j, s + j, y);
+      const double v = j == m - 1 ? y : __builtin_fma(-ga[j], y, __builtin_fma(-al[j], yp, de[j]));
+      if (j < m) {
+        dst.write(j, s + j, v);
+        if constexpr (TOP) top.take(static_cast<double>(static_cast<S>(v)));
+      }
     }
   }
   __syncthreads();
@@ -1009,6 +1014,7 @@ __device__ __forceinline__ void block_backsub_body(const BlockIfaceSpace& w, S* 
     if (cb.chunk0 == 0) out[d.off] = static_cast<S>(d.a);
     if (cb.chunk0 + kReduceBlock >= sys.chunks) out[d.off + d.n - 1] = static_cast<S>(d.b);
   }
+  return top.value();
 }
 
 // Block partition, backward half: the block repeats the forward reduction (keeping its chunks'
@@ -1040,22 +1046,22 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_backsub_kernel(
   block_rows(sys, cb.chunk0, rs, re);
   stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
   __syncthreads();
-  if (block_full(sys, cb.chunk0, Pb)) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-  else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  if (block_full(sys, cb.chunk0, Pb)) block_backsub_body<true, false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  else block_backsub_body<false, false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
 }
 
 // Step `step` of a call, from u to out, of the instances beyond the windows' bound (state 1), whose solved unknowns
 // are in LX: the backward half of it and (NEXT) the forward half of the next step, whose rows the block still holds in
-// LDS.  The windows of one step take the step, and all later ones, of an instance whose state has come within the
-// bound (a workgroup takes one of either: the launch mostly finds nothing to do): top holds max|u| of step s's states at s mod 3, gathered as they are formed.  By the
-// maximum principle such an instance stays within it (its boundary values are, or the plan has no such calls), so steps
-// are solved alike however a call is split.
+// LDS.  The windows of one step take the step, and all later ones, of an instance whose state has come within the bound
+// (a workgroup takes one of either: the launch mostly finds nothing to do).  beyond tells at s mod 3 if step s's state
+// is not within it, from its rows as they are formed.  By the maximum principle an instance within the bound stays
+// within it (its boundary values are, or the plan has no such calls), so steps are solved alike however a call is split.
 template <typename S, bool NEXT>
 __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
     const InstDesc* __restrict__ inst, const SysDesc* __restrict__ systems, const ChunkBlock* __restrict__ blocks,
     int n_blocks, const ChunkWin* __restrict__ wins, int n_wins, const S* __restrict__ u, S* __restrict__ out,
     double* __restrict__ LA, double* __restrict__ LC, double* __restrict__ LD, const double* __restrict__ LX, int* state,
-    unsigned long long* top, int64_t count, int64_t step, double theta_lim) {
+    int* beyond, int64_t count, int64_t step, double theta_lim) {
   using T = double;
   constexpr int NT = kReduceBlock;
   constexpr int kStageBytes = padded_size(kRedRows) * static_cast<int>(sizeof(S));
@@ -1065,41 +1071,38 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
   __shared__ int iface_flags[2 * kSpikeWaves];
   __shared__ uint64_t iface_votes[2 * InterfaceSpace<T, NT>::kVoteWords];
   __shared__ double wave_max[NT / 64];
-  if (state[-1] == 0) return;
+  // (both roles' tables and states read at once: their latencies would add up)
+  const int turn = static_cast<int>(blockIdx.x);
+  const int any = state[-1];
+  const ChunkWin cw = wins[turn < n_wins ? turn : 0];
+  const ChunkBlock cb = blocks[turn < n_blocks ? turn : 0];
+  if (any == 0) return;
+  const int* now = beyond + step % 3 * count;
+  const SysDesc sys = systems[cb.sys];
+  const int win_state = state[cw.inst], win_beyond = now[cw.inst];
+  const int sys_state = state[sys.inst], sys_beyond = now[sys.inst];
   S* stage = reinterpret_cast<S*>(smem);
   T* lds = reinterpret_cast<T*>(smem);
-  auto within = [&](const InstDesc& d, int i) {
-    return step > 0 && theta_bound(d, __builtin_bit_cast(double, top[step % 3 * count + i])) <= theta_lim;
-  };
   // a window, ...
-  const int turn = static_cast<int>(blockIdx.x);
-  const ChunkWin cw = turn < n_wins ? wins[turn] : ChunkWin{};
-  const int was = turn < n_wins ? state[cw.inst] : 0;
-  if (was != 0) {
+  if (turn < n_wins && (win_state == 2 || (win_state == 1 && step > 0 && win_beyond == 0))) {
+    if (threadIdx.x == 0) state[cw.inst] = 2;    // (other workgroups of the launch find 1 or 2, and decide alike)
     const InstDesc d = inst[cw.inst];
-    if (was == 2 || within(d, cw.inst)) {
-      if (threadIdx.x == 0) state[cw.inst] = 2;   // (other workgroups of the launch find 1 or 2, and decide alike)
-      const InterfaceSpace<T, NT> ws{lds, lds + 3 * NT, iface_votes};
-      ws.clear_votes();
-      const Frame f(system_rows(d), cw);
-      const int dir = d.bc == kDirichlet ? 1 : 0;
-      window_load<S, NT, false>(u + d.off + dir, stage, f);
-      __syncthreads();
-      window_advance<S, NT>(ws, stage, f, cw, d, 1, kMaxPcr, [](const auto&) {});
-      S* __restrict__ y = out + d.off + dir;
-      window_kept<NT>(f, cw, [&](int k, int i) { y[k] = stage[padded(i)]; });
-      window_ends<S>(f, cw, d, out);
-      __syncthreads();                           // (the rows below take their place)
-    }
+    const InterfaceSpace<T, NT> ws{lds, lds + 3 * NT, iface_votes};
+    ws.clear_votes();
+    const Frame f(system_rows(d), cw);
+    const int dir = d.bc == kDirichlet ? 1 : 0;
+    window_load<S, NT, false>(u + d.off + dir, stage, f);
+    __syncthreads();
+    window_advance<S, NT>(ws, stage, f, cw, d, 1, kMaxPcr, [](const auto&) {});
+    S* __restrict__ y = out + d.off + dir;
+    window_kept<NT>(f, cw, [&](int k, int i) { y[k] = stage[padded(i)]; });
+    window_ends<S>(f, cw, d, out);
+    __syncthreads();                             // (the rows below take their place)
   }
   // ... then a block
-  if (turn >= n_blocks) return;
   const BlockIfaceSpace w{lds, lds + 3 * BlockIfaceSpace::kN, iface_flags};
-  const ChunkBlock cb = blocks[blockIdx.x];
-  const SysDesc sys = systems[cb.sys];
-  if (state[sys.inst] != 1) return;
+  if (turn >= n_blocks || sys_state != 1 || (step > 0 && sys_beyond == 0)) return;
   const InstDesc d = inst[sys.inst];
-  if (within(d, sys.inst)) return;
   const bool dir = d.bc == kDirichlet;
   const int Pb = min(kReduceBlock, sys.chunks - cb.chunk0);
   int rs, re;
@@ -1107,14 +1110,12 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
   stage_in(stage, u + d.off + (dir ? 1 : 0) + rs, re - rs);
   __syncthreads();
   const bool full = block_full(sys, cb.chunk0, Pb);
-  if (full) block_backsub_body<true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-  else block_backsub_body<false>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
-  Magnitude m;
-  for (int i = threadIdx.x; i < re - rs; i += NT) m.take(static_cast<double>(stage[padded(i)]));
-  const double M = workgroup_max<NT>(m.value(), wave_max);
+  const double top = full ? block_backsub_body<true, true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX)
+                          : block_backsub_body<false, true>(w, stage, d, sys, cb, rs, re, Pb, u, out, LX);
+  const double M = workgroup_max<NT>(top, wave_max);
   if (threadIdx.x == 0) {
-    atomicMax(top + (step + 1) % 3 * count + sys.inst, __builtin_bit_cast(unsigned long long, M));
-    if (cb.chunk0 == 0) top[(step + 2) % 3 * count + sys.inst] = 0;   // (the last step's, read by the launch before)
+    if (!(theta_bound(d, M) <= theta_lim)) beyond[(step + 1) % 3 * count + sys.inst] = 1;
+    if (cb.chunk0 == 0) beyond[(step + 2) % 3 * count + sys.inst] = 0;   // (the last step's, read by the launch before)
   }
   if constexpr (NEXT) {
     if (full) block_reduce_body<true>(w, stage, d, sys, cb, rs, Pb, LA, LC, LD);
@@ -1207,7 +1208,7 @@ template <typename S>
 void beyond_run(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int64_t nsteps) {
   const InstDesc* inst = ctx->inst.as<InstDesc>();
   int* state = win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0);
-  unsigned long long* top = beyond_top(plan.deep_words.as<int>(), ctx->count);
+  int* beyond = deep_beyond(plan.deep_words.as<int>(), ctx->count);
   double* LA = ctx->level_a.as<double>();
   double* LC = ctx->level_c.as<double>();
   double* LD = ctx->level_d.as<double>();
@@ -1224,8 +1225,8 @@ void beyond_run(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* work, int
     else reduced_wg_launch(plan.levels[1], LA, LC, LD, LX, ctx->stream, state);
     auto kernel = two && s + 1 < nsteps ? btcs_block_turn_kernel<S, true> : btcs_block_turn_kernel<S, false>;
     kernel<<<n, kReduceBlock, 0, ctx->stream>>>(inst, lv.sys->as<SysDesc>(), lv.blocks->as<ChunkBlock>(), lv.n_blocks,
-                                                plan.turn->as<ChunkWin>(), static_cast<int>(plan.n_turn), from, to, LA, LC, LD, LX, state, top,
-                                                ctx->count, s, lim);
+                                                plan.turn->as<ChunkWin>(), static_cast<int>(plan.n_turn), from, to, LA,
+                                                LC, LD, LX, state, beyond, ctx->count, s, lim);
   }
 }
 

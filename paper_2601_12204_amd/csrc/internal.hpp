@@ -126,13 +126,11 @@ inline int64_t win_flags_words(int64_t count) { return 3 * count + 2; }
 inline int* win_flag_slot(int* base, int64_t count, int64_t step) { return base + (step & 1) * (count + 1) + 1; }
 inline int* win_sticky(int* base, int64_t count) { return base + 2 * (count + 1); }
 // Words of the windows of several steps over `count` instances: per instance the bits of max|u| (64 bits, zero
-// between calls), then those of the states of three consecutive steps of the instances beyond the bound (3 x 64 bits,
-// zero at the start of a call) and, after all of those, its PCR steps per solve for the call under way.
-inline int64_t deep_words(int64_t count) { return 9 * count; }
-inline unsigned long long* beyond_top(int* base, int64_t count) {
-  return reinterpret_cast<unsigned long long*>(base) + count;
-}
-inline int* deep_code(int* base, int64_t count) { return base + 8 * count; }
+// between calls) and, after all of those, its PCR steps per solve for the call under way; then, for the instances beyond
+// the bound, whether the states of three consecutive steps are (zero at the start of a call).
+inline int64_t deep_words(int64_t count) { return 6 * count; }
+inline int* deep_code(int* base, int64_t count) { return base + 2 * count; }
+inline int* deep_beyond(int* base, int64_t count) { return base + 3 * count; }
 
 // A block of consecutive chunks of one system (reduce and back-substitution kernels).
 struct ChunkBlock {

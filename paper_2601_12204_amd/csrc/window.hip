@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
 __global__ __launch_bounds__(256) void btcs_decide_kernel(const InstDesc* __restrict__ inst,
                                                           const int32_t* __restrict__ members, int n,
                                                           unsigned long long* __restrict__ top,
-                                                          unsigned long long* __restrict__ beyond, int64_t count,
+                                                          int* __restrict__ beyond, int64_t count,
                                                           int* __restrict__ code, int* __restrict__ flags, int* __restrict__ sticky,
                                                           ThetaLimits lim, const int32_t* __restrict__ fresh,
                                                           int transposed) {
@@ -313,7 +313,7 @@ hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const
   else
     btcs_top_kernel<float><<<n, 256, 0, ctx->stream>>>(inst, wins, static_cast<const float*>(u), top);
   btcs_decide_kernel<<<1, 256, 0, ctx->stream>>>(inst, plan.deep_inst->as<int32_t>(), static_cast<int>(plan.n_deep_inst),
-                                                 top, beyond_top(plan.deep_words.as<int>(), ctx->count), ctx->count,
+                                                 top, deep_beyond(plan.deep_words.as<int>(), ctx->count), ctx->count,
                                                  deep_code(plan.deep_words.as<int>(), ctx->count),
                                                  win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0),
                                                  win_sticky(plan.win_flags.as<int>(), ctx->count), theta_limits(),
