@@ -18,7 +18,7 @@
 // PCR steps the couplings are within (D + C) theta^(n_S - 1).  With (D + C) theta^257 <= 2^-55 (S = 4) or (D + C)
 // theta^(n_S) <= 2^-56 (S < 4), theta from the largest |u| at the start of the call (the states' maximum principle), what
 // is dropped costs about 2^-53 max|mu| at most.  Systems beyond the bound are solved whole by one workgroup of 1024
-// lanes (up to 16384 rows, with registers spilled) or by the partition levels' array path.
+// lanes (up to 16384 rows) or by the partition levels' array path.
 #include "interface.hpp"
 #include "internal.hpp"
 #include "staging.hpp"
@@ -244,6 +244,62 @@ __device__ __forceinline__ void reverse_steps(const AdjSpace<NT, MC>& ws, const 
   if (slot) *slot = g;
 }
 
+// The same of a whole system on 1024 lanes, whose 128 registers hold the elimination and no states beside it: each step
+// reads u^k for its rows and, once mu stands where the elimination was, u^(k+1) for the finish, with nothing in flight
+// behind the solve.  (256 systems of 16384 rows, us per reverse step: 26.5; 49 with both states and a prefetch in
+// registers as above, most of them spilled.)
+template <int NT, int MC, int M, bool FULL, typename Lay, typename State>
+__device__ __forceinline__ void reverse_steps_lean(const AdjSpace<NT, MC>& ws, const InstDesc& d, const Lay& lay,
+                                                   const SlotLane& l, const State& state, int k_lo, int k_hi,
+                                                   const double* __restrict__ lam_in, double* __restrict__ lam_out,
+                                                   double* __restrict__ slot) {
+  double de[M];
+  auto read = [&](const double* src, double (&out)[M]) {
+    double V[2 * ((M + 1) / 2)];
+#pragma unroll
+    for (int j = 0; j < M; ++j) out[j] = 0.0;    // (or the last step's values are carried for lanes without rows)
+    fetch<M>(src, lay, V);
+    spread<M>(V, ws.region, lay, out);
+  };
+  read(lam_in, de);
+  double g = *slot;
+  for (int k = k_hi - 1; k >= k_lo; --k) {
+    unsigned up = 0;                             // bit j: y_j >= 0
+    double y, yp;
+    {
+      double al[M], ga[M], Y[M], yl, yr, ia, ib, ic, id;
+      read(state(k), Y);
+      neighbours<NT>(Y, ws.ends, lay.L, true, l.dummy, yl, yr);
+#pragma unroll
+      for (int j = 0; j < M; ++j) up |= Y[j] >= 0.0 ? 1u << j : 0u;
+      up = static_cast<unsigned>(opaque_lane(static_cast<int>(up)));   // (formed here, not from Y kept)
+      slot_eliminate<M, FULL>(TransposedRows<M>{Y, yl, yr, d.r, d.D}, l, al, ga, de, ia, ib, ic, id);
+      const bool f = !FULL && l.dummy;
+      interface_solve<double, NT, true>(ws.iface, lay.L, f ? al[1] : al[0], f ? ga[1] : ga[0], f ? de[1] : de[0],
+                                        al[M - 2], ga[M - 2], de[M - 2], ia, ib, ic, id, y, yp);
+#pragma unroll
+      for (int j = 0; j < M; ++j) de[j] = slot_value<M>(j, al, ga, de, yp, y);   // mu
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    double X[M], xl, xr;
+    read(state(k + 1), X);
+    neighbours<NT>(X, ws.ends, lay.L, true, l.dummy, xl, xr);   // (the solve's barriers follow the last read of ends)
+    if (l.first) xl = d.a;
+    if (l.last) xr = d.b;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      const double xm = j > 0 ? X[j > 0 ? j - 1 : 0] : xl, xp = j < M - 1 ? X[j < M - 1 ? j + 1 : j] : xr;
+      const double G = up >> j & 1u ? d.r * (X[j] - xm) : d.r * (xp - X[j]);
+      const double term = __builtin_fma(-de[j], (2.0 * X[j] - xm) - xp, g);
+      g = j == 0 && l.dummy ? g : term;
+      de[j] = (1.0 - G) * de[j];
+    }
+    wg_barrier<true>();                          // ends read before they are written again
+  }
+  put_rows<M>(de, ws.region, lay, 0, lay.R, lam_out);
+  *slot = g;
+}
+
 template <int NT, int MC>
 struct AdjWholeRun {
   const AdjSpace<NT, MC>& ws;
@@ -260,8 +316,11 @@ struct AdjWholeRun {
     const WholeLayout<M> lay(d, R, P);
     const SlotLane l = slot_lane<M, FULL>(t, R, P, dir);
     auto state = [&](int k) { return (k == 0 ? u0 : useg + static_cast<int64_t>(k - 1) * ustride) + d.off; };
-    reverse_steps<NT, MC, M, FULL, false>(ws, d, lay, l, l.first, l.last, 0, state, k_lo, k_hi, lamp + d.off,
-                                          lam + d.off, 0, R, l.own ? slot + t : nullptr);
+    if constexpr (NT == 1024)
+      reverse_steps_lean<NT, MC, M, FULL>(ws, d, lay, l, state, k_lo, k_hi, lamp + d.off, lam + d.off, slot + t);
+    else
+      reverse_steps<NT, MC, M, FULL, false>(ws, d, lay, l, l.first, l.last, 0, state, k_lo, k_hi, lamp + d.off,
+                                            lam + d.off, 0, R, l.own ? slot + t : nullptr);
   }
 };
 
