@@ -994,7 +994,7 @@ __device__ __forceinline__ double block_backsub_body(const BlockIfaceSpace& w, S
     }
   }
   __syncthreads();                             // the interface rows read before the stage is rewritten
-  Magnitude top;
+  Magnitude<S> top;
   if (tid < Pb) {
     const LdsDst<S> dst{stage, rs};
 #pragma unroll
@@ -1002,7 +1002,7 @@ __device__ __forceinline__ double block_backsub_body(const BlockIfaceSpace& w, S
       const double v = j == m - 1 ? y : __builtin_fma(-ga[j], y, __builtin_fma(-al[j], yp, de[j]));
       if (j < m) {
         dst.write(j, s + j, v);
-        if constexpr (TOP) top.take(static_cast<double>(static_cast<S>(v)));
+        if constexpr (TOP) top.take(static_cast<S>(v));
       }
     }
   }
@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
     __syncthreads();
     window_advance<S, NT>(ws, stage, f, cw, d, 1, kMaxPcr, [](const auto&) {});
     S* __restrict__ y = out + d.off + dir;
-    window_kept<NT>(f, cw, [&](int k, int i) { y[k] = stage[padded(i)]; });
+    window_kept<NT, kStepHalo>(f, cw, [&](int k, int i) { y[k] = stage[padded(i)]; });
     window_ends<S>(f, cw, d, out);
     __syncthreads();                             // (the rows below take their place)
   }

@@ -41,7 +41,6 @@ namespace burgers {
 namespace {
 
 constexpr int kMaxS = kMaxPcr;
-constexpr int kStepHalo = 1 << kMaxS;
 constexpr int kWatched = 8;   // beside the PCR steps of an instance's code: a pool's, beyond the bound at the tick's start
 
 // The largest theta for S PCR steps, with slack for rounding (of its own evaluation, and for S < 4 of the growth of
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
     }
   }
   window_advance<S, NT>(ws, stage, f, w, d, 1, kMaxS, [](const auto&) {});
-  window_kept<NT>(f, w, [&](int k, int i) {
+  window_kept<NT, kStepHalo>(f, w, [&](int k, int i) {
     const S val = stage[padded(i)];
     y[k] = w.cn ? static_cast<S>(2.0 * static_cast<double>(val) - static_cast<double>(x[k])) : val;
   });
@@ -133,7 +132,7 @@ __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
     if constexpr (WATCH) {
       const int t = opaque_lane(static_cast<int>(threadIdx.x));
       if ((word & kWatched) && t >= w.lo && t < w.lo + w.count) {
-        Magnitude m;
+        Magnitude<double> m;
 #pragma unroll
         for (int j = 0; j < kChunkRows; ++j) m.take(rows[j]);
         if (!(theta_bound(d, m.value()) <= theta_lim)) sticky[w.inst] = 1;
@@ -141,7 +140,7 @@ __global__ __launch_bounds__(kDeepLanes, 4) void btcs_deep_kernel(
     }
   });
   S* __restrict__ y = out + d.off + dir;
-  window_kept<NT>(f, w, [&](int k, int i) { y[k] = stage[padded(i)]; });
+  window_kept<NT, kDeepHalo>(f, w, [&](int k, int i) { y[k] = stage[padded(i)]; });
   window_ends<S>(f, w, d, out);
 }
 
@@ -182,9 +181,9 @@ __global__ __launch_bounds__(256) void btcs_top_kernel(const InstDesc* __restric
   int c = w.first + w.lo;
   if (c >= f.ch.P) c -= f.ch.P;
   const int first = f.ch.base(c), count = f.ch.rows(c, w.count);
-  Magnitude m;
+  Magnitude<S> m;
 #pragma unroll 8
-  for (int i = threadIdx.x; i < count; i += 256) m.take(static_cast<double>(x[first + i]));
+  for (int i = threadIdx.x; i < count; i += 256) m.take(x[first + i]);
   const double M = workgroup_max<256>(m.value(), wave_max);
   if (threadIdx.x == 0) atomicMax(top + w.inst, __builtin_bit_cast(unsigned long long, M));
 }

@@ -15,6 +15,7 @@ namespace burgers {
 
 constexpr int kChunkRows = 16;     // rows (slots) of a window's chunk
 constexpr int kMaxPcr = 4;         // PCR steps of a window's solve at most
+constexpr int kStepHalo = 1 << kMaxPcr;   // chunks lost at either end of a window over one step
 constexpr int kDeepLanes = 512;
 // Chunks lost at either end of a window over a launch of several steps: with S = 3, the usual case at ten times
 // the CFL step, 6 steps a launch (one grid of 2^24 rows, 128 steps: 32 chunks 3.48 ms, 48: 3.16, 64: 3.21).
@@ -123,13 +124,19 @@ __host__ __device__ __forceinline__ double theta_bound(const InstDesc& d, double
 
 // A running maximum of |v|, infinite once a value is not finite, so that its instance fails the bound (`zero` turns into
 // a NaN then, which the maximum itself would pass over).
+template <typename S>
 struct Magnitude {
-  double big = 0.0, zero = 0.0;
-  __device__ __forceinline__ void take(double v) {
-    big = __builtin_fmax(big, __builtin_fabs(v));
-    zero = __builtin_fma(v, 0.0, zero);
+  S big = S(0), zero = S(0);
+  __device__ __forceinline__ void take(S v) {
+    if constexpr (sizeof(S) == 8) {
+      big = __builtin_fmax(big, __builtin_fabs(v));
+      zero = __builtin_fma(v, 0.0, zero);
+    } else {
+      big = __builtin_fmaxf(big, __builtin_fabsf(v));
+      zero = __builtin_fmaf(v, 0.0f, zero);
+    }
   }
-  __device__ __forceinline__ double value() const { return zero == 0.0 ? big : __builtin_inf(); }
+  __device__ __forceinline__ double value() const { return zero == S(0) ? static_cast<double>(big) : __builtin_inf(); }
 };
 
 // LDS of a window: its rows staged between HBM and the lanes, overlaid by the interface solve.
@@ -175,9 +182,17 @@ __device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>&
   const SlotRows rows{d.r, d.D, dir && w.first == 0 ? d.a : 0.0,
                       dir && w.first + w.chunks == f.ch.P ? d.b : 0.0};
   double al[kChunkRows], ga[kChunkRows], de[kChunkRows];
+  // (a window without short chunks, as most are: its lanes' rows begin at multiples of 16, one address each)
+  const bool plain = f.total == kChunkRows * w.chunks;
+  if (plain) {
+    const S* rows_at = stage + padded(kChunkRows * t);
 #pragma unroll
-  for (int j = 0; j < kChunkRows; ++j)
-    de[j] = l.own ? static_cast<double>(stage[padded(j == 0 && at < 0 ? 0 : at + j)]) : 0.0;
+    for (int j = 0; j < kChunkRows; ++j) de[j] = l.own ? static_cast<double>(rows_at[j]) : 0.0;
+  } else {
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j)
+      de[j] = l.own ? static_cast<double>(stage[padded(j == 0 && at < 0 ? 0 : at + j)]) : 0.0;
+  }
   __syncthreads();                           // every lane's rows read: the interface LDS overlays them
   for (int step = 0; step < steps; ++step) {
     watch(de);
@@ -192,8 +207,13 @@ __device__ __forceinline__ void window_advance(const InterfaceSpace<double, NT>&
   }
   __syncthreads();                           // the interface unknowns read before the rows are rewritten
   SlotLane o;                                // (formed anew: not held across the solve)
-  const int to = window_lane(f, w, opaque_lane(t), o);
-  if (o.own) {
+  const int again = opaque_lane(t), to = window_lane(f, w, again, o);
+  if (plain) {
+    S* rows_at = stage + padded(kChunkRows * again);
+#pragma unroll
+    for (int j = 0; j < kChunkRows; ++j)
+      if (o.own) rows_at[j] = static_cast<S>(de[j]);
+  } else if (o.own) {
 #pragma unroll
     for (int j = 0; j < kChunkRows; ++j)
       if (j > 0 || !o.dummy) stage[padded(to + j)] = static_cast<S>(de[j]);
@@ -219,17 +239,18 @@ __device__ __forceinline__ double window_load(const S* __restrict__ x, S* stage,
       v[j] = x[k];
     }
   }
-  Magnitude m;                                 // (rows beyond the window's at most raise it)
+  Magnitude<S> m;                              // (rows beyond the window's at most raise it)
 #pragma unroll
   for (int j = 0; j < kChunkRows; ++j) {
-    if constexpr (MAX) m.take(static_cast<double>(v[j]));
+    if constexpr (MAX) m.take(v[j]);
     stage[padded(t + j * NT)] = v[j];
   }
   return m.value();
 }
 
-// The window's kept rows, put(row of the system, row of the window); the lane index is formed anew.
-template <int NT, typename Put>
+// The window's kept rows, put(row of the system, row of the window), of NT - 2 HALO chunks at most; the lane index is
+// formed anew.
+template <int NT, int HALO, typename Put>
 __device__ __forceinline__ void window_kept(const Frame& f, const ChunkWin& w, Put&& put) {
   int c = w.first + w.lo;
   if (c >= f.ch.P) c -= f.ch.P;
@@ -237,7 +258,7 @@ __device__ __forceinline__ void window_kept(const Frame& f, const ChunkWin& w, P
   const int from = first - f.r0 + (first < f.r0 ? f.ch.R : 0);
   const int t = opaque_lane(static_cast<int>(threadIdx.x));
 #pragma unroll
-  for (int j = 0; j < kChunkRows; ++j) {
+  for (int j = 0; j < (kChunkRows * (NT - 2 * HALO) + NT - 1) / NT; ++j) {
     const int o = t + j * NT;
     if (o < count) put(first + o, from + o);   // (kept chunks of a window do not wrap)
   }
