@@ -466,6 +466,8 @@ burgers_status ensure_btcs(burgers_ctx* ctx, int set) {
       g.shape = burgers::WidthClass{kv.first.first, kv.first.second, stream};
       g.sys = std::make_unique<DevBuf>();
       g.n = static_cast<int32_t>(kv.second.size());
+      g.exact = std::all_of(kv.second.begin(), kv.second.end(),
+                            [&](const SysDesc& sd) { return sd.rows == g.shape.lanes * g.shape.chunk; });
       hipError_t err = upload_on(ctx->stream, *g.sys, kv.second);
       if (err != hipSuccess) return err;
       out.push_back(std::move(g));

@@ -202,6 +202,7 @@ struct WgGroup {
   WidthClass shape;
   std::unique_ptr<DevBuf> sys;               // SysDesc[]
   int32_t n = 0;
+  bool exact = false;                        // every one of them has lanes x chunk rows
 };
 
 // Launch list of the BTCS solve for a set of instances, built once per context and set.
