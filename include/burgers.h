@@ -139,7 +139,7 @@ typedef struct burgers_ctx burgers_ctx; /* opaque */
  *                  of each scheme) and those stepped through HBM (explicit windows, per-step BTCS
  *                  solves).  0 (default): the groups run concurrently, on side streams of the context
  *                  forked from and joined back into its stream with events (parallel branches of a
- *                  captured graph); 1: one after another on the context's stream.
+ *                  captured graph); 1: one after another on the context's stream.  (Gradients likewise.)
  *   btcs_pipeline  how the per-step path (btcs_path 1) solves systems of exactly 8192 rows: 1 persistent
  *                  workgroups, one per CU, each walking its share of the systems with the next system's
  *                  rows streaming into LDS while it solves the current one (systems whose first row is

@@ -1526,7 +1526,7 @@ burgers_status burgers_adjoint(burgers_ctx* ctx, const void* u0, const void* lam
         if (in == lam_next) return hipSuccess;
         return burgers::launch_copy_tiles(ctx, ap.long_copy->as<Tile>(), ap.n_long_copy, in, lam_next, beyond);
       }});
-    if ((e = burgers::run_tasks(ctx, tasks, false)) != hipSuccess) return note(ctx, e);
+    if ((e = burgers::run_tasks(ctx, tasks, ctx->plan.serial == 1)) != hipSuccess) return note(ctx, e);
     if (!ctx->set_btcs.empty()) std::swap(lam, lam_next);
   }
   const bool split = lam_e != lam && !ctx->set_explicit.empty() && !ctx->set_btcs.empty();

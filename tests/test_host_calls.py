@@ -26,3 +26,26 @@ assert fake.fake_streams_live() > made
 lib.burgers_destroy(ctx)
 assert fake.fake_streams_live() == made and fake.fake_events_live() == events
 """, tmp_path)
+
+
+def test_serial_gradients_keep_to_the_callers_stream(tmp_path):
+    """plan.serial = 1: every launch of a gradient goes to the context's stream, with one checkpoint segment and with
+    several; without it the chains fork."""
+    fake_hip.run("""
+batch = W.random_batch(7, 12, 3, 20000)
+for p in batch.problems:
+    p.dt = 1e-4
+ctx = create(batch.problems)
+u, lam, g, gn = (state(batch.problems) for _ in range(4))
+at = lambda a: vp(a.ctypes.data)
+def gradient(ckpt):
+    fake.fake_reset()
+    assert lib.burgers_adjoint(ctx, at(u), at(lam), i64(40), i64(ckpt), at(g), at(gn)) == 0
+    assert fake.fake_launches() > 0
+    return fake.fake_streams_used()
+assert gradient(10) > 1
+assert lib.burgers_set_plan(ctx, ctypes.byref(B.CPlan(0, 0, 0, 0, 0, 0, 1, 0))) == 0
+for ckpt in (40, 10, 1):
+    assert gradient(ckpt) == 1 and fake.fake_stream_used(MAIN), ckpt
+lib.burgers_destroy(ctx)
+""", tmp_path)
