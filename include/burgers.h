@@ -322,7 +322,7 @@ burgers_status burgers_set_plan(burgers_ctx* ctx, const burgers_plan* plan);
  * with the others at their best so far, and only the knobs that matter for the context's instances:
  * the explicit path and, when some instance exceeds the on-chip limit, the temporal-blocking depth of
  * its windows (4, 8, 16, 32, 64, 128, 256 steps per pass over HBM); the lanes per 8192-row BTCS system
- * (512, 1024); the solver of BTCS systems longer than 8192 rows (truncated windows of 4096 or 8192 rows,
+ * (512, 1024); the solver of BTCS systems longer than 16384 rows (truncated windows of 4096 or 8192 rows,
  * or the partition levels: the crossover between one-pass windows and the three-pass partition method);
  * concurrent launch groups on or off; and graph replay on or off.  Each candidate runs twice and the
  * second run is timed.  *best (optional) receives the chosen plan and *best_ms (optional) its time.  The

@@ -9,13 +9,15 @@
 //   mu = A(y)^{-T} lam',   lam = (1 - G) mu,   G_i = r [H (x_i - x_{i-1}) + (1 - H)(x_{i+1} - x_i)],
 //   dJ/dD += -sum_i mu_i (2 x_i - x_{i-1} - x_{i+1}),
 // with the Dirichlet values standing in as x_0 = a, x_{n-1} = b.  A^T is tridiagonal with the neighbours'
-// coefficients (sub p_{i-1}, super l_{i+1}, the cyclic corners swapped); it is assembled with unit
-// diagonal into binary64 arrays and solved by the partition solver's array path.
+// coefficients (sub p_{i-1}, super l_{i+1}, the cyclic corners swapped).  adjoint_btcs.hip solves it on chip; here are
+// the explicit reverse steps and, for the BTCS systems of more than 16384 rows that are beyond the windows' bound, the
+// array path: A^T assembled with unit diagonal into binary64 arrays, solved by the partition levels, and finished.
 //
-// dJ/dD is accumulated per tile of nodes in a fixed order (for the explicit instances per tile and step,
-// whatever the grouping of steps into launches), so the sums are deterministic.
+// dJ/dD is accumulated in a fixed order, whatever the grouping of steps into launches: per 16 nodes of an explicit
+// instance and per chunk of a BTCS system over all steps, per tile of nodes and step on the array path.
 #include "internal.hpp"
 #include "stencil.hpp"
+#include "wave.hpp"
 
 #pragma clang fp contract(off)
 
@@ -67,35 +69,10 @@ constexpr int kAdjRegion = 32 * (kAdjChunk + 1);   // a half-wave's chunks, padd
 static_assert(64 * kAdjChunk == kAdjWinNodes && kAdjChunk == kAdjSumNodes, "window layout");
 static_assert(kAdjRun % kAdjGroup == 0 && kAdjRun + kAdjGroup - 1 <= kAdjHalo, "run of a launch");
 
-__device__ __forceinline__ int apad(int i) { return i + (i >> 4); }
+__device__ __forceinline__ int fresh_lane() { return opaque_lane(static_cast<int>(threadIdx.x) & 63); }
 
-// A lane index that the compiler cannot treat as known, so that the addresses built on it are formed
-// where they are used rather than kept live across the step loop.
-__device__ __forceinline__ int fresh_lane() {
-  int v = static_cast<int>(threadIdx.x) & 63;
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
-// Wave-private LDS exchanges are ordered by the wave's own in-order LDS accesses; the fences keep the
-// compiler from moving them.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Whole-wave DPP moves: the value of the lane before (after), around the wave.
-template <int CTRL>
-__device__ __forceinline__ double wave_rotate(double x) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const int lo = static_cast<int>(b & 0xffffffffu), hi = static_cast<int>(b >> 32);
-  const uint32_t l = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
-  const uint32_t h = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false));
-  return __builtin_bit_cast(double, (static_cast<uint64_t>(h) << 32) | l);
-}
-__device__ __forceinline__ double from_left(double x) { return wave_rotate<0x13C>(x); }
-__device__ __forceinline__ double from_right(double x) { return wave_rotate<0x134>(x); }
+__device__ __forceinline__ double from_left(double x) { return wave_move<0x13C>(x); }
+__device__ __forceinline__ double from_right(double x) { return wave_move<0x134>(x); }
 
 // Instance nodes of the window nodes lane, lane + 64, lane + 128, ...: an instance shorter than the window is gone
 // around as often as it takes (beyond a Dirichlet window's end the nodes are any).

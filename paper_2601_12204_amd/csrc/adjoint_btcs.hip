@@ -30,14 +30,6 @@
 namespace burgers {
 namespace {
 
-__device__ __forceinline__ int apad(int i) { return i + (i >> 4); }
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Where a lane's rows lie: lane t of L holds rows [row(t), row(t + 1)) (past a periodic system's end in a window),
 // node(k) is the instance node of such a row.
 template <int M>

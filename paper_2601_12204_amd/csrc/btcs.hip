@@ -138,21 +138,18 @@ __device__ __forceinline__ void stage_transpose(T* st, const T (&v)[MC], int R, 
 // reduced rows are
 //   F row:  AF * E_prev + F + CF * E      = DF
 //   E row:  AE * F      + E + CE * F_next = DE.
-// IN_PLACE: de[j] holds row j's old state value on entry (read just before de[j] is overwritten).
-template <typename T, int M, bool IN_PLACE = false, typename Src>
+template <typename T, int M, typename Src>
 __device__ __forceinline__ void chunk_eliminate(const Src& src, int s, int m, int R, T (&al)[M],
                                                 T (&ga)[M], T (&de)[M], T& AF, T& CF, T& DF, T& AE,
                                                 T& CE, T& DE) {
   T a0, b0, c0, d0;
-  if constexpr (IN_PLACE) src.row_value(de[0], s, R, a0, b0, c0, d0);
-  else src.row(0, s, R, a0, b0, c0, d0);
+  src.row(0, s, R, a0, b0, c0, d0);
   // forward: x_j + al[j] x_0 + ga[j] x_{j+1} = de[j]
 #pragma unroll
   for (int j = 1; j < M; ++j) {
     if (j < m) {
       T aj, bj, cj, dj;
-      if constexpr (IN_PLACE) src.row_value(de[j], s + j, R, aj, bj, cj, dj);
-      else src.row(j, s + j, R, aj, bj, cj, dj);
+      src.row(j, s + j, R, aj, bj, cj, dj);
       // (binary64 only: one reciprocal per pivot; in binary32, scaling all three coefficients by one
       // rounded reciprocal biases the row enough to accumulate over many steps)
       if (j == 1) {
@@ -208,19 +205,6 @@ __device__ __forceinline__ void chunk_recover(const Dst& dst, int s, int m, cons
   for (int j = 1; j < M; ++j) {
     if (j < m - 1) dst.write(j, s + j, __builtin_fma(-ga[j], E, __builtin_fma(-al[j], F, de[j])));
     if (j == m - 1) dst.write(j, s + j, E);
-  }
-}
-
-// In-place recovery for the resident solver: de[j] becomes row j's new value, rounded through the
-// state type S exactly as a store to and reload from the state buffer would round it.
-template <typename S, typename T, int M>
-__device__ __forceinline__ void chunk_recover_in_place(int m, const T (&al)[M], const T (&ga)[M], T (&de)[M],
-                                                       T F, T E) {
-  de[0] = static_cast<T>(static_cast<S>(F));
-#pragma unroll
-  for (int j = 1; j < M; ++j) {
-    if (j < m - 1) de[j] = static_cast<T>(static_cast<S>(__builtin_fma(-ga[j], E, __builtin_fma(-al[j], F, de[j]))));
-    if (j == m - 1) de[j] = static_cast<T>(static_cast<S>(E));
   }
 }
 
@@ -801,7 +785,7 @@ __device__ __forceinline__ int block_iface_step(const BlockIfaceSpace& w, const 
   if (tid < Pb) {
     chunk_span(cb.chunk0 + tid, sys.rows, sys.chunks, s, m);
     if constexpr (FULL) m = kRedChunk;         // the value chunk_span gives, as a constant
-    interface_eliminate<T, kRedChunk, false>(LdsRows<S>{stage, rs, d.r, d.D, DirichletEnds{d.a, d.b, dir}}, s, m,
+    interface_eliminate<T, kRedChunk>(LdsRows<S>{stage, rs, d.r, d.D, DirichletEnds{d.a, d.b, dir}}, s, m,
                                              sys.rows, al, ga, de, ia, ib, ic, id);
 #pragma unroll
     for (int j = 0; j < kRedChunk; ++j) {
@@ -1243,8 +1227,7 @@ hipError_t launch_step(const burgers_ctx* ctx, const BtcsPlan& plan, const void*
   if (plan.n_win > 0) {
     int* now = win_flag_slot(plan.win_flags.as<int>(), ctx->count, step);
     const hipError_t e = launch_btcs_windows(ctx, plan, inst, u, out, now,
-                                             win_flag_slot(plan.win_flags.as<int>(), ctx->count, step + 1),
-                                             win_sticky(plan.win_flags.as<int>(), ctx->count));
+                                             win_flag_slot(plan.win_flags.as<int>(), ctx->count, step + 1));
     if (e != hipSuccess) return e;
     only = now;
   }

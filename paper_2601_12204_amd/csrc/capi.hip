@@ -315,9 +315,7 @@ burgers_status ensure_explicit(burgers_ctx* ctx, int set) {
     if ((e = upload_on(ctx->stream, *plan->whole, whole)) != hipSuccess || (e = upload_on(ctx->stream, *plan->win, win)) != hipSuccess ||
         (e = upload_on(ctx->stream, *plan->win_copy, wc)) != hipSuccess)
       return from_hip(e);
-    plan->n_whole = static_cast<int64_t>(whole.size());
     plan->n_win = static_cast<int64_t>(win.size());
-    plan->n_whole_rk4 = std::count_if(whole.begin(), whole.end(), [](const BlockTile& b) { return b.rk4 != 0; });
     plan->n_win_rk4 = std::count_if(win.begin(), win.end(), [](const BlockTile& b) { return b.rk4 != 0; });
     plan->n_win_copy = static_cast<int64_t>(wc.size());
   }
@@ -806,9 +804,6 @@ burgers_status advance(burgers_ctx* ctx, void* u, int64_t nsteps, int set, int s
 }
 
 
-// Adjoint launch lists: 256-node tiles of every instance (explicit and BTCS lists), one dJ/dD slot per
-// tile, and the partition hierarchy over the transposed BTCS systems, which sit at the start of the
-// adjoint arrays followed by their reduced rows.
 // Partition hierarchy for systems stored as unit-diagonal rows in binary64 arrays: root (instance, row
 // offset, rows) triples; systems of up to 8192 rows are solved whole, longer ones reduced by chunk-
 // partition levels whose reduced rows are appended after `rows_used` (updated).
@@ -918,6 +913,9 @@ burgers_status ensure_newton(burgers_ctx* ctx, const std::vector<int32_t>& membe
   return BURGERS_OK;
 }
 
+// Launch lists and buffers of the adjoint: windows and dJ/dD slots of the explicit instances, the BTCS systems by the
+// solver of their transposed ones (whole, windows and what takes those beyond the bound), and the array path's hierarchy
+// over the systems of more than 16384 rows, which sit at the start of the adjoint arrays followed by their reduced rows.
 burgers_status ensure_adjoint(burgers_ctx* ctx) {
   if (ctx->adjoint) return BURGERS_OK;
   auto ap = std::make_unique<burgers::AdjointPlan>();

@@ -26,6 +26,7 @@
 //    bitwise identical results.
 #include "internal.hpp"
 #include "stencil.hpp"
+#include "wave.hpp"
 
 #pragma clang fp contract(off)
 
@@ -132,7 +133,6 @@ __global__ __launch_bounds__(kStreamThreads) void explicit_stream_kernel(
 // every 16 nodes so that lanes reading their 16-node chunks (a stride of 17 elements) hit distinct banks.
 template <int NT>
 constexpr int stage_nodes() { return NT * kBlockChunk / 2; }
-__device__ __forceinline__ int spad(int i) { return i + (i >> 4); }
 
 // One step of a lane's chunk: out[j] from in[j-1], in[j], in[j+1], with the neighbours' end values
 // `left` and `right`; fixed nodes (a Dirichlet end, a window edge) keep their value: they run the same
@@ -292,8 +292,7 @@ __device__ __forceinline__ void record_window(const T (&x)[kBlockChunk], T* stag
   constexpr int M = kBlockChunk, kHalf = 32, kRegion = kHalf * (M + 1);
   static_assert((NT / 64) * kRegion <= stage_nodes<NT>() + stage_nodes<NT>() / 16 + 1,
                 "every wave's region must fit in the staging buffer");
-  int lt = static_cast<int>(threadIdx.x);
-  asm volatile("" : "+v"(lt));
+  const int lt = opaque_lane(static_cast<int>(threadIdx.x));
   const int lane = lt & 63, wave = lt >> 6;
   T* region = stage + wave * kRegion;
   const int lo = bt.lo, hi = bt.lo + bt.count;
@@ -301,16 +300,14 @@ __device__ __forceinline__ void record_window(const T (&x)[kBlockChunk], T* stag
   for (int h = 0; h < 2; ++h) {
     if ((lane >> 5) == h) {
 #pragma unroll
-      for (int j = 0; j < M; ++j) region[spad(M * (lane & 31) + j)] = x[j];
+      for (int j = 0; j < M; ++j) region[apad(M * (lane & 31) + j)] = x[j];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     const int w0 = M * (64 * wave + kHalf * h);   // window node of the half-wave's first slot
 #pragma unroll
     for (int i = 0; i < kHalf * M / 64; ++i) {
       const int q = lane + 64 * i;
-      const T v = region[spad(q)];
+      const T v = region[apad(q)];
       const int w = w0 + q;
       if (w >= lo && w < hi) {
         int g = bt.first + w;
@@ -318,9 +315,7 @@ __device__ __forceinline__ void record_window(const T (&x)[kBlockChunk], T* stag
         rec[g] = v;
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
   }
 }
 
@@ -366,13 +361,13 @@ __device__ __forceinline__ void block_body(const BlockTile& bt, const InstDesc& 
     for (int w = r0 + t; w < r1; w += NT) {
       int g = bt.first + w;
       if (g >= n) g -= n;
-      stage[spad(w - r0)] = src[g];
+      stage[apad(w - r0)] = src[g];
     }
     __syncthreads();
     if (active && (h == 0) == (t < half)) {
 #pragma unroll
       for (int j = 0; j < M; ++j)
-        if (EXACT || j < m) v[j] = stage[spad(s + j - r0)];
+        if (EXACT || j < m) v[j] = stage[apad(s + j - r0)];
     }
     __syncthreads();
   }
@@ -447,7 +442,7 @@ __device__ __forceinline__ void block_body(const BlockTile& bt, const InstDesc& 
     if (active && (h == 0) == (t < half)) {
 #pragma unroll
       for (int j = 0; j < M; ++j)
-        if (EXACT || j < m) stage[spad(s + j - r0)] = v[j];
+        if (EXACT || j < m) stage[apad(s + j - r0)] = v[j];
     }
     __syncthreads();
     const int o0 = r0 > bt.lo ? r0 : bt.lo;
@@ -455,7 +450,7 @@ __device__ __forceinline__ void block_body(const BlockTile& bt, const InstDesc& 
     for (int w = o0 + t; w < o1; w += NT) {
       int g = bt.first + w;
       if (g >= n) g -= n;
-      dst[g] = stage[spad(w - r0)];
+      dst[g] = stage[apad(w - r0)];
     }
     __syncthreads();
   }
@@ -540,22 +535,6 @@ __global__ __launch_bounds__(kBlockThreads) void explicit_record_kernel(
 // 256, which shared workgroups; here 56 and 94 ns.  A wave per instance of up to 1024 nodes, each with 64
 // lanes of M nodes, and several waves with overlapping outer lanes for longer ones were tried too: the
 // latter lost to the blocks, whose barriers the chip's other workgroups cover.)
-// Whole-wave DPP move of a lane value: CTRL 0x138 / 0x130 from lane - 1 / lane + 1 (lane 0 / lane 63 keep
-// their own), 0x13C / 0x134 the same with wrap-around.
-template <int CTRL>
-__device__ __forceinline__ float wave_move(float x) {
-  const int b = __builtin_bit_cast(int, x);
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, CTRL, 0xf, 0xf, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double wave_move(double x) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const int lo = static_cast<int>(b & 0xffffffffu), hi = static_cast<int>(b >> 32);
-  const uint32_t l = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
-  const uint32_t h = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false));
-  return __builtin_bit_cast(double, (static_cast<uint64_t>(h) << 32) | l);
-}
-
 // Neighbours' end values of a lane's chunk x: `left` the last of the lane before, `right` the first of the
 // lane after.  ROT: around the wave.  A lane whose slot 0 is no node (`dummy`) offers its slot 1 and takes
 // `left` into slot 0, so that slot 1 reads it there.

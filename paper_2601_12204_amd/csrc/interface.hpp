@@ -6,6 +6,7 @@
 
 #include "internal.hpp"
 #include "stencil.hpp"
+#include "wave.hpp"
 
 #pragma clang fp contract(off)
 
@@ -84,9 +85,8 @@ __device__ __forceinline__ void pcr_combine(T a0, T c0, T d0, T am, T cm, T dm, 
 // neighbouring lanes.
 
 // Eliminates the interior rows and returns the interface row's coefficients (ia on the neighbour
-// x_{m-2}, ib, ic on the row after the chunk, id).  IN_PLACE: de[j] holds row j's old state value on
-// entry; otherwise the source assembles row j itself.
-template <typename T, int M, bool IN_PLACE = true, typename Src>
+// x_{m-2}, ib, ic on the row after the chunk, id).
+template <typename T, int M, typename Src>
 __device__ __forceinline__ void interface_eliminate(const Src& src, int s, int m, int R, T (&al)[M], T (&ga)[M],
                                                     T (&de)[M], T& ia, T& ib, T& ic, T& id) {
   const DirichletEnds& ends = src.ends;
@@ -94,8 +94,7 @@ __device__ __forceinline__ void interface_eliminate(const Src& src, int s, int m
   for (int j = 0; j < M; ++j) {
     if (j < m) {
       T aj, bj, cj, dj;
-      if constexpr (IN_PLACE) src.row_value(de[j], s + j, R, aj, bj, cj, dj);
-      else src.row(j, s + j, R, aj, bj, cj, dj);
+      src.row(j, s + j, R, aj, bj, cj, dj);
       if (j == 0 && ends.dirichlet && s == 0) {   // x_{-1} = a
         dj = __builtin_fma(-aj, static_cast<T>(ends.a), dj);
         aj = T(0);
@@ -166,23 +165,6 @@ struct NextChunk {
   T y;            // y_{t+1}
 };
 
-// A binary64 value of the lane at byte address `at` (4 x lane); of the lane before / after by a whole-wave DPP move
-// around the wave (CTRL 0x13C / 0x134).
-__device__ __forceinline__ double lane_value(double v, int at) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(at, static_cast<int>(b & 0xffffffffu)));
-  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(at, static_cast<int>(b >> 32)));
-  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
-}
-template <int CTRL>
-__device__ __forceinline__ double rotated(double v) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const int l = static_cast<int>(b & 0xffffffffu), h = static_cast<int>(b >> 32);
-  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(l, l, CTRL, 0xf, 0xf, false));
-  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(h, h, CTRL, 0xf, 0xf, false));
-  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 // interface_solve on one wave: the rows cross lanes by permutes (between neighbours of a full wave by DPP moves)
 // instead of LDS, and the stop vote is a ballot.  full: P = 64.  (us a step of one / 4096 systems, with the rows written
 // to LDS, waited for and read back and with the votes there: 101 rows 1.56 / 3.19, 200 rows 1.50 / 3.52, 500 rows
@@ -198,9 +180,9 @@ __device__ __forceinline__ void wave_interface_solve(int P, double al0, double g
   const int before = (4 * t - 4) & mask, after = (4 * t + 4) & mask;
   double a = 0.0, c = 0.0, d = 0.0, nal, nga, nde;
   if (full) {
-    nal = rotated<0x134>(al0);
-    nga = rotated<0x134>(ga0);
-    nde = rotated<0x134>(de0);
+    nal = wave_move<0x134>(al0);
+    nga = wave_move<0x134>(ga0);
+    nde = wave_move<0x134>(de0);
   } else {
     nal = lane_value(al0, after);
     nga = lane_value(ga0, after);
@@ -227,15 +209,15 @@ __device__ __forceinline__ void wave_interface_solve(int P, double al0, double g
     done = __ballot(live) == 0;
   };
   if constexpr (full)
-    combine(rotated<0x13C>(a), rotated<0x13C>(c), rotated<0x13C>(d), rotated<0x134>(a), rotated<0x134>(c), rotated<0x134>(d));
+    combine(wave_move<0x13C>(a), wave_move<0x13C>(c), wave_move<0x13C>(d), wave_move<0x134>(a), wave_move<0x134>(c), wave_move<0x134>(d));
   for (int s = full ? 2 : 1; s < P && !done; s <<= 1) {
     const int mi = (4 * (t - s)) & mask, pi = (4 * (t + s)) & mask;
     combine(lane_value(a, mi), lane_value(c, mi), lane_value(d, mi), lane_value(a, pi), lane_value(c, pi), lane_value(d, pi));
   }
   y = d;
   if (!done) y = d / ((1.0 + a) + c);   // (uniform) every row still coupled couples only to itself
-  yp = full ? rotated<0x13C>(y) : lane_value(y, before);
-  if (next) next->y = full ? rotated<0x134>(y) : lane_value(y, after);
+  yp = full ? wave_move<0x13C>(y) : lane_value(y, before);
+  if (next) next->y = full ? wave_move<0x134>(y) : lane_value(y, after);
 }
 
 // Solves the interface system.  Lane t < P passes its chunk's first interior row (al0, ga0, de0), its

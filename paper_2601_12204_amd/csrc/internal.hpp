@@ -257,8 +257,8 @@ struct ExplicitPlan {
   int64_t n_stream = 0;
   // temporal blocking: whole instances (all steps in place) and windows of long instances
   std::unique_ptr<DevBuf> whole, win;        // BlockTile[]
-  int64_t n_whole = 0, n_win = 0;            // of which the last n_*_rk4 take RK4 steps
-  int64_t n_whole_rk4 = 0, n_win_rk4 = 0;
+  int64_t n_win = 0;                         // of which the last n_win_rk4 take RK4 steps
+  int64_t n_win_rk4 = 0;
   // whole instances by workgroup width: `whole` holds each class's tiles contiguously (forward Euler
   // first, then RK4)
   struct WholeClass {
@@ -437,9 +437,9 @@ int btcs_wg_capacity();                 // longest system of the exact 512-lane 
                                         // partition levels' reduced systems (8192 rows)
 int btcs_whole_capacity();              // longest system one workgroup solves whole (16384 rows)
 bool btcs_solved_whole(int64_t rows);   // up to 16384 rows: one workgroup per system
-int btcs_wg_chunks(int rows);
-int btcs_wg_lanes(const std::vector<SysDesc>& systems);
-bool btcs_wg_exact(const std::vector<SysDesc>& systems);   // all of 512 chunks x 16 rows (a constant layout)   // workgroup width that serves all of them           // chunk count the workgroup solver uses for `rows` rows
+int btcs_wg_chunks(int rows);           // chunk count the workgroup solver uses for `rows` rows
+int btcs_wg_lanes(const std::vector<SysDesc>& systems);    // workgroup width that serves all of them
+bool btcs_wg_exact(const std::vector<SysDesc>& systems);   // all of 512 chunks x 16 rows (a constant layout)
 int btcs_reduce_chunk();                // target rows per chunk in the partition levels
 constexpr int kReduceBlock = 256;       // chunks per workgroup in the partition kernels
 // One BTCS step of the plan from u to out; `step` counts the steps of the current call from 0 (it selects
@@ -458,7 +458,7 @@ double btcs_window_theta(const InstDesc& d, double M);   // ... and that of an i
 // One step of plan.win from u to out (inst: half-dt coefficients for Crank-Nicolson systems); the instances with
 // a window beyond the bound are flagged in `now`, and `next` is cleared.
 hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const void* u,
-                               void* out, int* now, int* next, int* sticky);
+                               void* out, int* now, int* next);
 // For a call from the states in u: the PCR steps of plan.deep's instances, and the flags (slot 0 of the window
 // flags) of those beyond the bound, which launch_btcs_deep leaves alone.  `fresh` (a pool's, one word per instance):
 // it steps those too, and their sticky words tell of steps that fail the bound; an instance's sticky word starts anew

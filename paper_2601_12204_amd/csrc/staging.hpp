@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "internal.hpp"
+#include "wave.hpp"
 
 namespace burgers {
 
@@ -13,16 +14,6 @@ constexpr int kRedChunk = 16;     // chunk length in the partition levels
 // stride of q rows, and without the pad q = 16 or 32 would put every lane of a wave on one bank.
 __device__ __forceinline__ int padded(int i) { return i + (i >> 5); }
 constexpr int padded_size(int rows) { return rows + rows / 32 + 1; }
-
-// Old state values of rows s..s+m-1 staged in LDS (row k at padded(k - base)) into de[], the input of
-// the in-place elimination over ValueRows: every LDS read is issued before the pivot chain starts.
-// The rows then round exactly as LdsRows would assemble them.
-template <typename S, typename T, int M>
-__device__ __forceinline__ void load_staged(const S* st, int base, int s, int m, T (&de)[M]) {
-#pragma unroll
-  for (int j = 0; j < M; ++j)
-    if (j < m) de[j] = static_cast<T>(st[padded(s + j - base)]);
-}
 
 // Coalesced copies of a block's rows between HBM and LDS: all loads are issued before the first LDS
 // store, so a wave has its whole share of the block in flight at once.
@@ -61,14 +52,6 @@ __device__ __forceinline__ void stage_out_cn(const S* stage, const S* __restrict
     if (i < cnt)
       dst[i] = static_cast<S>(2.0 * static_cast<double>(stage[padded(i)]) - static_cast<double>(old[i]));
   }
-}
-
-// An opaque copy of a lane value: address arithmetic built on it cannot be hoisted above this point, so
-// per-lane addresses are formed in the phase that uses them rather than kept live (or spilled) across
-// the kernel.
-__device__ __forceinline__ int opaque_lane(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
 }
 
 }  // namespace burgers

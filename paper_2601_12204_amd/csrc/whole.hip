@@ -36,9 +36,7 @@ __device__ __forceinline__ void record_rows(const double (&de)[M], double* lds, 
 #pragma unroll
       for (int j = 0; j < M; ++j) region[(M + 1) * (lane & 31) + j] = de[j];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
 #pragma unroll 2   // (fully unrolled, the loads held for the stores spill across the solve)
     for (int i = 0; i < (kSlots + 63) / 64; ++i) {
       const int q = lane + 64 * i;
@@ -47,9 +45,7 @@ __device__ __forceinline__ void record_rows(const double (&de)[M], double* lds, 
       const SlotLane o = slot_lane<M, FULL>(owner, R, P, false);
       if ((kSlots % 64 == 0 || q < kSlots) && o.own && (j > 0 || !o.dummy)) x[o.base + j] = static_cast<S>(v);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
   }
 }
 

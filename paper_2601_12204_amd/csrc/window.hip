@@ -66,8 +66,7 @@ ThetaLimits theta_limits() {
 template <typename S, int NT>
 __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
     const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const S* __restrict__ u,
-    S* __restrict__ out, int* __restrict__ flag_now, int* __restrict__ flag_next, int* __restrict__ sticky,
-    double theta_lim) {
+    S* __restrict__ out, int* __restrict__ flag_now, int* __restrict__ flag_next, double theta_lim) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[WindowSpace<S, NT>::kBytes];
   __shared__ uint64_t iface_votes[2 * InterfaceSpace<double, NT>::kVoteWords];
   __shared__ double wave_max[NT / 64];
@@ -87,7 +86,6 @@ __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
     if (!(theta_bound(d, M) <= theta_lim)) {
       flag_now[w.inst] = 1;
       flag_now[-1] = 1;
-      sticky[w.inst] = 1;
     }
   }
   window_advance<S, NT>(ws, stage, f, w, d, 1, kMaxS, [](const auto&) {});
@@ -253,14 +251,14 @@ hipError_t deep_launch(const burgers_ctx* ctx, const BtcsPlan& plan, S* u, S* wo
 
 template <typename S>
 hipError_t step_launch(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const S* u, S* out,
-                       int* now, int* next, int* sticky) {
+                       int* now, int* next) {
   const unsigned n = static_cast<unsigned>(plan.n_win);
   const double lim = btcs_window_limit();
   const ChunkWin* wins = plan.win->as<ChunkWin>();
   if (plan.win_rows == kChunkRows * 512)
-    btcs_window_kernel<S, 512><<<n, 512, 0, ctx->stream>>>(inst, wins, u, out, now, next, sticky, lim);
+    btcs_window_kernel<S, 512><<<n, 512, 0, ctx->stream>>>(inst, wins, u, out, now, next, lim);
   else
-    btcs_window_kernel<S, 256><<<n, 256, 0, ctx->stream>>>(inst, wins, u, out, now, next, sticky, lim);
+    btcs_window_kernel<S, 256><<<n, 256, 0, ctx->stream>>>(inst, wins, u, out, now, next, lim);
   return hipGetLastError();
 }
 
@@ -296,10 +294,10 @@ int64_t btcs_deep_windows_max(int64_t rows) {
 }
 
 hipError_t launch_btcs_windows(const burgers_ctx* ctx, const BtcsPlan& plan, const InstDesc* inst, const void* u,
-                               void* out, int* now, int* next, int* sticky) {
+                               void* out, int* now, int* next) {
   if (ctx->dtype == BURGERS_F64)
-    return step_launch<double>(ctx, plan, inst, static_cast<const double*>(u), static_cast<double*>(out), now, next, sticky);
-  return step_launch<float>(ctx, plan, inst, static_cast<const float*>(u), static_cast<float*>(out), now, next, sticky);
+    return step_launch<double>(ctx, plan, inst, static_cast<const double*>(u), static_cast<double*>(out), now, next);
+  return step_launch<float>(ctx, plan, inst, static_cast<const float*>(u), static_cast<float*>(out), now, next);
 }
 
 hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const void* u, const int32_t* fresh) {
