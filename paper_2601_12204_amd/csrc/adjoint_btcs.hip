@@ -16,7 +16,7 @@
 // (A_w^{-1})_{f',i}, f' the run's row beside f.  A_w is a strictly row-diagonally dominant M-matrix with row sums >= 1, so
 // A_w^{-1} >= 0 with row sums <= 1, and its columns decay from the diagonal like theta of the forward windows: after S
 // PCR steps the couplings are within (D + C) theta^(n_S - 1).  With (D + C) theta^257 <= 2^-55 (S = 4) or (D + C)
-// theta^(n_S) <= 2^-56 (S < 4), theta from the largest |u| at the start of the call (the states' maximum principle), what
+// theta^(15 2^S) <= 2^-56 (S < 4), theta from the largest |u| at the start of the call (the states' maximum principle), what
 // is dropped costs about 2^-53 max|mu| at most.  Systems beyond the bound are solved whole by one workgroup of 1024
 // lanes (up to 16384 rows) or by the partition levels' array path.
 #include "interface.hpp"

@@ -1055,12 +1055,11 @@ __global__ __launch_bounds__(kReduceBlock, 3) void btcs_block_turn_kernel(
   __shared__ int iface_flags[2 * kSpikeWaves];
   __shared__ uint64_t iface_votes[2 * InterfaceSpace<T, NT>::kVoteWords];
   __shared__ double wave_max[NT / 64];
+  if (state[-1] == 0) return;                    // (one word, before the tables: an idle launch is most of them)
   // (both roles' tables and states read at once: their latencies would add up)
   const int turn = static_cast<int>(blockIdx.x);
-  const int any = state[-1];
   const ChunkWin cw = wins[turn < n_wins ? turn : 0];
   const ChunkBlock cb = blocks[turn < n_blocks ? turn : 0];
-  if (any == 0) return;
   const int* now = beyond + step % 3 * count;
   const SysDesc sys = systems[cb.sys];
   const int win_state = state[cw.inst], win_beyond = now[cw.inst];

@@ -45,14 +45,19 @@ constexpr int kWatched = 8;   // beside the PCR steps of an instance's code: a p
 
 // The largest theta for S PCR steps, with slack for rounding (of its own evaluation, and for S < 4 of the growth of
 // max|u| by rounding over a call's steps: S = 4 has it in hand).
+// S < 4 asks for n_S rows where one instance alone is stepped, and otherwise for a little more: instances run side by
+// side, each as many steps a launch as its S allows, so one of a smaller S than the others makes every launch longer
+// where the chip is not full.  At ten times the CFL step diffusion alone gives a theta of 0.537: within 63 rows for S = 2
+// (0.540), not within 60 (0.524).  (One grid of 2^24 rows, 128 steps: 3.39 ms with 63 rows, 3.60 with 60; 87 problems of
+// up to 30484 nodes, 78 steps: 1.50 and 1.42.)
 struct ThetaLimits {
   double of[kMaxS];     // S = 1 .. kMaxS: theta^rows <= 2^-56
-  double rows[kMaxS];   // n_S; S = 4: 257
+  double rows[kMaxS];   // 16 2^S - 1 or 15 2^S; S = 4: 257
 };
-ThetaLimits theta_limits() {
+ThetaLimits theta_limits(bool alone = false) {
   ThetaLimits t;
   for (int s = 1; s <= kMaxS; ++s) {
-    t.rows[s - 1] = s < kMaxS ? (kChunkRows << s) - 1 : 257;
+    t.rows[s - 1] = s == kMaxS ? 257 : alone ? (kChunkRows << s) - 1 : (kChunkRows - 1) << s;
     t.of[s - 1] = std::exp2(-56.0 / t.rows[s - 1]) * (1.0 - (s < kMaxS ? 1e-9 : 1e-12));
   }
   return t;
@@ -313,7 +318,8 @@ hipError_t launch_btcs_bound(const burgers_ctx* ctx, const BtcsPlan& plan, const
                                                  top, deep_beyond(plan.deep_words.as<int>(), ctx->count), ctx->count,
                                                  deep_code(plan.deep_words.as<int>(), ctx->count),
                                                  win_flag_slot(plan.win_flags.as<int>(), ctx->count, 0),
-                                                 win_sticky(plan.win_flags.as<int>(), ctx->count), theta_limits(),
+                                                 win_sticky(plan.win_flags.as<int>(), ctx->count),
+                                                 theta_limits(plan.n_deep_inst == 1 && !plan.transposed),
                                                  fresh, plan.transposed ? 1 : 0);
   return hipGetLastError();
 }
