@@ -60,8 +60,8 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // the same 16 nodes in every window that keeps them, so the gradient does not depend on how the steps are grouped into
 // launches (the checkpoint interval).
 //
-// Bound by vector issue: 23 to 24 instructions per node and step, 4.5 of them the states' second computation, with 12%
-// of the nodes halo.  (256 x 16384 nodes, us per reverse step, the recording of the states on another stream included: 7 here;
+// Bound by vector issue: 31 instructions per node and step (counted, 92% of the slots; 26 per node of a window, about 4.5
+// of them the states' second computation, and one in six of a window's nodes halo or beyond it).  (256 x 16384 nodes, us per reverse step, the recording of the states on another stream included: 7 here;
 // 18 with every state recorded and read, 8 + 8 bytes per node and step, by workgroups of 256 lanes with
 // an exchange and a barrier a step.)
 constexpr int kAdjChunk = 16;

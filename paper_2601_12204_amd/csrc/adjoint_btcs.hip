@@ -11,6 +11,9 @@
 // each step, and how the steps are spread over launches does not show.  dJ/dD is carried per lane over its rows and all steps, in a slot per
 // chunk of the system, so the sums do not depend on how the steps are grouped into launches.
 //
+// What bounds the windows: the latency of the transposed solve, two waves per SIMD that issue half of the time; 58 vector
+// instructions per row of a window and step (counted), 85 per row kept.
+//
 // Error of a window's kept row, per step: as of the forward windows, that of the couplings dropped.  A row that couples
 // mu_f outside a run of rows to mu_i inside it through A_w^{-T} does so with at most D + C (C = r max|u|) times
 // (A_w^{-1})_{f',i}, f' the run's row beside f.  A_w is a strictly row-diagonally dominant M-matrix with row sums >= 1, so

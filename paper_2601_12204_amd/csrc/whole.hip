@@ -3,9 +3,9 @@
 // launch through HBM (btcs_whole_kernel).  Both run the same operations in the same order, so they agree
 // bitwise.
 //
-// What bounds them: vector issue in binary64 (about 20 instructions per row and step, 4 of them the row's
-// assembly, one a quarter-rate reciprocal), and the interface solve, 100 to 150 instructions and four or
-// five barriers per lane and step, which the other workgroups of a CU cover in part.
+// What bounds them: vector issue in binary64 (25 instructions per row and step over all, counted at 8192 rows on 512
+// lanes, 87% of the slots: five of them the row's assembly, one a quarter-rate reciprocal), and the interface solve, 100
+// to 150 of a lane's instructions and four or five barriers a step, which the other workgroups of a CU cover in part.
 #include "interface.hpp"
 #include "internal.hpp"
 #include "staging.hpp"

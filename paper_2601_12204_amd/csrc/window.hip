@@ -67,7 +67,8 @@ ThetaLimits theta_limits(bool alone = false) {
 // fails; the partition levels then redo that instance's step (the old state is still in u).
 //
 // Bound by HBM and the latency of load, solve and store in turn: 16 x 256 rows per window, so that four
-// workgroups a CU overlap them (58.6 us a step at 2^24 rows, binary64, the idle launches of the levels included).
+// workgroups a CU overlap them (2^24 rows: 46.4 us, binary32 40.1; with chunks at fixed rows of the window, before a
+// chunk's rows were the same in every window, 45.9 and 38.6).
 template <typename S, int NT>
 __global__ __launch_bounds__(NT, 4) void btcs_window_kernel(
     const InstDesc* __restrict__ inst, const ChunkWin* __restrict__ wins, const S* __restrict__ u,

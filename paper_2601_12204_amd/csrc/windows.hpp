@@ -17,8 +17,9 @@ constexpr int kChunkRows = 16;     // rows (slots) of a window's chunk
 constexpr int kMaxPcr = 4;         // PCR steps of a window's solve at most
 constexpr int kStepHalo = 1 << kMaxPcr;   // chunks lost at either end of a window over one step
 constexpr int kDeepLanes = 512;
-// Chunks lost at either end of a window over a launch of several steps: with S = 3, the usual case at ten times
-// the CFL step, 6 steps a launch (one grid of 2^24 rows, 128 steps: 32 chunks 3.48 ms, 48: 3.16, 64: 3.21).
+// Chunks lost at either end of a window over a launch of several steps: 24, 12, 6 or 3 of them with S = 1 to 4, at ten
+// times the CFL step 12 or 6.  (One grid of 2^24 rows, 128 steps / 10^4 ragged problems, ms: 32 chunks 3.16 / 19.9, 48:
+// 3.18 / 19.4, 64: 3.32 / 19.5, repeated on a warm chip.)
 constexpr int kDeepHalo = 48;
 
 // Chunks of a system of R > 8192 rows: P = ceil(R / 16) of them, all of 16 rows but `lack` < 16 of 15 rows, the chunks

@@ -50,6 +50,9 @@ def test_states_that_come_within_the_bound(dtype):
         same = [np.array_equal(want[a:b], levels[a:b]) for a, b in zip(batch.offsets[:-1], batch.offsets[1:])]
         assert any(same) and not all(same)
         assert per_instance_rel(batch, want, oracle_run(batch, 12, "f64")).max() <= TOL_F64
+    # graphs replayed between calls of the context's own, the flags decided anew each time
+    assert np.array_equal(device_run(batch, 4, dtype, reps=3), want)
+    assert np.array_equal(device_run(batch, 4, dtype, plan=dict(use_graph=1), reps=3), want)
     u, off = _static_run(batch, dtype, 12)
     assert np.array_equal(want, _dense(u, off, batch.problems))
     # beside a long Crank-Nicolson system every step is a launch of its own
