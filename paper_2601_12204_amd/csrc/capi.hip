@@ -676,7 +676,7 @@ hipError_t enqueue_stepped(burgers_ctx* ctx, const burgers::BtcsPlan& pl, void* 
 
 // Windows of several steps serve calls of three steps and more: they begin with a pass over the states for the
 // bound that holds for the whole call, and keep 416 of 512 chunks against 224 of 256.  (2^24 rows, us per step with the
-// copy of the state, by windows of one step / of several: 2 steps 83 / 110, 3 steps 87 / 82, 4 steps 85 / 66.)
+// copy of the state, by windows of one step / of several: 2 steps 79 / 107, 3 steps 83 / 78, 4 steps 66 / 63.)
 constexpr int64_t kDeepLeast = 3, kDeepCall = int64_t{1} << 24;
 bool takes_deep(const burgers::BtcsPlan& pl, int64_t nsteps) { return pl.n_deep > 0 && nsteps >= kDeepLeast; }
 
